@@ -382,8 +382,9 @@ sc_status sc_stream_read_probe(const void *src, size_t bytes, void *sink, void *
  *                          <= 0 (the default) = 2, or 1 for a call of a few thousand tokens in all
  *   "gsc_chunks_per_item"  generic path: chunks per work item
  *   "gsc_grid_x"           workgroups per pass and (sequence, KV head); <= 0 = chosen from N_max
- *   "multi_block_rows"     sc_multi_attn: query rows per workgroup, 16 or 32; <= 0 = chosen from the shape
- *   "multi_target_wgs"     sc_multi_attn: workgroups the split count aims at (default 256)
+ *   "multi_block_rows"     sc_multi_attn: query rows per workgroup, 32 (every wavefront holds all of them) or 128 (32
+ *                          per wavefront); anything else = chosen from the shape
+ *   "multi_target_wgs"     sc_multi_attn: compute units the split count reckons with (default 256)
  *                          (these two enter sc_multi_attn_workspace_bytes: set them before asking for the
  *                          size; a workspace that has become too small is refused with SC_ERR_WORKSPACE)
  * Return 0 / the value, or -1 for an unknown key.

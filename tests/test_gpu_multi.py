@@ -167,3 +167,45 @@ def test_multi_attn_launch_shapes(knobs):
     err = np.abs(O.float().cpu().numpy().astype(np.float64) - want_O) / np.maximum(1.0, np.abs(want_O))
     assert err.max() <= 4e-3, (knobs, err.max())
     assert np.abs(lse.cpu().numpy().astype(np.float64) - want_L).max() <= 1e-3
+
+
+@pytest.mark.parametrize("Hkv,G,B,cap,tcap,nq,causal,o_f32,scale", [
+    (2, 4, 1, 700, 0, 16, False, False, 0.0),       # 64 rows: the fewest that take the block kernel, half a workgroup idle
+    (1, 1, 2, 1500, 0, 129, False, True, -0.05),    # one row beyond a block of 128; a negative scale; several splits
+    (3, 7, 1, 63, 70, 37, True, False, 0.0),        # 259 rows, cache shorter than a tile, tiles that hold merged and tail rows
+    (1, 8, 2, 900, 300, 60, True, True, 0.2),       # 480 rows; a sequence with fewer tail rows than query rows
+    (8, 8, 10, 40, 0, 100, False, False, 0.0),      # as many blocks as fill the chip: one split, no second kernel
+])
+def test_multi_attn_blocks_against_oracle(Hkv, G, B, cap, tcap, nq, causal, o_f32, scale):
+    rng = np.random.default_rng(77 + cap + nq)
+    Hq, d = Hkv * G, 128
+    Q = _round_like(rng.standard_normal((nq, B, Hq, d)), True)
+    Kc, Vc = _round_like(rng.standard_normal((B, Hkv, cap, d)), True), _round_like(rng.standard_normal((B, Hkv, cap, d)), True)
+    counts = rng.integers(1, 40, (B, Hkv, cap)).astype(np.int32)
+    lens = rng.integers(cap // 2, cap + 1, (B, Hkv)).astype(np.int32)
+    lens[0, 0] = cap
+    if B > 1:
+        lens[-1, -1] = 0
+    dQ, dKc, dVc = g.to_device(Q, True), g.to_device(Kc, True), g.to_device(Vc, True)
+    dcounts, dlens = torch.from_numpy(counts).to(g.DEV), torch.from_numpy(lens).to(g.DEV)
+    O = torch.full((nq, B, Hq, d), 7.0, dtype=torch.float32 if o_f32 else torch.bfloat16, device=g.DEV)
+    tail = {}
+    if tcap:
+        Kt, Vt = _round_like(rng.standard_normal((B, Hkv, tcap, d)), True), _round_like(rng.standard_normal((B, Hkv, tcap, d)), True)
+        tails = np.full((B,), tcap - 3, np.int32)
+        tails[-1] = nq // 2 if B > 1 else tcap
+        tail = dict(Kt=g.to_device(Kt, True), Vt=g.to_device(Vt, True), tail_lens=torch.from_numpy(tails).to(g.DEV), causal=causal)
+        want_O, want_L = oracle.multi_attn_tail(Q, Kc, Vc, counts, lens, Kt, Vt, tails, causal, scale or None)
+    else:
+        want_O, want_L = oracle.multi_attn(Q, Kc, Vc, counts, lens, scale or None)
+    O, lse = sc.sc_multi_attn(dQ, dKc, dVc, dcounts, dlens, scale=scale, O=O, want_lse=True, **tail)
+    torch.cuda.synchronize()
+    got = O.float().cpu().numpy().astype(np.float64)
+    # probabilities enter with 16 bits (2^-17 each), sums in fp32: 2e-5 of the largest output; bf16 output adds half an ulp
+    tol = 4e-5 if o_f32 else 4e-3
+    err = np.abs(got - want_O) / np.maximum(1.0, np.abs(want_O))
+    assert err.max() <= tol, (err.max(), np.unravel_index(err.argmax(), err.shape))
+    got_l = lse.cpu().numpy().astype(np.float64)
+    finite = np.isfinite(want_L)
+    assert np.array_equal(np.isneginf(got_l), np.isneginf(want_L))
+    assert np.abs(got_l[finite] - want_L[finite]).max() <= 1e-3
