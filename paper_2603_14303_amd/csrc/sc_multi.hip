@@ -599,6 +599,7 @@ __global__ __launch_bounds__(kMqCombineRows *kWave) void multi_attn_combine_kern
 }
 
 // ------------------------------------------------------------------------------------------------
+constexpr int kMbMostRounds = 4;      // multi_block_kernel: splits end at this many workgroups per compute unit
 static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail rows */, int &row_blocks, int &max_splits, int &min_rows, int &block_rows) {
     const int G = Hq / Hkv;
     // Up to 32 query rows per KV head fit the lanes of every wavefront, and the wavefronts share out the cache rows; more of
@@ -626,6 +627,7 @@ static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail ro
     max_splits = 1;
     for (int s = 1; s <= most; ++s) {
         const int64_t wgs = (int64_t)base * s;
+        if (s > 1 && wgs > kMbMostRounds * units) break;         // what the workspace is sized for
         const int64_t per_tile = wgs <= units ? 30 : 43 * ((wgs + 2 * units - 1) / (2 * units));
         const int64_t cost = per_tile * ((tiles + s - 1) / s) + (s > 1 ? 30 + wgs / 5 : 0);
         if (cost < best) { best = cost; max_splits = s; }
@@ -636,10 +638,16 @@ static bool mq_fast(const MultiArgs &a) {
     return a.d == kMqD && a.q_dtype == DType::BF16 && a.kv_dtype == DType::BF16;
 }
 
+// Partials of the largest split count that mq_shape may choose, not of the one it does choose: the choice falls and rises with
+// the shape, and a workspace sized for the longest chunk and the fullest cache has to serve every shorter one.  One split
+// writes no partials.
 size_t multi_fast_workspace_bytes(int B, int Hq, int Hkv, int nq, int cap) {
     int rb, ms, mr, br;
     mq_shape(B, Hq, Hkv, nq, cap, rb, ms, mr, br);
-    return align_up((size_t)B * Hkv * rb * ms * br * kMqPart * 4, 256);
+    const int64_t most = min(kMqMaxSplits, (cap + mr - 1) / mr), units = max(1, tuning().multi_target_wgs);
+    if (most <= 1) return 0;
+    const int64_t wgs = min((int64_t)B * Hkv * rb * most, br == kMwRows ? units * 3 / 4 : kMbMostRounds * units);
+    return align_up((size_t)wgs * br * kMqPart * 4, 256);
 }
 
 size_t multi_workspace_bytes(int B, int Hq, int Hkv, int nq, int cap, int d) {
