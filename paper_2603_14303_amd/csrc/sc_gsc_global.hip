@@ -4,21 +4,18 @@
 //
 // Alg. 1 over one chunk of n rows is sequential in its seeds (a row is a seed iff no earlier seed takes
 // it; a row joins the EARLIEST seed it resembles) but every similarity it can ask for is known in
-// advance, so the work is split into a dense part for the whole chip and a short sequential part:
+// advance, so the work is split into a dense part and a sparse one:
 //   norms    reciprocal norms of all rows.
 //   pairs    all pairwise comparisons "Sim(i, j) > tau" for i < j on the matrix cores
 //            (v_mfma_f32_16x16x32_bf16, 64 x 64 rows per product block): one 64-bit word per (row j,
 //            block of 64 earlier rows), "surely above" and "inside the +-1e-4 band" (decided later in
-//            fp64), stored column block by column block so that both this kernel and the next one
-//            move whole 512-byte runs.  n^2 * d MACs: 69 GMAC and 2 x 67 MB of bits per head at 32k.
-//   resolve  one workgroup per (sequence, head) walks the 64-row blocks in order.  Per block: the rows
-//            nobody has taken yet run Alg. 1 among themselves on the block's own 64 x 64 bits (one
-//            wavefront), then every later row that is still free looks at its word for this block: the
-//            first new seed whose bit is set takes it.  Because the blocks come in order, the first
-//            seed that takes a row is the earliest one that resembles it, as in Alg. 1.  The same
-//            workgroup numbers the members of every cluster in row order.
+//            fp64).  Only blocks that hold such a pair are written; a bit per block says which.
+//   decide   which rows are seeds and which seed every row joins, all blocks of 64 rows at once.
+//   number   one workgroup per (sequence, head) numbers the clusters and their members in row order.
 //   sum      one 16-lane group per cluster adds up its members' keys and values in row order (fp32),
 //            scales by 1/size and writes the output row: Eq. 3.
+// 8 heads x 32768 tokens, tau 0.7, us per call: 2550 with every word written, read back into candidate lists and resolved
+// block by block in order (pairs 1370, lists 307, resolve 762, sum 107); now 1060 (pairs 948, decide 14, number 92, sum 42).
 // Everything else (other element types, head dims, longer sequences) is handed to the ordinary kernels
 // of sc_gsc_merge with offsets that describe one chunk per sequence.
 #include "sc_device.h"
@@ -38,9 +35,9 @@ constexpr int kGlD = 128;
 constexpr int kGlBlock = 64;                    // rows per block
 constexpr int kGlTileRowBytes = 272;            // 256 B of keys + 16 B pad: conflict-free operand reads
 constexpr int kGlPairWaves = 4;                 // row blocks per workgroup of the pairs kernel
-constexpr int kGlResolveThreads = 1024;
+constexpr int kGlNumberThreads = 1024;
 constexpr int kGlSegment = 64;                  // column blocks per work item of the pairs kernel
-constexpr int kGlList = 32;                     // candidate list entries kept per row
+constexpr int kGlLeader = 1 << 16;              // place of the first row of a cluster in a block
 
 struct GlobParams {
     const bf16_t *K, *V;
@@ -57,10 +54,13 @@ struct GlobParams {
     long long tri;                // words of one bit array: 64 * nbp * (nbp + 1) / 2
     float *rinv;                  // [nbp * 64]
     unsigned long long *Y, *U;    // [tri]: column block I holds the words of rows 64 I .. 64 nbp - 1
-    unsigned char *uflag;         // [nbp][nbp]: (row block J, column block I) has any unsure bit; U is only written (and read) where it has
-    int32_t *lists;               // [nbp * 64][kGlList]: earlier rows (of earlier blocks) a row resembles, ascending; bit 31 = unsure
-    int32_t *lcount;              // [nbp * 64]: entries of the list (more than kGlList: the list is incomplete, the words decide)
-    int32_t *cid, *rank, *order;  // [nbp * 64]
+    int nseg;                     // words of a row of tile flags: one per 64 column blocks
+    unsigned long long *tany, *tuns;   // [nbp][nseg]: bit I of row J: block (J, I) has any bit set / any unsure bit; Y and U are only written (and read) where it has
+    unsigned long long *state;    // [2 nbp]: per 32 rows, low half: decided, high half: is a seed
+    int32_t *join;                // [npad]: the seed row that a row belongs to (a seed: itself)
+    int32_t *place;               // [npad]: place inside the own block's rows of the cluster, see glob_decide_block
+    int32_t *lead, *order;        // [npad]
+    int polls;                    // looks at another block's rows before the number kernel takes over
     int32_t *mbase, *csize;       // [nbp * 64 + 1], [nbp * 64]
     int32_t *nclusters;           // [1]
 };
@@ -124,6 +124,7 @@ __global__ __launch_bounds__(256) void glob_norms_kernel(GlobParams p) {
         for (int e = 0; e < 8; ++e) nsq = fmaf(x[e], x[e], nsq);
     }
     nsq = row_allreduce_sum<16>(nsq);
+    if (c == 0 && (row & 31) == 0) p.state[(int64_t)bh * p.nbp * 2 + row / 32] = 0ull;      // nothing decided yet
     if (c == 0)
         p.rinv[(int64_t)bh * p.nbp * 64 + row] = (row < n && nsq > 1e-30f && nsq < 1e30f) ? __frsqrt_rn(nsq) : __builtin_nanf("");
 }
@@ -131,12 +132,14 @@ __global__ __launch_bounds__(256) void glob_norms_kernel(GlobParams p) {
 // ------------------------------------------------------------------------------------------------
 // pairs: workgroup (JG, bh) owns the row blocks J = 4 JG + wave and walks the column blocks I = 0 .. max J.
 // The rows of block J are the B operand and stay in registers (lane (g, c): row 16 Jt + c, elements
-// 32 ks + 8 g .. + 7 -- v_mfma_f32_16x16x32_bf16, the form that runs at the full bf16 rate of this chip); the rows of block I pass through an LDS tile shared by the four wavefronts and are
-// the A operand.  The product tile leaves lane (g, c) with the dot products of row 16 Jt + c of block J
-// and rows 16 It + 4 g + i of block I: four bits of that row's word, completed by an OR over the lane groups.
+// 32 ks + 8 g .. + 7 -- v_mfma_f32_16x16x32_bf16, the form that runs at the full bf16 rate of this chip);
+// the rows of block I pass through an LDS tile shared by the four wavefronts and are the A operand.  The
+// product tile leaves lane (g, c) with the dot products of row 16 Jt + c of block J and rows
+// 16 It + 4 g + i of block I: four bits of that row's word, completed by an OR over the lane groups.
 __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(GlobParams p) {
     __shared__ __attribute__((aligned(16))) char s_tiles[2][kGlBlock * kGlTileRowBytes];      // two tiles: one worked on, one being filled
-    __shared__ float s_rinvs[2][kGlBlock];
+    __shared__ __attribute__((aligned(16))) float s_rinvs[2][kGlBlock];
+    __shared__ int s_odd[2];      // a row of the tile has no usable norm
     const int bh = blockIdx.y, b = bh / p.Hkv, h = bh - b * p.Hkv;
     const int n = gl_seq_len(p, b);
     const int nb = (n + kGlBlock - 1) / kGlBlock;
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
     const int sb = (int)p.stride_n * 2;      // bytes between rows
     // rows of block J as B operands, through a descriptor that ends after the sequence's last row
     uint4 bq[4][4];
-    float hn[4], wn[4];
+    float hn[4], wn[4], ln[4];
     bool bad_j = false;      // a row of block J without a usable norm (also: beyond the end of the sequence)
     {
         const int rows_j = active ? min(kGlBlock, n - J * kGlBlock) : 0;
@@ -182,6 +185,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
             const float norm = __builtin_amdgcn_rcpf(rn);
             hn[Jt] = (p.tau + kBand) * norm;
             wn[Jt] = (2.0f * kBand) * norm;
+            ln[Jt] = (p.tau - 1.1f * kBand) * norm;      // safely below everything that the band holds
         }
     }
     bad_j = ballot64(bad_j) != 0ull;
@@ -207,8 +211,13 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
         char *t = s_tiles[I & 1];
 #pragma unroll
         for (int r = 0; r < 4; ++r) *reinterpret_cast<uint4 *>(t + (lrow + 16 * r) * kGlTileRowBytes + 16 * lc) = pre[r];
-        if (tid < kGlBlock) s_rinvs[I & 1][tid] = pre_r;
+        if (wave == 0) {
+            s_rinvs[I & 1][lane] = pre_r;
+            const bool odd = ballot64(!(pre_r == pre_r)) != 0ull;
+            if (lane == 0) s_odd[I & 1] = odd ? 1 : 0;
+        }
     };
+    uint64_t any_bits = 0ull, uns_bits = 0ull;      // of this segment's column blocks
     fetch(I_first);
     park(I_first);
     if (I_first < I_last) fetch(I_first + 1);
@@ -221,9 +230,11 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
         const char *s_tile = s_tiles[I & 1];
         const float *s_rinv = s_rinvs[I & 1];
         if (!active || I > J) continue;    // wave-uniform
+        const bool odd = bad_j || __builtin_amdgcn_readfirstlane(s_odd[I & 1]) != 0;
         uint32_t yl[4], yh[4], ul[4], uh[4];
 #pragma unroll
         for (int Jt = 0; Jt < 4; ++Jt) yl[Jt] = yh[Jt] = ul[Jt] = uh[Jt] = 0u;
+        bool touched = odd;
 #pragma unroll
         for (int It = 0; It < 4; ++It) {
             gl_float4 acc[4];
@@ -238,15 +249,23 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
                                                                       __builtin_bit_cast(gl_bf16x8, bq[Jt][ks]), acc[Jt], 0, 0, 0);
             }
             const gl_float4 rm = *reinterpret_cast<const gl_float4 *>(s_rinv + 16 * It + 4 * g);
-            // sim(m, n) > t  <=>  dot * rinv_m > t * norm_n:  dd = (tau + band) * norm_n - dot * rinv_m is negative
-            // for a sure yes and at most 2 * band * norm_n inside the band.  Common case, three instructions per
-            // pair: the sign bit of dd is shifted into a nibble, an unsigned minimum over the bit patterns keeps the
-            // smallest non-negative dd (negative values compare as huge).  Only if some lane saw a value inside
-            // the band, or a row without a usable norm is involved, are the nibbles redone with real comparisons
-            // (anything that is not a number is "inside the band" and never a sure yes).
+            // sim(m, n) > t  <=>  dot * rinv_m > t * norm_n.  Hardly any tile holds a pair that comes near: one multiply-add
+            // and half a maximum per pair tell.
+            float top = fmaf(acc[0][0], rm[0], -ln[0]);
+#pragma unroll
+            for (int Jt = 0; Jt < 4; ++Jt)
+#pragma unroll
+                for (int i = (Jt == 0) ? 1 : 0; i < 4; ++i) top = fmaxf(top, fmaf(acc[Jt][i], rm[i], -ln[Jt]));
+            if (!odd && ballot64(top >= 0.f) == 0ull) continue;
+            touched = true;
+            // dd = (tau + band) * norm_n - dot * rinv_m is negative for a sure yes and at most 2 * band * norm_n inside the
+            // band: the sign bit of dd is shifted into a nibble, an unsigned minimum over the bit patterns keeps the smallest
+            // non-negative dd (negative values compare as huge).  Only if some lane saw a value inside the band, or a row
+            // without a usable norm is involved, are the nibbles redone with real comparisons (anything that is not a number
+            // is "inside the band" and never a sure yes).
             const int sh = 16 * (It & 1) + 4 * g;
             uint32_t yn[4];
-            bool close = bad_j || !(rm[0] == rm[0]) || !(rm[1] == rm[1]) || !(rm[2] == rm[2]) || !(rm[3] == rm[3]);
+            bool close = odd;
 #pragma unroll
             for (int Jt = 0; Jt < 4; ++Jt) {
                 uint32_t nib = 0u, dmin = 0x7F800000u;
@@ -280,6 +299,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
                 if (It < 2) yl[Jt] |= yn[Jt] << sh; else yh[Jt] |= yn[Jt] << sh;
             }
         }
+        if (!touched && I != J) continue;
         // complete the words over the four lane groups; lane 16 Jt + c keeps the words of row 16 Jt + c
         uint32_t myl = 0u, myh = 0u, mul = 0u, muh = 0u;
 #pragma unroll
@@ -288,291 +308,379 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
             const uint32_t b0 = gl_or_rows(ul[Jt]), b1 = gl_or_rows(uh[Jt]);
             if (g == Jt) { myl = a0; myh = a1; mul = b0; muh = b1; }
         }
+        if (J * kGlBlock + lane >= n) myl = myh = mul = muh = 0u;      // no such row
         const long long w = (long long)bh * p.tri + gl_col_base(I, p.nbp) + (long long)(J - I) * kGlBlock + lane;
-        p.Y[w] = ((unsigned long long)myh << 32) | myl;
-        const bool any_u = ballot64((mul | muh) != 0u) != 0ull;
-        if (any_u || I == J) p.U[w] = ((unsigned long long)muh << 32) | mul;      // a block's own words are always read
-        if (lane == 0) p.uflag[((long long)bh * p.nbp + J) * p.nbp + I] = any_u ? 1 : 0;
+        const bool any = ballot64((myl | myh | mul | muh) != 0u) != 0ull, any_u = ballot64((mul | muh) != 0u) != 0ull;
+        if (any || I == J) p.Y[w] = ((unsigned long long)myh << 32) | myl;      // a block's own words are always read
+        if (any_u || I == J) p.U[w] = ((unsigned long long)muh << 32) | mul;
+        any_bits |= any ? 1ull << (I & 63) : 0ull;
+        uns_bits |= any_u ? 1ull << (I & 63) : 0ull;
+    }
+    if (active && lane == 0) {      // (a segment is the 64 column blocks of one word)
+        const int64_t at = ((int64_t)bh * p.nbp + J) * p.nseg + seg;
+        p.tany[at] = any_bits;
+        p.tuns[at] = uns_bits;
     }
 }
 
 // ------------------------------------------------------------------------------------------------
-// lists: one wavefront per row block J, lane r = row r.  The row's candidates in earlier blocks (set bits
-// of its words, column block after column block) in ascending order; bit 31 of an entry = unsure.  The
-// first kGlList are kept, the count says how many there were.
-__global__ __launch_bounds__(kWave) void glob_lists_kernel(GlobParams p) {
-    const int bh = blockIdx.y, b = bh / p.Hkv;
-    const int n = gl_seq_len(p, b);
-    const int nb = (n + kGlBlock - 1) / kGlBlock;
-    const int J = (int)gridDim.x - 1 - (int)blockIdx.x;       // the longest rows first
-    if (J >= nb) return;
-    const int lane = threadIdx.x, row = J * kGlBlock + lane;
-    const unsigned long long *Y = p.Y + (long long)bh * p.tri, *U = p.U + (long long)bh * p.tri;
-    const unsigned char *fl = p.uflag + ((long long)bh * p.nbp + J) * p.nbp;
-    int32_t *my_list = p.lists + ((int64_t)bh * p.nbp * kGlBlock + row) * kGlList;
-    int n_cand = 0;
-    constexpr int kBatch = 8;
-    for (int I0 = 0; I0 < J; I0 += kBatch) {
-        unsigned long long yw[kBatch], uw[kBatch];
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            const int I = I0 + k;
-            const bool in = I < J;
-            const long long w = gl_col_base(in ? I : 0, p.nbp) + (long long)(row - (in ? I : 0) * kGlBlock);
-            yw[k] = in ? Y[w] : 0ull;
-            uw[k] = (in && fl[in ? I : 0] != 0) ? U[w] : 0ull;
-        }
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            uint64_t cw = row < n ? (yw[k] | uw[k]) : 0ull;      // rows beyond the end have no list
-            while (cw != 0ull) {
-                const int bit = first_bit(cw);
-                cw &= cw - 1ull;
-                if (n_cand < kGlList) my_list[n_cand] = ((I0 + k) * kGlBlock + bit) | (((yw[k] >> bit) & 1ull) ? 0 : (int)0x80000000);
-                n_cand += 1;
+// decide: one wavefront per row block J, lane r = row r, all blocks at once.
+//
+// A row joins the earliest SEED it resembles and is a seed if there is none, so what is known about a row only ever depends
+// on earlier rows.  Each row looks at its candidates (set bits of its words) in row order: one that is decided and not a seed is
+// passed over, one that is a seed takes the row (an unsure one after a comparison in fp64), one that is undecided is
+// waited for.  What has been decided is published at once, 32 rows to a word (decided | seeds, so that one load gives a
+// consistent view).  Rows whose candidates all lie in their own block are decided before anything is waited for:
+// the members of a cluster mostly sit close together, so a block hardly ever waits for one that waits itself, and
+// the rounds are a few microseconds for all blocks instead of 1.4 us for each of them in turn.
+//
+// Waiting is bounded (p.polls looks in all); blocks that are left undecided are finished in order by the number kernel.
+// Blocks are dispatched in row order, so the ones waited for are running or done.
+struct GlobBlock {       // what a wavefront knows about its block
+    uint64_t decided, seeds, published;
+    int target;          // lane: seed row of the lane's row once decided
+};
+
+__device__ __forceinline__ uint64_t gl_uniform64(uint64_t x) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+}
+__device__ __forceinline__ void gl_load_state(const unsigned long long *st, int I, uint64_t &decided, uint64_t &seeds) {
+    const uint64_t w0 = gl_uniform64(__hip_atomic_load(st + 2 * I, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const uint64_t w1 = gl_uniform64(__hip_atomic_load(st + 2 * I + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    decided = (w0 & 0xFFFFFFFFull) | (w1 << 32);
+    seeds = (w0 >> 32) | (w1 & 0xFFFFFFFF00000000ull);
+}
+__device__ __forceinline__ void gl_publish(unsigned long long *st, int J, GlobBlock &k, int lane) {
+    if (k.decided == k.published) return;
+    if (lane == 0) __hip_atomic_store(st + 2 * J, (k.decided & 0xFFFFFFFFull) | (k.seeds << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 1) __hip_atomic_store(st + 2 * J + 1, (k.decided >> 32) | (k.seeds & 0xFFFFFFFF00000000ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    k.published = k.decided;
+}
+
+// One candidate word (64 earlier rows from `first_row` on; decided / seeds: what is known about them) for every lane with
+// `open`: follows the candidates as far as they are known.  Lanes that find their seed join k.decided; returns the lanes that
+// wait for an undecided row.  uw loses the bits that fp64 has turned down.
+__device__ __forceinline__ uint64_t gl_follow(const GlobParams &p, const bf16_t *Kbh, uint64_t yw, uint64_t &uw, int first_row, uint64_t decided,
+                                              uint64_t seeds, bool open, int j0, int lane, GlobBlock &k) {
+    for (;;) {
+        const bool undecided = open && ((k.decided >> lane) & 1ull) == 0ull;
+        const uint64_t c = undecided ? (yw | uw) & ~(decided & ~seeds) : 0ull;
+        const int f = (c != 0ull) ? first_bit(c) : 0;
+        const bool known = c != 0ull && ((decided >> f) & 1ull) != 0ull;
+        const bool sure = known && ((yw >> f) & 1ull) != 0ull;
+        if (sure) k.target = first_row + f;
+        k.decided |= ballot64(sure);
+        uint64_t ask = ballot64(known && !sure);
+        if (ask == 0ull) return ballot64(c != 0ull && !known);
+        while (ask != 0ull) {
+            const int r = __builtin_amdgcn_readfirstlane(first_bit(ask));
+            ask &= ask - 1ull;
+            const int fr = __builtin_amdgcn_readlane(f, r);
+            const bool ok = gl_cosine_exceeds_f64(Kbh + (int64_t)(first_row + fr) * p.stride_n, Kbh + (int64_t)(j0 + r) * p.stride_n, p.tau, lane);
+            if (ok) k.decided |= 1ull << r;
+            if (lane == r) {
+                if (ok) k.target = first_row + fr;
+                else uw &= ~(1ull << fr);
             }
         }
     }
-    if (row < n) p.lcount[(int64_t)bh * p.nbp * kGlBlock + row] = n_cand;
+}
+
+// Alg. 1 among the rows of the block as far as it can be told: `cleared` rows have no seed in an earlier block
+__device__ __forceinline__ void gl_own_block(const GlobParams &p, const bf16_t *Kbh, uint64_t y, uint64_t &u, uint64_t cleared, int j0, int lane, GlobBlock &k) {
+    const bool open = ((cleared >> lane) & 1ull) != 0ull;
+    for (;;) {
+        const uint64_t before = k.decided;
+        gl_follow(p, Kbh, y, u, j0, k.decided, k.seeds, open, j0, lane, k);
+        // no candidate left that is a seed or may become one: a seed itself
+        const bool seed = open && ((k.decided >> lane) & 1ull) == 0ull && ((y | u) & ~(k.decided & ~k.seeds)) == 0ull;
+        if (seed) k.target = j0 + lane;
+        const uint64_t more = ballot64(seed);
+        k.seeds |= more;
+        k.decided |= more;
+        if (k.decided == before) return;
+    }
+}
+
+// Decides the rows of block J of one (sequence, head); false if it gave up waiting.
+__device__ __forceinline__ bool glob_decide_block(const GlobParams &p, int bh, const bf16_t *Kbh, int n, int J, int lane, int polls) {
+    const int npad = p.nbp * kGlBlock, j0 = J * kGlBlock;
+    const bool valid = j0 + lane < n;
+    const uint64_t all = ballot64(valid);
+    const unsigned long long *Y = p.Y + (long long)bh * p.tri, *U = p.U + (long long)bh * p.tri;
+    const unsigned long long *any_row = p.tany + ((int64_t)bh * p.nbp + J) * p.nseg, *uns_row = p.tuns + ((int64_t)bh * p.nbp + J) * p.nseg;
+    unsigned long long *st = p.state + (int64_t)bh * p.nbp * 2;
+    int32_t *join = p.join + (int64_t)bh * npad + j0, *place = p.place + (int64_t)bh * npad + j0;
+    GlobBlock k;
+    gl_load_state(st, J, k.decided, k.seeds);
+    k.published = k.decided;
+    k.target = ((k.decided >> lane) & 1ull) ? join[lane] : -1;
+    const int segs = J >> 6;
+    uint64_t y, u;
+    {
+        const long long w = gl_col_base(J, p.nbp) + lane;
+        const uint64_t mine = valid ? gl_bits_below(lane) : 0ull;
+        y = Y[w] & mine;
+        u = U[w] & mine;
+    }
+    // the earlier blocks with a bit in any row, in order, up to kBatch at a time
+    constexpr int kBatch = 4;
+    int seg;
+    uint64_t rest_any, rest_uns;
+    auto rewind = [&](int s) {
+        seg = s;
+        rest_any = gl_uniform64(any_row[s]);
+        rest_uns = gl_uniform64(uns_row[s]);
+        if (s == segs) rest_any &= gl_bits_below(J & 63);      // without the block itself
+    };
+    int tile[kBatch];
+    uint64_t yw[kBatch], uw[kBatch];
+    auto next_batch = [&]() {
+        int got = 0;
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+            while (rest_any == 0ull && seg < segs) rewind(seg + 1);
+            tile[q] = -1;
+            yw[q] = uw[q] = 0ull;
+            if (rest_any != 0ull) {
+                const int bit = first_bit(rest_any);
+                rest_any &= rest_any - 1ull;
+                tile[q] = __builtin_amdgcn_readfirstlane(seg * 64 + bit);
+                const long long w = gl_col_base(tile[q], p.nbp) + (long long)(J - tile[q]) * kGlBlock + lane;
+                yw[q] = Y[w];
+                if ((rest_uns >> bit) & 1ull) uw[q] = U[w];
+                got = q + 1;
+            }
+        }
+        return got;
+    };
+    rewind(0);
+    bool has_cross = false, first = true, kept = false;      // kept: the only batch is still in the registers
+    while (next_batch() != 0) {
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) has_cross = has_cross || (yw[q] | uw[q]) != 0ull;
+        kept = first && tile[kBatch - 1] < 0;
+        first = false;
+        if (tile[kBatch - 1] < 0 || ballot64(valid && !has_cross) == 0ull) break;
+    }
+    uint64_t cleared = ballot64(valid && !has_cross);
+    gl_own_block(p, Kbh, y, u, cleared, j0, lane, k);
+    gl_publish(st, J, k, lane);
+    bool gave_up = false;
+    if (cleared != all) {
+        if (!kept) rewind(0);
+        while (!gave_up && k.decided != all) {
+            if (!kept && next_batch() == 0) break;
+            uint64_t dec[kBatch], sds[kBatch];
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) {
+                dec[q] = sds[q] = 0ull;
+                if (tile[q] >= 0) gl_load_state(st, tile[q], dec[q], sds[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) {
+                if (tile[q] < 0 || gave_up) continue;
+                uint64_t waiting = gl_follow(p, Kbh, yw[q], uw[q], tile[q] * kGlBlock, dec[q], sds[q], valid && has_cross, j0, lane, k);
+                while (waiting != 0ull) {
+                    // rows that have just joined may settle others of the block, which other blocks may be waiting for
+                    gl_own_block(p, Kbh, y, u, cleared, j0, lane, k);
+                    gl_publish(st, J, k, lane);
+                    if (--polls < 0) { gave_up = true; break; }
+                    __builtin_amdgcn_s_sleep(4);
+                    gl_load_state(st, tile[q], dec[q], sds[q]);
+                    waiting = gl_follow(p, Kbh, yw[q], uw[q], tile[q] * kGlBlock, dec[q], sds[q], valid && has_cross, j0, lane, k);
+                }
+            }
+            if (!gave_up) {
+                gl_own_block(p, Kbh, y, u, cleared, j0, lane, k);
+                gl_publish(st, J, k, lane);
+            }
+            if (kept) break;
+        }
+        if (!gave_up) {
+            cleared = all;
+            gl_own_block(p, Kbh, y, u, cleared, j0, lane, k);
+            gl_publish(st, J, k, lane);
+        }
+    }
+    if ((k.decided >> lane) & 1ull) join[lane] = k.target;
+    if (k.decided != all) return false;
+    // places of the rows inside their clusters as far as this block goes: the first row of a cluster files 64 + the number of its
+    // rows here (at most 64), the others file their distance from it and its lane
+    int mine = 0;
+    uint64_t rem = all;
+    while (rem != 0ull) {
+        const int l0 = __builtin_amdgcn_readfirstlane(first_bit(rem));
+        const uint64_t same = ballot64(valid && k.target == __builtin_amdgcn_readlane(k.target, l0));
+        if ((same >> lane) & 1ull) mine = (lane == l0) ? kGlLeader | __popcll(same) : (l0 << 8) | __popcll(same & gl_bits_below(lane));
+        rem &= ~same;
+    }
+    if (valid) place[lane] = mine;
+    return true;
+}
+
+__global__ __launch_bounds__(kWave) void glob_decide_kernel(GlobParams p) {
+    const int n_bh = p.B * p.Hkv;
+    const int J = (int)blockIdx.x / n_bh, bh = (int)blockIdx.x - J * n_bh;      // row order; with a multiple of 8 heads a head stays on one XCD
+    const int b = bh / p.Hkv, h = bh - b * p.Hkv;
+    const int n = __builtin_amdgcn_readfirstlane(gl_seq_len(p, b));
+    if (J * kGlBlock >= n) return;
+    glob_decide_block(p, bh, p.K + b * p.stride_b + h * p.stride_h, n, J, threadIdx.x, p.polls);
 }
 
 // ------------------------------------------------------------------------------------------------
-// resolve: one workgroup per (sequence, head) walks the blocks in order; one barrier per block.
-//   wavefront 0 (lane r = row r of block J) is the sequential part.  A row that an earlier block's seed
-//   resembles is taken by the earliest such seed: the row walks its candidate list (written by the pairs
-//   kernel in ascending order) and stops at the first entry that is a seed.  The rows left over run Alg. 1
-//   among themselves on the block's own bits; the new seeds go into the seed mask.
-//   wavefront 1 brings the lists of block J + 1 into LDS meanwhile (they do not depend on the seeds),
-//   wavefront 2 numbers the members of block J - 1 per cluster in row order.
-// Unsure candidates (inside the band) are settled by wavefront 0 in fp64, in list order; a row with more
-// candidates than the list holds falls back to its words of the bit arrays, column block by column block.
-__global__ __launch_bounds__(kGlResolveThreads) void glob_resolve_kernel(GlobParams p) {
-    extern __shared__ unsigned short s_csz[];       // members filed per cluster (16 bits: n <= 32768); later their first slot
+// number: one workgroup per (sequence, head).  Clusters are numbered in seed order and their members in row order: every row gets
+// its cluster, the first row of a cluster in a block takes the next slots of that cluster for all its rows there (one
+// wavefront, in block order: LDS additions of one wavefront execute in order and nothing waits for their results but
+// the stores), sizes become first slots, rows go to their slots.
+__global__ __launch_bounds__(kGlNumberThreads) void glob_number_kernel(GlobParams p) {
+    extern __shared__ unsigned int s_size2[];       // members filed per cluster, two 16-bit fields a word (n <= 32768); later first slots
     __shared__ unsigned long long s_mask[512];      // seeds of every block
-    __shared__ int s_pref[513];                     // clusters before block J
-    __shared__ int s_list[2][kGlBlock][kGlList + 1];      // [block parity][row][entries]: + 1 keeps the rows on different banks
-    __shared__ int s_lcnt[2][kGlBlock];
-    __shared__ int s_mine[2][kGlBlock];             // cluster of every row of the block, handed to wavefront 2
-    __shared__ int s_scan[kGlResolveThreads];
+    __shared__ int s_pref[512];                     // clusters before block J
+    __shared__ int s_scan[kGlNumberThreads];
+    __shared__ int s_undecided;
     const int bh = blockIdx.x, b = bh / p.Hkv, h = bh - b * p.Hkv;
-    const int n = gl_seq_len(p, b);
+    const int n = __builtin_amdgcn_readfirstlane(gl_seq_len(p, b));
     const int nb = (n + kGlBlock - 1) / kGlBlock;
     const int npad = p.nbp * kGlBlock;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const bf16_t *Kbh = p.K + b * p.stride_b + h * p.stride_h;
-    const unsigned long long *Y = p.Y + (long long)bh * p.tri, *U = p.U + (long long)bh * p.tri;
-    const unsigned char *uflag = p.uflag + (long long)bh * p.nbp * p.nbp;
-    const int32_t *lists = p.lists + (int64_t)bh * npad * kGlList, *lcount = p.lcount + (int64_t)bh * npad;
-    int32_t *cid_g = p.cid + (int64_t)bh * npad, *rank_g = p.rank + (int64_t)bh * npad, *order_g = p.order + (int64_t)bh * npad;
+    const unsigned long long *st = p.state + (int64_t)bh * p.nbp * 2;
+    const int32_t *join = p.join + (int64_t)bh * npad, *place = p.place + (int64_t)bh * npad;
+    int32_t *lead = p.lead + (int64_t)bh * npad, *order = p.order + (int64_t)bh * npad;
     int32_t *cid_out = p.cluster_id ? p.cluster_id + (int64_t)bh * p.N_max : nullptr;
-    for (int i = tid; i < npad; i += kGlResolveThreads) s_csz[i] = 0;
-    if (tid == 0) s_pref[0] = 0;
-    if (tid < kGlBlock) s_lcnt[0][tid] = 0;      // block 0 has no earlier block
+    unsigned short *s_size = reinterpret_cast<unsigned short *>(s_size2);
+    if (tid == 0) s_undecided = 0;
+    for (int i = tid; i < npad / 2; i += kGlNumberThreads) s_size2[i] = 0u;
     __syncthreads();
-
-    // wavefront 0: words of block J's rows in its own column block
-    unsigned long long dy = 0ull, du = 0ull;
-    if (wave == 0 && nb > 0) { dy = Y[lane]; du = U[lane]; }
-    for (int J = 0; J <= nb; ++J) {      // one extra step: wavefront 2 files the last block
-        if (wave == 0 && J < nb) {
-            const int j = J * kGlBlock + lane;
-            const bool valid = j < n;
-            // ---- earliest seed of an earlier block that resembles the row
-            const int cnt = valid ? s_lcnt[J & 1][lane] : 0;
-            int seed_row = -1;
-            bool slow = false;
-            {
-                // the list holds the row's kGlList earliest candidates: if one of them is a seed, the earliest seed
-                // is among them; if none is and the list is incomplete, the words decide
-                const int cmax = __builtin_amdgcn_readfirstlane(wave_max_i32(min(cnt, kGlList)));
-                bool done = false;
-                for (int e = 0; e < cmax; ++e) {
-                    const int ent = s_list[J & 1][lane][e];
-                    const int i = (e < cnt) ? (ent & 0x7FFFFFFF) : 0;      // beyond the list: whatever the buffer held before
-                    const bool is_seed = !done && e < cnt && ((s_mask[i >> 6] >> (i & 63)) & 1ull) != 0ull;
-                    if (is_seed) {
-                        done = true;
-                        if (ent >= 0) seed_row = i;      // sure
-                        else slow = true;                // unsure: decided below, in list order
-                    }
-                }
-                if (!done && cnt > kGlList) slow = true;
-            }
-            uint64_t slow_rows = ballot64(slow);
-            while (slow_rows != 0ull) {
-                const int r = __builtin_amdgcn_readfirstlane(first_bit(slow_rows));
-                slow_rows &= slow_rows - 1ull;
-                const int jr = J * kGlBlock + r;
-                const int cr = __builtin_amdgcn_readlane(cnt, r);
-                int found = -1;
-                for (int e = 0; e < min(cr, kGlList) && found < 0; ++e) {
-                    const int ent = s_list[J & 1][r][e];
-                    const int i = ent & 0x7FFFFFFF;
-                    if (((s_mask[i >> 6] >> (i & 63)) & 1ull) == 0ull) continue;
-                    bool ok = ent >= 0;
-                    if (!ok) ok = gl_cosine_exceeds_f64(Kbh + (int64_t)i * p.stride_n, Kbh + (int64_t)jr * p.stride_n, p.tau, lane);
-                    if (ok) found = i;
-                }
-                if (found < 0 && cr > kGlList) {
-                    for (int I0 = 0; I0 < J && found < 0; I0 += kWave) {
-                        const int I = I0 + lane;
-                        unsigned long long yy = 0ull, cc = 0ull;
-                        if (I < J) {
-                            const long long w = gl_col_base(I, p.nbp) + (long long)(jr - I * kGlBlock);
-                            const unsigned long long m = s_mask[I];
-                            yy = Y[w] & m;
-                            cc = yy | (uflag[(long long)J * p.nbp + I] ? (U[w] & m) : 0ull);
-                        }
-                        uint64_t cols = ballot64(cc != 0ull);
-                        while (cols != 0ull && found < 0) {
-                            const int l = __builtin_amdgcn_readfirstlane(first_bit(cols));
-                            cols &= cols - 1ull;
-                            const unsigned long long ycol = __builtin_bit_cast(unsigned long long, make_uint2(
-                                __builtin_amdgcn_readlane((unsigned)yy, l), __builtin_amdgcn_readlane((unsigned)(yy >> 32), l)));
-                            unsigned long long ccol = __builtin_bit_cast(unsigned long long, make_uint2(
-                                __builtin_amdgcn_readlane((unsigned)cc, l), __builtin_amdgcn_readlane((unsigned)(cc >> 32), l)));
-                            while (ccol != 0ull && found < 0) {
-                                const int bit = first_bit(ccol);
-                                ccol &= ccol - 1ull;
-                                const int srow = (I0 + l) * kGlBlock + bit;
-                                bool ok = ((ycol >> bit) & 1ull) != 0ull;
-                                if (!ok) ok = gl_cosine_exceeds_f64(Kbh + (int64_t)srow * p.stride_n, Kbh + (int64_t)jr * p.stride_n, p.tau, lane);
-                                if (ok) found = srow;
-                            }
-                        }
-                    }
-                }
-                if (lane == r) seed_row = found;
-            }
-            int mine = -1;
-            if (seed_row >= 0) {
-                const int I = seed_row >> 6, bit = seed_row & 63;
-                mine = s_pref[I] + __popcll(s_mask[I] & gl_bits_below(bit));
-            }
-            // ---- Alg. 1 among the rows of block J that nobody has taken
-            const bool open = valid && seed_row < 0;
-            const uint64_t y = dy & gl_bits_below(lane), u = du & gl_bits_below(lane);
-            uint64_t todo = ballot64(open), seeds = 0ull;
-            int my_seed = 0;
-            {
-                // Shortcut: guess that a free row is a seed iff no earlier free row of the block resembles it.  If every
-                // other free row then resembles an earlier guessed seed, and no unsure pair is involved, induction over
-                // the rows shows that the guess is the outcome of Alg. 1 (a guessed seed has no earlier similar free
-                // row, hence no earlier similar seed; any other row joins the first guessed seed it resembles).
-                const uint64_t free_before = todo & gl_bits_below(lane);
-                const bool guess = open && (y & free_before) == 0ull;
-                const uint64_t S = ballot64(guess);
-                const uint64_t hits = y & S;
-                const bool fine = !open || ((u & free_before) == 0ull && (guess || hits != 0ull));
-                if (ballot64(fine) == ~0ull) {
-                    seeds = S;
-                    my_seed = guess ? lane : (hits != 0ull ? first_bit(hits) : 0);
-                    todo = 0ull;
-                }
-            }
-            while (todo != 0ull) {
-                const int s = __builtin_amdgcn_readfirstlane(first_bit(todo));     // lowest free row: nobody before it took it
-                const bool cand = ((todo >> lane) & 1ull) != 0ull && lane > s;
-                bool yes = cand && ((y >> s) & 1ull) != 0ull;
-                uint64_t recheck = ballot64(cand && !yes && ((u >> s) & 1ull) != 0ull);
-                while (recheck != 0ull) {
-                    const int jl = __builtin_amdgcn_readfirstlane(first_bit(recheck));
-                    recheck &= recheck - 1ull;
-                    const bool res = gl_cosine_exceeds_f64(Kbh + (int64_t)(J * kGlBlock + s) * p.stride_n,
-                                                           Kbh + (int64_t)(J * kGlBlock + jl) * p.stride_n, p.tau, lane);
-                    if (lane == jl) yes = res;
-                }
-                const uint64_t got = ballot64(yes);
-                if (lane == s || yes) my_seed = s;
-                seeds |= 1ull << s;
-                todo &= ~(got | (1ull << s));
-            }
-            const int first = s_pref[J];
-            if (open) mine = first + __popcll(seeds & gl_bits_below(my_seed));
-            if (lane == 0) { s_mask[J] = seeds; s_pref[J + 1] = first + __popcll(seeds); }
-            s_mine[J & 1][lane] = valid ? mine : -1;
-            // the next block's own words, requested now, used after the barrier
-            if (J + 1 < nb) {
-                const long long w = gl_col_base(J + 1, p.nbp) + lane;
-                dy = Y[w];
-                du = U[w];
-            }
-        } else if (wave == 1 && J + 1 < nb) {
-            // ---- lists of block J + 1 into LDS
-            const int T = J + 1, jrow = T * kGlBlock + lane;
-            const int cnt = jrow < n ? lcount[jrow] : 0;
-            s_lcnt[T & 1][lane] = cnt;
-            // 64 rows x 32 entries, 16 bytes per lane and load
-#pragma unroll
-            for (int q = 0; q < (kGlBlock * kGlList) / (kWave * 4); ++q) {
-                const int flat = (q * kWave + lane) * 4;            // entry index inside the block's 64 x 32 array
-                const int r = flat / kGlList, e = flat % kGlList;
-                const int4 v = *reinterpret_cast<const int4 *>(lists + ((int64_t)T * kGlBlock + r) * kGlList + e);
-                s_list[T & 1][r][e] = v.x; s_list[T & 1][r][e + 1] = v.y; s_list[T & 1][r][e + 2] = v.z; s_list[T & 1][r][e + 3] = v.w;
-            }
-        } else if (wave == 2 && J >= 1) {
-            // ---- members of block J - 1 in row order
-            const int Jb = J - 1, j = Jb * kGlBlock + lane;
-            const bool valid = j < n;
-            const int mine = s_mine[Jb & 1][lane];
-            if (valid) {
-                cid_g[j] = mine;
-                if (cid_out) cid_out[j] = mine;
-            }
-            // rank of row j among the members of its cluster = members filed so far + earlier rows of this block in
-            // the same cluster.  All lanes read the old sizes first, then the first row of every cluster in the block
-            // files the new size (distinct clusters, distinct addresses): no chain of dependent LDS updates.
-            int lower = 0, total = 0;
-            uint64_t rem = ballot64(valid);
-            while (rem != 0ull) {      // once per cluster that has rows in the block
-                const int l0 = __builtin_amdgcn_readfirstlane(first_bit(rem));
-                const int c0 = __builtin_amdgcn_readlane(mine, l0);
-                const uint64_t same = ballot64(valid && mine == c0);
-                if ((same >> lane) & 1ull) { lower = __popcll(same & gl_bits_below(lane)); total = __popcll(same); }
-                rem &= ~same;
-            }
-            const int before = valid ? (int)s_csz[mine] : 0;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            if (valid && lower == 0) s_csz[mine] = (unsigned short)(before + total);
-            if (valid) rank_g[j] = before + lower;
+    {
+        bool open = false;
+        if (tid < 2 * nb) {
+            const int rows = n - tid * 32;
+            const uint32_t want = rows <= 0 ? 0u : (rows >= 32 ? 0xFFFFFFFFu : (1u << rows) - 1u);
+            open = ((uint32_t)st[tid] & want) != want;
         }
+        if (open) s_undecided = 1;
+    }
+    __syncthreads();
+    if (s_undecided != 0) {      // (2 * nb <= 1024 words: one look each)
+        if (wave == 0) {
+            const bf16_t *Kbh = p.K + b * p.stride_b + h * p.stride_h;
+            for (int J = 0; J < nb; ++J) {
+                uint64_t dec, sds;
+                gl_load_state(st, J, dec, sds);
+                const uint64_t all = gl_bits_below(min(kGlBlock, n - J * kGlBlock));
+                if (dec == all) continue;
+                glob_decide_block(p, bh, Kbh, n, J, lane, 0);      // every earlier row is decided: nothing to wait for
+                __threadfence();                                   // the next block's wavefront-wide loads see it
+            }
+        }
+        __threadfence();
         __syncthreads();
     }
-    // ---- cluster sizes -> first member slot of every cluster; sizes and length to the outputs
-    const int P = s_pref[nb];
+    // ---- clusters before every block
+    int mine = 0;
+    if (tid < 512) {
+        uint64_t m = 0ull;
+        if (tid < nb) {
+            const unsigned long long w0 = __hip_atomic_load(st + 2 * tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long w1 = __hip_atomic_load(st + 2 * tid + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            m = (w0 >> 32) | (w1 & 0xFFFFFFFF00000000ull);
+        }
+        s_mask[tid] = m;
+        mine = __popcll(m);
+    }
+    // exclusive sum over the workgroup; total in the last entry
+    auto scan = [&](int x) {
+        int incl = x;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int up = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += up;
+        }
+        if (lane == kWave - 1) s_scan[wave] = incl;
+        __syncthreads();
+        int before = 0;
+        for (int w = 0; w < wave; ++w) before += s_scan[w];
+        return before + incl - x;
+    };
+    const int pref = scan(mine);
+    if (tid < 512) s_pref[tid] = pref;
+    int P = 0;
+    for (int w = 0; w < kGlNumberThreads / kWave; ++w) P += s_scan[w];
+    __syncthreads();
+    // ---- the cluster of every row
+    constexpr int kPer = 32;             // 1024 threads x 32 = 32768 clusters at most
+    auto cluster_of = [&](int seed_row) { return s_pref[seed_row >> 6] + (int)__popcll(s_mask[seed_row >> 6] & gl_bits_below(seed_row & 63)); };
+    for (int j0 = tid; j0 < n; j0 += 8 * kGlNumberThreads) {
+        int t[8], pl[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int j = j0 + q * kGlNumberThreads;
+            t[q] = j < n ? join[j] : 0;
+            pl[q] = j < n ? place[j] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int j = j0 + q * kGlNumberThreads;
+            if (j < n) {
+                const int c = cluster_of(t[q]);
+                if (cid_out) cid_out[j] = c;
+                lead[j] = (pl[q] & kGlLeader) ? c | ((pl[q] & 0x7F) << 16) : -1;
+            }
+        }
+    }
+    __syncthreads();
+    // ---- slots inside the clusters, in row order
+    if (wave == 0) {
+        constexpr int kAhead = 8;
+        int v[kAhead], w[kAhead];
+        auto get = [&](int J0, int (&x)[kAhead]) {
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                const int j = (J0 + q) * kGlBlock + lane;
+                x[q] = j < n ? lead[j] : -1;
+            }
+        };
+        get(0, v);
+        for (int J0 = 0; J0 < nb; J0 += kAhead) {
+            get(J0 + kAhead, w);
+            unsigned int old[kAhead];
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q)
+                if (v[q] >= 0) old[q] = atomicAdd(&s_size2[(v[q] & 0xFFFF) >> 1], (unsigned)(v[q] >> 16) << (16 * (v[q] & 1)));
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q)
+                if (v[q] >= 0) lead[(J0 + q) * kGlBlock + lane] = (int)((old[q] >> (16 * (v[q] & 1))) & 0xFFFFu);
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) v[q] = w[q];
+        }
+    }
+    __syncthreads();
+    // ---- cluster sizes -> first slot of every cluster; sizes and length to the outputs
     {
-        constexpr int kPer = 32;             // 1024 threads x 32 = 32768 clusters at most
+        const int per = (P + kGlNumberThreads - 1) / kGlNumberThreads;
         int local[kPer];
         int sum = 0;
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int cidx = tid * kPer + k;
-            local[k] = (cidx < P) ? (int)s_csz[cidx] : 0;
-            sum += local[k];
+        for (int q = 0; q < kPer; ++q) {
+            const int c = tid * per + q;
+            local[q] = (q < per && c < P) ? (int)s_size[c] : 0;
+            sum += local[q];
         }
-        s_scan[tid] = sum;
-        __syncthreads();
-        for (int off = 1; off < kGlResolveThreads; off <<= 1) {
-            const int v = (tid >= off) ? s_scan[tid - off] : 0;
-            __syncthreads();
-            s_scan[tid] += v;
-            __syncthreads();
-        }
-        int run = s_scan[tid] - sum;
+        int run = scan(sum);
         int32_t *mbase = p.mbase + (int64_t)bh * (npad + 1), *csize = p.csize + (int64_t)bh * npad;
         int32_t *counts_bh = p.counts + (int64_t)bh * p.cap;
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int cidx = tid * kPer + k;
-            if (cidx < P) {
-                mbase[cidx] = run;
-                csize[cidx] = local[k];
-                if (cidx < p.cap) counts_bh[cidx] = local[k];
-                s_csz[cidx] = (unsigned short)run;      // n <= 32768: a slot index fits 16 bits
-                run += local[k];
+        for (int q = 0; q < kPer; ++q) {
+            const int c = tid * per + q;
+            if (q < per && c < P) {
+                mbase[c] = run;
+                csize[c] = local[q];
+                if (c < p.cap) counts_bh[c] = local[q];
+                s_size[c] = (unsigned short)run;      // n <= 32768: a slot index fits 16 bits
+                run += local[q];
             }
         }
         if (tid == 0) {
@@ -581,11 +689,29 @@ __global__ __launch_bounds__(kGlResolveThreads) void glob_resolve_kernel(GlobPar
         }
     }
     __syncthreads();
-    for (int j = tid; j < n; j += kGlResolveThreads) order_g[(int)s_csz[cid_g[j]] + rank_g[j]] = j;
+    for (int j0 = tid; j0 < n; j0 += 8 * kGlNumberThreads) {
+        int t[8], pl[8], at[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int j = j0 + q * kGlNumberThreads;
+            t[q] = j < n ? join[j] : 0;
+            pl[q] = j < n ? place[j] : kGlLeader;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int j = j0 + q * kGlNumberThreads;
+            at[q] = j < n ? lead[(pl[q] & kGlLeader) ? j : (j & ~63) + (pl[q] >> 8)] + ((pl[q] & kGlLeader) ? 0 : (pl[q] & 0x7F)) : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int j = j0 + q * kGlNumberThreads;
+            if (j < n) order[(int)s_size[cluster_of(t[q])] + at[q]] = j;
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
-// sum: Eq. 3.  16 lanes per cluster, members in row order, four rows in flight.
+// sum: Eq. 3.  16 lanes per cluster, members in row order.
 template <typename TO>
 __global__ __launch_bounds__(256) void glob_sum_kernel(GlobParams p) {
     const int bh = blockIdx.y, b = bh / p.Hkv, h = bh - b * p.Hkv;
@@ -600,21 +726,30 @@ __global__ __launch_bounds__(256) void glob_sum_kernel(GlobParams p) {
     float ka[8], va[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) ka[e] = va[e] = 0.f;
-    for (int t0 = 0; t0 < size; t0 += 4) {
-        float kk[4][8], vv[4][8];
+    const int first_lane = (threadIdx.x & (kWave - 1)) & ~15;
+    constexpr int kRows = 8;      // in flight: a cluster of a hundred rows is the kernel's tail, its trips to memory are what that costs
+    for (int t0 = 0; t0 < size; t0 += 16) {
+        const int members = min(16, size - t0);
+        const int mine = (c < members) ? order[t0 + c] : 0;      // sixteen members in one load
+        for (int u0 = 0; u0 < members; u0 += kRows) {
+            uint4 kk[kRows], vv[kRows];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (t0 + u < size) {
-                const int64_t row = order[t0 + u];
-                load8(Kbh + row * p.stride_n, kk[u]);
-                load8(Vbh + row * p.stride_n, vv[u]);
+            for (int u = 0; u < kRows; ++u) {
+                const int64_t row = __shfl(mine, first_lane + u0 + u, kWave);
+                if (u0 + u < members) {
+                    kk[u] = *reinterpret_cast<const uint4 *>(Kbh + row * p.stride_n);
+                    vv[u] = *reinterpret_cast<const uint4 *>(Vbh + row * p.stride_n);
+                }
             }
-        }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (t0 + u < size) {
+            for (int u = 0; u < kRows; ++u) {
+                if (u0 + u < members) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) { ka[e] += kk[u][e]; va[e] += vv[u][e]; }
+                    for (int e = 0; e < 4; ++e) {
+                        ka[2 * e] += bf16_lo(dword_of(kk[u], e)); ka[2 * e + 1] += bf16_hi(dword_of(kk[u], e));
+                        va[2 * e] += bf16_lo(dword_of(vv[u], e)); va[2 * e + 1] += bf16_hi(dword_of(vv[u], e));
+                    }
+                }
             }
         }
     }
@@ -645,10 +780,10 @@ static bool glob_fast_ok(const GscMergeArgs &a) {
            tuning().gsc_fast_path != 0;
 }
 static size_t glob_head_bytes(int N_max) {   // upper bound of what launch_gsc_global lays out per (sequence, head)
-    const size_t nbp = (size_t)(N_max + kGlBlock - 1) / kGlBlock, npad = nbp * kGlBlock;
+    const size_t nbp = (size_t)(N_max + kGlBlock - 1) / kGlBlock, npad = nbp * kGlBlock, nseg = (nbp + kGlSegment - 1) / kGlSegment;
     const size_t tri = 64 * nbp * (nbp + 1) / 2;
-    return 6 * align_up(npad * 4, 256) + 2 * align_up(tri * 8, 256) + align_up((npad + 1) * 4, 256) + align_up(nbp * nbp, 256) +
-           align_up(npad * kGlList * 4, 256);
+    return 6 * align_up(npad * 4, 256) + 2 * align_up(tri * 8, 256) + align_up((npad + 1) * 4, 256) + 2 * align_up(nbp * nseg * 8, 256) +
+           align_up(nbp * 16, 256);
 }
 // workspace: [one-chunk offsets and counts | the larger of (ordinary sc_gsc_merge workspace, arrays of this path)]
 static size_t glob_prefix_bytes(int B) { return align_up((size_t)B * 3 * 4, 256); }
@@ -689,15 +824,18 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     p.rinv = reinterpret_cast<float *>(rest + o); o += align_up(npad * 4 * BH, 256);
     p.Y = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.tri * 8 * BH, 256);
     p.U = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.tri * 8 * BH, 256);
-    p.cid = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
-    p.rank = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
+    p.join = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
+    p.place = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
+    p.lead = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
     p.order = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
     p.mbase = reinterpret_cast<int32_t *>(rest + o); o += align_up((npad + 1) * 4 * BH, 256);
     p.csize = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
     p.nclusters = reinterpret_cast<int32_t *>(rest + o); o += align_up(4 * BH, 256);
-    p.uflag = reinterpret_cast<unsigned char *>(rest + o); o += align_up((size_t)p.nbp * p.nbp * BH, 256);
-    p.lists = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * kGlList * 4 * BH, 256);
-    p.lcount = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
+    p.nseg = (p.nbp + kGlSegment - 1) / kGlSegment;
+    p.tany = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * p.nseg * 8 * BH, 256);
+    p.tuns = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * p.nseg * 8 * BH, 256);
+    p.state = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * 16 * BH, 256);
+    p.polls = tuning().global_polls;
 
     hipLaunchKernelGGL(glob_norms_kernel, dim3((unsigned)(npad / 16), (unsigned)BH), dim3(256), 0, stream, p);
     hipError_t e = hipGetLastError();
@@ -708,7 +846,7 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     hipLaunchKernelGGL(glob_pairs_kernel, dim3((unsigned)items, (unsigned)BH), dim3(kGlPairWaves * kWave), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(glob_lists_kernel, dim3((unsigned)p.nbp, (unsigned)BH), dim3(kWave), 0, stream, p);
+    hipLaunchKernelGGL(glob_decide_kernel, dim3((unsigned)(p.nbp * BH)), dim3(kWave), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t dyn = npad * sizeof(unsigned short);
@@ -721,12 +859,12 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
         if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         std::lock_guard<std::mutex> lock(mu);
         if (!raised[dev]) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(glob_resolve_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(glob_number_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
             if (e != hipSuccess) return e;
             raised[dev] = true;
         }
     }
-    hipLaunchKernelGGL(glob_resolve_kernel, dim3((unsigned)BH), dim3(kGlResolveThreads), dyn, stream, p);
+    hipLaunchKernelGGL(glob_number_kernel, dim3((unsigned)BH), dim3(kGlNumberThreads), dyn, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int max_clusters = a.N_max < a.cap ? a.N_max : a.cap;

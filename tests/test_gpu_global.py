@@ -127,6 +127,21 @@ def test_more_candidates_than_a_list_holds_and_none_is_a_seed():
     assert ref["cid"][150] == ref["cid"][70] and ref["cid"][3] == ref["cid"][0] and ref["cid"][150] != ref["cid"][0]
 
 
+@pytest.mark.parametrize("n,tau,polls", [(1000, 0.25, 4096), (1000, 0.25, 0), (3000, 0.9745, 0), (64 * 64 + 65, 0.3, 4096), (700, 0.7, 0)])
+def test_blocks_that_wait_for_others(n, tau, polls):
+    # thresholds that random rows exceed: nearly every block has candidates in many earlier ones (batches of words, words
+    # of flags beyond the first); without patience the ordered pass finishes the blocks, with the same outcome
+    w = wl.get_workload("layer32k")
+    old = sc.tune_get("global_polls")
+    try:
+        sc.tune_set("global_polls", polls)
+        case = _global_case(w, tau, n_max=n, heads=2)
+        out = g.check_compress(case)
+    finally:
+        sc.tune_set("global_polls", old)
+    print("n=%d tau=%g polls=%d rows %s" % (n, tau, polls, out["comp_lens"].tolist()))
+
+
 def test_zero_rows_duplicates_and_scaled_rows():
     # zero rows resemble nothing (also inside a block and across blocks), exact duplicates and scaled copies merge
     rng = np.random.default_rng(5)
