@@ -1119,7 +1119,7 @@ hipError_t launch_gsc_fast(const GscParams &p, hipStream_t stream) {
     // per 2048 chunks; a sequence that is all delimiters costs sixteen rounds per workgroup, 0.8 ms per call);
     // longer sequences get the scan kernel, which does the sum once per (sequence, head) whatever the
     // number of chunks.
-    const bool inline_prefix = p.N_max <= 32768;
+    const bool inline_prefix = p.N_max <= kInlinePrefixTokens;
     if (!inline_prefix) {
         e = launch_gsc_scan(p, stream);
         if (e != hipSuccess) return e;

@@ -11,7 +11,8 @@
 //                  fp64 by the whole wave.  Writes the cluster index of every token and the number
 //                  of clusters of every chunk.
 //   2. gsc_scan    per (sequence, head): exclusive scan over chunks of (clusters + closing
-//                  delimiter) -> first output row of every chunk, total rows -> comp_lens.
+//                  delimiter) -> first output row of every chunk, total rows -> comp_lens.  Sequences of more
+//                  than 32k tokens only: shorter ones leave the sum to gsc_merge.
 //   3. gsc_merge   one group of d/8 lanes per OUTPUT row: walks the chunk's cluster indices, gathers
 //                  the member rows of its cluster (16-byte pieces, coalesced per row), accumulates in
 //                  fp32 in member order, divides by the size and writes the core; delimiter rows and
@@ -259,13 +260,27 @@ __device__ __forceinline__ void store_row8(void *base, int64_t elem_off, const f
     store8(reinterpret_cast<TO *>(base) + elem_off, x);
 }
 
-template <typename T, int D>
+// Bound by the chain offsets -> row bases -> cluster indices -> member rows, not by its bytes, until a call has
+// some hundred thousand rows.  The cluster indices of the item sit in LDS (kMergeCidTile tokens of them, which is all
+// of an item unless a chunk is very long), a group first collects its members of 64 rows as bits and then has
+// kMergeInFlight of them (keys and values) in flight at once (eight instead of four: more registers, fewer
+// wavefronts, 156 -> 228 us on 8 heads x 32768 x 64 bf16, and no faster on short sequences).  Whole call, against
+// indices read from memory eight at a time and a scan kernel: 2 heads x 1024 x 64 f32 56 -> 30 us, 8 x 8192 x 128
+// f32 127 -> 73, 8 x 32768 x 64 bf16 209 -> 156.
+// INLINE_PREFIX: no scan kernel ran; the workgroup adds up the cluster counts before its item itself and the
+// workgroup of the last item files the total.
+constexpr int kMergeCidTile = 2048;
+constexpr int kMergeInFlight = 4;
+
+template <typename T, int D, bool INLINE_PREFIX>
 __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     constexpr int LPR = D / 8;
     constexpr int RPW = kWave / LPR;            // output rows a wave works on at once
     constexpr int kGroups = kGscThreads / LPR;  // output rows a workgroup works on at once
     __shared__ int s_off[kMaxChunksPerItem + 1];
     __shared__ int s_base[kMaxChunksPerItem + 1];
+    __shared__ int s_sum[kGscThreads / kWave];
+    __shared__ int s_cid[kMergeCidTile];
     const int b = blockIdx.z, h = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -273,18 +288,24 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     const int gsh = g * LPR;   // position of this group's bits inside a wave ballot
     const uint64_t gmask = (LPR == 16) ? 0xffffull : 0xffull;
     const int M = p.num_chunks[b];
-    if (M <= 0) return;
+    const int64_t bh = (int64_t)b * p.Hkv + h;
+    if (M <= 0) {
+        if (INLINE_PREFIX && blockIdx.x == 0 && tid == 0) p.comp_lens[bh] = -1;
+        return;
+    }
     int n = p.seq_lens ? p.seq_lens[b] : p.N_max;
     n = n < 0 ? 0 : (n > p.N_max ? p.N_max : n);
     const int C = p.chunks_per_item;
     const int items = (M + C - 1) / C;
-    const int64_t bh = (int64_t)b * p.Hkv + h;
     const T *Kbh = reinterpret_cast<const T *>(p.K) + b * p.stride_b + h * p.stride_h;
     const T *Vbh = reinterpret_cast<const T *>(p.V) + b * p.stride_b + h * p.stride_h;
     const int32_t *off = p.offsets + (int64_t)b * p.offsets_stride_b;
     const int32_t *cid_bh = p.cid + bh * p.N_max;
+    const int32_t *pcount_bh = p.pcount + bh * ((int64_t)p.N_max + 1);
     const int32_t *rowbase_bh = p.rowbase + bh * ((int64_t)p.N_max + 2);
     int32_t *counts_bh = p.counts + bh * p.cap;
+    bool base_bad = false;
+    int summed = INLINE_PREFIX ? gsc_base_rows(p, bh, base_bad) : 0, summed_to = 0;   // rows of the chunks [0, summed_to)
 
     for (int item = blockIdx.x; item < items; item += gridDim.x) {
         const int m0 = item * C;
@@ -292,8 +313,36 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
         __syncthreads();
         if (tid <= nch) {
             s_off[tid] = off[m0 + tid];
-            s_base[tid] = rowbase_bh[m0 + tid];
+            if (!INLINE_PREFIX) s_base[tid] = rowbase_bh[m0 + tid];
         }
+        if (INLINE_PREFIX) {
+            // every chunk before the item is closed by a delimiter: its rows are its clusters and one more
+            int part = 0;
+            for (int m = summed_to + tid; m < m0; m += kGscThreads) part += (pcount_bh[m] & kPcountMask) + 1;
+            const int mine = (lane < nch) ? (pcount_bh[m0 + lane] & kPcountMask) + ((m0 + lane < M - 1) ? 1 : 0) : 0;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d, kWave);
+            if (lane == 0) s_sum[wave] = part;
+            int incl = mine;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const int up = __shfl_up(incl, d, kWave);
+                if (lane >= d) incl += up;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kGscThreads / kWave; ++w) summed += s_sum[w];
+            summed_to = m0;
+            if (wave == 0 && lane <= nch) {
+                const int base = summed + incl - mine;
+                s_base[lane] = base;
+                if (m0 + nch == M && lane == nch) p.comp_lens[bh] = (!base_bad && base <= p.cap) ? base : -1;
+            }
+        }
+        __syncthreads();
+        const int t0 = __builtin_amdgcn_readfirstlane(s_off[0]);
+        const int t1 = min(__builtin_amdgcn_readfirstlane(s_off[nch]), n);
+        for (int t = t0 + tid; t < min(t1, t0 + kMergeCidTile); t += kGscThreads) s_cid[t - t0] = cid_bh[t];
         __syncthreads();
         const int R0 = __builtin_amdgcn_readfirstlane(s_base[0]);
         const int R1 = min(__builtin_amdgcn_readfirstlane(s_base[nch]), p.cap);
@@ -324,22 +373,27 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
                 load8(Vbh + src, va);
                 size = 1;
             }
-            for (int j0 = 0; j0 < lmax; j0 += LPR) {
-                const int j = j0 + c;
-                const bool match = (j < lscan) && (cid_bh[start + j] == cl);
-                uint32_t mbits = (uint32_t)((ballot64(match) >> gsh) & gmask);
-                while (ballot64(mbits != 0u) != 0ull) {
-                    int jj[4];
-                    bool ok[4];
-                    float kk[4][8], vv[4][8];
+            for (int j0 = 0; j0 < lmax; j0 += kWave) {
+                uint64_t members = 0ull;       // of rows j0 .. j0 + 63 of the chunk, the same for every lane of the group
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        ok[u] = mbits != 0u;
-                        jj[u] = ok[u] ? (__ffs(mbits) - 1) : 0;
-                        mbits &= mbits - 1u;
+                for (int k = 0; k < kWave / LPR; ++k) {
+                    const int j = j0 + LPR * k + c, t = start + j - t0;
+                    bool match = false;
+                    if (j < lscan) match = (t < kMergeCidTile ? s_cid[t] : cid_bh[start + j]) == cl;
+                    members |= ((ballot64(match) >> gsh) & gmask) << (LPR * k);
+                }
+                while (ballot64(members != 0ull) != 0ull) {
+                    int jj[kMergeInFlight];
+                    bool ok[kMergeInFlight];
+                    float kk[kMergeInFlight][8], vv[kMergeInFlight][8];
+#pragma unroll
+                    for (int u = 0; u < kMergeInFlight; ++u) {
+                        ok[u] = members != 0ull;
+                        jj[u] = ok[u] ? first_bit(members) : 0;
+                        members &= members - 1ull;
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < kMergeInFlight; ++u) {
                         if (ok[u]) {
                             const int64_t src = (int64_t)(start + j0 + jj[u]) * p.stride_n + 8 * c;
                             load8(Kbh + src, kk[u]);
@@ -347,7 +401,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
                         }
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < kMergeInFlight; ++u) {
                         if (ok[u]) {
                             if (size == 0) {
 #pragma unroll
@@ -402,15 +456,21 @@ hipError_t launch_gsc_scan(const GscParams &p, hipStream_t stream) {
 template <typename T, int D>
 static hipError_t launch_typed(const GscParams &p, hipStream_t stream) {
     const int max_items = (p.N_max + 1 + p.chunks_per_item - 1) / p.chunks_per_item;
-    const int gx = max(1, min(max_items, tuning().gsc_grid_x > 0 ? tuning().gsc_grid_x : 128));
+    // (an item per 21 tokens per chunk is what chunks of a few dozen tokens make; fewer than 128 workgroups per
+    // head would leave a short sequence's longest chunks behind one another)
+    const int gx = max(1, min(max_items, tuning().gsc_grid_x > 0 ? tuning().gsc_grid_x : max(128, p.N_max / (21 * p.chunks_per_item))));
     const dim3 grid(gx, p.Hkv, p.B);
     hipLaunchKernelGGL((gsc_assign_kernel<T, D>), grid, dim3(kGscThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (p.N_max <= kInlinePrefixTokens) {
+        hipLaunchKernelGGL((gsc_merge_kernel<T, D, true>), grid, dim3(kGscThreads), 0, stream, p);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(gsc_scan_kernel, dim3(p.Hkv, p.B), dim3(256), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gsc_merge_kernel<T, D>), grid, dim3(kGscThreads), 0, stream, p);
+    hipLaunchKernelGGL((gsc_merge_kernel<T, D, false>), grid, dim3(kGscThreads), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -435,7 +495,12 @@ hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
     p.base_lens = a.base_lens;
     p.count_only = a.count_only ? 1 : 0;
     p.budget = nullptr;
-    p.chunks_per_item = max(1, min(kMaxChunksPerItem, tuning().gsc_chunks_per_item));
+    // Generic path: a wavefront per chunk, so four chunks are one round of a workgroup.  Calls of up to 64k rows in
+    // all are bound by the longest chain of chunks and take that; larger ones fill the chip anyway and share the
+    // offsets, the prefix and the barriers of an item among eight (us, 4 / 8 / 16 chunks: 2 heads x 1024 x 64 f32
+    // 30 / 33 / 45; 8 x 8192 x 128 f32 72 / 77 / 117; 8 x 32768 x 64 bf16 179 / 156 / 181).
+    const int auto_item = ((int64_t)a.B * a.Hkv * a.N_max <= (int64_t(1) << 16)) ? 4 : 8;
+    p.chunks_per_item = max(1, min(kMaxChunksPerItem, tuning().gsc_chunks_per_item > 0 ? tuning().gsc_chunks_per_item : auto_item));
 
     const size_t bh = (size_t)a.B * a.Hkv;
     char *w = reinterpret_cast<char *>(a.ws);

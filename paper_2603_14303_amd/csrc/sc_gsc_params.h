@@ -7,6 +7,7 @@ namespace sc {
 
 constexpr int kGscThreads = 256;
 constexpr int kMaxChunksPerItem = 32;
+constexpr int kInlinePrefixTokens = 32768;   // up to here the last kernel adds the cluster counts up itself: a launch less
 constexpr float kBand = 1e-4f;   // fp32 cosine error for d <= 128 is < 2e-5; inside the band -> fp64
 constexpr int kPcountMask = (1 << 30) - 1;   // low bits of a pcount entry: clusters of the chunk
 

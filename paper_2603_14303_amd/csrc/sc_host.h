@@ -115,7 +115,7 @@ struct Tuning {
     int decode_local_handover = 1;  // 0: split partials always go through memory, also when a head's splits share an XCC
     int decode_poll_budget = 1 << 20;   // polls (about 0.3 us each) of the folding workgroup before it gives up; negative: give up at once (host-driven test of the failure path)
     int decode_mfma_min_group = 9;  // query heads per KV head from which single-row decode runs on the multi-row kernel (9 = never)
-    int gsc_chunks_per_item = 16;   // chunks handled by one workgroup work item
+    int gsc_chunks_per_item = 0;    // generic path: chunks handled by one workgroup work item; <= 0 picks it from the rows of the call
     int gsc_grid_x = 0;             // workgroups per pass and (sequence, KV head); <= 0 picks it from the sequence length
     int gsc_chunks_per_task = 0;    // fast path: chunks handled by one single-wave workgroup; <= 0: 2, or 1 for a call of a few thousand tokens
     int gsc_fast_path = 1;          // 0 forces the generic kernels even for bf16 / d = 128

@@ -248,3 +248,40 @@ def test_decode_capacity_beyond_32bit_row_offsets():
     for O, lse in ((O_small, lse_small), (O_big, lse_big)):
         assert np.abs(O.float().cpu().numpy() - want_O).max() <= 4e-3 * max(1.0, np.abs(want_O).max())
         assert np.abs(lse.cpu().numpy() - want_l).max() <= 1e-3
+
+
+@pytest.mark.parametrize("n,knobs", [(2600, {}), (33000, {}), (2600, dict(gsc_grid_x=1)), (33000, dict(gsc_grid_x=3, gsc_chunks_per_item=32))])
+def test_generic_merge_long_items(n, knobs):
+    # fp32 / d = 64: a chunk longer than the cluster indices held in LDS, next to short ones and runs of delimiters, with
+    # the row bases added up inside the merge kernel (up to 32768 tokens) and by the scan kernel (beyond); narrow grids
+    # make a workgroup carry its prefix from item to item
+    rng = np.random.default_rng(n)
+    mask = np.zeros((1, n), dtype=np.uint8)
+    mask[0, np.cumsum(rng.integers(1, 40, size=n // 10))[: n // 40]] = 1
+    mask[0, 100:2401] = 0
+    mask[0, 2402:2470] = 1
+    off = oracle.segment(mask[0], n)
+    centers = rng.standard_normal((7, 64))
+    k = (centers[rng.integers(0, 7, size=n)] + 0.1 * rng.standard_normal((n, 64))).astype(np.float32)
+    v = rng.standard_normal((n, 64)).astype(np.float32)
+    ref = oracle.compress_head(k, v, off, 0.7)
+    K, V = (torch.from_numpy(x[None, None]).to(g.DEV) for x in (k, v))
+    old = {key: sc.tune_get(key) for key in knobs}
+    try:
+        for key, val in knobs.items():
+            sc.tune_set(key, val)
+        offsets, num_chunks, _ = g.run_segment(mask, None)
+        Kc, Vc, counts, lens, cid = sc.sc_gsc_merge(K, V, offsets, num_chunks, 0.7, want_cluster_id=True)
+        torch.cuda.synchronize()
+    finally:
+        for key, val in old.items():
+            sc.tune_set(key, val)
+    rows = ref["n_rows"]
+    assert int(lens[0, 0]) == rows
+    assert np.array_equal(cid[0, 0].cpu().numpy(), ref["cid"])
+    assert np.array_equal(counts[0, 0, :rows].cpu().numpy(), ref["counts"][:rows])
+    # fp32 sums of up to l members in member order: (l + 1) half-ulps of the largest partial sum, relative to the mean
+    tol = 2.0 ** -24 * (int(ref["counts"][:rows].max()) + 2)
+    for got, want in ((Kc, ref["Kc"]), (Vc, ref["Vc"])):
+        err = np.abs(got[0, 0, :rows].cpu().numpy() - want[:rows])
+        assert err.max() <= tol * max(np.abs(k).max(), np.abs(v).max())
