@@ -175,7 +175,8 @@ __device__ __forceinline__ void store16_stream(void *p, const uint4 &v) {
 }
 __device__ __forceinline__ int first_bit(uint64_t m) { return __ffsll((unsigned long long)m) - 1; }
 
-// fp64 sum over the wave, every lane gets the total: DPP moves inside the rows of 16 lanes and row
+// fp64 sums over the 16 lanes of a row, over the four lanes at one position of the rows, and over the wave, every
+// lane gets its total: DPP moves inside the rows of 16 lanes and row
 // swaps across them, on the two halves of the value (a __shfl_xor butterfly on doubles is twelve trips
 // through the LDS crossbar)
 template <int CTRL>
@@ -185,11 +186,14 @@ __device__ __forceinline__ double dpp_f64(double x) {
     const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
-__device__ __forceinline__ double wave_allreduce_sum(double x) {
+__device__ __forceinline__ double row_allreduce_sum(double x) {
     x += dpp_f64<kDppQuadXor1>(x);
     x += dpp_f64<kDppQuadXor2>(x);
     x += dpp_f64<kDppHalfMirror>(x);
     x += dpp_f64<kDppMirror>(x);
+    return x;
+}
+__device__ __forceinline__ double rows_allreduce_sum(double x) {
     {
         const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
         const auto l = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
@@ -206,5 +210,6 @@ __device__ __forceinline__ double wave_allreduce_sum(double x) {
     }
     return x;
 }
+__device__ __forceinline__ double wave_allreduce_sum(double x) { return rows_allreduce_sum(row_allreduce_sum(x)); }
 
 }  // namespace sc

@@ -48,8 +48,7 @@ __device__ __forceinline__ uint64_t bits_below(int x) {   // bits [0, x), 0 <= x
 // LDS layout of a wavefront
 constexpr int kLdsRowBytes = 272;                         // 256 B of keys + 16 B pad: conflict-free tile reads
 constexpr int kLdsRinvOff = kWin * kLdsRowBytes;          // 64 reciprocal norms
-constexpr int kLdsBitsOff = kLdsRinvOff + 256;            // per row: yes lo/hi, unsure lo/hi (16 B)
-constexpr int kLdsIdxOff = kLdsBitsOff + kWin * 16;       // 64 output-index bytes
+constexpr int kLdsIdxOff = kLdsRinvOff + 256;             // 64 output-index bytes
 constexpr int kLdsSeedRinvOff = kLdsIdxOff + 64;          // reciprocal norms of the first 16 seeds of a long chunk
 constexpr int kLdsWaveBytes = kLdsSeedRinvOff + 64;
 
@@ -98,25 +97,20 @@ __device__ __forceinline__ void load_rows(RowRegs &x, const RowSource &rs) {
     }
 }
 
-// fp64 re-evaluation of one (seed, candidate) pair by the whole wave: Eq. 2 in double precision
-__device__ __forceinline__ bool cosine_exceeds_f64_fast(const bf16_t *seed_row, const bf16_t *cand_row, float tau, int lane) {
-    double dot = 0.0, ss = 0.0, cc = 0.0;
+// eight elements of two rows into the sums of Eq. 2 in double precision (products of bf16 values are exact there)
+__device__ __forceinline__ void cosine_sums_f64(const uint4 &a, const uint4 &b, double &dot, double &aa, double &bb) {
 #pragma unroll
-    for (int k = 0; k < kFastD / kWave; ++k) {
-        const int e = (lane & (kWave - 1)) + k * kWave;
-        const double s = load1_f64(seed_row + e), c = load1_f64(cand_row + e);
-        dot += s * c; ss += s * s; cc += c * c;
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t wa = dword_of(a, k), wb = dword_of(b, k);
+        const double a0 = (double)__uint_as_float(wa << 16), a1 = (double)__uint_as_float(wa & 0xFFFF0000u);
+        const double b0 = (double)__uint_as_float(wb << 16), b1 = (double)__uint_as_float(wb & 0xFFFF0000u);
+        dot += a0 * b0; aa += a0 * a0; bb += b0 * b0;
+        dot += a1 * b1; aa += a1 * a1; bb += b1 * b1;
     }
-    dot = wave_allreduce_sum(dot);
-    ss = wave_allreduce_sum(ss);
-    cc = wave_allreduce_sum(cc);
-    return dot / (sqrt(ss) * sqrt(cc)) > (double)tau;   // NaN compares false
 }
-
-// the same for two rows of the window / block parked in LDS by gram_bitmatrix (the parked bf16 values are
-// the inputs themselves, so the result is the same; the rows come back in a tenth of the time of a
-// trip to memory, which matters when tau lies inside the band of the similarities and many pairs are redone)
-__device__ __forceinline__ bool cosine_exceeds_f64_lds(const char *lds, int row_a, int row_b, float tau, int lane);
+__device__ __forceinline__ bool cosine_exceeds_f64(double dot, double aa, double bb, float tau) {
+    return dot / (sqrt(aa) * sqrt(bb)) > (double)tau;   // NaN compares false
+}
 
 __device__ __forceinline__ float safe_rinv(float nsq) {
     // a norm that is zero, denormal, huge or not a number makes every cosine with that row "unsure"
@@ -337,11 +331,9 @@ __device__ __forceinline__ void gram_bitmatrix(char *lds, const RowRegs &x, int 
                                                uint64_t &yes_row, uint64_t &unsure_row) {
     const int g = lane >> 4, c = lane & 15;
     float *s_rinv = reinterpret_cast<float *>(lds + kLdsRinvOff);
-    uint32_t *s_bits = reinterpret_cast<uint32_t *>(lds + kLdsBitsOff);
 #pragma unroll
     for (int t = 0; t < 16; ++t)
         *reinterpret_cast<uint4 *>(lds + (4 * t + g) * kLdsRowBytes + 16 * c) = x.r[t];
-    *reinterpret_cast<uint4 *>(s_bits + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
     wave_lds_fence();
 
     const int nt = (R + 15) >> 4;   // 16-row tiles in use
@@ -422,6 +414,7 @@ __device__ __forceinline__ void gram_bitmatrix(char *lds, const RowRegs &x, int 
     if (ballot64(close) != 0ull) {
         // the same products and bounds as above, so that "yes", "no" and "unsure" partition the pairs
         constexpr int base[4] = {0, 4, 7, 9};
+        uint32_t ul = 0u, uh = 0u;
 #pragma unroll
         for (int J = 0; J < 4; ++J) {
             uint32_t u0 = 0u, u1 = 0u;
@@ -439,13 +432,12 @@ __device__ __forceinline__ void gram_bitmatrix(char *lds, const RowRegs &x, int 
                 }
             }
             if (J < nt) {
-                __hip_atomic_fetch_or(s_bits + 4 * (16 * J + c) + 2, u0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                __hip_atomic_fetch_or(s_bits + 4 * (16 * J + c) + 3, u1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                u0 = or_rows(u0);
+                u1 = (nt > 2) ? or_rows(u1) : 0u;
+                if (g == J) { ul = u0; uh = u1; }
             }
         }
-        wave_lds_fence();
-        const uint2 w = *reinterpret_cast<const uint2 *>(s_bits + 4 * lane + 2);
-        unsure_row = ((uint64_t)w.y << 32) | w.x;
+        unsure_row = ((uint64_t)uh << 32) | ul;
     } else {
         unsure_row = 0ull;
     }
@@ -454,19 +446,36 @@ __device__ __forceinline__ void gram_bitmatrix(char *lds, const RowRegs &x, int 
     wave_lds_fence();   // the LDS area is reused by the next window
 }
 
-__device__ __forceinline__ bool cosine_exceeds_f64_lds(const char *lds, int row_a, int row_b, float tau, int lane) {
-    double dot = 0.0, ss = 0.0, cc = 0.0;
+// Pairs (other, j), one for every lane j in `todo` (`other` is that lane's own value): returns the lanes whose pair is
+// above tau in fp64.  Both rows are parked in LDS by gram_bitmatrix (the parked bf16 values are the inputs themselves).
+// A pair takes the 16 lanes of a row, so four are settled at once: the chain of a pair (two LDS reads, the sums, two
+// square roots and a division) is long, and a threshold inside the band of the similarities asks for many.  Whole calls, one
+// pair at a time on all 64 lanes before: 4 x 8 heads x 32768 tokens, tau 0.979, 293.9 -> 291.3 us; twelve counting probes
+// and a merge of 8 x 32768 481.4 -> 476.2 us.
+__device__ __forceinline__ uint64_t settle_pairs_f64(const char *lds, uint64_t todo, int other, float tau, int lane) {
+    const int g = lane >> 4, c = lane & 15;
+    uint64_t above = 0ull;
+    while (todo != 0ull) {
+        int at[4];
 #pragma unroll
-    for (int k = 0; k < kFastD / kWave; ++k) {
-        const int e = (lane & (kWave - 1)) + k * kWave;
-        const double a = load1_f64(reinterpret_cast<const bf16_t *>(lds + row_a * kLdsRowBytes) + e);
-        const double b = load1_f64(reinterpret_cast<const bf16_t *>(lds + row_b * kLdsRowBytes) + e);
-        dot += a * b; ss += a * a; cc += b * b;
+        for (int q = 0; q < 4; ++q) {
+            at[q] = (todo != 0ull) ? first_bit(todo) : at[0];     // (a short last round repeats its first pair)
+            todo &= todo - 1ull;
+        }
+        const int j = (g == 0) ? at[0] : ((g == 1) ? at[1] : ((g == 2) ? at[2] : at[3]));
+        const int i = lane_gather(other, j);
+        const uint4 a = *reinterpret_cast<const uint4 *>(lds + i * kLdsRowBytes + 16 * c);
+        const uint4 b = *reinterpret_cast<const uint4 *>(lds + j * kLdsRowBytes + 16 * c);
+        double dot = 0.0, aa = 0.0, bb = 0.0;
+        cosine_sums_f64(a, b, dot, aa, bb);
+        dot = row_allreduce_sum(dot);
+        aa = row_allreduce_sum(aa);
+        bb = row_allreduce_sum(bb);
+        const uint64_t yes = ballot64(cosine_exceeds_f64(dot, aa, bb, tau));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) above |= ((yes >> (16 * q)) & 1ull) << at[q];
     }
-    dot = wave_allreduce_sum(dot);
-    ss = wave_allreduce_sum(ss);
-    cc = wave_allreduce_sum(cc);
-    return dot / (sqrt(ss) * sqrt(cc)) > (double)tau;   // NaN compares false
+    return above;
 }
 
 // Alg. 1 over the open rows of a window or block without walking the seeds one by one.  Seeds are taken in row
@@ -497,22 +506,17 @@ __device__ __forceinline__ bool first_fit_fixed_point(const char *lds, uint64_t 
         const uint64_t mine = ye & S;                                   // not empty unless the row is a seed
         const int first = is_seed ? lane : first_bit(mine);
         const uint64_t doubt = ue & S & (is_seed ? ~0ull : bits_below(first & 63));
-        uint64_t doubtful = ballot64(is_open && doubt != 0ull);
+        const uint64_t doubtful = ballot64(is_open && doubt != 0ull);
         if (doubtful == 0ull) {
             seeds = S;
             my_seed = is_open ? first : -1;
             return true;
         }
         const int sd_mine = first_bit(doubt);
-        while (doubtful != 0ull) {
-            const int j = first_bit(doubtful);
-            doubtful &= doubtful - 1ull;
-            const int sd = __builtin_amdgcn_readlane(sd_mine, j);
-            const bool res = cosine_exceeds_f64_lds(lds, sd, j, tau, lane);
-            if (lane == j) {
-                ue &= ~(1ull << sd);
-                if (res) ye |= 1ull << sd;
-            }
+        const uint64_t above = settle_pairs_f64(lds, doubtful, sd_mine, tau, lane);
+        if ((doubtful >> lane) & 1ull) {
+            ue &= ~(1ull << sd_mine);
+            if ((above >> lane) & 1ull) ye |= 1ull << sd_mine;
         }
     }
     return false;
@@ -665,14 +669,9 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
                     const bool is_seed = open && (s == lane);
                     const bool cand = open && (s != lane);
                     bool yes = cand && ((yes_row >> (s & 63)) & 1ull);
-                    uint64_t recheck = ballot64(cand && ((unsure_row >> (s & 63)) & 1ull));
-                    while (recheck != 0ull) {
-                        const int j = __builtin_amdgcn_readfirstlane(first_bit(recheck));
-                        recheck &= recheck - 1ull;
-                        const int sj = __builtin_amdgcn_readlane(s, j);
-                        const bool res = cosine_exceeds_f64_lds(s_lds, sj, j, tau, lane);
-                        if (lane == j) yes = res;
-                    }
+                    const uint64_t recheck = ballot64(cand && ((unsure_row >> (s & 63)) & 1ull));
+                    const uint64_t above = settle_pairs_f64(s_lds, recheck, s, tau, lane);
+                    yes = yes || ((above >> lane) & 1ull);
                     const uint64_t seeds_now = ballot64(is_seed);
                     const uint64_t got = ballot64(yes);
                     if (is_seed || yes) my_seed = s;
@@ -727,7 +726,6 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
                     const int g = lane >> 4, c = lane & 15;
                     const int R = min(kWin, l - rb);
                     const int nt = (R + 15) >> 4;
-                    const bf16_t *block0 = Kbh + (int64_t)(start + rb) * p.stride_n;
                     uint64_t yes_row, unsure_row;
                     {
                         RowRegs x;
@@ -804,20 +802,36 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
                         uint32_t cyes = open ? (cw & valid) : 0u;
                         uint32_t cuns = open ? ((cw >> 16) & valid) : 0u;
                         // first fit over the seeds of the group; a pair inside the band is settled in fp64
-                        // when it is the first candidate of its row
+                        // when it is the first candidate of its row.  The keys of seed c are in the registers of
+                        // the four lanes (c, g) and the rows in LDS, so every seed settles one row at a time
+                        // (before: one pair at a time, through the seed list to two rows in memory).
                         for (;;) {
                             const uint32_t pend = cyes | cuns;
                             const int f = (pend != 0u) ? (__ffs(pend) - 1) : -1;
                             const uint64_t need = ballot64(f >= 0 && ((cuns >> (f & 31)) & 1u));
                             if (need == 0ull) break;
-                            const int j = __builtin_amdgcn_readfirstlane(first_bit(need));
-                            const int fj = __builtin_amdgcn_readlane(f, j);
-                            const int srow = __hip_atomic_load(seed_bh + start + 16 * sg + fj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            const bool res = cosine_exceeds_f64_fast(Kbh + (int64_t)(start + srow) * p.stride_n,
-                                                                     block0 + (int64_t)j * p.stride_n, tau, lane);
-                            if (lane == j) {
-                                cuns &= ~(1u << fj);
-                                if (res) cyes |= 1u << fj;
+                            int row = -1;      // the first row that waits for this lane's seed
+                            for (uint64_t left = need; left != 0ull; left &= left - 1ull) {
+                                const int j = first_bit(left);
+                                const int fj = __builtin_amdgcn_readlane(f, j);
+                                if (row < 0 && fj == c) row = j;
+                            }
+                            double dot = 0.0, ss = 0.0, rr = 0.0;
+#pragma unroll
+                            for (int ks = 0; ks < 4; ++ks) {
+                                const uint4 v = *reinterpret_cast<const uint4 *>(s_lds + max(row, 0) * kLdsRowBytes + (32 * ks + 8 * g) * 2);
+                                uint4 u = sb[ks];
+                                asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w));   // (the seed's doubles stay out of the registers between rounds)
+                                cosine_sums_f64(u, v, dot, ss, rr);
+                            }
+                            dot = rows_allreduce_sum(dot);
+                            ss = rows_allreduce_sum(ss);
+                            rr = rows_allreduce_sum(rr);
+                            const int above = cosine_exceeds_f64(dot, ss, rr, tau) ? 1 : 0;
+                            const int settled = lane_gather(row, max(f, 0)), res = lane_gather(above, max(f, 0));
+                            if (settled == lane) {     // (rows that wait for no seed are nobody's `row`)
+                                cuns &= ~(1u << f);
+                                if (res) cyes |= 1u << f;
                             }
                         }
                         if (cyes != 0u) my_o = 16 * sg + __ffs(cyes) - 1;
@@ -850,13 +864,9 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
                         if (o < 16 && c == o) new_row = i;
                         const bool cand = (todo >> lane) & 1ull;
                         bool yes = cand && ((yes_row >> i) & 1ull);
-                        uint64_t recheck = ballot64(cand && ((unsure_row >> i) & 1ull));
-                        while (recheck != 0ull) {
-                            const int j = __builtin_amdgcn_readfirstlane(first_bit(recheck));
-                            recheck &= recheck - 1ull;
-                            const bool res = cosine_exceeds_f64_lds(s_lds, i, j, tau, lane);
-                            if (lane == j) yes = res;
-                        }
+                        const uint64_t recheck = ballot64(cand && ((unsure_row >> i) & 1ull));
+                        const uint64_t above = settle_pairs_f64(s_lds, recheck, i, tau, lane);
+                        yes = yes || ((above >> lane) & 1ull);
                         const uint64_t got = ballot64(yes);
                         todo &= ~got;
                         if (lane == i || yes) my_o = o;

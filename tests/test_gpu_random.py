@@ -248,3 +248,39 @@ def test_chains_where_every_row_resembles_only_its_neighbours():
             ev = g.rowwise_err(Vc[0, h, :rows].cpu().numpy(), r["Vc"][:rows])
             assert ek <= 1e-3 and ev <= 1e-3, (tau, h, ek, ev)
         print("tau", tau, "rows", clens.cpu().numpy().tolist())
+
+
+@pytest.mark.parametrize("seeds,followers", [(1, 1), (1, 2), (1, 3), (1, 4), (1, 5), (3, 9), (3, 61), (3, 62), (15, 113), (16, 112), (17, 111), (35, 93)])
+def test_rows_at_the_threshold_of_their_seed(seeds, followers):
+    """A chunk opens with `seeds` rows far apart, and every further row has a cosine with one of them that lies at tau
+    to within the rounding of bf16 (about 5e-5): each is settled in fp64 against a seed of its window, of its block,
+    or carried along from an earlier block, alone or with others, and the outcomes differ from row to row."""
+    rng = np.random.default_rng(100 * seeds + followers)
+    d, H, tau, chunks = 128, 2, float(np.float32(0.9)), 6   # (tau travels as fp32: 0.9 itself is 2e-8 off, more than some margins)
+    L = seeds + followers
+    N = chunks * (L + 1)
+    mask = np.zeros((1, N), np.uint8)
+    mask[0, L::L + 1] = 1
+    K = np.zeros((1, H, N, d), np.float32)
+    for h in range(H):
+        for c in range(chunks):
+            basis = np.linalg.qr(rng.standard_normal((d, d)))[0]
+            rows = basis[:L].copy()
+            of = rng.integers(0, seeds, size=followers)
+            rows[seeds:] = tau * basis[of] + np.sqrt(1 - tau * tau) * rows[seeds:]
+            K[0, h, c * (L + 1):c * (L + 1) + L] = rows
+            K[0, h, c * (L + 1) + L] = rng.standard_normal(d)
+    K = wl.round_to_bf16(K * 2.0)
+    V = wl.round_to_bf16(rng.standard_normal((1, H, N, d)).astype(np.float32))
+    dK, dV = g.to_device(K, True), g.to_device(V, True)
+    off, nch, sl = g.check_segment(mask, np.array([N], np.int32))
+    Kc, Vc, counts, clens, cid = sc.sc_gsc_merge(dK, dV, off, nch, tau, seq_lens=sl, out_dtype=torch.float32, want_cluster_id=True)
+    torch.cuda.synchronize()
+    o = oracle.segment(mask[0], N)
+    for h in range(H):
+        r = oracle.compress_head(K[0, h], V[0, h], o, tau)
+        assert r["chunk_margin"].min() > 1e-12, r["chunk_margin"].min()
+        rows = r["n_rows"]
+        assert int(clens[0, h]) == rows, (h, int(clens[0, h]), rows)
+        assert np.array_equal(cid[0, h].cpu().numpy(), r["cid"]), h
+        assert np.array_equal(counts[0, h, :rows].cpu().numpy(), r["counts"][:rows]), h
