@@ -564,8 +564,12 @@ __device__ __forceinline__ void store_sizes(const floatx4_t &Dn, int ot, int n_o
     }
 }
 
-template <typename TO>
-__global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscParams p) {
+// COUNT: a probe of the budget search.  Only the clusters per chunk are wanted: no values are read and nothing is merged,
+// which leaves 146 vector registers instead of 245, so that the LDS of a window (17.8 KB) and not the registers
+// sets the wavefronts per compute unit (nine instead of eight).  Twelve probes and a merge of 8 heads x 32768 tokens:
+// 471.5 us with the merging kernel as the probe and an empty value descriptor, now 457.5.
+template <typename TO, bool COUNT>
+__global__ __launch_bounds__(kFastTaskThreads, COUNT ? 3 : 2) void gsc_compress_kernel(GscParams p) {
     __shared__ __attribute__((aligned(16))) char s_lds[kLdsWaveBytes];
     // One-dimensional grid: workgroup id = (pass * grid_x + x) * (B * Hkv) + (sequence, head).  The
     // workgroups of pass 0 are dispatched first and take the tasks that need more than one window, pass 1
@@ -603,7 +607,6 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
     TO *vtmp_c = reinterpret_cast<TO *>(p.vtmp) + bh * (int64_t)p.N_max * kFastD;
     const int64_t tmp_rows = p.N_max;
     const float tau = p.tau_dev ? *p.tau_dev : p.tau;
-    const bool count_only = p.count_only != 0;
 
     for (int task = wg_x; task < tasks; task += p.grid_x) {
         TaskOffsets to;
@@ -637,11 +640,11 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
                     idx_hi += 1;
                 }
                 const int nchw = idx_hi - idx;
-                RowRegs xk, xv;
+                RowRegs xk;
+                [[maybe_unused]] RowRegs xv;
                 load_rows(xk, row_source(Kbh, p.stride_n, w0, R, g, c));
                 // the values are not needed before the merge: requested now, they arrive under the Gram step
-                // (a counting call reads none: the descriptor is empty and the loads come back as zeros)
-                load_rows(xv, row_source(Vbh, p.stride_n, w0, count_only ? 0 : R, g, c));
+                if constexpr (!COUNT) load_rows(xv, row_source(Vbh, p.stride_n, w0, R, g, c));
                 // chunk range [lo, hi) of every row; a delimiter is a one-row range of its own
                 int lo = lane, hi = lane + 1;
                 bool in_chunk = false;
@@ -688,18 +691,20 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
                     const int ce = __shfl(to.v, min(idx + lane + 1, 63), kWave) - 1 - w0;
                     if (lane < nchw) pcount_bh[m0 + idx + lane] = __popcll(seedmask & bits_range(cs, ce));
                 }
-                // cluster means -> provisional rows [w0, w0 + nseed): keys (back from LDS), then values
-                uint32_t ob[4];
-                orow_to_operand_bytes_lds(s_lds + kLdsIdxOff, my_o, lane, ob);
-                const int q_hi = (R + 15) >> 4;
-                for (int ot = 0; ot * 16 < nseed && !count_only; ++ot) {
-                    floatx4_t DK[8], DV[8], Dn = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (!COUNT) {
+                    // cluster means -> provisional rows [w0, w0 + nseed): keys (back from LDS), then values
+                    uint32_t ob[4];
+                    orow_to_operand_bytes_lds(s_lds + kLdsIdxOff, my_o, lane, ob);
+                    const int q_hi = (R + 15) >> 4;
+                    for (int ot = 0; ot * 16 < nseed; ++ot) {
+                        floatx4_t DK[8], DV[8], Dn = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) DK[j] = DV[j] = Dn;
-                    membership_mfma_kv(s_lds, xv, ob, 16 * ot + c, q_hi, lane, DK, DV, Dn);
-                    store_tile<TO>(DK, Dn, ot, nseed, ktmp_c, (int64_t)w0, tmp_rows, lane);
-                    store_tile<TO>(DV, Dn, ot, nseed, vtmp_c, (int64_t)w0, tmp_rows, lane);
-                    store_sizes(Dn, ot, nseed, stmp_bh, (int64_t)w0, tmp_rows, lane);
+                        for (int j = 0; j < 8; ++j) DK[j] = DV[j] = Dn;
+                        membership_mfma_kv(s_lds, xv, ob, 16 * ot + c, q_hi, lane, DK, DV, Dn);
+                        store_tile<TO>(DK, Dn, ot, nseed, ktmp_c, (int64_t)w0, tmp_rows, lane);
+                        store_tile<TO>(DV, Dn, ot, nseed, vtmp_c, (int64_t)w0, tmp_rows, lane);
+                        store_sizes(Dn, ot, nseed, stmp_bh, (int64_t)w0, tmp_rows, lane);
+                    }
                 }
                 idx = idx_hi;
             } else {
@@ -732,8 +737,8 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
                         load_rows(x, row_source(Kbh, p.stride_n, start + rb, R, g, c));
                         gram_bitmatrix(s_lds, x, R, tau, lane, yes_row, unsure_row);
                     }
-                    RowRegs xv;
-                    load_rows(xv, row_source(Vbh, p.stride_n, start + rb, count_only ? 0 : R, g, c));
+                    [[maybe_unused]] RowRegs xv;
+                    if constexpr (!COUNT) load_rows(xv, row_source(Vbh, p.stride_n, start + rb, R, g, c));
                     uint64_t todo = bits_range(0, R);
                     int my_o = -1;
                     const int seeds_before = nseeds;
@@ -892,14 +897,16 @@ __global__ __launch_bounds__(kFastTaskThreads, 2) void gsc_compress_kernel(GscPa
                     // beyond the sixteenth read back below (through L2, by this wave only)
                     if (lane < R) __hip_atomic_store(cid32_bh + start + rb + lane, my_o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     // sums of the first sixteen clusters
-                    uint32_t ob[4];
-                    orow_to_operand_bytes_lds(s_lds + kLdsIdxOff, (lane < R) ? my_o : -1, lane, ob);
-                    if (!count_only) membership_mfma_kv(s_lds, xv, ob, c, nt, lane, DK, DV, Dn);
+                    if constexpr (!COUNT) {
+                        uint32_t ob[4];
+                        orow_to_operand_bytes_lds(s_lds + kLdsIdxOff, (lane < R) ? my_o : -1, lane, ob);
+                        membership_mfma_kv(s_lds, xv, ob, c, nt, lane, DK, DV, Dn);
+                    }
                     wave_lds_fence();   // the next block overwrites the parked keys and the seed tables are read above
                 }
                 if (closed && lane == 0 && cid_bh) cid_bh[start + l] = -1;
                 if (lane == 0) pcount_bh[m0 + idx] = nseeds;
-                if (count_only) {
+                if constexpr (COUNT) {
                     idx += 1;
                     continue;
                 }
@@ -1120,8 +1127,9 @@ hipError_t launch_gsc_fast(const GscParams &p, hipStream_t stream) {
     pc.grid_x = gx;
     const dim3 grid2((unsigned)(2 * gx * p.Hkv * p.B));   // two passes over the tasks: long ones first
     const dim3 grid1((unsigned)(gx * p.Hkv * p.B));
-    if (p.out_is_bf16) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t>), grid2, dim3(kFastTaskThreads), 0, stream, pc);
-    else hipLaunchKernelGGL((gsc_compress_kernel<float>), grid2, dim3(kFastTaskThreads), 0, stream, pc);
+    if (p.count_only) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, true>), grid2, dim3(kFastTaskThreads), 0, stream, pc);
+    else if (p.out_is_bf16) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, false>), grid2, dim3(kFastTaskThreads), 0, stream, pc);
+    else hipLaunchKernelGGL((gsc_compress_kernel<float, false>), grid2, dim3(kFastTaskThreads), 0, stream, pc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (p.count_only) return launch_gsc_scan(p, stream);   // adds up the counts: comp_lens, and nothing else is wanted
