@@ -69,19 +69,21 @@ __device__ __forceinline__ float mq_halves_max(float x) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-// Softmax of T tiles of 32 x 32 raw logits (bias included): lane l holds query row l % 32 and, of a tile, the cache rows
+// Softmax of T tiles of 32 x 32 logits in units of log 2: lane l holds query row l % 32 and, of a tile, the cache rows
 // 8 (i / 4) + 4 (l / 32) + i % 4.
-// The accumulators are rescaled only when a maximum has grown by more than 2^8: the sums are normalised by the same
-// maximum in the end, so this changes no digit that fp32 holds.
+// The reference follows the maximum at once.  A weight enters the second product as two bf16 parts, which round it at about
+// 2^-18 unless it is a power of two: relative to the true maximum the largest weight is 1 and costs nothing.  (A reference
+// that moves only when the maximum has grown 2^8-fold saves most of the rescaling, 4 % of the block kernel's time, and
+// rounds the largest weights as well: rms error with fp32 outputs, 5 900 rows, scale 0.3, 8.8e-7 -> 1.9e-6.)
 template <int T>
-__device__ __forceinline__ void block_grow(const mb_float16 (&s)[T], float scale, float grow, float &m_run, float &l_run, mb_float16 (&o)[4]) {
+__device__ __forceinline__ void block_grow(const mb_float16 (&s)[T], float &m_run, float &l_run, mb_float16 (&o)[4]) {
     float mx = s[0][0];
 #pragma unroll
     for (int i = 1; i < 16 * T; ++i) mx = fmaxf(mx, s[i >> 4][i & 15]);
     mx = mq_halves_max(mx);
-    if (ballot64(mx > m_run + grow) != 0ull) {
+    if (ballot64(mx > m_run) != 0ull) {
         const float m_new = fmaxf(m_run, mx);
-        const float alpha = (m_new == -INFINITY) ? 1.0f : mq_exp2((m_run - m_new) * scale);
+        const float alpha = (m_new == -INFINITY) ? 1.0f : mq_exp2(m_run - m_new);
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
@@ -90,14 +92,24 @@ __device__ __forceinline__ void block_grow(const mb_float16 (&s)[T], float scale
             for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
     }
 }
+// Dot products of one tile -> logits; bias: log2 of the sizes of the tile's rows in LDS, -inf for a row that does not exist.  (Added
+// here and not started from in the accumulator: there every one of the eight steps of the product would round a larger sum.)
+__device__ __forceinline__ void block_logits(mb_float16 &s, float scale_log2, const float *bias, int half) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float4 bb = *reinterpret_cast<const float4 *>(bias + 8 * k + 4 * half);
+        s[4 * k] = fmaf(s[4 * k], scale_log2, bb.x); s[4 * k + 1] = fmaf(s[4 * k + 1], scale_log2, bb.y);
+        s[4 * k + 2] = fmaf(s[4 * k + 2], scale_log2, bb.z); s[4 * k + 3] = fmaf(s[4 * k + 3], scale_log2, bb.w);
+    }
+}
 // The probabilities of one tile as B operands of the second product: leading parts and remainders, a pair per 16 cache rows.
-__device__ __forceinline__ void block_probabilities(const mb_float16 &s, float scale, float m_run, float &l_run, uint4 (&ph)[2], uint4 (&pl)[2]) {
-    const float shift = (m_run == -INFINITY) ? 0.f : m_run * scale;
+__device__ __forceinline__ void block_probabilities(const mb_float16 &s, float m_run, float &l_run, uint4 (&ph)[2], uint4 (&pl)[2]) {
+    const float shift = (m_run == -INFINITY) ? 0.f : m_run;
     uint32_t h[8], l[8];
     float psum = 0.f;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const float e0 = mq_exp2(fmaf(s[2 * k], scale, -shift)), e1 = mq_exp2(fmaf(s[2 * k + 1], scale, -shift));
+        const float e0 = mq_exp2(s[2 * k] - shift), e1 = mq_exp2(s[2 * k + 1] - shift);
         h[k] = pack_bf16x2(e0, e1);
         l[k] = pack_bf16x2(e0 - bf16_lo(h[k]), e1 - bf16_hi(h[k]));
         psum += e0 + e1;
@@ -125,7 +137,7 @@ __device__ __forceinline__ void mq_store_row4(const MqParams &p, int64_t orow, i
 // LDS area of its own: no barrier until the end, and a wavefront's 16 KB of loads for the next step fly while it works on
 // this one (128 KB in flight per compute unit; what bounds the kernel is the trip to memory and the chain after it).
 // Arithmetic and operand layouts are those of multi_block_kernel below; the wavefronts fold through LDS at the end.
-// 8 heads x 32 query rows x 5 500 cache rows (22.6 MB): 17.0 us per call with the second kernel; 25.5 with 16 query rows per
+// 8 heads x 32 query rows x 5 500 cache rows (22.6 MB): 16.6 us per call with the second kernel; 25.4 with 16 query rows per
 // workgroup in registers only, whose 256 vector registers left nothing in flight while a step was worked on.
 constexpr int kMwThreads = kMqWaves * kWave;
 constexpr int kMwRows = 32;                       // query rows per workgroup
@@ -197,9 +209,6 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
     int base = r0 + wave * kMwStep;
     if (base < r1) fetch(base);
 
-    // a negative scale is the positive one with the query rows' signs flipped
-    const float scale = fmaxf(fabsf(p.scale_log2), 1e-30f), inv_scale = 1.0f / scale;
-    const uint32_t flip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
     const int R = rb * kMwRows + c;
     const bool valid = R < p.nq * p.G;
     const int j = valid ? R / p.G : 0, g = valid ? R - j * p.G : 0;
@@ -207,17 +216,12 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
     {
         const bf16_t *qp = p.Q + (((int64_t)j * p.B + b) * p.Hq + (int64_t)h * p.G + g) * kMqD + 8 * half;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            uint4 v = valid ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
-            v.x ^= flip; v.y ^= flip; v.z ^= flip; v.w ^= flip;
-            q[ks] = v;
-        }
+        for (int ks = 0; ks < 8; ++ks) q[ks] = valid ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
     }
     const bool masked = TAIL && p.causal;
     const int limit = masked ? rows_c + max(0, rows_t - p.nq + 1 + j) : rows_total;   // rows [0, limit) are visible
 
-    float m_run = -INFINITY, l_run = 0.f;      // of the lane's query row, in units of the raw logits; l: this half's share
-    const float grow = 8.0f * inv_scale;
+    float m_run = -INFINITY, l_run = 0.f;      // of the lane's query row; l: this half's share
     mb_float16 o[4];                           // o[dt][i]: column 32 dt + 8 (i / 4) + 4 half + i % 4 of the lane's query row
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
@@ -228,7 +232,7 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
     while (base < r1) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) *reinterpret_cast<uint4 *>(kt + (4 * r + g4) * kMwKRowBytes + 16 * c4) = kx[r];
-        if (lane < kMwStep) s_bias[wave][lane] = (cx > 0) ? __log2f((float)cx) * inv_scale : -INFINITY;
+        if (lane < kMwStep) s_bias[wave][lane] = (cx > 0) ? __log2f((float)cx) : -INFINITY;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -242,24 +246,20 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
         mq_wave_handover();
         const int next = base + kMqWaves * kMwStep;
         if (next < r1) fetch(next);
-        mb_float16 s[1];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float4 bb = *reinterpret_cast<const float4 *>(&s_bias[wave][8 * k + 4 * half]);
-            s[0][4 * k] = bb.x; s[0][4 * k + 1] = bb.y; s[0][4 * k + 2] = bb.z; s[0][4 * k + 3] = bb.w;
-        }
+        mb_float16 s[1] = {};
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
             const uint4 a = *reinterpret_cast<const uint4 *>(kt + c * kMwKRowBytes + 32 * ks + 16 * half);
             s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mq_op8(a), mq_op8(q[ks]), s[0], 0, 0, 0);
         }
+        block_logits(s[0], p.scale_log2, s_bias[wave], half);
         if (masked && base + kMwStep > rows_c) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[0][i] = (base + 8 * (i >> 2) + 4 * half + (i & 3) < limit) ? s[0][i] : -INFINITY;
         }
         uint4 ph[2], pl[2];
-        block_grow<1>(s, scale, grow, m_run, l_run, o);
-        block_probabilities(s[0], scale, m_run, l_run, ph, pl);
+        block_grow<1>(s, m_run, l_run, o);
+        block_probabilities(s[0], m_run, l_run, ph, pl);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -298,19 +298,18 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
         float l = 0.f;
 #pragma unroll
         for (int w = 0; w < kMqWaves; ++w) {
-            const float f = mq_exp2((s_m[w][row] - m_safe) * scale);
+            const float f = mq_exp2(s_m[w][row] - m_safe);
             const float4 t = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(s_tiles[w]) + row * kMwAccStride + 4 * q4);
             x.x = fmaf(t.x, f, x.x); x.y = fmaf(t.y, f, x.y); x.z = fmaf(t.z, f, x.z); x.w = fmaf(t.w, f, x.w);
             l = fmaf(s_l[w][row], f, l);
         }
-        const float m_log2 = (mw == -INFINITY) ? -INFINITY : mw * scale;
         if (Rr >= p.nq * p.G) continue;
         if (p.max_splits == 1) {
             const int jr = Rr / p.G, gr = Rr - jr * p.G;
-            mq_store_row4(p, ((int64_t)jr * p.B + b) * p.Hq + (int64_t)h * p.G + gr, 4 * q4, x, m_log2, l, q4 == 0);
+            mq_store_row4(p, ((int64_t)jr * p.B + b) * p.Hq + (int64_t)h * p.G + gr, 4 * q4, x, mw, l, q4 == 0);
         } else {
             *reinterpret_cast<float4 *>(part + (int64_t)row * kMqPart + 4 * q4) = x;
-            if (q4 == 0) *reinterpret_cast<float2 *>(part + (int64_t)row * kMqPart + kMqD) = make_float2(m_log2, l);
+            if (q4 == 0) *reinterpret_cast<float2 *>(part + (int64_t)row * kMqPart + kMqD) = make_float2(mw, l);
         }
     }
 }
@@ -321,21 +320,21 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
 // The four wavefronts of a workgroup own 32 query rows EACH and share
 // tiles of 64 cache rows in LDS, double-buffered (the next tile's loads fly while this one is worked on):
 //   * S^T = K Q^T with v_mfma_f32_32x32x16_bf16: cache rows are the A operand (LDS rows of 256 + 16 bytes, free of bank
-//     conflicts), query rows the B operand, which stays in registers.  The accumulator starts at log2(size) / scale, so
-//     the bias costs nothing, and a row that does not exist starts at -inf.
+//     conflicts), query rows the B operand, which stays in registers.
 //   * the result has the query row on the lane (l % 32) and sixteen cache rows in its registers: the running maximum and sum
 //     are one value per lane, a rescale is a multiplication by a lane's own factor, and the probabilities already are
 //     the B operand of  O^T += V^T P^T  (index (l / 32, j) of both operands stands for cache row 16 u + 8 (j / 4) + 4 (l / 32) + j % 4).
 //   * V^T comes from an LDS tile that is transposed while it is parked: a thread brings sixteen bytes of four
 //     neighbouring rows, regroups them with byte permutes and stores eight pieces of four cache rows.  The 16-byte slots of an
 //     LDS row are XORed with a function of the row (vt_slot) that keeps operand reads free of conflicts.
-//   * the accumulators are rescaled only when a maximum has grown by more than 2^8: the sums are normalised by the same
-//     maximum in the end, so this changes no digit that fp32 holds.
-// P enters as two bf16 parts (leading part and remainder), i.e. with 16 bits of every weight.
+// P enters as two bf16 parts (leading part and remainder), i.e. with 16 bits of every weight but the largest of a stretch, which
+// is 1.  A stretch (the rows of one split) is one sum in row order: level with four wavefronts that take a quarter each at
+// 1 500 rows (rms error with fp32 outputs 2.07e-6 / 2.05e-6 at scale 1/sqrt(d), 8.4e-7 / 8.2e-7 at 0.3), above it where one
+// split takes 8 192 (2.4e-6 / 2.1e-6 and 1.3e-6 / 8.7e-7): fewer largest weights, longer sums.
 // Bound by instruction issue: per 64 cache rows a wavefront spends 48 matrix instructions of 32 cycles and as many cycles
 // of vector work on the logits of its lanes, and the two wavefronts of a SIMD overlap little of it (counters: 46 % of the
 // time matrix, 46 % vector).  8 heads x 2048 query rows (nq = 512, G = 4) x 5 900 cache rows, 47 GFLOP: 402 us with 32 rows
-// per workgroup and no sharing of tiles (115 TFLOP/s), now 82 us + 10 us for the second kernel (580 TFLOP/s).
+// per workgroup and no sharing of tiles (115 TFLOP/s), now 102 us with the second kernel (460 TFLOP/s).
 constexpr int kMbWaves = 4;
 constexpr int kMbThreads = kMbWaves * kWave;
 constexpr int kMbRows = 32 * kMbWaves;            // query rows per workgroup
@@ -384,9 +383,6 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
     const bf16_t *Ktbh = TAIL ? p.Kt + bh * (int64_t)p.tail_cap * kMqD : nullptr;
     const bf16_t *Vtbh = TAIL ? p.Vt + bh * (int64_t)p.tail_cap * kMqD : nullptr;
 
-    // a negative scale is the positive one with the query rows' signs flipped
-    const float scale = fmaxf(fabsf(p.scale_log2), 1e-30f), inv_scale = 1.0f / scale;
-    const uint32_t flip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
     const int R = rb * kMbRows + wave * 32 + c;
     const bool valid = R < n_rows_q;
     const int j = valid ? R / p.G : 0, g = valid ? R - j * p.G : 0;
@@ -395,11 +391,7 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
     {
         const bf16_t *qp = p.Q + (((int64_t)j * p.B + b) * p.Hq + (int64_t)h * p.G + g) * kMqD + 8 * half;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            uint4 v = valid ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
-            v.x ^= flip; v.y ^= flip; v.z ^= flip; v.w ^= flip;
-            q[ks] = v;
-        }
+        for (int ks = 0; ks < 8; ++ks) q[ks] = valid ? *reinterpret_cast<const uint4 *>(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
     }
     const int limit = (masked && valid) ? rows_c + max(0, rows_t - p.nq + 1 + j) : rows_total;   // rows [0, limit) are visible
     int limit_min = limit;
@@ -439,7 +431,7 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
         if (tid < kMbTile) {
             const int row = base + tid;
             const int cnt = (row >= r1) ? 0 : ((TAIL && row >= rows_c) ? 1 : cnt_bh[row]);
-            bx = (cnt > 0) ? __log2f((float)cnt) * inv_scale : -INFINITY;
+            bx = (cnt > 0) ? __log2f((float)cnt) : -INFINITY;
         }
     };
     auto park = [&](int buf) {
@@ -459,8 +451,7 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
         if (tid < kMbTile) s_bias[buf][tid] = bx;
     };
 
-    float m_run = -INFINITY, l_run = 0.f;      // of the lane's query row, in units of the raw logits; l: this half's share
-    const float grow = 8.0f * inv_scale;
+    float m_run = -INFINITY, l_run = 0.f;      // of the lane's query row; l: this half's share
     mb_float16 o[4];                           // o[dt][i]: column 32 dt + 8 (i / 4) + 4 half + i % 4 of the lane's query row
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
@@ -479,15 +470,7 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
         if (wave_live) {
             const char *kt = s_k[buf], *vt = s_v[buf];
             __builtin_amdgcn_s_setprio(1);      // products first: 752 -> 729 us for eight calls of the shape above
-            mb_float16 s[2];
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float4 bb = *reinterpret_cast<const float4 *>(&s_bias[buf][32 * tt + 8 * k + 4 * half]);
-                    s[tt][4 * k] = bb.x; s[tt][4 * k + 1] = bb.y; s[tt][4 * k + 2] = bb.z; s[tt][4 * k + 3] = bb.w;
-                }
-            }
+            mb_float16 s[2] = {};
 #pragma unroll
             for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
@@ -495,6 +478,8 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
                     const uint4 a = *reinterpret_cast<const uint4 *>(kt + (32 * tt + c) * kMbKRowBytes + 32 * ks + 16 * half);
                     s[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mq_op8(a), mq_op8(q[ks]), s[tt], 0, 0, 0);
                 }
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) block_logits(s[tt], p.scale_log2, s_bias[buf] + 32 * tt, half);
             if (masked && base + kMbTile > limit_min) {
 #pragma unroll
                 for (int tt = 0; tt < 2; ++tt)
@@ -502,11 +487,11 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
                     for (int i = 0; i < 16; ++i) s[tt][i] = (base + 32 * tt + 8 * (i >> 2) + 4 * half + (i & 3) < limit) ? s[tt][i] : -INFINITY;
             }
             __builtin_amdgcn_s_setprio(0);
-            block_grow<2>(s, scale, grow, m_run, l_run, o);
+            block_grow<2>(s, m_run, l_run, o);
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) {
                 uint4 ph[2], pl[2];
-                block_probabilities(s[tt], scale, m_run, l_run, ph, pl);
+                block_probabilities(s[tt], m_run, l_run, ph, pl);
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -524,7 +509,6 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
 
     l_run = mq_halves_sum(l_run);
     if (!valid) return;
-    const float m_log2 = (m_run == -INFINITY) ? -INFINITY : m_run * scale;
     if (p.max_splits == 1) {      // nothing to fold: the outputs themselves
         const int64_t orow = ((int64_t)j * p.B + b) * p.Hq + (int64_t)h * p.G + g;
 #pragma unroll
@@ -532,7 +516,7 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 mq_store_row4(p, orow, 32 * dt + 8 * k + 4 * half, make_float4(o[dt][4 * k], o[dt][4 * k + 1], o[dt][4 * k + 2], o[dt][4 * k + 3]),
-                              m_log2, l_run, half == 0 && dt == 0 && k == 0);
+                              m_run, l_run, half == 0 && dt == 0 && k == 0);
         return;
     }
     float *part = p.part + (((bh * p.row_blocks + rb) * (int64_t)p.max_splits + split) * kMbRows + wave * 32 + c) * kMqPart;
@@ -542,7 +526,7 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
         for (int k = 0; k < 4; ++k)
             *reinterpret_cast<float4 *>(part + 32 * dt + 8 * k + 4 * half) =
                 make_float4(o[dt][4 * k], o[dt][4 * k + 1], o[dt][4 * k + 2], o[dt][4 * k + 3]);
-    if (half == 0) { part[kMqD] = m_log2; part[kMqD + 1] = l_run; }
+    if (half == 0) { part[kMqD] = m_run; part[kMqD + 1] = l_run; }
 }
 
 // One wavefront per query row of a (sequence, KV head), four of them per workgroup.  The (m, l) of all splits are fetched

@@ -209,3 +209,42 @@ def test_multi_attn_blocks_against_oracle(Hkv, G, B, cap, tcap, nq, causal, o_f3
     finite = np.isfinite(want_L)
     assert np.array_equal(np.isneginf(got_l), np.isneginf(want_L))
     assert np.abs(got_l[finite] - want_L[finite]).max() <= 1e-3
+
+
+# rms error of fp32 outputs over the rms of the outputs, in 1e-7, at the scales 1/sqrt(128), 0.3 and 1.  A weight enters the
+# second product in two bf16 parts: rounded at 2^-18 at most, 2.3e-6 (rms) over many weights; less where a few rows
+# carry the sum, as long as the largest weight is 1 and not rounded.  The bounds are 1.1 times what 16 x 16 x 32 products with
+# 32 query rows per workgroup and the true maximum as reference gave (15.4 / 5.6 / 7.4 and 20.6 / 8.3 / 9.0); a reference
+# that lags behind the maximum by up to 2^8 gives 19.3 / 6.5 / 8.4 and 24.6 / 19.4 / 12.9.
+@pytest.mark.parametrize("nq,rows,tcap,causal,bounds", [
+    (8, 5500, 0, False, (16.9, 6.2, 8.1)),        # 32 query rows per head
+    (512, 5400, 512, True, (22.6, 9.2, 9.9)),      # sixteen blocks of 128
+])
+def test_multi_attn_error_of_fp32_outputs(nq, rows, tcap, causal, bounds):
+    B, Hkv, G, d = 1, 8, 4, 128
+    gen = torch.Generator().manual_seed(nq)
+    bf16 = lambda *s: torch.randn(s, generator=gen).to(torch.bfloat16).to(g.DEV)
+    Q, Kc, Vc = bf16(nq, B, Hkv * G, d), bf16(B, Hkv, rows, d), bf16(B, Hkv, rows, d)
+    counts = (1 + torch.empty((B, Hkv, rows)).exponential_(1 / 6.0, generator=gen).int()).to(g.DEV)
+    lens = torch.full((B, Hkv), rows, dtype=torch.int32, device=g.DEV)
+    tail = dict(Kt=bf16(B, Hkv, tcap, d), Vt=bf16(B, Hkv, tcap, d), causal=causal,
+                tail_lens=torch.full((B,), tcap, dtype=torch.int32, device=g.DEV)) if tcap else {}
+    O = torch.empty((nq, B, Hkv * G, d), dtype=torch.float32, device=g.DEV)
+    for scale, bound in zip((1 / np.sqrt(d), 0.3, 1.0), bounds):
+        sc.sc_multi_attn(Q, Kc, Vc, counts, lens, scale=float(scale), O=O, **tail)
+        err, total = 0.0, 0.0
+        for h in (0, Hkv - 1):
+            k, v, bias = Kc[0, h].double(), Vc[0, h].double(), counts[0, h].double().log()
+            if tcap:
+                k, v = torch.cat([k, tail["Kt"][0, h].double()]), torch.cat([v, tail["Vt"][0, h].double()])
+                bias = torch.cat([bias, torch.zeros(tcap, dtype=torch.float64, device=g.DEV)])
+            z = Q[:, 0, h * G:(h + 1) * G].double().reshape(nq * G, d) @ k.t().contiguous() * float(scale) + bias
+            if causal:
+                seen = rows + tcap - nq + 1 + torch.arange(nq, device=g.DEV).repeat_interleave(G)
+                z.masked_fill_(torch.arange(rows + tcap, device=g.DEV)[None, :] >= seen[:, None], -np.inf)
+            want = (torch.softmax(z, 1) @ v).reshape(nq, G, d)
+            err += float((O[:, 0, h * G:(h + 1) * G].double() - want).square().sum())
+            total += float(want.square().sum())
+        rel = np.sqrt(err / total)
+        print("nq %d scale %.3f: rms error %.3e" % (nq, scale, rel))
+        assert rel <= bound * 1e-7, (scale, rel)
