@@ -323,7 +323,7 @@ sc_status sc_gsc_merge_budget(const void *K, const void *V, sc_dtype in_dtype,
  *                   call has the layout of an sc_decode_attn query)
  *   nq              number of query rows, 1..4096
  *   Kc, Vc, counts, comp_lens, scale    as for sc_decode_attn
- *   O               device [nq, B, Hq, d] of o_dtype;  lse  device f32 [nq, B, Hq] or NULL
+ *   O               device [nq, B, Hq, d] of o_dtype, at a multiple of 4 bytes;  lse  device f32 [nq, B, Hq] or NULL
  *   ws              sc_multi_attn_workspace_bytes(B, Hq, Hkv, nq, cap, d) bytes; carries no state
  *
  * bf16 queries and cache with d = 128 run on the matrix cores (probabilities enter the second product

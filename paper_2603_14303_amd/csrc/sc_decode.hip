@@ -291,13 +291,8 @@ __device__ __forceinline__ void combine_splits(const DecParams &p, const float *
         }
         const float l = my_l;
         const float inv = (l > 0.f) ? 1.0f / l : 0.f;
-        const float o0 = a.x * inv, o1 = a.y * inv, o2 = a.z * inv, o3 = a.w * inv;
         const int64_t ooff = ((int64_t)b * p.Hq + (int64_t)h * G + g) * D + 4 * q4;
-        if (p.o_is_bf16) {
-            *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(p.O) + ooff) = make_uint2(pack_bf16x2(o0, o1), pack_bf16x2(o2, o3));
-        } else {
-            *reinterpret_cast<float4 *>(reinterpret_cast<float *>(p.O) + ooff) = make_float4(o0, o1, o2, o3);
-        }
+        store_row4(p.O, p.o_is_bf16, ooff, make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv));
         if (q4 == 0 && p.lse)
             p.lse[(int64_t)b * p.Hq + (int64_t)h * G + g] = (l > 0.f) ? (my_mx + __log2f(l)) * kLn2 : -INFINITY;
     }

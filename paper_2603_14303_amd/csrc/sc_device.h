@@ -173,6 +173,14 @@ __device__ __forceinline__ void store16_stream(void *p, const uint4 &v) {
     const stream_u32x4_t t = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(t, reinterpret_cast<stream_u32x4_t *>(p));
 }
+// Four columns of an output row of sc_multi_attn, which takes O at any multiple of four bytes: the types say so, and the
+// compiler writes one wide store where the target allows it at that alignment (gfx950 does).
+typedef float row4_f32_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int row4_bf16_t __attribute__((ext_vector_type(2), aligned(4)));
+__device__ __forceinline__ void store_row4(void *base, bool is_bf16, int64_t elem_off, const float4 &x) {
+    if (is_bf16) *reinterpret_cast<row4_bf16_t *>(reinterpret_cast<uint16_t *>(base) + elem_off) = row4_bf16_t{pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w)};
+    else *reinterpret_cast<row4_f32_t *>(reinterpret_cast<float *>(base) + elem_off) = row4_f32_t{x.x, x.y, x.z, x.w};
+}
 __device__ __forceinline__ int first_bit(uint64_t m) { return __ffsll((unsigned long long)m) - 1; }
 
 // fp64 sums over the 16 lanes of a row, over the four lanes at one position of the rows, and over the wave, every

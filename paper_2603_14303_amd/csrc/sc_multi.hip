@@ -124,9 +124,7 @@ __device__ __forceinline__ void block_probabilities(const mb_float16 &s, float m
 // four columns of a finished query row: sums x over the denominator l
 __device__ __forceinline__ void mq_store_row4(const MqParams &p, int64_t orow, int col, const float4 &x, float m_log2, float l, bool write_lse) {
     const float inv = (l > 0.f) ? 1.0f / l : 0.f;
-    const float x0 = x.x * inv, x1 = x.y * inv, x2 = x.z * inv, x3 = x.w * inv;
-    if (p.o_is_bf16) *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(p.O) + orow * kMqD + col) = make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
-    else *reinterpret_cast<float4 *>(reinterpret_cast<float *>(p.O) + orow * kMqD + col) = make_float4(x0, x1, x2, x3);
+    store_row4(p.O, p.o_is_bf16, orow * kMqD + col, make_float4(x.x * inv, x.y * inv, x.z * inv, x.w * inv));
     if (write_lse && p.lse) p.lse[orow] = (l > 0.f) ? (m_log2 + __log2f(l)) * kMqLn2 : -INFINITY;
 }
 

@@ -211,6 +211,33 @@ def test_multi_attn_blocks_against_oracle(Hkv, G, B, cap, tcap, nq, causal, o_f3
     assert np.abs(got_l[finite] - want_L[finite]).max() <= 1e-3
 
 
+@pytest.mark.parametrize("o_f32", [True, False])
+@pytest.mark.parametrize("kv_bf16,d,cap,nq", [
+    (True, 128, 2000, 3),       # few rows, partials folded by the second kernel
+    (True, 128, 100, 3),        # few rows, one split
+    (True, 128, 2000, 40),      # blocks of 128 rows
+    (True, 128, 100, 40),       # ... one split
+    (False, 64, 700, 3),        # row by row through the decode kernels
+])
+def test_multi_attn_output_at_a_multiple_of_four_bytes(kv_bf16, d, cap, nq, o_f32):
+    rng = np.random.default_rng(cap + nq)
+    B, Hkv, G = 1, 2, 4
+    Q = g.to_device(_round_like(rng.standard_normal((nq, B, Hkv * G, d)), kv_bf16), kv_bf16)
+    Kc, Vc = (g.to_device(_round_like(rng.standard_normal((B, Hkv, cap, d)), kv_bf16), kv_bf16) for _ in range(2))
+    counts = torch.from_numpy(rng.integers(1, 40, (B, Hkv, cap)).astype(np.int32)).to(g.DEV)
+    lens = torch.full((B, Hkv), cap, dtype=torch.int32, device=g.DEV)
+    dt = torch.float32 if o_f32 else torch.bfloat16
+    step = 4 // dt.itemsize
+    want = torch.zeros(Q.shape, dtype=dt, device=g.DEV)
+    sc.sc_multi_attn(Q, Kc, Vc, counts, lens, O=want)
+    for at in (1, 2, 3):        # 4, 8 and 12 bytes behind a 16-byte boundary
+        buf = torch.full((want.numel() + 8 * step,), 7.0, dtype=dt, device=g.DEV)
+        sc.sc_multi_attn(Q, Kc, Vc, counts, lens, O=buf[at * step:at * step + want.numel()].view(want.shape))
+        torch.cuda.synchronize()
+        assert torch.equal(buf[at * step:at * step + want.numel()].view(want.shape), want), at
+        assert (buf[:at * step] == 7.0).all() and (buf[at * step + want.numel():] == 7.0).all(), at
+
+
 # rms error of fp32 outputs over the rms of the outputs, in 1e-7, at the scales 1/sqrt(128), 0.3 and 1.  A weight enters the
 # second product in two bf16 parts: rounded at 2^-18 at most, 2.3e-6 (rms) over many weights; less where a few rows
 # carry the sum, as long as the largest weight is 1 and not rounded.  The bounds are 1.1 times what 16 x 16 x 32 products with
