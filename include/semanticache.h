@@ -380,7 +380,8 @@ sc_status sc_stream_read_probe(const void *src, size_t bytes, void *sink, void *
  *   "gsc_fast_path"        0 forces the generic kernels even for bf16 / d = 128
  *   "gsc_chunks_per_task"  fast path: chunks handled by one single-wave workgroup task (1..32);
  *                          <= 0 (the default) = 2, or 1 for a call of a few thousand tokens in all
- *   "gsc_chunks_per_item"  generic path: chunks per work item; <= 0 = chosen from B * Hkv * N_max
+ *   "gsc_chunks_per_item"  generic path: chunks per work item; <= 0 = chosen from B * Hkv * N_max and
+ *                          from the mean chunk length of the sequence
  *   "gsc_grid_x"           workgroups per pass and (sequence, KV head); <= 0 = chosen from N_max
  *   "global_polls"         sc_gsc_merge_global: looks at rows that another workgroup decides before the ordered pass
  *                          takes over (default 4096; <= 0: gives up at the first; the outcome is the same)

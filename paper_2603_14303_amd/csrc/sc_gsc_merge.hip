@@ -149,10 +149,51 @@ __device__ int gsc_chunk(const T *__restrict__ Kbh, int64_t stride_n, int start,
     return nseeds;
 }
 
+// Chunks per work item of a sequence of n tokens in M chunks, the same in both kernels.  Short chunks make few rows: an item of
+// four or eight of them leaves most groups of gsc_merge without one, and its barriers and trips to memory are for next to
+// nothing.  us per call, delimiters at a fixed distance, 8 / 16 / 32 chunks (16 and a scan kernel):
+//   distance                  1                     2                     4                     8                    12
+//   8 heads x 32768 x 64 f32  265 / 138 / 107 (152) 187 / 104 / 101 (110) 150 / 126 / 129 (128) 118 /  96 /  97 (98)  96 /  92 / 105 (124)
+//   64 x 1200 x 64 f32         82 /  56 /  41 (46)   61 /  41 /  39 (40)   53 /  50 /  59 (54)   46 /  45 /  56 (53)  40 /  40 /  65 (65)
+// Calls that would take four, 4 / 8 / 16 / 32 chunks, distance 1, 2, 3, 6 (up to four tokens eight, up to two 16 or 32):
+//   2 x 32768 x 64 f32        123 / 80 / 75 / 56 (99), 85 / 57 / 52 / 50 (65), 79 / 64 / 87 / 80 (95), 52 / 57 / 71 / 87 (76)
+// and with an item for every workgroup anyway (2 x 1024 x 64 f32, distance 4) 14.4 / 15.4 / 21.2 / 35.9 (23.9).
+//
+// Workgroups per (sequence, head) that take such items: an item per 21 tokens per chunk is what chunks of a few dozen tokens make;
+// fewer than 128 would leave a short sequence's longest chunks behind one another, but 2048 over all heads fill the chip, and idle
+// ones cost a launch slot each (128 for every head / this: 128 x 2000 x 64 f32 83 / 68, 16 x 8 x 8192 x 64 bf16 398 / 265; with the
+// item order below).  The grid is for p.chunks_per_item.  (With every
+// workgroup of it on items of 16, 8 x 32768 x 64 f32, distance 1, takes 169 instead of 140 us and distance 2 118 instead of 104: not
+// all of them are on the chip at once, and the later ones start from the first item again.)
+static int gsc_item_workgroups(int heads, int N_max, int C) { return max(min(128, 2048 / heads), N_max / (21 * C)); }
+__device__ __forceinline__ void gsc_item_shape(const GscParams &p, int M, int n, int &C, int &wgs) {
+    C = p.chunks_per_item;
+    wgs = gridDim.y;
+    if (p.short_wgs[0] == 0) return;
+    const int64_t tokens = n, chunks = M;
+    const bool dense = 2 * tokens < 5 * chunks;
+    if (p.chunks_per_item >= 8) {
+        if (tokens < 10 * chunks) C = dense ? 32 : 16;
+    } else if (2 * tokens < 9 * chunks && chunks > p.chunks_per_item * wgs) {
+        C = dense ? (chunks > 16 * wgs ? 32 : 16) : 8;
+    }
+    if (C != p.chunks_per_item) wgs = min(wgs, p.short_wgs[C >= 16]);
+}
+
+// Grid (sequence and head, first item): workgroup ids go to the eight XCDs in turn, and a short sequence has work for a few of its
+// workgroups only.  With the items fastest and a multiple of eight of them, those few were the same XCDs and the same part of
+// their compute units for every head (64 heads x 1200 x 64 f32, us per call: 60 with 76 of them, 86 with 128).  (The
+// z dimension is for more than 2^23 heads.)
+constexpr int kGridHeadsLog2 = 23;
+__device__ __forceinline__ int gsc_grid_head() { return (int)(blockIdx.x + (blockIdx.z << kGridHeadsLog2)); }
+
 template <typename T, int D>
 __global__ __launch_bounds__(kGscThreads) void gsc_assign_kernel(GscParams p) {
     __shared__ int s_off[kMaxChunksPerItem + 1];
-    const int b = blockIdx.z, h = blockIdx.y;
+    __shared__ int s_rows[kGscThreads / kWave];
+    const int bh_i = gsc_grid_head();
+    if (bh_i >= p.B * p.Hkv) return;
+    const int b = bh_i / p.Hkv, h = bh_i - b * p.Hkv;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     // wave index as a scalar: everything derived from it (chunk bounds, loop trip counts) stays
     // wave-uniform for the compiler, so the cross-lane operations below always see all 64 lanes
@@ -161,20 +202,32 @@ __global__ __launch_bounds__(kGscThreads) void gsc_assign_kernel(GscParams p) {
     if (M <= 0) return;
     int n = p.seq_lens ? p.seq_lens[b] : p.N_max;
     n = n < 0 ? 0 : (n > p.N_max ? p.N_max : n);
-    const int C = p.chunks_per_item;
+    int C, wgs;
+    gsc_item_shape(p, M, n, C, wgs);
+    if ((int)blockIdx.y >= wgs) return;
     const int items = (M + C - 1) / C;
     const float tau = p.tau_dev ? *p.tau_dev : p.tau;
-    const int64_t bh = (int64_t)b * p.Hkv + h;
+    const int64_t bh = bh_i;
     const T *Kbh = reinterpret_cast<const T *>(p.K) + b * p.stride_b + h * p.stride_h;
     const int32_t *off = p.offsets + (int64_t)b * p.offsets_stride_b;
     int32_t *cid_bh = p.cid + bh * p.N_max;
     int32_t *seed_bh = p.seedrow + bh * p.N_max;
     int32_t *pcount_bh = p.pcount + bh * ((int64_t)p.N_max + 1);
+    int32_t *item_rows_bh = p.rowbase + bh * ((int64_t)p.N_max + 2);   // clusters of every item, see gsc_merge
+    auto file_item = [&](int item) {
+        int rows = 0;
+#pragma unroll
+        for (int w = 0; w < kGscThreads / kWave; ++w) rows += s_rows[w];
+        item_rows_bh[item] = rows;
+    };
 
-    for (int item = blockIdx.x; item < items; item += gridDim.x) {
+    int item = blockIdx.y;
+    for (; item < items; item += wgs) {
         const int m0 = item * C;
         const int nch = min(C, M - m0);
+        int rows = 0;
         __syncthreads();
+        if (tid == 0 && item != (int)blockIdx.y) file_item(item - wgs);
         if (tid <= nch) s_off[tid] = off[m0 + tid];
         __syncthreads();
         for (int idx = wave; idx < nch; idx += kGscThreads / kWave) {
@@ -182,13 +235,17 @@ __global__ __launch_bounds__(kGscThreads) void gsc_assign_kernel(GscParams p) {
             const int l = __builtin_amdgcn_readfirstlane(s_off[idx + 1]) - 1 - start;
             int pc = 0;
             if (l > 0) pc = gsc_chunk<T, D>(Kbh, p.stride_n, start, l, tau, cid_bh, seed_bh, lane);
+            rows += pc;
             if (lane == 0) {
                 pcount_bh[m0 + idx] = pc;
                 const int delim = start + l;
                 if (delim < n) cid_bh[delim] = -1;
             }
         }
+        if (lane == 0) s_rows[wave] = rows;
     }
+    __syncthreads();
+    if (tid == 0 && item != (int)blockIdx.y) file_item(item - wgs);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -267,8 +324,10 @@ __device__ __forceinline__ void store_row8(void *base, int64_t elem_off, const f
 // wavefronts, 156 -> 228 us on 8 heads x 32768 x 64 bf16, and no faster on short sequences).  Whole call, against
 // indices read from memory eight at a time and a scan kernel: 2 heads x 1024 x 64 f32 56 -> 30 us, 8 x 8192 x 128
 // f32 127 -> 73, 8 x 32768 x 64 bf16 209 -> 156.
-// INLINE_PREFIX: no scan kernel ran; the workgroup adds up the cluster counts before its item itself and the
-// workgroup of the last item files the total.
+// INLINE_PREFIX: no scan kernel ran; the workgroup adds up the rows of the items before its own itself, from the clusters
+// that gsc_assign has filed per item, and the workgroup of the last item files the total.  (From the clusters of every chunk that
+// is eight times as much to read for every item in turn: where a chunk is a token or two and a sequence many items, 8 heads
+// x 32768 x 64 f32 with a delimiter per token, a call of items of eight took 323 us, 265 so.)
 constexpr int kMergeCidTile = 2048;
 constexpr int kMergeInFlight = 4;
 
@@ -281,21 +340,25 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     __shared__ int s_base[kMaxChunksPerItem + 1];
     __shared__ int s_sum[kGscThreads / kWave];
     __shared__ int s_cid[kMergeCidTile];
-    const int b = blockIdx.z, h = blockIdx.y;
+    const int bh_i = gsc_grid_head();
+    if (bh_i >= p.B * p.Hkv) return;
+    const int b = bh_i / p.Hkv, h = bh_i - b * p.Hkv;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int g = lane / LPR, c = lane % LPR;
     const int gsh = g * LPR;   // position of this group's bits inside a wave ballot
     const uint64_t gmask = (LPR == 16) ? 0xffffull : 0xffull;
     const int M = p.num_chunks[b];
-    const int64_t bh = (int64_t)b * p.Hkv + h;
+    const int64_t bh = bh_i;
     if (M <= 0) {
-        if (INLINE_PREFIX && blockIdx.x == 0 && tid == 0) p.comp_lens[bh] = -1;
+        if (INLINE_PREFIX && blockIdx.y == 0 && tid == 0) p.comp_lens[bh] = -1;
         return;
     }
     int n = p.seq_lens ? p.seq_lens[b] : p.N_max;
     n = n < 0 ? 0 : (n > p.N_max ? p.N_max : n);
-    const int C = p.chunks_per_item;
+    int C, wgs;
+    gsc_item_shape(p, M, n, C, wgs);
+    if ((int)blockIdx.y >= wgs) return;
     const int items = (M + C - 1) / C;
     const T *Kbh = reinterpret_cast<const T *>(p.K) + b * p.stride_b + h * p.stride_h;
     const T *Vbh = reinterpret_cast<const T *>(p.V) + b * p.stride_b + h * p.stride_h;
@@ -305,9 +368,9 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     const int32_t *rowbase_bh = p.rowbase + bh * ((int64_t)p.N_max + 2);
     int32_t *counts_bh = p.counts + bh * p.cap;
     bool base_bad = false;
-    int summed = INLINE_PREFIX ? gsc_base_rows(p, bh, base_bad) : 0, summed_to = 0;   // rows of the chunks [0, summed_to)
+    int summed = INLINE_PREFIX ? gsc_base_rows(p, bh, base_bad) : 0, summed_to = 0;   // rows of the items [0, summed_to)
 
-    for (int item = blockIdx.x; item < items; item += gridDim.x) {
+    for (int item = blockIdx.y; item < items; item += wgs) {
         const int m0 = item * C;
         const int nch = min(C, M - m0);
         __syncthreads();
@@ -316,9 +379,9 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
             if (!INLINE_PREFIX) s_base[tid] = rowbase_bh[m0 + tid];
         }
         if (INLINE_PREFIX) {
-            // every chunk before the item is closed by a delimiter: its rows are its clusters and one more
+            // every chunk of the items before is closed by a delimiter: its rows are its clusters and one more
             int part = 0;
-            for (int m = summed_to + tid; m < m0; m += kGscThreads) part += (pcount_bh[m] & kPcountMask) + 1;
+            for (int i = summed_to + tid; i < item; i += kGscThreads) part += rowbase_bh[i] + C;
             const int mine = (lane < nch) ? (pcount_bh[m0 + lane] & kPcountMask) + ((m0 + lane < M - 1) ? 1 : 0) : 0;
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d, kWave);
@@ -332,7 +395,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
             __syncthreads();
 #pragma unroll
             for (int w = 0; w < kGscThreads / kWave; ++w) summed += s_sum[w];
-            summed_to = m0;
+            summed_to = item;
             if (wave == 0 && lane <= nch) {
                 const int base = summed + incl - mine;
                 s_base[lane] = base;
@@ -456,10 +519,10 @@ hipError_t launch_gsc_scan(const GscParams &p, hipStream_t stream) {
 template <typename T, int D>
 static hipError_t launch_typed(const GscParams &p, hipStream_t stream) {
     const int max_items = (p.N_max + 1 + p.chunks_per_item - 1) / p.chunks_per_item;
-    // (an item per 21 tokens per chunk is what chunks of a few dozen tokens make; fewer than 128 workgroups per
-    // head would leave a short sequence's longest chunks behind one another)
-    const int gx = max(1, min(max_items, tuning().gsc_grid_x > 0 ? tuning().gsc_grid_x : max(128, p.N_max / (21 * p.chunks_per_item))));
-    const dim3 grid(gx, p.Hkv, p.B);
+    const int heads = p.B * p.Hkv;
+    const int gx = max(1, min(max_items, tuning().gsc_grid_x > 0 ? tuning().gsc_grid_x : gsc_item_workgroups(heads, p.N_max, p.chunks_per_item)));
+    const int per_layer = min(heads, 1 << kGridHeadsLog2);
+    const dim3 grid(per_layer, min(gx, 65535), (heads + per_layer - 1) / per_layer);
     hipLaunchKernelGGL((gsc_assign_kernel<T, D>), grid, dim3(kGscThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -501,6 +564,9 @@ hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
     // 30 / 33 / 45; 8 x 8192 x 128 f32 72 / 77 / 117; 8 x 32768 x 64 bf16 179 / 156 / 181).
     const int auto_item = ((int64_t)a.B * a.Hkv * a.N_max <= (int64_t(1) << 16)) ? 4 : 8;
     p.chunks_per_item = max(1, min(kMaxChunksPerItem, tuning().gsc_chunks_per_item > 0 ? tuning().gsc_chunks_per_item : auto_item));
+    const bool fixed = tuning().gsc_chunks_per_item > 0 || tuning().gsc_grid_x > 0;
+    p.short_wgs[0] = fixed ? 0 : max(1, gsc_item_workgroups(a.B * a.Hkv, p.N_max, 8));
+    p.short_wgs[1] = fixed ? 0 : max(1, gsc_item_workgroups(a.B * a.Hkv, p.N_max, 16));
 
     const size_t bh = (size_t)a.B * a.Hkv;
     char *w = reinterpret_cast<char *>(a.ws);

@@ -82,12 +82,13 @@ struct GscParams {
     int32_t *cluster_id;  // the caller's buffer, or NULL if not requested
     int32_t *seedrow;     // [B, Hkv, N_max]   seed positions of a chunk that spans several blocks
     int32_t *pcount;      // [B, Hkv, N_max + 1] clusters per chunk (+ flag bit 30)
-    int32_t *rowbase;     // [B, Hkv, N_max + 2] first output row of every chunk
+    int32_t *rowbase;     // [B, Hkv, N_max + 2] first output row of every chunk; without a scan kernel, generic path: clusters of every item
     void *ktmp;           // [B, Hkv, N_max, d] merged keys at provisional rows (fast path)
     void *vtmp;           // [B, Hkv, N_max, d] merged values at provisional rows (fast path)
     int32_t *stmp;        // [B, Hkv, N_max]   cluster sizes at provisional rows (fast path)
     int count_only;       // fast path: cluster and count only (per-chunk cluster counts and comp_lens); no values are read, no rows written
     int chunks_per_item;
+    int short_wgs[2];     // generic path: workgroups per (sequence, head) where short chunks make items of 8 / of 16 or 32, 0: they don't (see gsc_item_shape)
     int grid_x;           // fast path: workgroups per pass and (sequence, head) of the compress kernel
 };
 

@@ -285,3 +285,45 @@ def test_generic_merge_long_items(n, knobs):
     for got, want in ((Kc, ref["Kc"]), (Vc, ref["Vc"])):
         err = np.abs(got[0, 0, :rows].cpu().numpy() - want[:rows])
         assert err.max() <= tol * max(np.abs(k).max(), np.abs(v).max())
+
+
+@pytest.mark.parametrize("H,n,gap", [
+    (17, 2000, 1), (17, 2000, 2.6), (17, 2000, 9.9), (17, 2000, 10.1),    # more than 64k rows: items of 32, 16, 16 and eight chunks
+    (2, 9000, 2.4), (2, 4500, 2.4), (2, 9000, 2.6), (2, 9000, 4.4), (2, 9000, 4.6),     # fewer: of 32, 16, eight, eight, four
+    (1, 34000, 2), (1, 34000, 3),                                          # with the scan kernel
+])
+def test_generic_merge_short_chunks(H, n, gap):
+    # fp32 / d = 64, two sequences, one of them with chunks long enough for the items of other calls, appended to three rows: the
+    # same bits as with a fixed item size, and the oracle's rows
+    rng = np.random.default_rng(int(10 * gap) + n)
+    mask = np.zeros((2, n), dtype=np.uint8)
+    at = np.floor(np.arange(1, int((n - 1) / gap) + 1) * gap).astype(np.int64) - 1
+    mask[0, at] = 1
+    mask[1, 30::31] = 1
+    K = rng.standard_normal((2, H, n, 64)).astype(np.float32)
+    K[:, :, 1::2] = K[:, :, :n - n % 2:2] + 0.1 * K[:, :, 1::2]
+    V = rng.standard_normal((2, H, n, 64)).astype(np.float32)
+    dK, dV = torch.from_numpy(K).to(g.DEV), torch.from_numpy(V).to(g.DEV)
+    offsets, num_chunks, _ = g.run_segment(mask, None)
+    base = torch.full((2, H), 3, dtype=torch.int32, device=g.DEV)
+
+    def call():
+        Kc, Vc = (torch.zeros((2, H, n + 3, 64), dtype=torch.float32, device=g.DEV) for _ in range(2))
+        counts = torch.zeros((2, H, n + 3), dtype=torch.int32, device=g.DEV)
+        out = sc.sc_gsc_merge(dK, dV, offsets, num_chunks, 0.7, cap=n + 3, Kc=Kc, Vc=Vc, counts=counts, base_lens=base,
+                              comp_lens=torch.zeros_like(base), want_cluster_id=True)
+        torch.cuda.synchronize()
+        return out
+    got = call()
+    sc.tune_set("gsc_chunks_per_item", 3)
+    try:
+        fixed = call()
+    finally:
+        sc.tune_set("gsc_chunks_per_item", 0)
+    for a, b in zip(got, fixed):
+        assert torch.equal(a, b)
+    for b in range(2):
+        ref = oracle.compress_head(K[b, H - 1], V[b, H - 1], oracle.segment(mask[b], n), 0.7)
+        assert int(got[3][b, H - 1]) == 3 + ref["n_rows"]
+        assert np.array_equal(got[4][b, H - 1].cpu().numpy(), ref["cid"])
+        assert np.array_equal(got[2][b, H - 1, 3:3 + ref["n_rows"]].cpu().numpy(), ref["counts"][:ref["n_rows"]])
