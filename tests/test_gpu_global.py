@@ -142,6 +142,24 @@ def test_blocks_that_wait_for_others(n, tau, polls):
     print("n=%d tau=%g polls=%d rows %s" % (n, tau, polls, out["comp_lens"].tolist()))
 
 
+@pytest.mark.parametrize("n,step,tau,polls", [(700, 0.2, 0.9, 4096), (700, 0.4, 0.8, 0), (900, 0.1, 0.8, 4096), (700, 0.05, 0.99875, 4096)])
+def test_rows_that_drift(n, step, tau, polls):
+    # every row resembles its neighbours: chains through a block, taken in order, from block to block; clusters of a few
+    # rows, of dozens, and (last) neighbours whose cosines lie in the band that fp64 settles
+    rng = np.random.default_rng(n)
+    K = rng.standard_normal((n, 128))
+    for i in range(1, n):
+        K[i] = np.sqrt(1 - step * step) * K[i - 1] + step * K[i]
+    K[200:203] = 0.0
+    old = sc.tune_get("global_polls")
+    try:
+        sc.tune_set("global_polls", polls)
+        ref = _run_rows(_bf16_exact(K), _bf16_exact(rng.standard_normal((n, 128))), tau)
+    finally:
+        sc.tune_set("global_polls", old)
+    assert 4 < ref["n_rows"] < 0.8 * n
+
+
 def test_zero_rows_duplicates_and_scaled_rows():
     # zero rows resemble nothing (also inside a block and across blocks), exact duplicates and scaled copies merge
     rng = np.random.default_rng(5)
