@@ -384,7 +384,7 @@ sc_status sc_stream_read_probe(const void *src, size_t bytes, void *sink, void *
  *                          from the mean chunk length of the sequence
  *   "gsc_grid_x"           workgroups per pass and (sequence, KV head); <= 0 = chosen from N_max
  *   "global_polls"         sc_gsc_merge_global: looks at rows that another workgroup decides before the ordered pass
- *                          takes over (default 4096; <= 0: gives up at the first; the outcome is the same)
+ *                          takes over (default 1 << 20, half a second; <= 0: gives up at the first; the outcome is the same)
  *   "multi_block_rows"     sc_multi_attn: query rows per workgroup, 32 (every wavefront holds all of them) or 128 (32
  *                          per wavefront); anything else = chosen from the shape
  *   "multi_target_wgs"     sc_multi_attn: compute units the split count reckons with (default 256)

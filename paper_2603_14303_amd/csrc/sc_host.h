@@ -119,7 +119,7 @@ struct Tuning {
     int gsc_grid_x = 0;             // workgroups per pass and (sequence, KV head); <= 0 picks it from the sequence length
     int gsc_chunks_per_task = 0;    // fast path: chunks handled by one single-wave workgroup; <= 0: 2, or 1 for a call of a few thousand tokens
     int gsc_fast_path = 1;          // 0 forces the generic kernels even for bf16 / d = 128
-    int global_polls = 1 << 12;     // sc_gsc_merge_global: looks (about 1 us each) at rows another block decides before the ordered pass takes over
+    int global_polls = 1 << 20;     // sc_gsc_merge_global: looks (about 0.5 us each) at rows another block decides before the ordered pass takes over
     int multi_block_rows = 0;       // query rows per workgroup of sc_multi_attn: 32 or 128; anything else picks it from the shape of the call
     int multi_target_wgs = 256;     // compute units the split count of sc_multi_attn reckons with
 };
