@@ -868,7 +868,7 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t stream) {
     int splits = clamp_splits();
     if (tuning().decode_max_splits <= 0) splits = max(2, min(32, 256 / max(1, a.B * a.Hkv)));
     // never more splits than the capacity can feed
-    const int by_cap = (a.cap + p.tail_cap + p.min_rows - 1) / p.min_rows;
+    const int by_cap = (int)(((int64_t)a.cap + p.tail_cap + p.min_rows - 1) / p.min_rows);
     p.max_splits = max(1, min(splits, by_cap));
     const int G = a.Hq / a.Hkv;
     if (a.kv_dtype == DType::BF16)

@@ -591,7 +591,7 @@ static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail ro
     if (tuning().multi_block_rows == kMwRows || tuning().multi_block_rows == kMbRows) block_rows = tuning().multi_block_rows;
     row_blocks = (nq * G + block_rows - 1) / block_rows;
     min_rows = 128;
-    const int by_cap = (cap + min_rows - 1) / min_rows;      // never more splits than the capacity can feed
+    const int by_cap = (int)(((int64_t)cap + min_rows - 1) / min_rows);      // never more splits than the capacity can feed
     const int most = max(1, min(kMqMaxSplits, by_cap));
     const int base = B * Hkv * row_blocks;
     if (block_rows == kMwRows) {
@@ -604,7 +604,7 @@ static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail ro
     // round of pairs takes as long as the first; partials cost the second kernel 3 us and 20 ns per workgroup
     // (1400 rows, 4 heads, 5 200 cache rows: 57 us with 12 splits = 1.03 rounds, 46 us with 11).  In units of 0.1 us:
     const int64_t units = max(1, tuning().multi_target_wgs);
-    const int tiles = max(1, 3 * cap / (4 * kMbTile));       // the caches are hardly ever full
+    const int64_t tiles = max((int64_t)1, 3 * (int64_t)cap / (4 * kMbTile));       // the caches are hardly ever full
     int64_t best = INT64_MAX;
     max_splits = 1;
     for (int s = 1; s <= most; ++s) {
@@ -626,7 +626,7 @@ static bool mq_fast(const MultiArgs &a) {
 size_t multi_fast_workspace_bytes(int B, int Hq, int Hkv, int nq, int cap) {
     int rb, ms, mr, br;
     mq_shape(B, Hq, Hkv, nq, cap, rb, ms, mr, br);
-    const int64_t most = min(kMqMaxSplits, (cap + mr - 1) / mr), units = max(1, tuning().multi_target_wgs);
+    const int64_t most = min((int64_t)kMqMaxSplits, ((int64_t)cap + mr - 1) / mr), units = max(1, tuning().multi_target_wgs);
     if (most <= 1) return 0;
     const int64_t wgs = min((int64_t)B * Hkv * rb * most, br == kMwRows ? units * 3 / 4 : kMbMostRounds * units);
     return align_up((size_t)wgs * br * kMqPart * 4, 256);

@@ -193,13 +193,18 @@ def test_multi_attn_rejects_bad_arguments(lib):
     assert call(ws=None) == 4 and call(wsb=need - 1) == 4
 
 
+@pytest.mark.parametrize("knob", [0, 128])
 @pytest.mark.parametrize("B, Hkv, G", [(1, 1, 1), (1, 8, 4), (3, 5, 7), (8, 2, 8), (40, 8, 1)])
-def test_multi_attn_workspace_serves_smaller_calls(lib, B, Hkv, G):
+def test_multi_attn_workspace_serves_smaller_calls(lib, B, Hkv, G, knob):
     """A workspace sized for the longest chunk and the fullest cache is big enough for every shorter one: the size never
     falls when a dimension grows (the split count of the largest call may well be smaller than that of another)."""
     nqs = [1, 2, 3, 7, 8, 9, 16, 31, 33, 64, 100, 129, 256, 300, 512, 700, 1024, 2048, 4096]
-    caps = [1, 64, 127, 129, 300, 512, 1000, 1537, 2048, 3000, 5400, 8081, 8193, 20000, 34000, 100000, 1 << 20]
-    size = [[lib.sc_multi_attn_workspace_bytes(B, Hkv * G, Hkv, nq, cap, 128) for cap in caps] for nq in nqs]
+    caps = [1, 64, 127, 129, 300, 512, 1000, 1537, 2048, 3000, 5400, 8081, 8193, 20000, 34000, 100000, 1 << 20, 1 << 30, 2**31 - 1]
+    assert lib.sc_tune_set(b"multi_block_rows", knob) == 0
+    try:
+        size = [[lib.sc_multi_attn_workspace_bytes(B, Hkv * G, Hkv, nq, cap, 128) for cap in caps] for nq in nqs]
+    finally:
+        lib.sc_tune_set(b"multi_block_rows", 0)
     for row in size:
         assert row == sorted(row)
     for col in zip(*size):
