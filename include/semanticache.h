@@ -386,10 +386,10 @@ sc_status sc_stream_read_probe(const void *src, size_t bytes, void *sink, void *
  *   "global_polls"         sc_gsc_merge_global: looks at rows that another workgroup decides before the ordered pass
  *                          takes over (default 1 << 20, half a second; <= 0: gives up at the first; the outcome is the same)
  *   "multi_block_rows"     sc_multi_attn: query rows per workgroup, 32 (every wavefront holds all of them) or 128 (32
- *                          per wavefront); anything else = chosen from the shape
+ *                          per wavefront); anything else = chosen from the shape.  A single query row always takes 32
  *   "multi_target_wgs"     sc_multi_attn: compute units the split count reckons with (default 256)
- *                          (these two enter sc_multi_attn_workspace_bytes: set them before asking for the
- *                          size; a workspace that has become too small is refused with SC_ERR_WORKSPACE)
+ *                          (these two enter sc_multi_attn_workspace_bytes, the second sc_decode_attn_workspace_bytes
+ *                          as well: set them before asking for the size; a workspace that has become too small is refused with SC_ERR_WORKSPACE)
  * Return 0 / the value, or -1 for an unknown key.
  */
 int sc_tune_set(const char *key, int value);

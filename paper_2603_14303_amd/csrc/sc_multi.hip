@@ -33,9 +33,10 @@ struct MqParams {
     int tail_cap, causal;     // causal: the last nq tail rows are the query rows' own tokens
     int nq, cap, B, Hq, Hkv, G;
     float scale_log2;
-    float *part;              // [B*Hkv*row_blocks][max_splits][block_rows][kMqPart]
+    float *part;              // [B*Hkv*row_blocks][max_splits][part_rows][kMqPart]
     int row_blocks, max_splits, min_rows;
     int block_rows;           // query rows per workgroup: 32 (multi_wave_kernel) or 128 (multi_block_kernel)
+    int part_rows;            // rows of a partial: as many as the workgroups have query rows, block_rows at most
     void *O;                  // [nq, B, Hq, 128]
     int o_is_bf16;
     float *lse;               // [nq, B, Hq] or NULL
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
     __syncthreads();
     // thread: piece tid % 32 of the query rows tid / 32 + 8 r
     const int q4 = tid & 31;
-    float *part = p.part + (((bh * p.row_blocks + rb) * (int64_t)p.max_splits + split) * kMwRows) * kMqPart;
+    float *part = p.part + (((bh * p.row_blocks + rb) * (int64_t)p.max_splits + split) * p.part_rows) * kMqPart;
 #pragma unroll
     for (int r = 0; r < kMwRows / 8; ++r) {
         const int row = (tid >> 5) + 8 * r, Rr = rb * kMwRows + row;
@@ -517,7 +518,7 @@ __global__ __launch_bounds__(kMbThreads, 2) void multi_block_kernel(MqParams p) 
                               m_run, l_run, half == 0 && dt == 0 && k == 0);
         return;
     }
-    float *part = p.part + (((bh * p.row_blocks + rb) * (int64_t)p.max_splits + split) * kMbRows + wave * 32 + c) * kMqPart;
+    float *part = p.part + (((bh * p.row_blocks + rb) * (int64_t)p.max_splits + split) * p.part_rows + wave * 32 + c) * kMqPart;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -542,8 +543,8 @@ __global__ __launch_bounds__(kMqCombineRows *kWave) void multi_attn_combine_kern
     const int rows_total = min(max(p.comp_lens[bh], 0), p.cap) + (p.Kt ? min(max(p.tail_lens[b], 0), p.tail_cap) : 0);
     const int S = mq_splits_for(rows_total, p.max_splits, p.min_rows);
     const int rb = R / p.block_rows, row = R - rb * p.block_rows;
-    const float *part = p.part + (((bh * p.row_blocks + rb) * (int64_t)p.max_splits) * p.block_rows + row) * kMqPart;
-    const int64_t split_stride = (int64_t)p.block_rows * kMqPart;
+    const float *part = p.part + (((bh * p.row_blocks + rb) * (int64_t)p.max_splits) * p.part_rows + row) * kMqPart;
+    const int64_t split_stride = (int64_t)p.part_rows * kMqPart;
     constexpr int kPass = 8;
     float4 v[kPass];
     auto load_pass = [&](int s0) {
@@ -588,7 +589,8 @@ static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail ro
     // them are shared out themselves, 32 to a wavefront, so that a cache row is fetched once per 128 of them.
     // (8 heads x 5 400 cache rows, us per call on either kernel: 32 rows 17.0 / 19.4, 64 rows 28.7 / 23.1.)
     block_rows = (nq * G <= kMwRows) ? kMwRows : kMbRows;
-    if (tuning().multi_block_rows == kMwRows || tuning().multi_block_rows == kMbRows) block_rows = tuning().multi_block_rows;
+    // (a single query row always takes the first kernel: sc_decode_attn's workspace has room for that route, whatever the knob says)
+    if (nq > 1 && (tuning().multi_block_rows == kMwRows || tuning().multi_block_rows == kMbRows)) block_rows = tuning().multi_block_rows;
     row_blocks = (nq * G + block_rows - 1) / block_rows;
     min_rows = 128;
     const int by_cap = (int)(((int64_t)cap + min_rows - 1) / min_rows);      // never more splits than the capacity can feed
@@ -616,6 +618,8 @@ static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail ro
     }
 }
 
+static int mq_part_rows(int nq, int G, int block_rows) { return min(nq * G, block_rows); }
+
 static bool mq_fast(const MultiArgs &a) {
     return a.d == kMqD && a.q_dtype == DType::BF16 && a.kv_dtype == DType::BF16;
 }
@@ -629,7 +633,7 @@ size_t multi_fast_workspace_bytes(int B, int Hq, int Hkv, int nq, int cap) {
     const int64_t most = min((int64_t)kMqMaxSplits, ((int64_t)cap + mr - 1) / mr), units = max(1, tuning().multi_target_wgs);
     if (most <= 1) return 0;
     const int64_t wgs = min((int64_t)B * Hkv * rb * most, br == kMwRows ? units * 3 / 4 : kMbMostRounds * units);
-    return align_up((size_t)wgs * br * kMqPart * 4, 256);
+    return align_up((size_t)wgs * mq_part_rows(nq, Hq / Hkv, br) * kMqPart * 4, 256);
 }
 
 size_t multi_workspace_bytes(int B, int Hq, int Hkv, int nq, int cap, int d) {
@@ -679,6 +683,7 @@ hipError_t launch_multi_fast(const MultiArgs &a, hipStream_t stream) {
     p.scale_log2 = a.scale * kMqLog2e;
     p.part = reinterpret_cast<float *>(a.ws);
     mq_shape(a.B, a.Hq, a.Hkv, a.nq, a.cap + p.tail_cap, p.row_blocks, p.max_splits, p.min_rows, p.block_rows);
+    p.part_rows = mq_part_rows(a.nq, p.G, p.block_rows);
     p.O = a.O; p.o_is_bf16 = a.o_dtype == DType::BF16; p.lse = a.lse;
     const dim3 grid((unsigned)(p.max_splits * p.row_blocks * a.Hkv * a.B));
     if (p.block_rows == kMbRows) {

@@ -211,6 +211,22 @@ def test_multi_attn_workspace_serves_smaller_calls(lib, B, Hkv, G, knob):
         assert list(col) == sorted(col)
 
 
+def test_decode_workspace_does_not_depend_on_the_multi_row_knob(lib):
+    """The optional route of sc_decode_attn through sc_multi_attn's kernels needs no more than its own kernel: partials of G rows
+    for 64 splits of every head, and the flags."""
+    shapes = [(B, H, G) for B in (1, 3, 32) for H in (1, 2, 8) for G in (1, 4, 7, 8)]
+    size = lambda: [lib.sc_decode_attn_workspace_bytes(B, H * G, H, 5000, 128) for B, H, G in shapes]
+    want = size()
+    for (B, H, G), got in zip(shapes, want):
+        assert got <= 64 * B * H * G * 132 * 4 + 520 * B * H + 3 * 256
+    for knob in (32, 128):
+        assert lib.sc_tune_set(b"multi_block_rows", knob) == 0
+        try:
+            assert size() == want
+        finally:
+            lib.sc_tune_set(b"multi_block_rows", 0)
+
+
 def test_gsc_merge_budget_rejects_bad_arguments(lib):
     f = lib.sc_gsc_merge_budget
     need = lib.sc_gsc_merge_budget_workspace_bytes(1, 2, 1024, 64)
