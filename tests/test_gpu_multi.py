@@ -1,8 +1,8 @@
 """GPU parity for sc_multi_attn (Eq. 4 with a matrix of query rows, Sec. 2.4) against the CPU oracle.
 
-Same bounds as for single-row decode on the same cache: <= 4e-3 * max(1, |O|) with bf16 output (the
-matrix-core path also rounds the probabilities to bf16, relative 2^-9 per term), 2e-5 with fp32 output
-through the row-by-row path; lse <= 1e-3."""
+Same bounds as for single-row decode on the same cache: <= 4e-3 * max(1, |O|) with bf16 output (half an ulp of the
+output; on the matrix-core path the probabilities enter as two bf16 parts, 2^-18 at most per term), 2e-5 with
+fp32 output through the row-by-row path; lse <= 1e-3."""
 import numpy as np
 import pytest
 import torch
@@ -137,29 +137,43 @@ def test_multi_attn_tail_mask_needs_the_matrix_core_path():
     assert torch.allclose(O, torch.full_like(O, 2.0), atol=1e-5)
 
 
+@pytest.mark.parametrize("nq,tcap", [(7, 0), (7, 30), (33, 0), (33, 70)])      # 28 and 132 query rows per KV head
 @pytest.mark.parametrize("knobs", [
-    dict(multi_block_rows=16, multi_target_wgs=64), dict(multi_block_rows=32, multi_target_wgs=1024),
-    dict(multi_block_rows=16, multi_target_wgs=1024), dict(multi_block_rows=32, multi_target_wgs=8),
+    dict(multi_block_rows=32, multi_target_wgs=64), dict(multi_block_rows=128, multi_target_wgs=1024),
+    dict(multi_block_rows=32, multi_target_wgs=1024), dict(multi_block_rows=128, multi_target_wgs=8),
 ])
-def test_multi_attn_launch_shapes(knobs):
-    # one or two tiles of query rows per workgroup, few and many splits: the workspace query and the launch
-    # follow the same knobs, the result stays within the bound of the default shape
+def test_multi_attn_launch_shapes(knobs, nq, tcap):
+    # either kernel with rows for a part of its workgroup and for several of them, few and many splits, without a tail and with
+    # a masked one: the workspace query and the launch follow the same knobs, the result stays within the bound of the default
+    # shape, and a decode workspace made before serves sc_decode_attn as before
     rng = np.random.default_rng(641)
-    B, Hkv, G, cap, nq, d = 2, 4, 4, 3000, 7, 128          # 28 query rows per KV head
+    B, Hkv, G, cap, d = 2, 4, 4, 3000, 128
     Hq = Hkv * G
     Q = _round_like(rng.standard_normal((nq, B, Hq, d)), True)
     Kc, Vc = _round_like(rng.standard_normal((B, Hkv, cap, d)), True), _round_like(rng.standard_normal((B, Hkv, cap, d)), True)
     counts = rng.integers(1, 40, (B, Hkv, cap)).astype(np.int32)
     lens = rng.integers(cap // 2, cap + 1, (B, Hkv)).astype(np.int32)
     lens[0, 0] = cap
-    want_O, want_L = oracle.multi_attn(Q, Kc, Vc, counts, lens)
+    tail = {}
+    if tcap:
+        Kt, Vt = _round_like(rng.standard_normal((B, Hkv, tcap, d)), True), _round_like(rng.standard_normal((B, Hkv, tcap, d)), True)
+        tails = np.array([tcap, nq + 1], np.int32)
+        want_O, want_L = oracle.multi_attn_tail(Q, Kc, Vc, counts, lens, Kt, Vt, tails, True)
+        tail = dict(Kt=g.to_device(Kt, True), Vt=g.to_device(Vt, True), tail_lens=torch.from_numpy(tails).to(g.DEV), causal=True)
+    else:
+        want_O, want_L = oracle.multi_attn(Q, Kc, Vc, counts, lens)
     dQ, dKc, dVc = g.to_device(Q, True), g.to_device(Kc, True), g.to_device(Vc, True)
     dcounts, dlens = torch.from_numpy(counts).to(g.DEV), torch.from_numpy(lens).to(g.DEV)
+    ws = sc.decode_attn_workspace(B, Hq, Hkv, cap, d, g.DEV)
+    want_D, _ = sc.sc_decode_attn(dQ[0].contiguous(), dKc, dVc, dcounts, dlens, workspace=ws)
     old = {k: sc.tune_get(k) for k in knobs}
     try:
         for k, v in knobs.items():
             sc.tune_set(k, v)
-        O, lse = sc.sc_multi_attn(dQ, dKc, dVc, dcounts, dlens, want_lse=True)
+        O, lse = sc.sc_multi_attn(dQ, dKc, dVc, dcounts, dlens, want_lse=True, **tail)
+        if knobs["multi_target_wgs"] <= 256:      # (a larger target may ask for a larger workspace)
+            got_D, _ = sc.sc_decode_attn(dQ[0].contiguous(), dKc, dVc, dcounts, dlens, workspace=ws)
+            assert torch.equal(got_D, want_D)
         torch.cuda.synchronize()
     finally:
         for k, v in old.items():
