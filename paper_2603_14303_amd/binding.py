@@ -10,7 +10,10 @@ import ctypes
 import os
 from typing import Optional
 
-import torch
+try:
+    import torch
+except ImportError:      # the library, its host-side queries and its error codes are there without torch, the wrappers are not
+    torch = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsemanticache.so")
@@ -123,7 +126,7 @@ def _check(status: int, what: str) -> None:
 # they look at (device, layout, type, shape) is read once per tensor, in expressions rather than through helpers called per
 # tensor.  Host time of a decode call with a tail, launch included: 13.4 us with helpers, now 10.0, so that the GPU is not kept
 # waiting (32 layers, 5400 rows: 434 -> 346 us a token; segment, merge and eight decode steps on 1024 tokens: 111 -> 89).
-_DTYPE_CODES = {torch.float32: SC_F32, torch.bfloat16: SC_BF16}
+_DTYPE_CODES = {torch.float32: SC_F32, torch.bfloat16: SC_BF16} if torch is not None else {}
 
 
 def _dtype_code(t) -> int:

@@ -3,6 +3,8 @@ header declares, and rejects bad arguments before anything is launched."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -17,6 +19,13 @@ def lib():
         from paper_2603_14303_amd import build
         build.build(force=True)
     return sc.load_library()
+
+
+def test_library_loads_without_torch(lib):
+    code = ("import sys; sys.modules['torch'] = None\n"
+            "from paper_2603_14303_amd import binding as sc\n"
+            "assert sc.load_library().sc_decode_attn_workspace_bytes(1, 8, 2, 512, 128) > 0 and sc.tune_get('gsc_grid_x') == 0")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
 
 
 def _declared_symbols():
