@@ -4,7 +4,7 @@
 //
 // Fast path (bf16 queries and cache, d = 128) on the matrix cores.  The query rows that share a KV head -- (query j, head g of
 // the group), nq * G of them -- are the columns of 32 x 32 product tiles, the cache rows are cut into splits:
-//   multi_wave_kernel   up to 32 query rows: every wavefront holds all of them and takes cache rows of its own;
+//   multi_wave_kernel   few query rows: every wavefront of a workgroup holds the same 32 and takes cache rows of its own;
 //   multi_block_kernel  more: the wavefronts of a workgroup hold 32 query rows each and share tiles of cache rows in LDS.
 // Both form S^T = K Q^T and O^T += V^T P^T, so that a query row stays on one lane pair from the logits to the output, and
 // write one partial (sums, maximum, denominator) per query row and split; multi_attn_combine_kernel folds them.  Two launches instead of a
@@ -130,14 +130,15 @@ __device__ __forceinline__ void mq_store_row4(const MqParams &p, int64_t orow, i
 }
 
 // ------------------------------------------------------------------------------------------------
-// A few query rows (nq * G <= 32 per KV head): multi_wave_kernel.
+// A few query rows (nq * G <= 32 per KV head, more in small calls): multi_wave_kernel.
 //
 // The four wavefronts of a workgroup hold the same 32 query rows and take alternate steps of 32 cache rows, each in an
 // LDS area of its own: no barrier until the end, and a wavefront's 16 KB of loads for the next step fly while it works on
-// this one (128 KB in flight per compute unit; what bounds the kernel is the trip to memory and the chain after it).
+// this one (64 KB in flight per workgroup; what bounds the kernel is the trip to memory and the chain after it).
 // Arithmetic and operand layouts are those of multi_block_kernel below; the wavefronts fold through LDS at the end.
-// 8 heads x 32 query rows x 5 500 cache rows (22.6 MB): 16.6 us per call with the second kernel; 25.4 with 16 query rows per
-// workgroup in registers only, whose 256 vector registers left nothing in flight while a step was worked on.
+// 8 heads x 32 query rows behind 5 385 + 108 rows (22.5 MB): 15.4 us per call with the second kernel, 24.0 with 16 query rows per
+// workgroup in registers only, whose 256 vector registers left nothing in flight while a step was worked on; 5 400 rows without
+// a tail 14.5 / 14.7.
 constexpr int kMwThreads = kMqWaves * kWave;
 constexpr int kMwRows = 32;                       // query rows per workgroup
 constexpr int kMwStep = 32;                       // cache rows per wavefront and step
@@ -332,8 +333,8 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
 // split takes 8 192 (2.4e-6 / 2.1e-6 and 1.3e-6 / 8.7e-7): fewer largest weights, longer sums.
 // Bound by instruction issue: per 64 cache rows a wavefront spends 48 matrix instructions of 32 cycles and as many cycles
 // of vector work on the logits of its lanes, and the two wavefronts of a SIMD overlap little of it (counters: 46 % of the
-// time matrix, 46 % vector).  8 heads x 2048 query rows (nq = 512, G = 4) x 5 900 cache rows, 47 GFLOP: 402 us with 32 rows
-// per workgroup and no sharing of tiles (115 TFLOP/s), now 102 us with the second kernel (460 TFLOP/s).
+// time matrix, 46 % vector).  8 heads x 2048 query rows (nq = 512, G = 4) x 5 900 cache rows, 49 GFLOP: 238 us with 32 rows
+// per workgroup and no sharing of tiles (208 TFLOP/s), now 100 us with the second kernel (496 TFLOP/s).
 constexpr int kMbWaves = 4;
 constexpr int kMbThreads = kMbWaves * kWave;
 constexpr int kMbRows = 32 * kMbWaves;            // query rows per workgroup
@@ -585,10 +586,19 @@ __global__ __launch_bounds__(kMqCombineRows *kWave) void multi_attn_combine_kern
 constexpr int kMbMostRounds = 4;      // multi_block_kernel: splits end at this many workgroups per compute unit
 static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail rows */, int &row_blocks, int &max_splits, int &min_rows, int &block_rows) {
     const int G = Hq / Hkv;
-    // Up to 32 query rows per KV head fit the lanes of every wavefront, and the wavefronts share out the cache rows; more of
-    // them are shared out themselves, 32 to a wavefront, so that a cache row is fetched once per 128 of them.
-    // (8 heads x 5 400 cache rows, us per call on either kernel: 32 rows 17.0 / 19.4, 64 rows 28.7 / 23.1.)
-    block_rows = (nq * G <= kMwRows) ? kMwRows : kMbRows;
+    // Up to 32 query rows per KV head fit the lanes of every wavefront, and the wavefronts share out the cache rows.  More of
+    // them are shared out themselves, 32 to a wavefront, so that a cache row is fetched once per 128 of them: that pays once
+    // the products do, and not while a call waits for its cache rows on chains that are longer with fewer rows per workgroup and step.
+    // us per call, first / second kernel / 16 or 32 rows per workgroup in registers, rows of a KV head x cache rows:
+    //   8 heads   64 x 5 400  15.8 / 20.6 / 19.5   128  20.8 / 24.2 / 27.5   256  30.3 / 30.2 / 40.9   384  39.6 / 34.4 / 83.4
+    //   8 heads, masked tail  64  17.4 / 21.1 / 27.3   128  24.0 / 24.7 / 42.7   160  30.0 / 28.9 / 48.6
+    //   2 heads  160 x 5 400  15.7 / 18.7 / 17.3   256  16.2 / 21.6 / 19.1;  1 head  64 x 30 000  18.2 / 28.1 / 22.3   256  30.8 / 31.8 / 31.8
+    //   32 heads  96 x 2 000  22.1 / 24.8 / 41.0   128  28.4 / 26.7 / 35.8;  64 heads  64 x 4 000  48.5 / 43.3 / 61.2
+    //   128 heads  64 x 500  14.1 / 24.0 / 27.8 (one split, all workgroups at once, four steps)
+    const int blocks = (nq * G + kMwRows - 1) / kMwRows;
+    const int64_t groups = (int64_t)B * Hkv * blocks, steps = 3 * (int64_t)cap / (4 * kMqWaves * kMwStep);
+    const bool wave = blocks <= 1 || (blocks <= 4 && (groups <= 96 || (groups <= 256 && steps <= 8))) || (blocks <= 8 && groups <= 16);
+    block_rows = wave ? kMwRows : kMbRows;
     // (a single query row always takes the first kernel: sc_decode_attn's workspace has room for that route, whatever the knob says)
     if (nq > 1 && (tuning().multi_block_rows == kMwRows || tuning().multi_block_rows == kMbRows)) block_rows = tuning().multi_block_rows;
     row_blocks = (nq * G + block_rows - 1) / block_rows;
@@ -598,7 +608,9 @@ static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail ro
     const int base = B * Hkv * row_blocks;
     if (block_rows == kMwRows) {
         // Bound by the trip to memory: three workgroups on four compute units have enough in flight, and every further split
-        // only adds partials for the second kernel (32 rows, 8 heads x 5 500 cache rows: 17.0 us with 24 splits, 19.4 with 43).
+        // only adds partials for the second kernel (32 rows, 8 heads x 5 500 cache rows: 14.7 us with 24 splits, 19.2 with 42).
+        // From 97 (sequence, KV head, row block) groups on that is one split: 128 x 2 000 cache rows 29.9 us, 30.0 with three,
+        // 192 x 500 14.8 / 20.5, 192 x 2 000 35.3 / 41.8, but 104 x 2 000 28.8 / 27.4 and 128 x 4 000 53.3 / 49.0.
         max_splits = max(1, min(most, max(1, tuning().multi_target_wgs) * 3 / 4 / base));
         return;
     }
