@@ -828,10 +828,11 @@ static hipError_t launch_td(const DecParams &p, int G, hipStream_t stream) {
 }
 
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t stream) {
-    // Optional route (knob, off by default): a single query row through the kernel for blocks of query rows,
-    // which treats the G heads as one 16-row tile, writes partials and folds them in a second launch.  The
-    // decode kernel above measured level or slightly ahead of it for every group size (35.3 against 36.1 us
-    // at G = 7 on a ragged batch of 32).  Its partials go behind the flags, which it neither needs nor touches.
+    // Optional route (knob, off by default): a single query row through multi_wave_kernel, whose tiles of 32 query rows hold
+    // the G heads; with several splits the partials are folded in a second launch.  us per call,
+    // kernel above / route: 8 heads, G = 4, 5 400 rows 10.2 / 11.9; ragged batch of 32 x 4, G = 7, 2 035 rows 28.9 / 34.5; 64 heads, G = 8, 4 000
+    // rows 26.0 / 28.1; but 256 heads, G = 8, 2 000 rows 48.8 / 43.8.
+    // Its partials go behind the flags, which it neither needs nor touches.
     if (a.kv_dtype == DType::BF16 && a.q_dtype == DType::BF16 && a.d == 128 &&
         a.Hq / a.Hkv >= tuning().decode_mfma_min_group) {
         MultiArgs m;

@@ -28,7 +28,6 @@ namespace sc {
 
 typedef float gl_float4 __attribute__((ext_vector_type(4)));
 typedef unsigned int gl_u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int gl_u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 gl_bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kGlD = 128;
@@ -92,16 +91,6 @@ __device__ __forceinline__ bool gl_cosine_exceeds_f64(const bf16_t *a_row, const
     aa = wave_allreduce_sum(aa);
     bb = wave_allreduce_sum(bb);
     return dot / (sqrt(aa) * sqrt(bb)) > (double)tau;
-}
-__device__ __forceinline__ int wave_max_i32(int x) {      // maximum over the wavefront, every lane gets it
-    x = max(x, dpp<kDppQuadXor1>(x));
-    x = max(x, dpp<kDppQuadXor2>(x));
-    x = max(x, dpp<kDppHalfMirror>(x));
-    x = max(x, dpp<kDppMirror>(x));
-    auto r = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
-    x = max((int)r[0], (int)r[1]);
-    r = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
-    return max((int)r[0], (int)r[1]);
 }
 __device__ __forceinline__ int gl_seq_len(const GlobParams &p, int b) {
     int n = p.seq_lens ? p.seq_lens[b] : p.N_max;
