@@ -449,9 +449,9 @@ __device__ __forceinline__ void gram_bitmatrix(char *lds, const RowRegs &x, int 
 // Pairs (other, j), one for every lane j in `todo` (`other` is that lane's own value): returns the lanes whose pair is
 // above tau in fp64.  Both rows are parked in LDS by gram_bitmatrix (the parked bf16 values are the inputs themselves).
 // A pair takes the 16 lanes of a row, so four are settled at once: the chain of a pair (two LDS reads, the sums, two
-// square roots and a division) is long, and a threshold inside the band of the similarities asks for many.  Whole calls, one
-// pair at a time on all 64 lanes before: 4 x 8 heads x 32768 tokens, tau 0.979, 293.9 -> 291.3 us; twelve counting probes
-// and a merge of 8 x 32768 481.4 -> 476.2 us.
+// square roots and a division) is long, and a threshold inside the band of the similarities asks for many.  Whole calls change
+// little by it and by the carried seeds below: against one pair at a time on all 64 lanes, twelve counting probes and a merge of
+// 8 heads x 32768 481 -> 476 us, 4 x 8 x 32768 at tau 0.979 293 -> 292, 1 x 8 x 131072 with long chunks at 0.7 178 -> 176.5.
 __device__ __forceinline__ uint64_t settle_pairs_f64(const char *lds, uint64_t todo, int other, float tau, int lane) {
     const int g = lane >> 4, c = lane & 15;
     uint64_t above = 0ull;
@@ -809,7 +809,9 @@ __global__ __launch_bounds__(kFastTaskThreads, COUNT ? 3 : 2) void gsc_compress_
                         // first fit over the seeds of the group; a pair inside the band is settled in fp64
                         // when it is the first candidate of its row.  The keys of seed c are in the registers of
                         // the four lanes (c, g) and the rows in LDS, so every seed settles one row at a time
-                        // (before: one pair at a time, through the seed list to two rows in memory).
+                        // (one pair at a time, through the seed list to a row in memory: long chunks at a threshold above the
+                        // band 2 % slower, in the band 1 to 2 % faster where a call is a few windows: 8 heads x 8000 tokens
+                        // 57.2 us against 55.5 at tau 0.7, 126.7 against 128.5 at 0.979).
                         for (;;) {
                             const uint32_t pend = cyes | cuns;
                             const int f = (pend != 0u) ? (__ffs(pend) - 1) : -1;
