@@ -102,7 +102,7 @@ def main():
          "fetch_scale %.5f" % ff, "write_scale %.5f" % wf]
     total = {}
     for key, pats in (("gsc_compress", ("gsc_compress_kernel",)), ("gsc_scan", ("gsc_scan_kernel",)), ("gsc_relocate", ("gsc_relocate_kernel",)),
-                      ("decode", ("decode_bf16_kernel",)), ("decode_mfma", ("multi_attn_kernel",)), ("decode_mfma_combine", ("multi_attn_combine_kernel",)),
+                      ("decode", ("decode_bf16_kernel",)), ("decode_mfma", ("multi_wave_kernel",)), ("decode_mfma_combine", ("multi_attn_combine_kernel",)),
                       ("segment", ("segment_kernel",))):
         f = [(n, v) for (k, c), (n, v) in F.items() if c == "FETCH_SIZE" and all(p in k for p in pats)]
         wv = [(n, v) for (k, c), (n, v) in W.items() if c == "WRITE_SIZE" and all(p in k for p in pats)]
