@@ -156,16 +156,16 @@ __device__ int gsc_chunk(const T *__restrict__ Kbh, int64_t stride_n, int start,
 //   8 heads x 32768 x 64 f32  265 / 138 / 107 (152) 187 / 104 / 101 (110) 150 / 126 / 129 (128) 118 /  96 /  97 (98)  96 /  92 / 105 (124)
 //   64 x 1200 x 64 f32         82 /  56 /  41 (46)   61 /  41 /  39 (40)   53 /  50 /  59 (54)   46 /  45 /  56 (53)  40 /  40 /  65 (65)
 // Calls that would take four, 4 / 8 / 16 / 32 chunks, distance 1, 2, 3, 6 (up to four tokens eight, up to two 16 or 32):
-//   2 x 32768 x 64 f32        123 / 80 / 75 / 56 (99), 85 / 57 / 52 / 50 (65), 79 / 64 / 87 / 80 (95), 52 / 57 / 71 / 87 (76)
+//   2 x 32768 x 64 f32 (128 workgroups per head)  123 / 80 / 75 / 56 (99), 85 / 57 / 52 / 50 (65), 79 / 64 / 87 / 80 (95), 52 / 57 / 71 / 87 (76)
 // and with an item for every workgroup anyway (2 x 1024 x 64 f32, distance 4) 14.4 / 15.4 / 21.2 / 35.9 (23.9).
 //
-// Workgroups per (sequence, head) that take such items: an item per 21 tokens per chunk is what chunks of a few dozen tokens make;
-// fewer than 128 would leave a short sequence's longest chunks behind one another, but 2048 over all heads fill the chip, and idle
-// ones cost a launch slot each (128 for every head / this: 128 x 2000 x 64 f32 83 / 68, 16 x 8 x 8192 x 64 bf16 398 / 265; with the
-// item order below).  The grid is for p.chunks_per_item.  (With every
-// workgroup of it on items of 16, 8 x 32768 x 64 f32, distance 1, takes 169 instead of 140 us and distance 2 118 instead of 104: not
-// all of them are on the chip at once, and the later ones start from the first item again.)
-static int gsc_item_workgroups(int heads, int N_max, int C) { return max(min(128, 2048 / heads), N_max / (21 * C)); }
+// Workgroups per (sequence, head): an item per 21 tokens per chunk is what chunks of a few dozen tokens make.  Fewer than 1024 in all
+// would leave a short sequence's longest chunks behind one another (128 per head / this: 2 x 32768 x 64 f32, distance 1 55 / 35, 8 42 / 37;
+// 4 x 70000 x 64 f32, distance 2 173 / 156), more than 2048 only fill the queue (128 per head / this: 128 x 2000 x 64 f32 83 / 68,
+// 16 x 8 x 8192 x 64 bf16 398 / 265; with the item order below).  The grid is for p.chunks_per_item.  (With every workgroup of it on items of
+// 16, 8 x 32768 x 64 f32, distance 1, takes 169 instead of 140 us and distance 2 118 instead of 104: not all of them are on the chip
+// at once, and the later ones start from the first item again.)
+static int gsc_item_workgroups(int heads, int N_max, int C) { return max(heads <= 8 ? 1024 / heads : min(128, 2048 / heads), N_max / (21 * C)); }
 __device__ __forceinline__ void gsc_item_shape(const GscParams &p, int M, int n, int &C, int &wgs) {
     C = p.chunks_per_item;
     wgs = gridDim.y;

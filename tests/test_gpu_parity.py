@@ -289,7 +289,8 @@ def test_generic_merge_long_items(n, knobs):
 
 @pytest.mark.parametrize("H,n,gap", [
     (17, 2000, 1), (17, 2000, 2.6), (17, 2000, 9.9), (17, 2000, 10.1),    # more than 64k rows: items of 32, 16, 16 and eight chunks
-    (2, 9000, 2.4), (2, 4500, 2.4), (2, 9000, 2.6), (2, 9000, 4.4), (2, 9000, 4.6),     # fewer: of 32, 16, eight, eight, four
+    (9, 3600, 1), (9, 3600, 2.4), (9, 3600, 2.6), (9, 3600, 4.4), (9, 3600, 4.6),     # fewer: of 32, 16, eight, eight, four
+    (1, 700, 2),                                                            # fewer chunks than workgroups
     (1, 34000, 2), (1, 34000, 3),                                          # with the scan kernel
 ])
 def test_generic_merge_short_chunks(H, n, gap):
