@@ -13,26 +13,32 @@ namespace sc {
 constexpr int kSegThreads = 1024;
 constexpr int kSegBytesPerThread = 32;
 
-__device__ __forceinline__ uint32_t nonzero_bytes4(uint32_t w) {
-    // bit k set iff byte k of w is nonzero
-    uint32_t r = 0;
-    r |= (w & 0x000000ffu) ? 1u : 0u;
-    r |= (w & 0x0000ff00u) ? 2u : 0u;
-    r |= (w & 0x00ff0000u) ? 4u : 0u;
-    r |= (w & 0xff000000u) ? 8u : 0u;
-    return r;
+// top bit of every byte that is not zero
+__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w) { return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u; }
+__device__ __forceinline__ uint32_t top_bits4(uint32_t f) {      // the four of them side by side, lowest byte first
+    const uint32_t t = f >> 7;
+    return (t | (t >> 7) | (t >> 14) | (t >> 21)) & 0xFu;
 }
 
-// delimiter bits of the 32 mask bytes of a thread that start at byte i0 of a row (bytes at and beyond n dropped)
+// delimiter bits of the 32 mask bytes of a thread that start at byte i0 of a row (bytes at and beyond n dropped).  COUNT: only their number
+// is asked for, which leaves out putting the bits together: half of the instructions, and with sixteen wavefronts on one compute unit they are most
+// of what a further tile costs.  (A test per byte and two barriers before: 32768 tokens 4.7 us, now 4.0; 131072 tokens, three further tiles, 7.8 and 6.4.)
+template <bool COUNT>
 __device__ __forceinline__ uint32_t delimiter_bits32(const uint8_t *row, int i0, int n, int n_max, bool aligned) {
     // (whether the 32 bytes may be read depends on the row's capacity, not on the sequence length: the
     // request does not wait for seq_lens[b])
     if (i0 + kSegBytesPerThread <= n_max && aligned) {
         const uint4 v0 = *reinterpret_cast<const uint4 *>(row + i0), v1 = *reinterpret_cast<const uint4 *>(row + i0 + 16);
-        const uint32_t lo = nonzero_bytes4(v0.x) | (nonzero_bytes4(v0.y) << 4) | (nonzero_bytes4(v0.z) << 8) | (nonzero_bytes4(v0.w) << 12);
-        const uint32_t hi = nonzero_bytes4(v1.x) | (nonzero_bytes4(v1.y) << 4) | (nonzero_bytes4(v1.z) << 8) | (nonzero_bytes4(v1.w) << 12);
-        const uint32_t x = lo | (hi << 16);
         const int keep = n - i0;   // bytes of this thread inside the sequence
+        if (COUNT && keep >= kSegBytesPerThread) {
+            // (the flags of eight words in the bits 7, 6, .. 0 of their bytes)
+            const uint32_t a = nonzero_bytes(v0.x) | (nonzero_bytes(v0.y) >> 1) | (nonzero_bytes(v0.z) >> 2) | (nonzero_bytes(v0.w) >> 3);
+            const uint32_t b = (nonzero_bytes(v1.x) >> 4) | (nonzero_bytes(v1.y) >> 5) | (nonzero_bytes(v1.z) >> 6) | (nonzero_bytes(v1.w) >> 7);
+            return a | b;
+        }
+        const uint32_t lo = top_bits4(nonzero_bytes(v0.x)) | (top_bits4(nonzero_bytes(v0.y)) << 4) | (top_bits4(nonzero_bytes(v0.z)) << 8) | (top_bits4(nonzero_bytes(v0.w)) << 12);
+        const uint32_t hi = top_bits4(nonzero_bytes(v1.x)) | (top_bits4(nonzero_bytes(v1.y)) << 4) | (top_bits4(nonzero_bytes(v1.z)) << 8) | (top_bits4(nonzero_bytes(v1.w)) << 12);
+        const uint32_t x = lo | (hi << 16);
         return (keep >= kSegBytesPerThread) ? x : ((keep <= 0) ? 0u : (x & ((1u << keep) - 1u)));
     }
     uint32_t x = 0;
@@ -50,7 +56,6 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(
     int32_t *__restrict__ offsets, int64_t offsets_stride_b, int offsets_cap, int32_t *__restrict__ num_chunks) {
     __shared__ int s_wave_total[kSegThreads / kWave];
     __shared__ int s_wave_before[kSegThreads / kWave];
-    __shared__ int s_tile_total, s_before_total;
     constexpr int kTile = kSegThreads * kSegBytesPerThread;
 
     const int b = blockIdx.x, t = blockIdx.y;
@@ -66,9 +71,10 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(
     if (t == 0 && tid == 0) off[0] = 0;
     // delimiters in the tiles before this one (this thread's share), then this tile's own
     int before = 0;
-    for (int j = 0; j < t; ++j) before += __popc(delimiter_bits32(row, j * kTile + tid * kSegBytesPerThread, n, n_max, aligned));
+#pragma unroll 4
+    for (int j = 0; j < t; ++j) before += __popc(delimiter_bits32<true>(row, j * kTile + tid * kSegBytesPerThread, n, n_max, aligned));
     const int i0 = t * kTile + tid * kSegBytesPerThread;
-    uint32_t bits = delimiter_bits32(row, i0, n, n_max, aligned);
+    uint32_t bits = delimiter_bits32<false>(row, i0, n, n_max, aligned);
     const int cnt = __popc(bits);
     // inclusive scan inside the wave (own tile), sum over the wave (tiles before)
     int incl = cnt, bsum = before;
@@ -81,23 +87,18 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(
     if (lane == kWave - 1) s_wave_total[wave] = incl;
     if (lane == 0) s_wave_before[wave] = bsum;
     __syncthreads();
-    if (wave == 0) {
-        int v = (lane < kSegThreads / kWave) ? s_wave_total[lane] : 0;
-        int vb = (lane < kSegThreads / kWave) ? s_wave_before[lane] : 0;
-        int ti = v;
+    // every wavefront adds the sixteen totals up itself (lanes 16 k + w all hold wavefront w's): one barrier
+    constexpr int kWaves = kSegThreads / kWave;
+    const int v = s_wave_total[lane & (kWaves - 1)];
+    int upto = v, running = s_wave_before[lane & (kWaves - 1)];
 #pragma unroll
-        for (int d = 1; d < kSegThreads / kWave; d <<= 1) {
-            const int up = __shfl_up(ti, d, kWave);
-            if (lane >= d) ti += up;
-            vb += __shfl_xor(vb, d, kWave);
-        }
-        if (lane < kSegThreads / kWave) s_wave_total[lane] = ti - v;  // exclusive wave prefix
-        if (lane == kSegThreads / kWave - 1) s_tile_total = ti;
-        if (lane == 0) s_before_total = vb;
+    for (int d = 1; d < kWaves; d <<= 1) {
+        const int up = __shfl_up(upto, d, kWaves);
+        if ((lane & (kWaves - 1)) >= d) upto += up;
+        running += __shfl_xor(running, d, kWaves);
     }
-    __syncthreads();
-    const int running = s_before_total;
-    int rank = running + s_wave_total[wave] + incl - cnt;  // delimiters before this thread's bytes
+    const int tile_total = __shfl(upto, kWaves - 1, kWave), waves_before = __shfl(upto - v, wave, kWave);
+    int rank = running + waves_before + incl - cnt;  // delimiters before this thread's bytes
     while (bits) {
         const int k = __ffs((int)bits) - 1;
         bits &= bits - 1;
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(
         if (rank < offsets_cap) off[rank] = i0 + k + 1;
     }
     if (last_tile && tid == 0) {
-        const int M = running + s_tile_total + 1;
+        const int M = running + tile_total + 1;
         if (M + 1 <= offsets_cap) {
             off[M] = n + 1;
             num_chunks[b] = M;
