@@ -433,9 +433,9 @@ def main():
         "attainable": {"stream_read_GBps": read_gbps, "d2d_copy_GBps": copy_gbps,
                        "note": "1 GiB streamed by sc_stream_read_probe (16 B per lane); 512 MiB copied device to device "
                                "(read + write counted)"},
-        # The call's algorithmic bytes over the duration of ALL kernels of the call (cluster + merge,
-        # relocation, back to back on one stream); the first of them dominates.
-        "roofline": {"kernel": "sc_gsc_merge = gsc_compress_kernel + gsc_relocate_kernel", "bound": "hbm",
+        # The call's algorithmic bytes over the duration of ALL kernels of the call (plan, cluster +
+        # merge, back to back on one stream); the second of them dominates.
+        "roofline": {"kernel": "sc_gsc_merge = gsc_plan_kernel + gsc_compress_kernel", "bound": "hbm",
                      "achieved": gsc_bytes / (gsc_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": gsc_bytes / (gsc_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
                      "traffic": tr["gsc_merge_bytes"] if tr else None, "traffic_source": tr_src,

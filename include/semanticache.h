@@ -108,10 +108,10 @@ sc_status sc_segment(const uint8_t *mask, int64_t mask_stride_b, const int32_t *
  * Inputs are expected to be finite: the sums run on matrix cores over groups of neighbouring chunks
  * with 0/1 weights, so a NaN or Inf element can turn the same column of other rows of its group into
  * NaN.  The clustering decisions themselves treat NaN similarities as "not above tau".
- * With bf16 inputs, bf16 or fp32 outputs and d = 128 the call runs two kernels (cluster + merge
- * into provisional rows; relocation to the final rows, which adds up the row counts itself), three
- * for sequences of more than 32768 tokens (an exclusive scan of the row counts in between); other
- * combinations run a generic three-kernel path with the same results.
+ * With bf16 inputs, bf16 or fp32 outputs and d = 128 the call runs two kernels (the sequences are cut
+ * into windows of whole chunks; every window is clustered, merged and written to its final rows, whose
+ * place it learns from the row counts that the windows before it publish); other combinations run a
+ * generic three-kernel path with the same results.
  *
  *   K, V            device [B, Hkv, N_max, d] of in_dtype, addressed as
  *                   base + b*stride_b + h*stride_h + n*stride_n (+ e), strides in ELEMENTS;
@@ -132,7 +132,7 @@ sc_status sc_segment(const uint8_t *mask, int64_t mask_stride_b, const int32_t *
  * misaligned base pointers or strides not multiples of 16 bytes, workspace too small.
  *
  * Workspace: sc_gsc_merge_workspace_bytes(B, Hkv, N_max, d) bytes serve either output type.  The
- * largest part holds the merged rows of Eq. 3 at provisional positions, in the output type:
+ * largest part has room for the merged rows of Eq. 3 in the output type:
  * sc_gsc_merge_workspace_bytes_for(..., out_dtype) is what a call with that out_dtype needs (for
  * bf16 about half: 544 instead of 1056 bytes per token and KV head at d = 128), and sc_gsc_merge and
  * sc_gsc_merge_append accept a workspace of that size.  0 for a non-positive size or an unknown type.
@@ -378,11 +378,13 @@ sc_status sc_stream_read_probe(const void *src, size_t bytes, void *sink, void *
  *   "decode_mfma_min_group" sc_decode_attn (bf16, d = 128): query heads per KV head from which the
  *                          kernel of sc_multi_attn is used for the single row; 9 = never (the default)
  *   "gsc_fast_path"        0 forces the generic kernels even for bf16 / d = 128
- *   "gsc_chunks_per_task"  fast path: chunks handled by one single-wave workgroup task (1..32);
- *                          <= 0 (the default) = 2, or 1 for a call of a few thousand tokens in all
+ *   "gsc_chunks_per_task"  fast path: chunks that a window of 128 rows holds at most; <= 0 (the default) = as
+ *                          many as fit
+ *   "gsc_polls"            fast path: looks of a window at the row counts before it until it gives up and
+ *                          comp_lens becomes -1 (default 2^20, a second or so); negative: give up at the first
  *   "gsc_chunks_per_item"  generic path: chunks per work item; <= 0 = chosen from B * Hkv * N_max and
  *                          from the mean chunk length of the sequence
- *   "gsc_grid_x"           workgroups per pass and (sequence, KV head); <= 0 = chosen from N_max
+ *   "gsc_grid_x"           generic path: workgroups per pass and (sequence, KV head); <= 0 = chosen from N_max
  *   "global_polls"         sc_gsc_merge_global: looks at rows that another workgroup decides before the ordered pass
  *                          takes over (default 1 << 20, half a second; <= 0: gives up at the first; the outcome is the same)
  *   "multi_block_rows"     sc_multi_attn: query rows per workgroup, 32 (every wavefront holds all of them) or 128 (32

@@ -62,6 +62,7 @@ int sc_tune_set(const char *key, int value) {
     else if (!strcmp(key, "gsc_grid_x")) t.gsc_grid_x = value;
     else if (!strcmp(key, "gsc_fast_path")) t.gsc_fast_path = value;
     else if (!strcmp(key, "gsc_chunks_per_task")) t.gsc_chunks_per_task = value;
+    else if (!strcmp(key, "gsc_polls")) t.gsc_polls = value;
     else if (!strcmp(key, "multi_block_rows")) t.multi_block_rows = value;
     else if (!strcmp(key, "global_polls")) t.global_polls = value;
     else if (!strcmp(key, "multi_target_wgs")) t.multi_target_wgs = value;
@@ -81,6 +82,7 @@ int sc_tune_get(const char *key) {
     if (!strcmp(key, "gsc_grid_x")) return t.gsc_grid_x;
     if (!strcmp(key, "gsc_fast_path")) return t.gsc_fast_path;
     if (!strcmp(key, "gsc_chunks_per_task")) return t.gsc_chunks_per_task;
+    if (!strcmp(key, "gsc_polls")) return t.gsc_polls;
     if (!strcmp(key, "multi_block_rows")) return t.multi_block_rows;
     if (!strcmp(key, "global_polls")) return t.global_polls;
     if (!strcmp(key, "multi_target_wgs")) return t.multi_target_wgs;

@@ -67,6 +67,7 @@ hipError_t launch_gsc_budget(GscMergeArgs a, long long budget_rows, float tau_lo
         const bool probe = it < iterations;
         a.count_only = probe;
         a.budget_state = (probe && counting) ? state : nullptr;
+        a.planned = counting && it > 0;      // the windows do not depend on the threshold
         e = launch_gsc_merge(a, stream);
         if (e != hipSuccess) return e;
         if (!(probe && counting)) {

@@ -161,7 +161,7 @@ __device__ __forceinline__ int lane_gather(int x, int src_lane) {
     return __builtin_amdgcn_ds_bpermute(src_lane << 2, x);
 }
 
-__device__ __forceinline__ uint64_t ballot64(bool pred) { return __ballot(pred); }
+__device__ __forceinline__ uint64_t ballot64(bool pred) { return __builtin_amdgcn_ballot_w64(pred); }
 // 16 bytes that are read (written) once by this launch and not again soon: the non-temporal hint keeps
 // them from displacing lines that are (provisional rows, partials, offsets)
 typedef unsigned int stream_u32x4_t __attribute__((ext_vector_type(4)));

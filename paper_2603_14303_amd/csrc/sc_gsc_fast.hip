@@ -1,25 +1,27 @@
 // Fast path of sc_gsc_merge for bf16 keys/values with head dim 128 (paper Sec. 2.3 Alg. 1 / Eq. 2 and
 // Sec. 2.4 Eq. 3).
 //
-// Two launches (three for sequences of more than 32k tokens):
-//   compress  reads K and V once.  One single-wavefront workgroup handles a task of one or two consecutive
-//           chunks.  It packs whole chunks (each with its closing delimiter) into "windows" of at most 64
-//           rows.  Keys and values of a window are loaded together (16 lanes per row, 16-byte
-//           pieces); the keys are parked in LDS, the values wait in registers.  All pairwise
-//           cosines of the window come from one Gram matrix on the matrix cores, are compared with
-//           tau (decisions inside +-1e-4 of tau are redone in fp64 where they matter) and filed as a bit
-//           matrix, on which the seed set of Alg. 1 is found as the fixed point of the first-fit rule
-//           (a few bit operations per application; seed by seed as the fallback).  A delimiter is
-//           a one-row chunk, so the seeds in row order ARE the output rows of the window.  The
-//           cluster means are a second small matrix product: (output row x window row) 0/1
-//           membership times (window row x 128) keys or values, fp32 accumulate, with a ones column
-//           giving the sizes.  Results go to provisional rows (the window's own first rows), because
-//           the final row of a window depends on every window before it.
-//   scan      (beyond 32k tokens only; shorter sequences add the counts up inside relocate) exclusive scan of
-//           (clusters + delimiter) over the chunks of a (sequence, head).
-//   relocate  moves the merged rows and sizes from their provisional to their final rows.
-// A chunk longer than one window runs over several 64-row blocks with its seeds carried along: the first
-// sixteen in registers, further ones re-read through L2.
+// Two launches:
+//   plan      cuts every sequence into windows: whole chunks (each with its closing delimiter) of at most 128 rows in all, or one
+//             chunk that is longer.  Independent per 1024 rows of a sequence, shared by the heads.
+//   compress  reads K and V once and writes the merged rows to their final place.  One workgroup of four wavefronts per window and
+//             head.  The keys are parked in LDS, the values wait in registers.  All pairwise cosines inside the chunks come from a
+//             Gram matrix on the matrix cores, are compared with tau (decisions inside +-1e-4 of tau are redone in fp64 where
+//             they matter) and filed as a bit matrix, on which the seed set of Alg. 1 is found as the fixed point of the
+//             first-fit rule (a few bit operations per application; seed by seed as the fallback).  A delimiter is a
+//             one-row chunk, so the seeds in row order ARE the output rows of the window.  Their number is published at once,
+//             and the number of rows before the window is put together from what the windows before it have published
+//             while the cluster means are formed: a second matrix product, (128 columns x window rows) keys or values times
+//             (window row x output row) 0/1 membership, fp32 accumulate.
+// A chunk longer than a window runs over several 128-row blocks, its seeds re-read through L2, and its values are read once more for
+// the means.
+//
+// Bounds: the bytes of K, V and the merged rows where chunks are short (8 heads x 131072 tokens, bf16: 537 MB in, a third of
+// it out), fp64 pairs where tau lies inside the band of the similarities, the chain of blocks in long chunks.  Up to a few
+// hundred workgroups it is one window's chain: rows in, Gram product, decisions, the rows before, means, rows out, 20 us in all.
+// Merged rows that are written once, to their final place, and a decision by one wavefront with the pairs shared by four, against
+// provisional rows that a second launch moves, and one wavefront per 64-row task: 8 heads x 32768 54.5 us -> 48.8,
+// 8 x 131072 178 -> 165, 32 sequences x 8 heads x 4096 327 -> 265; tau inside the band, 4 layers x 8 x 32768: 291 -> 190 a layer.
 #include "sc_device.h"
 #include "sc_gsc_params.h"
 #include "sc_host.h"
@@ -27,74 +29,335 @@
 namespace sc {
 
 typedef __bf16 bf16x8f_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
-
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kFastD = 128;
-constexpr int kWin = 64;                 // rows of a window
+constexpr int kWinWaves = 4;
+constexpr int kWinThreads = kWinWaves * kWave;
+constexpr int kWinRows = 128;            // rows of a window
+constexpr int kSegRows = 1024;           // rows of a sequence whose chunks one wavefront of the plan kernel packs
 constexpr float kFastBand = 1e-4f;       // fp32 cosine error for d = 128 is < 2e-5; inside the band -> fp64
 
-__device__ __forceinline__ uint64_t bits_range(int lo, int hi) {   // bits [lo, hi), 0 <= lo <= hi <= 64
-    const uint64_t upto_hi = (hi >= 64) ? ~0ull : ((1ull << hi) - 1ull);
-    const uint64_t upto_lo = (lo >= 64) ? ~0ull : ((1ull << lo) - 1ull);
-    return upto_hi & ~upto_lo;
+// A window of one sequence, filed by the plan kernel.  rows == 0: the slot is not used.
+struct __attribute__((aligned(32))) GscWindow {
+    int32_t first;            // first row
+    int32_t rows;             // its rows (kWinLong: the rows of the chunk without its closing delimiter)
+    int32_t flags;
+    int32_t pad;
+    uint64_t delim[2];        // bit r: row r closes a chunk
+};
+// The windows of a segment that are one long chunk: its first kMaxLongs slots of them (it has no more).
+// The means of its first sixteen clusters over the keys wait in the workspace, at the chunk's own rows from kMeansAt on, for the workgroup of its slot.
+constexpr int kMeansAt = 64;
+constexpr int kMaxLongs = kSegRows / (kWinRows + 1) + 1;
+struct GscLongs {
+    int16_t slot[kMaxLongs];
+};
+constexpr int kWinLong = 1;      // one chunk with more than kWinRows rows
+constexpr int kWinLast = 2;      // the last window of its sequence
+constexpr int kWinClosed = 4;    // kWinLong: a delimiter follows
+
+// What a window's workgroup publishes as soon as it knows it: one word per (sequence, head) and slot with the number of rows
+// (kPubReady: a long chunk, and the clusters of its rows have arrived), and the rows added to a 64-bit word per (sequence, head) and
+// segment: rows of its windows in the low half, windows that have not added theirs in the high half; once all before are known
+// too, it holds kSegAll and the rows up to its end instead.
+constexpr uint32_t kPubRows = 1u << 30, kPubReady = 1u << 31;
+constexpr uint32_t kPubValue = (1u << 30) - 1u;
+constexpr unsigned long long kSegAll = 1ull << 63;
+constexpr int kSegFront = 8;                   // words before the segment words: they are read eight at a time, down to the first
+
+// Windows that can start in `rows` consecutive rows: two neighbours hold more than kWinRows rows together.  An odd number: the last slots of
+// every segment stay empty, and workgroups go to the shader engines in turn (with sixteen slots two of four engines got half
+// as much again as the others, and all waited for them: 8 heads x 32768 tokens 60 us, with seventeen 55).
+__host__ __device__ inline int gsc_slots_per_segment(int n_max, int max_chunks) {
+    const int rows = n_max < kSegRows ? n_max : kSegRows;
+    int slots = 2 * ((rows - 1) / (kWinRows + 1)) + 2;
+    if (max_chunks > 0) slots += rows / max_chunks + 1;
+    return (slots < rows ? slots : rows) | 1;
 }
+
 __device__ __forceinline__ uint64_t bits_below(int x) {   // bits [0, x), 0 <= x <= 64, from 32-bit operations
     const uint32_t l = (x >= 32) ? 0xFFFFFFFFu : ((1u << x) - 1u);
     const uint32_t h = (x <= 32) ? 0u : ((x >= 64) ? 0xFFFFFFFFu : ((1u << (x - 32)) - 1u));
     return ((uint64_t)h << 32) | l;
 }
-
-// LDS layout of a wavefront
-constexpr int kLdsRowBytes = 272;                         // 256 B of keys + 16 B pad: conflict-free tile reads
-constexpr int kLdsRinvOff = kWin * kLdsRowBytes;          // 64 reciprocal norms
-constexpr int kLdsIdxOff = kLdsRinvOff + 256;             // 64 output-index bytes
-constexpr int kLdsSeedRinvOff = kLdsIdxOff + 64;          // reciprocal norms of the first 16 seeds of a long chunk
-constexpr int kLdsWaveBytes = kLdsSeedRinvOff + 64;
-
-__device__ __forceinline__ void wave_lds_fence() {
-    // LDS traffic of one wavefront executes in order; this only stops the compiler from moving
-    // accesses of other lanes' data across the hand-over point
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+__device__ __forceinline__ int last_bit(uint64_t m) { return 63 - __clzll((long long)m); }      // m != 0
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+    return ((uint64_t)(uint32_t)uniform((int)(uint32_t)(x >> 32)) << 32) | (uint32_t)uniform((int)(uint32_t)x);
+}
+__device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {   // position of the k-th set bit, 0 <= k < popcount(m)
+    int pos = 0;
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) {
+        const uint64_t part = (m >> pos) & ((1ull << w) - 1ull);
+        const int cnt = __popcll(part);
+        if (k >= cnt) { k -= cnt; pos += w; }
+    }
+    return pos;
 }
 
-// Rows of a window / block as loaded: lane (g = lane/16, c = lane%16) holds elements 8c..8c+7 of rows
-// 4t + g, t = 0..15 (one coalesced 16-byte load per t covers four whole rows).
-struct RowRegs {
-    uint4 r[16];
-};
+// ------------------------------------------------------------------------------------------------
+// plan: one wavefront per (kSegRows rows, sequence) packs the chunks that start there into windows, greedily and in order.  Windows of
+// neighbouring wavefronts meet at the first chunk that starts in the later one's rows.  Slots that are left over are
+// filed as empty, and what the windows' workgroups will publish is cleared: the workspace may hold anything.
+// Bound by its chain: two trips to memory and the walk.
+__global__ __launch_bounds__(kWave) void gsc_plan_kernel(GscParams p) {
+    constexpr int kSpan = kSegRows + kWinRows;       // rows whose delimiters the walk can ask for
+    constexpr int kLook = 8;
+    __shared__ uint32_t s_bits[kWave];               // (kSpan / 32 + 5 <= 64 words)
+    __shared__ int s_off[kLook * kWave + 1];         // the offsets looked at
+    const int seg = (int)blockIdx.x / p.B, b = (int)blockIdx.x - seg * p.B;
+    const int lane = threadIdx.x;
+    const int M = uniform(p.num_chunks[b]);
+    int n = p.seq_lens ? uniform(p.seq_lens[b]) : p.N_max;
+    n = n < 0 ? 0 : (n > p.N_max ? p.N_max : n);
+    const int32_t *off = p.offsets + (int64_t)b * p.offsets_stride_b;
+    const int S = p.slots_per_segment, slots = p.win_slots;
+    GscWindow *win = p.windows + (int64_t)b * slots + (int64_t)seg * S;
+    const int seg0 = seg * kSegRows;
+    s_bits[lane] = 0u;
+    if (lane == 0) s_off[kLook * kWave] = 0x7FFFFFFF;
+    int used = 0, n_long = 0;
+    GscLongs *longs = p.longs + (int64_t)b * (slots / S) + seg;
+    if (M > 0) {
+        const int n_rows = min(uniform(off[M]) - 1, n);      // rows of the sequence
+        // m_lo, m_hi: first chunks that start at or behind seg0, seg0 + kSegRows (M if none).  Their places are guessed from the mean
+        // chunk length; kLook * 64 offsets around the guess are looked at together.
+        int m_lo = 0, m_hi = 0, first_hi = 0;      // and where the latter starts
+        bool found;
+        int look_base = 0;
+        {
+            const int guess = n > 0 ? (int)((int64_t)M * seg0 / n) : 0;
+            const int base = max(0, min(guess - kLook * kWave / 2 + (int)((int64_t)M * kSegRows / (2 * (int64_t)max(n, 1))), M - kLook * kWave));
+            int v[kLook];
+#pragma unroll
+            for (int q = 0; q < kLook; ++q) {
+                const int m = base + q * kWave + lane;
+                v[q] = m < M ? off[m] : 0x7FFFFFFF;
+            }
+#pragma unroll
+            for (int q = 0; q < kLook; ++q) {
+                if (base + q * kWave >= M) break;
+                m_lo += __popcll(ballot64(v[q] < seg0));
+                m_hi += __popcll(ballot64(v[q] < seg0 + kSegRows));
+            }
+            const int last = __builtin_amdgcn_readlane(v[kLook - 1], kWave - 1);
+            found = (base == 0 || m_lo > 0) && (base + kLook * kWave >= M || last >= seg0 + kSpan + 1);
+#pragma unroll
+            for (int q = 0; q < kLook; ++q) {
+                if ((m_hi >> 6) == q) first_hi = __builtin_amdgcn_readlane(v[q], m_hi & 63);
+            }
+            m_lo += base;
+            m_hi += base;
+            look_base = base;
+            if (found) {
+#pragma unroll
+                for (int q = 0; q < kLook; ++q) {
+                    if (base + q * kWave > M) break;      // (the first offset behind the last chunk's is looked at, too)
+                    const int m = base + q * kWave + lane, rel = v[q] - 1 - seg0;
+                    s_off[q * kWave + lane] = v[q];
+                    if (m > m_lo && m < M && rel >= 0 && rel < kSpan) atomicOr(&s_bits[rel >> 5], 1u << (rel & 31));
+                }
+            }
+        }
+        if (!found) {
+            int lo = 0, hi = M;       // off[m] < seg0 for m < lo, off[m] >= seg0 for m >= hi
+            while (hi > lo) {
+                const int step = (hi - lo + kWave - 1) / kWave;
+                const int m = lo + lane * step;
+                const int below = __popcll(ballot64(m < hi && off[min(m, M - 1)] < seg0));      // (the first `below` probes: offsets ascend)
+                if (below == 0) { hi = lo; break; }
+                const int l2 = lo + (below - 1) * step + 1;
+                hi = min(hi, lo + below * step);
+                lo = l2;
+            }
+            m_lo = m_hi = lo;
+            for (int m0 = lo; m0 < M; m0 += kWave) {
+                const int m = m0 + lane;
+                const int v = m < M ? off[m] : 0x7FFFFFFF;
+                const int rel = v - 1 - seg0;
+                if (m > m_lo && m < M && rel >= 0 && rel < kSpan) atomicOr(&s_bits[rel >> 5], 1u << (rel & 31));
+                m_hi += __popcll(ballot64(v < seg0 + kSegRows));
+                if (__builtin_amdgcn_readlane(v, kWave - 1) >= seg0 + kSpan + 1) break;
+            }
+            first_hi = (m_hi < M) ? uniform(off[m_hi]) : 0;
+        }
+        __syncthreads();
+        // The chunks m_lo .. m_hi - 1, 64 at a time: every lane works out the window that would start with its chunk, then the
+        // greedy walk only hops from lane to lane.  Rows relative to seg0.
+        const int end_rel = n_rows - seg0;
+        const int stop = (m_hi < M) ? min(first_hi - seg0, end_rel) : end_rel;
+        int m = m_lo;
+        while (m < m_hi && used < S) {
+            const int count = min(kWave, m_hi - m);
+            const int at = min(m + lane, m_hi - 1);
+            // (where the chunks were found among the offsets looked at, so were the next chunk's; there is nothing behind the last of all)
+            const int from = found ? s_off[at - look_base] : off[at], to = found ? s_off[at + 1 - look_base] : off[at + 1];
+            const int pos = from - seg0, chunk_end = min(to - 1, n_rows) - seg0;      // its closing delimiter, or the end of the sequence
+            const bool valid = lane < count && pos >= 0 && pos < min(stop, kSegRows);
+            // delimiters among the 128 rows from its start on
+            const int w = valid ? pos >> 5 : 0, sh = pos & 31;
+            uint32_t x[5];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) x[i] = s_bits[w + i];
+            uint64_t d0 = (((uint64_t)x[1] << 32) | x[0]) >> sh, d1 = (((uint64_t)x[3] << 32) | x[2]) >> sh;
+            if (sh != 0) {
+                d0 |= (uint64_t)x[2] << (64 - sh);
+                d1 |= (uint64_t)x[4] << (64 - sh);
+            }
+            const int lim = max(0, min(kWinRows, stop - pos));
+            d0 &= bits_below(min(lim, 64));
+            d1 &= bits_below(max(lim - 64, 0));
+            int rows = 0, flags = 0;
+            if (stop - pos <= kWinRows) rows = stop - pos;      // (ends with a delimiter or with the sequence)
+            else if (d1 != 0ull) rows = 65 + last_bit(d1);
+            else if (d0 != 0ull) rows = 1 + last_bit(d0);
+            if (p.max_chunks > 0 && rows > 0) {
+                const int c0 = __popcll(d0), c1 = __popcll(d1), k = p.max_chunks - 1;
+                if (c0 + c1 > k) rows = 1 + (k < c0 ? nth_set_bit(d0, k) : 64 + nth_set_bit(d1, k - c0));
+            }
+            int chunks = 1, next_pos;
+            if (rows > 0) {
+                d0 &= bits_below(min(rows, 64));
+                d1 &= bits_below(max(rows - 64, 0));
+                next_pos = pos + rows;
+                chunks = max(1, __popcll(d0) + __popcll(d1));
+                if (next_pos >= end_rel) chunks = M - at;      // the last window
+            } else {
+                rows = chunk_end - pos;
+                flags = kWinLong | ((at < M - 1) ? kWinClosed : 0);
+                next_pos = chunk_end + ((at < M - 1) ? 1 : 0);
+            }
+            if (next_pos >= end_rel) flags |= kWinLast;
+            const uint64_t usable = ballot64(valid && rows > 0);
+            const int hop = lane + chunks;
+            uint64_t starts = 0ull;
+            int cur = 0;
+            while (cur < count && ((usable >> cur) & 1ull) != 0ull) {
+                starts |= 1ull << cur;
+                cur = __builtin_amdgcn_readlane(hop, cur);
+            }
+            const int slot = used + __popcll(starts & bits_below(lane));
+            if (((starts >> lane) & 1ull) != 0ull && slot < S) {
+                GscWindow o;
+                o.first = seg0 + pos; o.rows = rows; o.flags = flags; o.pad = 0;
+                o.delim[0] = d0; o.delim[1] = d1;
+                win[slot] = o;
+            }
+            const uint64_t is_long = starts & ballot64((flags & kWinLong) != 0);
+            const int at_long = n_long + __popcll(is_long & bits_below(lane));
+            if (((is_long >> lane) & 1ull) != 0ull && slot < S && at_long < kMaxLongs) longs->slot[at_long] = (int16_t)slot;
+            n_long = min(kMaxLongs, n_long + (int)__popcll(is_long));
+            used = min(S, used + (int)__popcll(starts));
+            if (cur < count) break;      // the end of the sequence, or offsets that do not ascend
+            m += cur;
+        }
+        if (seg == 0 && n_rows <= 0) {       // nothing to do
+            for (int h = lane; h < p.Hkv; h += kWave) {
+                bool bad;
+                const int base = gsc_base_rows(p, (int64_t)b * p.Hkv + h, bad);
+                p.comp_lens[(int64_t)b * p.Hkv + h] = bad ? -1 : base;
+            }
+        }
+    } else if (seg == 0) {
+        for (int h = lane; h < p.Hkv; h += kWave) p.comp_lens[(int64_t)b * p.Hkv + h] = -1;
+    }
+    for (int k = used + lane; k < S; k += kWave) win[k].rows = 0;
+    if (lane == 0) p.long_count[(int64_t)b * (slots / S) + seg] = n_long;
+    // four heads at a time: a segment has seventeen slots
+    const int64_t bh0 = (int64_t)b * p.Hkv;
+    const int segments = slots / S;
+    for (int h = lane >> 4; h < p.Hkv; h += 4) {
+        const int64_t at = (bh0 + h) * slots + (int64_t)seg * S;
+        for (int k = lane & 15; k < S; k += 16) {
+            p.published[at + k] = 0u;
+            if (p.count_only) p.win_count[at + k] = 0;
+        }
+        if ((lane & 15) == 0) p.seg_rows[(bh0 + h) * segments + seg] = (unsigned long long)used << 32;
+    }
+    if (seg == 0)
+        for (int h = lane; h < p.Hkv; h += kWave) p.gave_up[bh0 + h] = 0;
+}
 
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-// cache policy of the key/value row loads: nt = read once by this launch.  Every input row is read exactly once;
-// without the hint the rows displace the provisional rows (which the relocation reads back) from the caches
-// (32k-token layer: 54.7 -> 50.7 us per call; with it the relocation's own reads and writes carry the hint too)
+// ------------------------------------------------------------------------------------------------
+// LDS of the compress kernel.  Four workgroups share a compute unit up to 39 680 bytes (31 pieces of 1280: with 32, which would fill it to the
+// last byte, three did).
+constexpr int kKeyRowBytes = 272;        // 256 B of keys + 16 B pad: conflict-free operand reads in both products
+struct CompressLds {
+    char rows[kWinRows * kKeyRowBytes];  // keys, later values
+    union {
+        uint32_t yes[kWinRows][4];       // bit m of row r: Sim(m, r) is surely above tau (m < r, same chunk)
+        uint16_t hot[kWinRows / 16][kWinRows];      // once decided: bit c of row r in tile t: r belongs to output row 16 t + c
+    };
+    union {
+        uint32_t unsure[kWinRows][4];    // bit m of row r: within the band, or a norm is unusable
+        struct {                         // once the deciding wavefront has read them: pairs to be settled in fp64, and their outcome
+            uint32_t list[kWinRows], above[kWinRows];
+        };
+    };
+    float rinv[kWinRows];
+    float seed_rinv[16];                 // a long chunk's first sixteen seeds: reciprocal norms, rows of the chunk
+    int seed_row[16];
+    int tile_steps[kWinRows / 16];       // bit ks of tile t: one of the rows 32 ks .. 32 ks + 31 belongs to it
+    int any_unsure, base_lo, base_ok;
+    unsigned char odd_norms[kWinWaves];  // wavefront w's rows hold one without a usable norm
+    int pairs, first_seed;               // pairs the deciding wavefront wants settled (0: it has decided); seed that the list counts from
+    int nseed, open;                     // outcome: seeds; a long chunk: rows still open
+};
+static_assert(sizeof(CompressLds) <= 39680, "four workgroups per compute unit");
+
+// cache policy of the key/value row loads: nt = read once by this launch
 constexpr int kAuxReadOnce = 2;
 
-// Rows [first_row, first_row + nrows) through a buffer descriptor that ends after the last wanted row:
-// the hardware returns zeros for every access beyond it, so no lane needs a predicate or a 64-bit
-// address.  row_stride_bytes * 64 must fit in 31 bits (checked by the launcher).
-struct RowSource {
-    __amdgpu_buffer_rsrc_t rsrc;
-    int voff;     // this lane's offset inside a group of four rows: g * stride + 16 * c
-    int step;     // four rows further: 4 * stride
+// A wavefront's 32 rows as loaded: lane (g = lane / 16, c = lane % 16) holds elements 8c .. 8c + 7 of rows 4t + g
+struct RowRegs {
+    uint4 r[8];
 };
-__device__ __forceinline__ RowSource row_source(const bf16_t *base, int64_t stride_n, int first_row, int nrows, int g, int c) {
-    RowSource rs;
+// Rows [first_row, first_row + nrows) through a buffer descriptor that ends after the last wanted row: the hardware returns zeros
+// for every access beyond it, so no lane needs a predicate or a 64-bit address.  row_stride_bytes * 32 must fit in 31
+// bits (checked by the launcher).
+template <int AUX = kAuxReadOnce>
+__device__ __forceinline__ void load_rows(RowRegs &x, const bf16_t *base, int64_t stride_n, int first_row, int nrows, int g, int c) {
     const int sb = (int)stride_n * 2;
-    rs.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(base + (int64_t)first_row * stride_n), (short)0,
-                                                nrows > 0 ? (nrows - 1) * sb + kFastD * 2 : 0, 0x00020000);
-    rs.voff = g * sb + 16 * c;
-    rs.step = 4 * sb;
-    return rs;
-}
-__device__ __forceinline__ void load_rows(RowRegs &x, const RowSource &rs) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(base + (int64_t)first_row * stride_n), (short)0,
+                                                                        nrows > 0 ? (nrows - 1) * sb + kFastD * 2 : 0, 0x00020000);
+    const int voff = g * sb + 16 * c;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs.rsrc, rs.voff + t * rs.step, 0, kAuxReadOnce);
+    for (int t = 0; t < 8; ++t) {
+        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 4 * t * sb, 0, AUX);
         x.r[t] = make_uint4(v.x, v.y, v.z, v.w);
     }
+}
+__device__ __forceinline__ void park_rows(CompressLds &s, const RowRegs &x, int wave, int g, int c) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) *reinterpret_cast<uint4 *>(s.rows + (32 * wave + 4 * t + g) * kKeyRowBytes + 16 * c) = x.r[t];
+}
+__device__ __forceinline__ float safe_rinv(float nsq) {
+    // a norm that is zero, denormal, huge or not a number makes every cosine with that row "unsure"
+    return (nsq > 1e-30f && nsq < 1e30f) ? __frsqrt_rn(nsq) : __builtin_nanf("");
+}
+// reciprocal norms of the wavefront's rows, 0 for rows that do not exist; whether one of them is unusable
+__device__ __forceinline__ void file_norms(CompressLds &s, const RowRegs &x, int nrows, int wave, int g, int c) {
+    float nsq[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        float a = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bf16x2_t w = __builtin_bit_cast(bf16x2_t, dword_of(x.r[t], k));
+            a = __builtin_amdgcn_fdot2_f32_bf16(w, w, a, false);
+        }
+        nsq[t] = a;
+    }
+    float mine = row_transpose_reduce<8>(nsq, c);      // lane c: row 4 (c % 8) + g, over eight of the sixteen lanes
+    mine += dpp<kDppRor8>(mine);
+    const float ri = (4 * c + g < nrows) ? safe_rinv(mine) : 0.f;      // (c < 8)
+    if (c < 8) s.rinv[32 * wave + 4 * c + g] = ri;
+    const bool odd = ballot64(c < 8 && !(ri == ri)) != 0ull;
+    if (c == 0 && g == 0) s.odd_norms[wave] = odd ? 1 : 0;
 }
 
 // eight elements of two rows into the sums of Eq. 2 in double precision (products of bf16 values are exact there)
@@ -108,190 +371,15 @@ __device__ __forceinline__ void cosine_sums_f64(const uint4 &a, const uint4 &b, 
         dot += a1 * b1; aa += a1 * a1; bb += b1 * b1;
     }
 }
+// Eq. 2 against tau, NaN compares false.  The roots and the division (half of a comparison's instructions) are left out where the squares
+// differ by more than all their roundings can add up to (a few 2^-53 of either side).
 __device__ __forceinline__ bool cosine_exceeds_f64(double dot, double aa, double bb, float tau) {
-    return dot / (sqrt(aa) * sqrt(bb)) > (double)tau;   // NaN compares false
+    const double t = (double)tau, q = dot * dot, r = (t * t) * (aa * bb), margin = r * 0x1p-44;
+    const bool above = q - r > margin, below = r - q > margin;
+    bool yes = above && dot > 0.0;
+    if (ballot64(!(tau > 0.f) || !(above || below)) != 0ull) yes = dot / (sqrt(aa) * sqrt(bb)) > t;
+    return yes;
 }
-
-__device__ __forceinline__ float safe_rinv(float nsq) {
-    // a norm that is zero, denormal, huge or not a number makes every cosine with that row "unsure"
-    return (nsq > 1e-30f && nsq < 1e30f) ? __frsqrt_rn(nsq) : __builtin_nanf("");
-}
-
-// ------------------------------------------------------------------------------------------------
-// Membership products on the matrix cores (Eq. 3 as a 0/1 matrix times the rows): membership_mfma_tiles and
-// membership_mfma_kv below.
-// scale the sums of tile `ot` by 1/size and store rows [16*ot, 16*ot+16) ∩ [0, n_out) at dst_row0 + o
-template <typename TO>
-__device__ __forceinline__ void store_tile(const floatx4_t (&D)[8], const floatx4_t &Dn, int ot, int n_out, TO *dst,
-                                           int64_t dst_row0, int64_t row_limit, int lane) {
-    const int g = lane >> 4;
-    // The provisional rows are read by the next launch from any chiplet: they are written through to the
-    // memory side (sc1) instead of staying dirty in this chiplet's L2 until the kernel ends.  dst is
-    // wave-uniform; its rows from dst_row0 on behind a descriptor, the lane's piece as offset.
-    constexpr int kRowBytes = kFastD * (int)sizeof(TO);
-    const int rows_left = (int)min(row_limit - dst_row0, (int64_t)(1 << 21));      // (n_out rows at most are stored)
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(dst + dst_row0 * kFastD, (short)0, rows_left * kRowBytes, 0x00020000);
-    constexpr int kAuxThrough = 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int o = 16 * ot + 4 * g + i;
-        if (o < n_out && dst_row0 + o < row_limit) {
-            // 1/size: exact for powers of two, 1 ulp otherwise; a row of size 1 is multiplied by exactly 1
-            const float inv = (Dn[i] > 1.5f) ? __builtin_amdgcn_rcpf(Dn[i]) : 1.0f;
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = D[j][i] * inv;
-            const int off = o * kRowBytes + 8 * (lane & 15) * (int)sizeof(TO);
-            if constexpr (sizeof(TO) == 2) {
-                const u32x4_t t = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-                __builtin_amdgcn_raw_buffer_store_b128(t, rs, off, 0, kAuxThrough);
-            } else {
-                const u32x4_t t0 = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
-                const u32x4_t t1 = {__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])};
-                __builtin_amdgcn_raw_buffer_store_b128(t0, rs, off, 0, kAuxThrough);
-                __builtin_amdgcn_raw_buffer_store_b128(t1, rs, off + 16, 0, kAuxThrough);
-            }
-        }
-    }
-}
-
-
-
-// output indices as bytes (0xFF = none) in the operand order of the membership product:
-// ob[q] byte i = index of row 16q + 4i + lane/16
-__device__ __forceinline__ void orow_to_operand_bytes(int rel_o, int lane, uint32_t (&ob)[4]) {
-    const int g = lane >> 4;
-    const int v = (rel_o >= 0 && rel_o < 255) ? rel_o : 255;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w |= (uint32_t)lane_gather(v, 16 * q + 4 * i + g) << (8 * i);
-        ob[q] = w;
-    }
-}
-// the same through 64 bytes of LDS: row r files its byte at (r % 4) * 16 + r / 4, so that the sixteen
-// bytes a lane group needs are one 16-byte read
-__device__ __forceinline__ void orow_to_operand_bytes_lds(char *lds_idx, int rel_o, int lane, uint32_t (&ob)[4]) {
-    const int g = lane >> 4;
-    const int v = (rel_o >= 0 && rel_o < 255) ? rel_o : 255;
-    reinterpret_cast<unsigned char *>(lds_idx)[(lane & 3) * 16 + (lane >> 2)] = (unsigned char)v;
-    wave_lds_fence();
-    const uint4 w = *reinterpret_cast<const uint4 *>(lds_idx + 16 * g);
-    ob[0] = w.x; ob[1] = w.y; ob[2] = w.z; ob[3] = w.w;
-    wave_lds_fence();
-}
-
-// For T consecutive tiles of sixteen output rows, t = 0..T-1:  D[t][j][i] += sum over rows of
-// [index byte of row == 16 t + 4 (lane / 16) + i] * x[row][8c + j];  Dn[t][i] += number of such rows.  Rows in
-// registers, on v_mfma_f32_16x16x32_bf16 (contraction step qq covers rows 32 qq .. 32 qq + 31; index
-// (lane / 16, i), i = 0..7, stands for row 32 qq + 4 i + lane / 16 = register 8 qq + i): the B operand is built once
-// per column group and shared by the tiles.  Index bytes are relative to the first of the T tiles.
-template <int T>
-__device__ __forceinline__ void membership_mfma_tiles(const RowRegs &x, const uint32_t (&ob)[4], int c, int q_hi,
-                                                      floatx4_t (&D)[T][8], floatx4_t (&Dn)[T]) {
-    const uint4 ones = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
-#pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-        if (2 * qq < q_hi) {
-            bf16x8f_t a[T];
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const uint32_t want = (uint32_t)(c + 16 * t);
-                uint32_t aw[4];
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2) {
-                    const uint32_t b4 = ob[2 * qq + h2];
-                    const uint32_t m0 = (((b4 >> 0) & 0xFFu) == want) ? 0x3F80u : 0u;
-                    const uint32_t m1 = (((b4 >> 8) & 0xFFu) == want) ? 0x3F80u : 0u;
-                    const uint32_t m2 = (((b4 >> 16) & 0xFFu) == want) ? 0x3F80u : 0u;
-                    const uint32_t m3 = (((b4 >> 24) & 0xFFu) == want) ? 0x3F80u : 0u;
-                    aw[2 * h2] = m0 | (m1 << 16);
-                    aw[2 * h2 + 1] = m2 | (m3 << 16);
-                }
-                a[t] = __builtin_bit_cast(bf16x8f_t, make_uint4(aw[0], aw[1], aw[2], aw[3]));
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                uint32_t w[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t d0 = dword_of(x.r[8 * qq + 2 * k], j >> 1), d1 = dword_of(x.r[8 * qq + 2 * k + 1], j >> 1);
-                    w[k] = (j & 1) ? pack_hi(d0, d1) : pack_lo(d0, d1);
-                }
-                const bf16x8f_t bop = __builtin_bit_cast(bf16x8f_t, make_uint4(w[0], w[1], w[2], w[3]));
-#pragma unroll
-                for (int t = 0; t < T; ++t) D[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], bop, D[t][j], 0, 0, 0);
-            }
-#pragma unroll
-            for (int t = 0; t < T; ++t) Dn[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], __builtin_bit_cast(bf16x8f_t, ones), Dn[t], 0, 0, 0);
-        }
-    }
-}
-
-// keys and values of a window in one sweep: the keys come back from the LDS copy made by gram_bitmatrix
-// (32 rows at a time), the values are in registers; both share the 0/1 operand.  v_mfma_f32_16x16x32_bf16:
-// contraction step qq covers rows 32 qq .. 32 qq + 31, its index (lane / 16, i), i = 0..7, stands for row
-// 32 qq + 4 i + lane / 16 = register 8 qq + i of the lane's own group.
-__device__ __forceinline__ void membership_mfma_kv(const char *lds, const RowRegs &xv, const uint32_t (&ob)[4], int want,
-                                                   int q_hi, int lane, floatx4_t (&DK)[8], floatx4_t (&DV)[8], floatx4_t &Dn) {
-    const int g = lane >> 4, c = lane & 15;
-    const uint4 ones = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
-#pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-        if (2 * qq < q_hi) {
-            uint4 r[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                r[i] = *reinterpret_cast<const uint4 *>(lds + (4 * (8 * qq + i) + g) * kLdsRowBytes + 16 * c);
-            uint32_t aw[4];
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-                const uint32_t b4 = ob[2 * qq + h2];
-                const uint32_t m0 = (((b4 >> 0) & 0xFFu) == (uint32_t)want) ? 0x3F80u : 0u;
-                const uint32_t m1 = (((b4 >> 8) & 0xFFu) == (uint32_t)want) ? 0x3F80u : 0u;
-                const uint32_t m2 = (((b4 >> 16) & 0xFFu) == (uint32_t)want) ? 0x3F80u : 0u;
-                const uint32_t m3 = (((b4 >> 24) & 0xFFu) == (uint32_t)want) ? 0x3F80u : 0u;
-                aw[2 * h2] = m0 | (m1 << 16);
-                aw[2 * h2 + 1] = m2 | (m3 << 16);
-            }
-            const bf16x8f_t a = __builtin_bit_cast(bf16x8f_t, make_uint4(aw[0], aw[1], aw[2], aw[3]));
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                {
-                    uint32_t w[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const uint32_t d0 = dword_of(r[2 * t], j >> 1), d1 = dword_of(r[2 * t + 1], j >> 1);
-                        w[t] = (j & 1) ? pack_hi(d0, d1) : pack_lo(d0, d1);
-                    }
-                    DK[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8f_t, make_uint4(w[0], w[1], w[2], w[3])), DK[j], 0, 0, 0);
-                }
-                {
-                    uint32_t w[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const uint32_t d0 = dword_of(xv.r[8 * qq + 2 * t], j >> 1), d1 = dword_of(xv.r[8 * qq + 2 * t + 1], j >> 1);
-                        w[t] = (j & 1) ? pack_hi(d0, d1) : pack_lo(d0, d1);
-                    }
-                    DV[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8f_t, make_uint4(w[0], w[1], w[2], w[3])), DV[j], 0, 0, 0);
-                }
-            }
-            Dn = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8f_t, ones), Dn, 0, 0, 0);
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// All pairwise similarities of a window at once (Eq. 2 for every pair the seeds of Alg. 1 can ask for).
-// The window's rows are parked in LDS (row stride 272 B) and read back in the operand layout of
-// v_mfma_f32_16x16x32_bf16 (lane l: row l%16 of a 16-row tile, elements 8*(l/16)..+7 of a 32-element
-// slice); a tile of keys is both the A operand (rows m) and the B operand (rows n) of the Gram tile
-// G[m][n] = k_m . k_n.  The ten upper-triangle tiles of the 64 x 64 Gram matrix take 40 MFMAs.
-// Each lane then turns its 4 x 10 dot products into cosines, compares them with tau and files the
-// outcome as bit m of a per-column word; an OR over the four lane groups completes the words, and lane
-// r (row order) ends up with  yes[r]: bit m set iff Sim(m, r) > tau + band   (m < r or same tile)
-//                             unsure[r]: bit m set iff the fp32 value is within the band (or not a number).
 __device__ __forceinline__ uint32_t or_rows(uint32_t x) {   // OR over the four 16-lane rows, same lane position
     auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
     x = r[0] | r[1];
@@ -299,184 +387,157 @@ __device__ __forceinline__ uint32_t or_rows(uint32_t x) {   // OR over the four 
     return r[0] | r[1];
 }
 
-// Gram tiles (I, J), I <= J < NT, of the rows parked in LDS; tile k = index in the 4 x 4 upper triangle
-template <int NT>
-__device__ __forceinline__ void gram_tiles(const char *lds, int g, int c, floatx4_t (&acc)[10]) {
-    // v_mfma_f32_16x16x32_bf16: 32 elements of the contraction per product (lane l: elements 8 * (l / 16) .. + 7
-    // of a 32-element slice), the form that runs at the full bf16 rate of this chip
+// sim(m, n) > t  <=>  dot * rinv_m > t * norm_n.  Per pair one fused multiply-add gives
+//     dd = (tau + band) * norm_n - dot * rinv_m :   dd < 0  the pair is above the band (a sure yes),
+//     0 <= dd <= 2 * band * norm_n  inside the band (unsure),  beyond that a sure no.
+// Its sign bit is shifted into a nibble (v_alignbit), and an unsigned minimum over the bit patterns keeps the smallest
+// non-negative dd (negative values compare as huge).  Only if some lane saw a pair inside the band, or a norm is unusable
+// (then dd is not a number and counts as unsure), are the unsure bits made, from the same dd: yes, no and unsure partition the pairs.
+struct Nibbles {
+    uint32_t yes, least;
+    float dd[4];
+};
+__device__ __forceinline__ Nibbles threshold_nibbles(const floatx4_t &acc, const floatx4_t &rm, float hn) {
+    Nibbles r;
+    r.yes = 0u;
+    r.least = 0x7F800000u;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        bf16x8f_t a[NT];
+    for (int i = 3; i >= 0; --i) {
+        r.dd[i] = fmaf(-acc[i], rm[i], hn);
+        r.yes = __builtin_amdgcn_alignbit(r.yes, __float_as_uint(r.dd[i]), 31);     // (yes << 1) | sign bit
+        r.least = min(r.least, __float_as_uint(r.dd[i]));
+    }
+    return r;
+}
+__device__ __forceinline__ uint32_t unsure_nibble(Nibbles &r, float wn) {
+    uint32_t unsure = 0u;
 #pragma unroll
-        for (int I = 0; I < NT; ++I) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(lds + (16 * I + c) * kLdsRowBytes + (32 * ks + 8 * g) * 2);
-            a[I] = __builtin_bit_cast(bf16x8f_t, v);
+    for (int i = 0; i < 4; ++i)
+        if (!(r.dd[i] < 0.f) && !(r.dd[i] > wn)) unsure |= 1u << i;
+    r.yes &= ~unsure;
+    return unsure;
+}
+
+// bounds of a column's row; one that does not exist resembles nothing
+__device__ __forceinline__ void column_bounds(float rn, bool exists, float tau, float &hn, float &wn) {
+    const float norm = __builtin_amdgcn_rcpf(rn);
+    hn = exists ? (tau + kFastBand) * norm : 1.0f;
+    wn = exists ? (2.0f * kFastBand) * norm : 0.0f;
+}
+
+// Gram tiles of column tile J (rows 16 J .. 16 J + 15 of the window as columns) with row tiles I_first .. J.  The parked rows are
+// both operands of v_mfma_f32_16x16x32_bf16 (lane l: row l % 16 of a tile, elements 8 (l / 16) .. + 7 of a 32-element slice); lane
+// (g, c) gets the products of rows 16 I + 4 g + i with row 16 J + c: four bits of that row's word, completed by an OR over the lane
+// groups.  Two row tiles are one word.
+// odd: a row of the window has no usable norm
+__device__ __forceinline__ void gram_column(CompressLds &s, int J, int I_first, int R, float tau, bool odd, int g, int c) {
+    bf16x8f_t bq[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+        bq[ks] = __builtin_bit_cast(bf16x8f_t, *reinterpret_cast<const uint4 *>(s.rows + (16 * J + c) * kKeyRowBytes + (32 * ks + 8 * g) * 2));
+    float hn, wn;
+    column_bounds(s.rinv[16 * J + c], 16 * J + c < R, tau, hn, wn);
+    for (int I2 = I_first >> 1; I2 <= J >> 1; ++I2) {
+        floatx4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const char *at = s.rows + (32 * I2 + c) * kKeyRowBytes + (32 * ks + 8 * g) * 2;
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8f_t, *reinterpret_cast<const uint4 *>(at)), bq[ks], acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8f_t, *reinterpret_cast<const uint4 *>(at + 16 * kKeyRowBytes)), bq[ks], acc1, 0, 0, 0);
         }
-#pragma unroll
-        for (int I = 0; I < NT; ++I)
-#pragma unroll
-            for (int J = I; J < NT; ++J) {
-                constexpr int base[4] = {0, 4, 7, 9};
-                const int k = base[I] + (J - I);
-                acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[I], a[J], acc[k], 0, 0, 0);
-            }
+        const floatx4_t rm0 = *reinterpret_cast<const floatx4_t *>(s.rinv + 32 * I2 + 4 * g), rm1 = *reinterpret_cast<const floatx4_t *>(s.rinv + 32 * I2 + 16 + 4 * g);
+        Nibbles n0 = threshold_nibbles(acc0, rm0, hn), n1 = threshold_nibbles(acc1, rm1, hn);
+        uint32_t u = 0u;
+        if (odd || ballot64(min(n0.least, n1.least) <= __float_as_uint(wn)) != 0ull) {
+            const uint32_t u0 = unsure_nibble(n0, wn), u1 = unsure_nibble(n1, wn);
+            u = or_rows((u0 << (4 * g)) | (u1 << (16 + 4 * g)));
+            if (ballot64(u != 0u) != 0ull) s.any_unsure = 1;
+        }
+        const uint32_t y = or_rows((n0.yes << (4 * g)) | (n1.yes << (16 + 4 * g)));
+        if (g == 0) {
+            s.yes[16 * J + c][I2] = y;
+            s.unsure[16 * J + c][I2] = u;
+        }
     }
 }
 
-// Outcome for lane r (row order):  yes_row: bit m set iff Sim(m, r) > tau + band (for m < r, and for the
-// m > r of r's own 16-row tile);  unsure_row: bit m set iff the fp32 value lies within the band or a
-// norm is unusable.  The common case (no pair of the window anywhere near tau) never builds the
-// unsure words: every lane tracks the smallest distance to tau it has seen instead.
-__device__ __forceinline__ void gram_bitmatrix(char *lds, const RowRegs &x, int R, float tau, int lane,
-                                               uint64_t &yes_row, uint64_t &unsure_row) {
-    const int g = lane >> 4, c = lane & 15;
-    float *s_rinv = reinterpret_cast<float *>(lds + kLdsRinvOff);
-#pragma unroll
-    for (int t = 0; t < 16; ++t)
-        *reinterpret_cast<uint4 *>(lds + (4 * t + g) * kLdsRowBytes + 16 * c) = x.r[t];
-    wave_lds_fence();
-
-    const int nt = (R + 15) >> 4;   // 16-row tiles in use
-    floatx4_t acc[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) acc[k] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    if (nt >= 4) gram_tiles<4>(lds, g, c, acc);
-    else if (nt == 3) gram_tiles<3>(lds, g, c, acc);
-    else if (nt == 2) gram_tiles<2>(lds, g, c, acc);
-    else gram_tiles<1>(lds, g, c, acc);
-    // squared norms are the diagonal of the Gram matrix: tile (I, I), row 4g+i == column c
-    {
-        const int kd[4] = {0, 4, 7, 9};
-#pragma unroll
-        for (int I = 0; I < 4; ++I) {
-            const int i = c - 4 * g;
-            const floatx4_t d = acc[kd[I]];
-            const float nsq = (i == 0) ? d[0] : ((i == 1) ? d[1] : ((i == 2) ? d[2] : d[3]));
-            if (i >= 0 && i < 4) s_rinv[16 * I + c] = safe_rinv(nsq);
-        }
-    }
-    wave_lds_fence();
-    // sim(m, n) > t  <=>  dot * rinv_m > t * norm_n.  Per pair one fused multiply-add gives
-    //     dd = (tau + band) * norm_n - dot * rinv_m :   dd < 0  the pair is above the band (a sure yes),
-    //     0 <= dd <= 2 * band * norm_n  inside the band (unsure),  beyond that a sure no;
-    // its sign bit is shifted into a nibble (v_alignbit), and an unsigned minimum over the bit patterns
-    // keeps the smallest non-negative dd the lane has seen (negative values compare as huge).
-    float hn[4], wn[4];
-    floatx4_t rm[4];
-    bool bad = false;
-#pragma unroll
-    for (int I = 0; I < 4; ++I) {
-        const float rn = s_rinv[16 * I + c];
-        const float norm = __builtin_amdgcn_rcpf(rn);
-        bad = bad || (16 * I + c < R && !(rn == rn));
-        hn[I] = (tau + kFastBand) * norm;
-        wn[I] = (2.0f * kFastBand) * norm;
-        rm[I] = *reinterpret_cast<const floatx4_t *>(s_rinv + 16 * I + 4 * g);
-    }
-    // per column tile J: bits m (0..63) as two dwords (row 16*I + 4g + i at bit 16*(I&1) + 4g + i of word I>>1)
-    uint32_t y[4][2];
-    uint32_t dmin[4];
-#pragma unroll
-    for (int J = 0; J < 4; ++J) { y[J][0] = y[J][1] = 0u; dmin[J] = 0x7F800000u; }
-    {
-        constexpr int base[4] = {0, 4, 7, 9};
-#pragma unroll
-        for (int I = 0; I < 4; ++I)
-#pragma unroll
-            for (int J = I; J < 4; ++J) {
-                if (J < nt) {
-                    const int k = base[I] + (J - I);
-                    uint32_t nib = 0u;
-#pragma unroll
-                    for (int i = 3; i >= 0; --i) {
-                        const uint32_t dd = __float_as_uint(fmaf(-acc[k][i], rm[I][i], hn[J]));
-                        nib = __builtin_amdgcn_alignbit(nib, dd, 31);     // (nib << 1) | sign bit
-                        dmin[J] = min(dmin[J], dd);
-                    }
-                    y[J][I >> 1] |= nib << (16 * (I & 1) + 4 * g);
-                }
-            }
-    }
-    // complete the words over the four lane groups; lane r = 16J + c keeps the words of its own row
-    uint32_t yl = 0u, yh = 0u;
-#pragma unroll
-    for (int J = 0; J < 4; ++J) {
-        if (J < nt) {
-            const uint32_t a0 = or_rows(y[J][0]);
-            const uint32_t a1 = (nt > 2) ? or_rows(y[J][1]) : 0u;   // rows 32.. exist only then
-            if (g == J) { yl = a0; yh = a1; }
-        }
-    }
-    // anything close to tau, or an unusable norm, anywhere in the window?  (rare)
-    bool close = bad;
-#pragma unroll
-    for (int J = 0; J < 4; ++J) close = close || (J < nt && dmin[J] <= __float_as_uint(wn[J]));
-    if (ballot64(close) != 0ull) {
-        // the same products and bounds as above, so that "yes", "no" and "unsure" partition the pairs
-        constexpr int base[4] = {0, 4, 7, 9};
-        uint32_t ul = 0u, uh = 0u;
-#pragma unroll
-        for (int J = 0; J < 4; ++J) {
-            uint32_t u0 = 0u, u1 = 0u;
-#pragma unroll
-            for (int I = 0; I <= J; ++I) {
-                if (J < nt) {
-                    const int k = base[I] + (J - I);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float dd = fmaf(-acc[k][i], rm[I][i], hn[J]);
-                        const bool uu = !(dd < 0.f) && !(dd > wn[J]);     // also true for a value that is not a number
-                        const uint32_t bit = 1u << (16 * (I & 1) + 4 * g + i);
-                        if (I < 2) u0 |= uu ? bit : 0u; else u1 |= uu ? bit : 0u;
-                    }
-                }
-            }
-            if (J < nt) {
-                u0 = or_rows(u0);
-                u1 = (nt > 2) ? or_rows(u1) : 0u;
-                if (g == J) { ul = u0; uh = u1; }
-            }
-        }
-        unsure_row = ((uint64_t)uh << 32) | ul;
-    } else {
-        unsure_row = 0ull;
-    }
-    // a pair that is unsure must not also count as a sure yes
-    yes_row = (((uint64_t)yh << 32) | yl) & ~unsure_row;
-    wave_lds_fence();   // the LDS area is reused by the next window
+// ------------------------------------------------------------------------------------------------
+// Decisions.  One wavefront of the workgroup takes them (which one differs from window to window: the wavefronts of a place share a
+// SIMD); lane l has rows l ("A") and 64 + l ("B").  The others wait and share in comparisons in fp64.
+struct Words {      // candidates of the lane's two rows: rows 0..63, and for row B rows 64..127
+    uint64_t a, b0, b1;
+};
+struct Pair64 {     // a set of rows
+    uint64_t a, b;
+};
+__device__ __forceinline__ uint64_t row_word(const uint32_t (*words)[4], int row, int half) {
+    return *reinterpret_cast<const uint64_t *>(&words[row][2 * half]);
 }
 
-// Pairs (other, j), one for every lane j in `todo` (`other` is that lane's own value): returns the lanes whose pair is
-// above tau in fp64.  Both rows are parked in LDS by gram_bitmatrix (the parked bf16 values are the inputs themselves).
-// A pair takes the 16 lanes of a row, so four are settled at once: the chain of a pair (two LDS reads, the sums, two
-// square roots and a division) is long, and a threshold inside the band of the similarities asks for many.  Whole calls change
-// little by it and by the carried seeds below: against one pair at a time on all 64 lanes, twelve counting probes and a merge of
-// 8 heads x 32768 481 -> 476 us, 4 x 8 x 32768 at tau 0.979 293 -> 292, 1 x 8 x 131072 with long chunks at 0.7 178 -> 176.5.
-__device__ __forceinline__ uint64_t settle_pairs_f64(const char *lds, uint64_t todo, int other, float tau, int lane) {
+// Pairs of s.list, `n` of them, by the whole workgroup: row, and partner (another row of the window, or with a chunk's seed rows given the
+// number of a carried seed, whose key is fetched from memory).  A pair takes the 16 lanes of a row, so sixteen are settled
+// at once: the chain of a pair is long, and a threshold inside the band of the similarities asks for many.
+__device__ __forceinline__ void settle_share(CompressLds &s, int n, float tau, int lane, int wave, const bf16_t *Kchunk, int64_t stride_n, const int32_t *seed_rows) {
     const int g = lane >> 4, c = lane & 15;
-    uint64_t above = 0ull;
-    while (todo != 0ull) {
-        int at[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            at[q] = (todo != 0ull) ? first_bit(todo) : at[0];     // (a short last round repeats its first pair)
-            todo &= todo - 1ull;
+    for (int e0 = 4 * wave; e0 < n; e0 += 4 * kWinWaves) {
+        const int e = e0 + g;
+        const uint32_t w = s.list[min(e, n - 1)];
+        const int i = (int)(w >> 8), j = (int)(w & 0xFFu);
+        uint4 a;
+        if (seed_rows) {
+            const int at = s.first_seed + i;
+            const int row = at < 16 ? s.seed_row[at] : __hip_atomic_load(seed_rows + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            a = *reinterpret_cast<const uint4 *>(Kchunk + (int64_t)row * stride_n + 8 * c);
+        } else {
+            a = *reinterpret_cast<const uint4 *>(s.rows + i * kKeyRowBytes + 16 * c);
         }
-        const int j = (g == 0) ? at[0] : ((g == 1) ? at[1] : ((g == 2) ? at[2] : at[3]));
-        const int i = lane_gather(other, j);
-        const uint4 a = *reinterpret_cast<const uint4 *>(lds + i * kLdsRowBytes + 16 * c);
-        const uint4 b = *reinterpret_cast<const uint4 *>(lds + j * kLdsRowBytes + 16 * c);
-        double dot = 0.0, aa = 0.0, bb = 0.0;
-        cosine_sums_f64(a, b, dot, aa, bb);
+        const uint4 bb = *reinterpret_cast<const uint4 *>(s.rows + j * kKeyRowBytes + 16 * c);
+        double dot = 0.0, sa = 0.0, sb = 0.0;
+        cosine_sums_f64(a, bb, dot, sa, sb);
         dot = row_allreduce_sum(dot);
-        aa = row_allreduce_sum(aa);
-        bb = row_allreduce_sum(bb);
-        const uint64_t yes = ballot64(cosine_exceeds_f64(dot, aa, bb, tau));
-#pragma unroll
-        for (int q = 0; q < 4; ++q) above |= ((yes >> (16 * q)) & 1ull) << at[q];
+        sa = row_allreduce_sum(sa);
+        sb = row_allreduce_sum(sb);
+        const bool above = cosine_exceeds_f64(dot, sa, sb, tau);
+        if (c == 0 && e < n) s.above[e] = above ? 1u : 0u;
     }
-    return above;
 }
+// The deciding wavefront asks for pairs, one for every row of `todo` (other_a, other_b: the partner of the lane's own rows), takes its share and
+// returns the rows whose pair is above tau.
+__device__ __forceinline__ Pair64 settle_pairs(CompressLds &s, const Pair64 &todo, int other_a, int other_b, float tau, int lane, int wave,
+                                               const bf16_t *Kchunk, int64_t stride_n, const int32_t *seed_rows) {
+    const int n_a = __popcll(todo.a), n = n_a + __popcll(todo.b);
+    const bool in_a = (todo.a >> lane) & 1ull, in_b = (todo.b >> lane) & 1ull;
+    const int at_a = __popcll(todo.a & bits_below(lane)), at_b = n_a + __popcll(todo.b & bits_below(lane));
+    if (in_a) s.list[at_a] = ((uint32_t)other_a << 8) | (uint32_t)lane;
+    if (in_b) s.list[at_b] = ((uint32_t)other_b << 8) | (uint32_t)(64 + lane);
+    if (lane == 0) s.pairs = n;
+    __syncthreads();
+    settle_share(s, n, tau, lane, wave, Kchunk, stride_n, seed_rows);
+    __syncthreads();
+    Pair64 r;
+    r.a = ballot64(in_a && s.above[min(at_a, kWinRows - 1)] != 0u);
+    r.b = ballot64(in_b && s.above[min(at_b, kWinRows - 1)] != 0u);
+    return r;
+}
+// the other wavefronts, until the deciding one is done
+__device__ __forceinline__ void settle_until_decided(CompressLds &s, float tau, int lane, int wave, const bf16_t *Kchunk, int64_t stride_n, const int32_t *seed_rows) {
+    for (;;) {
+        __syncthreads();
+        const int n = uniform(s.pairs);
+        if (n == 0) return;
+        settle_share(s, n, tau, lane, wave, Kchunk, stride_n, seed_rows);
+        __syncthreads();
+    }
+}
+__device__ __forceinline__ void decided(CompressLds &s, int lane) {
+    if (lane == 0) s.pairs = 0;
+    __syncthreads();
+}
+
+struct Decision {
+    Pair64 seeds;
+    int seed_a, seed_b;      // seed row of the lane's rows (-1: not an open row)
+};
 
 // Alg. 1 over the open rows of a window or block without walking the seeds one by one.  Seeds are taken in row
 // order and a seed absorbs every open row of its chunk that resembles it, so a row joins the FIRST seed before
@@ -484,682 +545,979 @@ __device__ __forceinline__ uint64_t settle_pairs_f64(const char *lds, uint64_t t
 //     r in T  <=>  no row of T before r (in r's chunk) resembles r            (induction over r: unique).
 // With F(S) = { r : no row of S before r resembles r }, T is the only fixed point of F.  Starting from the rows
 // that nothing earlier resembles (all of them seeds), F is applied until the set stops changing; when
-// "resembles" is transitive inside the chunks, the usual case, that is the first application.  Lane r brings,
-// restricted to the open rows before r in its own chunk, the rows it surely resembles (ye) and those inside
-// the band around tau (ue).  A pair inside the band can change the outcome only if its earlier row is a seed
-// that the later row, a seed itself, might resemble after all, or one before the seed the later row joins: the
-// first such pair of every row is settled in fp64 (the keys are parked in LDS) and the fixed point is taken
-// again.  Returns false, with nothing decided, if the set has not settled after a few applications of F or
+// "resembles" is transitive inside the chunks, the usual case, that is the first application.  The words hold, restricted to
+// the open rows before r in its own chunk, the rows it surely resembles (y) and those inside the band around tau (u).  A pair inside the band can
+// change the outcome only if its earlier row is a seed that the later row, a seed itself, might resemble after all, or one before the seed
+// the later row joins: the first such pair of every row is settled in fp64 and the fixed point is taken
+// again.  Returns false, with nothing decided but the settled pairs, if the set has not settled after a few applications of F or
 // pairs keep turning up: the caller then takes the seeds one at a time.
-__device__ __forceinline__ bool first_fit_fixed_point(const char *lds, uint64_t ye, uint64_t ue, bool is_open, float tau, int lane,
-                                                      uint64_t &seeds, int &my_seed) {
+__device__ __forceinline__ bool first_fit_fixed_point(CompressLds &s, Words &y, Words &u, bool open_a, bool open_b, float tau, int lane, int wave, Decision &d) {
     for (int pass = 0; pass < 8; ++pass) {
-        uint64_t S = ballot64(is_open && ye == 0ull);
+        Pair64 S;
+        S.a = ballot64(open_a && y.a == 0ull);
+        S.b = ballot64(open_b && (y.b0 | y.b1) == 0ull);
         bool settled = false;
         for (int it = 0; it < 8 && !settled; ++it) {
-            const uint64_t S2 = ballot64(is_open && (ye & S) == 0ull);
-            settled = S2 == S;
-            S = S2;
+            const uint64_t na = ballot64(open_a && (y.a & S.a) == 0ull);
+            const uint64_t nb = ballot64(open_b && ((y.b0 & S.a) | (y.b1 & S.b)) == 0ull);
+            settled = na == S.a && nb == S.b;
+            S.a = na;
+            S.b = nb;
         }
         if (!settled) return false;
-        const bool is_seed = (S >> lane) & 1ull;
-        const uint64_t mine = ye & S;                                   // not empty unless the row is a seed
-        const int first = is_seed ? lane : first_bit(mine);
-        const uint64_t doubt = ue & S & (is_seed ? ~0ull : bits_below(first & 63));
-        const uint64_t doubtful = ballot64(is_open && doubt != 0ull);
-        if (doubtful == 0ull) {
-            seeds = S;
-            my_seed = is_open ? first : -1;
+        const uint64_t ma = y.a & S.a, mb0 = y.b0 & S.a, mb1 = y.b1 & S.b;
+        const bool is_seed_a = ma == 0ull, is_seed_b = (mb0 | mb1) == 0ull;
+        const int first_a = is_seed_a ? lane : first_bit(ma);
+        const int first_b = is_seed_b ? 64 + lane : (mb0 != 0ull ? first_bit(mb0) : 64 + first_bit(mb1));
+        const uint64_t doubt_a = u.a & S.a & (is_seed_a ? ~0ull : bits_below(first_a));
+        const uint64_t doubt_b0 = u.b0 & S.a & bits_below(min(first_b, 64));
+        const uint64_t doubt_b1 = u.b1 & S.b & bits_below(max(first_b - 64, 0));
+        Pair64 doubtful;
+        doubtful.a = ballot64(open_a && doubt_a != 0ull);
+        doubtful.b = ballot64(open_b && (doubt_b0 | doubt_b1) != 0ull);
+        if ((doubtful.a | doubtful.b) == 0ull) {
+            d.seeds = S;
+            d.seed_a = open_a ? first_a : -1;
+            d.seed_b = open_b ? first_b : -1;
             return true;
         }
-        const int sd_mine = first_bit(doubt);
-        const uint64_t above = settle_pairs_f64(lds, doubtful, sd_mine, tau, lane);
-        if ((doubtful >> lane) & 1ull) {
-            ue &= ~(1ull << sd_mine);
-            if ((above >> lane) & 1ull) ye |= 1ull << sd_mine;
+        const int oa = doubt_a != 0ull ? first_bit(doubt_a) : 0;
+        const int ob = doubt_b0 != 0ull ? first_bit(doubt_b0) : (doubt_b1 != 0ull ? 64 + first_bit(doubt_b1) : 0);
+        const Pair64 above = settle_pairs(s, doubtful, oa, ob, tau, lane, wave, nullptr, 0, nullptr);
+        if ((doubtful.a >> lane) & 1ull) {
+            u.a &= ~(1ull << oa);
+            if ((above.a >> lane) & 1ull) y.a |= 1ull << oa;
+        }
+        if ((doubtful.b >> lane) & 1ull) {
+            const uint64_t bit = 1ull << (ob & 63);
+            const bool yes = (above.b >> lane) & 1ull;
+            if (ob < 64) { u.b0 &= ~bit; y.b0 |= yes ? bit : 0ull; }
+            else { u.b1 &= ~bit; y.b1 |= yes ? bit : 0ull; }
         }
     }
     return false;
 }
 
-__device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {   // position of the k-th set bit, 0 <= k < popcount(m)
-    int pos = 0;
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) {
-        const uint64_t part = (m >> pos) & ((1ull << w) - 1ull);
-        const int cnt = __popcll(part);
-        if (k >= cnt) { k -= cnt; pos += w; }
+// The literal loop: per round every chunk takes its first open row as its next seed, and the open rows with that bit set join it
+// (chunks never interact, so their loops run side by side; inside a chunk the order is exactly Alg. 1's).  ra, rb: the chunk's rows for the lane's rows.
+__device__ __forceinline__ void first_fit_by_seed(CompressLds &s, Words &y, Words &u, Pair64 todo, const Pair64 &ra, const Pair64 &rb, float tau, int lane, int wave, Decision &d) {
+    d.seeds.a = d.seeds.b = 0ull;
+    d.seed_a = d.seed_b = -1;
+    while ((todo.a | todo.b) != 0ull) {
+        const uint64_t a0 = todo.a & ra.a, a1 = todo.b & ra.b, b0 = todo.a & rb.a, b1 = todo.b & rb.b;
+        const int sa = a0 != 0ull ? first_bit(a0) : (a1 != 0ull ? 64 + first_bit(a1) : 128);
+        const int sb = b0 != 0ull ? first_bit(b0) : (b1 != 0ull ? 64 + first_bit(b1) : 128);
+        const bool open_a = (todo.a >> lane) & 1ull, open_b = (todo.b >> lane) & 1ull;
+        const bool seed_a = open_a && sa == lane, seed_b = open_b && sb == 64 + lane;
+        // (an open row's chunk has an open row, the row itself if no other: sa <= lane, sb <= 64 + lane)
+        const bool cand_a = open_a && sa < lane, cand_b = open_b && sb < 64 + lane;
+        bool yes_a = cand_a && ((y.a >> (sa & 63)) & 1ull);
+        bool yes_b = cand_b && (((sb < 64 ? y.b0 : y.b1) >> (sb & 63)) & 1ull);
+        Pair64 ask;
+        ask.a = ballot64(cand_a && ((u.a >> (sa & 63)) & 1ull));
+        ask.b = ballot64(cand_b && (((sb < 64 ? u.b0 : u.b1) >> (sb & 63)) & 1ull));
+        if ((ask.a | ask.b) != 0ull) {
+            const Pair64 above = settle_pairs(s, ask, sa & 127, sb & 127, tau, lane, wave, nullptr, 0, nullptr);
+            yes_a = yes_a || ((above.a >> lane) & 1ull);
+            yes_b = yes_b || ((above.b >> lane) & 1ull);
+        }
+        if (seed_a || yes_a) d.seed_a = sa;
+        if (seed_b || yes_b) d.seed_b = sb;
+        const uint64_t new_a = ballot64(seed_a), new_b = ballot64(seed_b);
+        const uint64_t got_a = ballot64(yes_a), got_b = ballot64(yes_b);
+        d.seeds.a |= new_a;
+        d.seeds.b |= new_b;
+        todo.a &= ~(new_a | got_a);
+        todo.b &= ~(new_b | got_b);
     }
-    return pos;
+}
+__device__ __forceinline__ int rows_below(const Pair64 &set, int row) {      // rows of the set before `row` (0..128)
+    return __popcll(set.a & bits_below(min(row, 64))) + __popcll(set.b & bits_below(max(row - 64, 0)));
 }
 
 // ------------------------------------------------------------------------------------------------
-// Work decomposition shared by both passes: a task is `chunks_per_item` (<= 32) consecutive chunks of
-// one (sequence, head), handled by one single-wavefront workgroup, so a finished task frees its
-// registers and LDS at once and the hardware dispatcher balances the load.  The task's chunk offsets
-// live in one register (lane j holds offsets[m0 + j]) and are read with v_readlane.
-struct TaskOffsets {
-    int v;      // lane j: offsets[m0 + j] for j <= nch
-    int m0, M;
-    __device__ __forceinline__ int at(int j) const { return __builtin_amdgcn_readlane(v, j); }
-    // rows of chunk idx of the task including its closing delimiter (the last chunk of a sequence has none)
-    __device__ __forceinline__ int rows(int idx) const {
-        return (m0 + idx < M - 1) ? (at(idx + 1) - at(idx)) : (at(idx + 1) - 1 - at(idx));
-    }
-};
-
-constexpr int kFastTaskThreads = kWave;
-
-// ------------------------------------------------------------------------------------------------
-// store the sizes of tile `ot` (from the ones column) at provisional rows
-__device__ __forceinline__ void store_sizes(const floatx4_t &Dn, int ot, int n_out, int32_t *dst, int64_t dst_row0,
-                                            int64_t row_limit, int lane) {
-    if ((lane & 15) == 0) {
-        const int g = lane >> 4;
+// Rows before a window: those of the windows before it in its segment, and of the segments before.  Workgroups are dispatched in slot order, so the
+// ones waited for are running or done; the wait is bounded all the same.
+// One wavefront asks through the scalar cache (glc: past it, from L2): a vector load would queue behind the rows that the compute unit's other
+// wavefronts have asked for, 3 us where this takes less than one.  Where the windows of a head are spread over XCDs (their number is no multiple
+// of eight), and every kVectorEvery-th time elsewhere, the look goes the other way, for words that another XCD's stores have changed in memory.
+constexpr int kVectorEvery = 8;
+typedef uint32_t u32x16_t __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ void load_words(u32x16_t &w, const void *at, bool scalar, int lane) {      // `at`: uniform
+    if (scalar) {
+        asm volatile("s_load_dwordx16 %0, %1, 0x0 glc\n\ts_waitcnt lgkmcnt(0)" : "=&s"(w) : "s"(at) : "memory");
+    } else {
+        const uint32_t v = __hip_atomic_load(static_cast<const uint32_t *>(at) + (lane & 15), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int o = 16 * ot + 4 * g + i;
-            if (o < n_out && dst_row0 + o < row_limit) dst[dst_row0 + o] = (int)(Dn[i] + 0.5f);
-        }
+        for (int k = 0; k < 16; ++k) w[k] = (uint32_t)__builtin_amdgcn_readlane((int)v, k);
     }
 }
-
-// COUNT: a probe of the budget search.  Only the clusters per chunk are wanted: no values are read and nothing is merged,
-// which leaves 146 vector registers instead of 245, so that the LDS of a window (17.8 KB) and not the registers
-// sets the wavefronts per compute unit (nine instead of eight).  Twelve probes and a merge of 8 heads x 32768 tokens:
-// 471.5 us with the merging kernel as the probe and an empty value descriptor, now 457.5.
-template <typename TO, bool COUNT>
-__global__ __launch_bounds__(kFastTaskThreads, COUNT ? 3 : 2) void gsc_compress_kernel(GscParams p) {
-    __shared__ __attribute__((aligned(16))) char s_lds[kLdsWaveBytes];
-    // One-dimensional grid: workgroup id = (pass * grid_x + x) * (B * Hkv) + (sequence, head).  The
-    // workgroups of pass 0 are dispatched first and take the tasks that need more than one window, pass 1
-    // takes the rest, so the long tasks never start last.  Inside a pass the task index x varies slowest:
-    // the workgroups beyond a sequence's last task (the host cannot know how many chunks there are) then
-    // come in one burst at the end of the pass instead of between the heads.
-    const int n_bh_grid = p.B * p.Hkv;
-    const int per_pass = p.grid_x * n_bh_grid;
-    const int pass = (int)blockIdx.x / per_pass;
-    const int rem_id = (int)blockIdx.x - pass * per_pass;
-    const int wg_x = rem_id / n_bh_grid, bh_id = rem_id - wg_x * n_bh_grid;
-    const int b = bh_id / p.Hkv, h = bh_id - b * p.Hkv;
-    const int lane_id = threadIdx.x;
-    const int C = p.chunks_per_item;
-    // The offsets of the workgroup's first task are requested together with the chunk count instead of
-    // after it (which offsets are meaningful is decided once the count is known; the index is clamped to
-    // the row, so the early request is always inside the array).  Most workgroups only look at one task,
-    // many only to find that it belongs to the other pass: for them this halves the time to the exit.
-    const int32_t *off = p.offsets + (int64_t)b * p.offsets_stride_b;
-    const int first_v = (lane_id <= C) ? off[min((int64_t)wg_x * C + lane_id, p.offsets_stride_b - 1)] : 0;
-    const int M = __builtin_amdgcn_readfirstlane(p.num_chunks[b]);
-    if (M <= 0) return;
-    int n = p.seq_lens ? __builtin_amdgcn_readfirstlane(p.seq_lens[b]) : p.N_max;
-    n = n < 0 ? 0 : (n > p.N_max ? p.N_max : n);
-    const int tasks = (M + C - 1) / C;
-    const int64_t bh = (int64_t)b * p.Hkv + h;
-    const bf16_t *Kbh = reinterpret_cast<const bf16_t *>(p.K) + b * p.stride_b + h * p.stride_h;
-    const bf16_t *Vbh = reinterpret_cast<const bf16_t *>(p.V) + b * p.stride_b + h * p.stride_h;
-    int32_t *pcount_bh = p.pcount + bh * ((int64_t)p.N_max + 1);
-    int32_t *seed_bh = p.seedrow + bh * p.N_max;
-    int32_t *cid_bh = p.cluster_id ? p.cluster_id + bh * p.N_max : nullptr;   // only when the caller asked
-    int32_t *cid32_bh = p.cid + bh * p.N_max;                                    // always there (workspace)
-    int32_t *stmp_bh = p.stmp + bh * p.N_max;
-    TO *ktmp_c = reinterpret_cast<TO *>(p.ktmp) + bh * (int64_t)p.N_max * kFastD;
-    TO *vtmp_c = reinterpret_cast<TO *>(p.vtmp) + bh * (int64_t)p.N_max * kFastD;
-    const int64_t tmp_rows = p.N_max;
-    const float tau = p.tau_dev ? *p.tau_dev : p.tau;
-
-    for (int task = wg_x; task < tasks; task += p.grid_x) {
-        TaskOffsets to;
-        to.m0 = task * C;
-        to.M = M;
-        const int m0 = to.m0;
-        const int nch = min(C, M - m0);
-        if (task == wg_x) to.v = (lane_id <= nch) ? first_v : 0;
-        else to.v = (lane_id <= nch) ? off[m0 + lane_id] : 0;
-        {
-            const int task_rows = to.at(nch) - to.at(0) - ((m0 + nch == M) ? 1 : 0);
-            if ((task_rows > kWin) != (pass == 0)) continue;
-        }
-        int idx = 0;
-        while (idx < nch) {
-            // Everything derived from the lane number is recomputed per window (and per block of a long
-            // chunk) instead of being carried in registers across the whole kernel: the optimiser cannot
-            // see through the empty asm statement.
-            int lane = lane_id;
-            asm volatile("" : "+v"(lane));
-            const int g = lane >> 4, c = lane & 15;
-            const int rows_first = to.rows(idx);
-            const int w0 = to.at(idx);
-            if (rows_first <= kWin) {
-                // ---------------- window of whole chunks, at most 64 rows
-                int idx_hi = idx, R = 0;
-                while (idx_hi < nch) {
-                    const int rr = to.rows(idx_hi);
-                    if (R + rr > kWin) break;
-                    R += rr;
-                    idx_hi += 1;
-                }
-                const int nchw = idx_hi - idx;
-                RowRegs xk;
-                [[maybe_unused]] RowRegs xv;
-                load_rows(xk, row_source(Kbh, p.stride_n, w0, R, g, c));
-                // the values are not needed before the merge: requested now, they arrive under the Gram step
-                if constexpr (!COUNT) load_rows(xv, row_source(Vbh, p.stride_n, w0, R, g, c));
-                // chunk range [lo, hi) of every row; a delimiter is a one-row range of its own
-                int lo = lane, hi = lane + 1;
-                bool in_chunk = false;
-                for (int j = 0; j < nchw; ++j) {
-                    const int cs = to.at(idx + j) - w0;
-                    const int ce = to.at(idx + j + 1) - 1 - w0;
-                    if (lane >= cs && lane < ce) { lo = cs; hi = ce; in_chunk = true; }
-                }
-                uint64_t yes_row, unsure_row;
-                gram_bitmatrix(s_lds, xk, R, tau, lane, yes_row, unsure_row);
-                // Alg. 1 on the bit matrix, one seed per chunk and round: the first unassigned row of a
-                // chunk is its next seed and absorbs the unassigned rows of the chunk whose bit is set
-                const uint64_t my_range = bits_range(lo, hi);
-                uint64_t todo = bits_range(0, R);
-                uint64_t seedmask = 0ull;
-                int my_seed = -1;
-                {
-                    const uint64_t earlier = bits_below(lane) & my_range;
-                    if (first_fit_fixed_point(s_lds, yes_row & earlier, unsure_row & earlier, lane < R, tau, lane, seedmask, my_seed)) todo = 0ull;
-                }
-                while (todo != 0ull) {
-                    const uint64_t mine = todo & my_range;
-                    const int s = (mine != 0ull) ? (__ffsll((unsigned long long)mine) - 1) : 64;
-                    const bool open = (todo >> lane) & 1ull;
-                    const bool is_seed = open && (s == lane);
-                    const bool cand = open && (s != lane);
-                    bool yes = cand && ((yes_row >> (s & 63)) & 1ull);
-                    const uint64_t recheck = ballot64(cand && ((unsure_row >> (s & 63)) & 1ull));
-                    const uint64_t above = settle_pairs_f64(s_lds, recheck, s, tau, lane);
-                    yes = yes || ((above >> lane) & 1ull);
-                    const uint64_t seeds_now = ballot64(is_seed);
-                    const uint64_t got = ballot64(yes);
-                    if (is_seed || yes) my_seed = s;
-                    seedmask |= seeds_now;
-                    todo &= ~(seeds_now | got);
-                }
-                // seeds in row order are the output rows of the window
-                const int nseed = __popcll(seedmask);
-                const int my_o = (lane < R) ? __popcll(seedmask & bits_range(0, my_seed)) : -1;
-                if (cid_bh && lane < R)
-                    cid_bh[w0 + lane] = in_chunk ? __popcll(seedmask & bits_range(lo, my_seed)) : -1;
-                {
-                    const int cs = __shfl(to.v, min(idx + lane, 63), kWave) - w0;
-                    const int ce = __shfl(to.v, min(idx + lane + 1, 63), kWave) - 1 - w0;
-                    if (lane < nchw) pcount_bh[m0 + idx + lane] = __popcll(seedmask & bits_range(cs, ce));
-                }
-                if constexpr (!COUNT) {
-                    // cluster means -> provisional rows [w0, w0 + nseed): keys (back from LDS), then values
-                    uint32_t ob[4];
-                    orow_to_operand_bytes_lds(s_lds + kLdsIdxOff, my_o, lane, ob);
-                    const int q_hi = (R + 15) >> 4;
-                    for (int ot = 0; ot * 16 < nseed; ++ot) {
-                        floatx4_t DK[8], DV[8], Dn = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) DK[j] = DV[j] = Dn;
-                        membership_mfma_kv(s_lds, xv, ob, 16 * ot + c, q_hi, lane, DK, DV, Dn);
-                        store_tile<TO>(DK, Dn, ot, nseed, ktmp_c, (int64_t)w0, tmp_rows, lane);
-                        store_tile<TO>(DV, Dn, ot, nseed, vtmp_c, (int64_t)w0, tmp_rows, lane);
-                        store_sizes(Dn, ot, nseed, stmp_bh, (int64_t)w0, tmp_rows, lane);
-                    }
-                }
-                idx = idx_hi;
-            } else {
-                // ---------------- one chunk longer than a window: one sweep over blocks of 64 rows.
-                // The first sixteen clusters live in registers across the blocks: their seeds' keys as the
-                // A operand of a (seed x row) Gram product, their key/value sums as MFMA accumulators.
-                // Clusters beyond the sixteenth (rare) take the slow way: seed by seed against the block,
-                // and a second pass over the chunk per sixteen further output rows.
-                const int start = w0;
-                const int l = to.at(idx + 1) - 1 - start;
-                const bool closed = (start + l) < n;
-                int nseeds = 0;
-                uint4 sa[4];   // lane (c, g): elements 32 ks + 8 g .. + 7 of the key of seed c (the MFMA's A operand)
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) sa[ks] = make_uint4(0u, 0u, 0u, 0u);
-                floatx4_t DK[8], DV[8], Dn = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int j = 0; j < 8; ++j) DK[j] = DV[j] = Dn;
-                float *s_rinv = reinterpret_cast<float *>(s_lds + kLdsRinvOff);
-                float *s_seed_rinv = reinterpret_cast<float *>(s_lds + kLdsSeedRinvOff);
-                for (int rb = 0; rb < l; rb += kWin) {
-                    int lane = lane_id;
-                    asm volatile("" : "+v"(lane));
-                    const int g = lane >> 4, c = lane & 15;
-                    const int R = min(kWin, l - rb);
-                    const int nt = (R + 15) >> 4;
-                    uint64_t yes_row, unsure_row;
-                    {
-                        RowRegs x;
-                        load_rows(x, row_source(Kbh, p.stride_n, start + rb, R, g, c));
-                        gram_bitmatrix(s_lds, x, R, tau, lane, yes_row, unsure_row);
-                    }
-                    [[maybe_unused]] RowRegs xv;
-                    if constexpr (!COUNT) load_rows(xv, row_source(Vbh, p.stride_n, start + rb, R, g, c));
-                    uint64_t todo = bits_range(0, R);
-                    int my_o = -1;
-                    const int seeds_before = nseeds;
-                    // carried seeds, sixteen at a time: their similarities with every row of the block are one
-                    // (seed x row) Gram product; the first group's keys sit in registers, further groups
-                    // (rare) are fetched again
-                    for (int sg = 0; sg * 16 < seeds_before && todo != 0ull; ++sg) {
-                        const int ns = min(16, seeds_before - 16 * sg);
-                        uint4 sb[4];
-                        floatx4_t rs;
-                        if (sg == 0) {
-#pragma unroll
-                            for (int ks = 0; ks < 4; ++ks) sb[ks] = sa[ks];
-                            rs = *reinterpret_cast<const floatx4_t *>(s_seed_rinv + 4 * g);
-                        } else {
-                            const int srow_c = (c < ns) ? __hip_atomic_load(seed_bh + start + 16 * sg + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-                            const bf16_t *sp = Kbh + (int64_t)(start + srow_c) * p.stride_n + 8 * g;
-#pragma unroll
-                            for (int ks = 0; ks < 4; ++ks)
-                                sb[ks] = (c < ns) ? *reinterpret_cast<const uint4 *>(sp + 32 * ks) : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const int sl = 16 * sg + 4 * g + i;
-                                rs[i] = (4 * g + i < ns) ? __int_as_float(__hip_atomic_load(stmp_bh + start + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0.f;
-                            }
-                        }
-                        // (seed x row) products: lane (c, g) gets seeds 4g .. 4g+3 against row 16 J + c
-                        floatx4_t cx[4];
-#pragma unroll
-                        for (int J = 0; J < 4; ++J) cx[J] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) {
-                            const bf16x8f_t a = __builtin_bit_cast(bf16x8f_t, sb[ks]);
-#pragma unroll
-                            for (int J = 0; J < 4; ++J) {
-                                if (J < nt) {
-                                    const uint4 v = *reinterpret_cast<const uint4 *>(s_lds + (16 * J + c) * kLdsRowBytes + (32 * ks + 8 * g) * 2);
-                                    cx[J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8f_t, v), cx[J], 0, 0, 0);
-                                }
-                            }
-                        }
-                        // per row one word: bit s = surely similar to seed s of the group, bit 16 + s = inside the
-                        // band.  A lane has the bits of its four seeds; an OR over the four lane groups completes
-                        // the word of row 16 J + c, and lane r keeps the word of row r.
-                        uint32_t cw = 0u;
-#pragma unroll
-                        for (int J = 0; J < 4; ++J) {
-                            if (J < nt) {
-                                const float norm = __builtin_amdgcn_rcpf(s_rinv[16 * J + c]);
-                                const float hn = (tau + kFastBand) * norm, ln = (tau - kFastBand) * norm;
-                                uint32_t w = 0u;
-#pragma unroll
-                                for (int i = 0; i < 4; ++i) {
-                                    const float t = cx[J][i] * rs[i];
-                                    const bool yy = t > hn;
-                                    const bool uu = !yy && !(t < ln);
-                                    w |= (yy ? 1u : 0u) << (4 * g + i);
-                                    w |= (uu ? 1u : 0u) << (16 + 4 * g + i);
-                                }
-                                w = or_rows(w);
-                                if (g == J) cw = w;
-                            }
-                        }
-                        const uint32_t valid = (1u << ns) - 1u;
-                        const bool open = (todo >> lane) & 1ull;
-                        uint32_t cyes = open ? (cw & valid) : 0u;
-                        uint32_t cuns = open ? ((cw >> 16) & valid) : 0u;
-                        // first fit over the seeds of the group; a pair inside the band is settled in fp64
-                        // when it is the first candidate of its row.  The keys of seed c are in the registers of
-                        // the four lanes (c, g) and the rows in LDS, so every seed settles one row at a time
-                        // (one pair at a time, through the seed list to a row in memory: long chunks at a threshold above the
-                        // band 2 % slower, in the band 1 to 2 % faster where a call is a few windows: 8 heads x 8000 tokens
-                        // 57.2 us against 55.5 at tau 0.7, 126.7 against 128.5 at 0.979).
-                        for (;;) {
-                            const uint32_t pend = cyes | cuns;
-                            const int f = (pend != 0u) ? (__ffs(pend) - 1) : -1;
-                            const uint64_t need = ballot64(f >= 0 && ((cuns >> (f & 31)) & 1u));
-                            if (need == 0ull) break;
-                            int row = -1;      // the first row that waits for this lane's seed
-                            for (uint64_t left = need; left != 0ull; left &= left - 1ull) {
-                                const int j = first_bit(left);
-                                const int fj = __builtin_amdgcn_readlane(f, j);
-                                if (row < 0 && fj == c) row = j;
-                            }
-                            double dot = 0.0, ss = 0.0, rr = 0.0;
-#pragma unroll
-                            for (int ks = 0; ks < 4; ++ks) {
-                                const uint4 v = *reinterpret_cast<const uint4 *>(s_lds + max(row, 0) * kLdsRowBytes + (32 * ks + 8 * g) * 2);
-                                uint4 u = sb[ks];
-                                asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w));   // (the seed's doubles stay out of the registers between rounds)
-                                cosine_sums_f64(u, v, dot, ss, rr);
-                            }
-                            dot = rows_allreduce_sum(dot);
-                            ss = rows_allreduce_sum(ss);
-                            rr = rows_allreduce_sum(rr);
-                            const int above = cosine_exceeds_f64(dot, ss, rr, tau) ? 1 : 0;
-                            const int settled = lane_gather(row, max(f, 0)), res = lane_gather(above, max(f, 0));
-                            if (settled == lane) {     // (rows that wait for no seed are nobody's `row`)
-                                cuns &= ~(1u << f);
-                                if (res) cyes |= 1u << f;
-                            }
-                        }
-                        if (cyes != 0u) my_o = 16 * sg + __ffs(cyes) - 1;
-                        todo &= ~ballot64(cyes != 0u);
-                    }
-                    // seeds inside the block, from the bit matrix
-                    // (the rows still open are decided among themselves; the new seeds continue the chunk's numbering)
-                    int new_row = -1;   // lane (c, g): block row of the seed that takes register slot c in this block
-                    uint64_t new_seeds = 0ull;
-                    {
-                        const uint64_t earlier_open = bits_below(lane) & todo;
-                        const bool is_open = (todo >> lane) & 1ull;
-                        uint64_t S = 0ull;
-                        int my_seed = -1;
-                        if (first_fit_fixed_point(s_lds, yes_row & earlier_open, unsure_row & earlier_open, is_open, tau, lane, S, my_seed)) {
-                            if (is_open) my_o = nseeds + __popcll(S & bits_below(my_seed));
-                            const int k = c - nseeds;
-                            if (k >= 0 && k < (int)__popcll(S)) new_row = nth_set_bit(S, k);
-                            new_seeds = S;
-                            nseeds += __popcll(S);
-                            todo = 0ull;
-                        }
-                    }
-                    while (todo != 0ull) {
-                        const int i = __builtin_amdgcn_readfirstlane(first_bit(todo));
-                        todo &= ~(1ull << i);
-                        new_seeds |= 1ull << i;
-                        const int o = nseeds;
-                        nseeds += 1;
-                        if (o < 16 && c == o) new_row = i;
-                        const bool cand = (todo >> lane) & 1ull;
-                        bool yes = cand && ((yes_row >> i) & 1ull);
-                        const uint64_t recheck = ballot64(cand && ((unsure_row >> i) & 1ull));
-                        const uint64_t above = settle_pairs_f64(s_lds, recheck, i, tau, lane);
-                        yes = yes || ((above >> lane) & 1ull);
-                        const uint64_t got = ballot64(yes);
-                        todo &= ~got;
-                        if (lane == i || yes) my_o = o;
-                    }
-                    // seed list of the chunk, filed by the new seeds themselves once the block is decided: row,
-                    // and reciprocal norm (in the size staging area, which gets its final contents only after
-                    // the last block)
-                    if ((new_seeds >> lane) & 1ull) {
-                        const float ri = s_rinv[lane];
-                        if (my_o < 16) s_seed_rinv[my_o] = ri;
-                        __hip_atomic_store(seed_bh + start + my_o, rb + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        __hip_atomic_store(stmp_bh + start + my_o, __float_as_int(ri), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    // new seeds move into their register slots (keys still parked in LDS)
-                    if (ballot64(new_row >= 0) != 0ull) {
-#pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) {
-                            const uint4 v = *reinterpret_cast<const uint4 *>(s_lds + max(new_row, 0) * kLdsRowBytes + (32 * ks + 8 * g) * 2);
-                            if (new_row >= 0) sa[ks] = v;
-                        }
-                    }
-                    // cluster index of every row: the caller's output, and what the passes for clusters
-                    // beyond the sixteenth read back below (through L2, by this wave only)
-                    if (lane < R) __hip_atomic_store(cid32_bh + start + rb + lane, my_o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    // sums of the first sixteen clusters
-                    if constexpr (!COUNT) {
-                        uint32_t ob[4];
-                        orow_to_operand_bytes_lds(s_lds + kLdsIdxOff, (lane < R) ? my_o : -1, lane, ob);
-                        membership_mfma_kv(s_lds, xv, ob, c, nt, lane, DK, DV, Dn);
-                    }
-                    wave_lds_fence();   // the next block overwrites the parked keys and the seed tables are read above
-                }
-                if (closed && lane == 0 && cid_bh) cid_bh[start + l] = -1;
-                if (lane == 0) pcount_bh[m0 + idx] = nseeds;
-                if constexpr (COUNT) {
-                    idx += 1;
-                    continue;
-                }
-                {
-                    const int n0 = min(nseeds, 16);
-                    store_tile<TO>(DK, Dn, 0, n0, ktmp_c, (int64_t)start, tmp_rows, lane);
-                    store_tile<TO>(DV, Dn, 0, n0, vtmp_c, (int64_t)start, tmp_rows, lane);
-                    store_sizes(Dn, 0, n0, stmp_bh, (int64_t)start, tmp_rows, lane);
-                }
-                if (nseeds > 16) {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // cluster index stores are done
-                    // kExtraTiles tiles of sixteen clusters per sweep over the chunk, keys and values in sweeps
-                    // of their own (the accumulators of both, or of a third tile, would not fit the registers).
-                    // The read-once hint stays on these loads: without it the large configurations lose more
-                    // to the displaced provisional rows than the sweeps gain from finding their rows cached.
-                    constexpr int kExtraTiles = 2;
-                    for (int src = 0; src < 2; ++src) {
-                        const bf16_t *Xbh = (src == 0) ? Kbh : Vbh;
-                        TO *dst_c = (src == 0) ? ktmp_c : vtmp_c;
-                        for (int ot = 1; ot * 16 < nseeds; ot += kExtraTiles) {
-                            floatx4_t D[kExtraTiles][8], Dm[kExtraTiles];
-#pragma unroll
-                            for (int t = 0; t < kExtraTiles; ++t) {
-                                Dm[t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                                for (int j = 0; j < 8; ++j) D[t][j] = Dm[t];
-                            }
-                            for (int rb = 0; rb < l; rb += kWin) {
-                                const int R = min(kWin, l - rb);
-                                RowRegs x;
-                                load_rows(x, row_source(Xbh, p.stride_n, start + rb, R, g, c));
-                                int my_o = -1;
-                                if (lane < R)
-                                    my_o = __hip_atomic_load(cid32_bh + start + rb + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                uint32_t ob[4];
-                                orow_to_operand_bytes(my_o - 16 * ot, lane, ob);
-                                membership_mfma_tiles<kExtraTiles>(x, ob, c, (R + 15) >> 4, D, Dm);
-                            }
-#pragma unroll
-                            for (int t = 0; t < kExtraTiles; ++t) {
-                                if ((ot + t) * 16 < nseeds) {
-                                    store_tile<TO>(D[t], Dm[t], ot + t, nseeds, dst_c, (int64_t)start, tmp_rows, lane);
-                                    if (src == 1) store_sizes(Dm[t], ot + t, nseeds, stmp_bh, (int64_t)start, tmp_rows, lane);
-                                }
-                            }
-                        }
-                    }
-                }
-                if (closed && start + nseeds < tmp_rows) {
-                    // the closing delimiter is output row `nseeds`: a copy with size 1
-                    if (g == 0) {
-                        float kv[8], vv[8];
-                        load8(Kbh + (int64_t)(start + l) * p.stride_n + 8 * c, kv);
-                        load8(Vbh + (int64_t)(start + l) * p.stride_n + 8 * c, vv);
-                        store8(ktmp_c + (int64_t)(start + nseeds) * kFastD + 8 * c, kv);
-                        store8(vtmp_c + (int64_t)(start + nseeds) * kFastD + 8 * c, vv);
-                    }
-                    if (lane == 0) stmp_bh[start + nseeds] = 1;
-                }
-                idx += 1;
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// Moves merged rows from their provisional position (first rows of their window / long chunk) to
-// their final position rowbase[first chunk] + o.  Pure copy: 16 lanes per row, four rows per access.
-// INLINE_PREFIX: no scan kernel ran; every workgroup adds up the cluster counts of the chunks before
-// its task itself (a few KB from L2), and the workgroup of the last task files the total.  Worth it
-// while a sequence has a few thousand chunks: it saves a launch whose only job is that sum.
-// APPEND: the rows go behind the base_lens[b, h] rows the outputs already hold (with the scan kernel in
-// between, its row bases already include them).
-template <typename TO, bool INLINE_PREFIX, bool APPEND>
-__global__ __launch_bounds__(kFastTaskThreads) void gsc_relocate_kernel(GscParams p) {
-    // one-dimensional grid, task index slowest (see the compress kernel)
-    const int n_bh_grid = p.B * p.Hkv;
-    const int wg_x = (int)blockIdx.x / n_bh_grid, bh_id = (int)blockIdx.x - wg_x * n_bh_grid;
-    const int b = bh_id / p.Hkv, h = bh_id - b * p.Hkv;
-    const int lane = threadIdx.x;
-    const int g = lane >> 4, c = lane & 15;
-    const int C = p.chunks_per_item;
-    const int32_t *off = p.offsets + (int64_t)b * p.offsets_stride_b;
-    // offsets of the first task requested together with the chunk count (index clamped to the row)
-    const int first_v = (lane <= C) ? off[min((int64_t)wg_x * C + lane, p.offsets_stride_b - 1)] : 0;
-    const int M = __builtin_amdgcn_readfirstlane(p.num_chunks[b]);
-    const int64_t bh = (int64_t)b * p.Hkv + h;
-    if (M <= 0) {
-        if (INLINE_PREFIX && wg_x == 0 && lane == 0) p.comp_lens[bh] = -1;
-        return;
-    }
-    const int tasks = (M + C - 1) / C;
-    const int32_t *rowbase_bh = p.rowbase + bh * ((int64_t)p.N_max + 2);
-    const int32_t *pcount_bh = p.pcount + bh * ((int64_t)p.N_max + 1);
-    const int32_t *stmp_bh = p.stmp + bh * p.N_max;
-    const TO *ktmp_c = reinterpret_cast<const TO *>(p.ktmp) + bh * (int64_t)p.N_max * kFastD + 8 * c;
-    const TO *vtmp_c = reinterpret_cast<const TO *>(p.vtmp) + bh * (int64_t)p.N_max * kFastD + 8 * c;
-    TO *Kc_c = reinterpret_cast<TO *>(p.Kc) + bh * (int64_t)p.cap * kFastD + 8 * c;
-    TO *Vc_c = reinterpret_cast<TO *>(p.Vc) + bh * (int64_t)p.cap * kFastD + 8 * c;
-    int32_t *counts_bh = p.counts + bh * p.cap;
-    const int64_t cap = p.cap;
-    constexpr int NP = (int)sizeof(TO) * 8 / 16;   // 16-byte pieces per lane and row
-    bool base_bad = false;
-    const int base_rows = (INLINE_PREFIX && APPEND) ? gsc_base_rows(p, bh, base_bad) : 0;
-
-    int summed = 0, summed_to = 0;      // INLINE_PREFIX: cluster counts of the chunks [0, summed_to), added up
-    for (int task = wg_x; task < tasks; task += p.grid_x) {
-        TaskOffsets to;
-        to.m0 = task * C;
-        to.M = M;
-        const int m0 = to.m0;
-        const int nch = min(C, M - m0);
-        if (task == wg_x) to.v = (lane <= nch) ? first_v : 0;
-        else to.v = (lane <= nch) ? off[m0 + lane] : 0;
-        int basev;
-        if (INLINE_PREFIX) {
-            // rows of the chunks before the task: every one of them is closed by a delimiter
-            // 2048 counts per round, four per lane and load, through a descriptor that ends at the task's first
-            // chunk (what lies beyond reads as zero): all loads of a round are in flight together, and a
-            // sequence of up to 32k tokens with chunks of 16 rows or more needs one round
-            // A workgroup that takes several tasks (more tasks than workgroups: very short chunks) carries the
-            // sum on from its previous task instead of starting at the first chunk again.
-            const __amdgpu_buffer_rsrc_t pc_src = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(pcount_bh + summed_to), (short)0,
-                                                                                    (m0 - summed_to) * 4, 0x00020000);
-            const int mine_raw = (lane < nch) ? pcount_bh[m0 + lane] : 0;
+__device__ __forceinline__ bool rows_before(const uint32_t *published, unsigned long long *seg_rows, int S, int slot, bool one_xcd, int &polls, int lane, int &rows) {
+    const int seg = slot / S, own = slot - seg * S;
+    int sum = 0, look = 0;
+    auto again = [&]() {
+        if (--polls < 0) return false;
+        look += 1;
+        __builtin_amdgcn_s_sleep(1);
+        return true;
+    };
+    // (sixteen words from the first on: of a segment's slots, the last is never anybody's predecessor; what lies behind the array is workspace)
+    for (int k0 = 0; k0 < own; k0 += 16) {
+        u32x16_t w;
+        for (;;) {
+            load_words(w, published + (int64_t)seg * S + k0, one_xcd && look % kVectorEvery != kVectorEvery - 1, lane);
+            bool there = true;
             int part = 0;
-            for (int mb = 0; mb < m0 - summed_to; mb += 32 * kWave) {
-                u32x4_t t[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) t[j] = __builtin_amdgcn_raw_buffer_load_b128(pc_src, (mb + 4 * kWave * j + 4 * lane) * 4, 0, 0);
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    part += (int)(((t[j].x & kPcountMask) + (t[j].y & kPcountMask)) + ((t[j].z & kPcountMask) + (t[j].w & kPcountMask)));
+            for (int k = 0; k < 16; ++k) {
+                if (k0 + k < own) {
+                    there = there && (w[k] & kPubRows) != 0u;
+                    part += (int)(w[k] & kPubValue);
+                }
             }
+            if (there) { sum += part; break; }
+            if (!again()) return false;
+        }
+    }
+    int before = 0;
+    bool known = seg == 0;
+    for (int top = seg; !known && top > 0; top -= 8) {      // segments top - 8 .. top - 1
+        u32x16_t w;
+        for (;;) {
+            load_words(w, seg_rows + top - 8, one_xcd && look % kVectorEvery != kVectorEvery - 1, lane);
+            bool there = true;
+            int part = 0;
+            known = false;
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d, kWave);
-            summed += part;
-            summed_to = m0;
-            const int before = summed;
-            // lane j: first output row of chunk m0 + j (lane nch: one past the task)
-            int mine = (lane < nch) ? (mine_raw & kPcountMask) + ((m0 + lane < M - 1) ? 1 : 0) : 0;
+            for (int k = 7; k >= 0; --k) {
+                if (!known && top - 8 + k >= 0) {
+                    there = there && ((w[2 * k + 1] >> 31) != 0u || w[2 * k + 1] == 0u);
+                    part += (int)w[2 * k];
+                    known = (w[2 * k + 1] >> 31) != 0u;
+                }
+            }
+            if (there) { before += part; break; }
+            if (!again()) return false;
+        }
+    }
+    // the end of the segment before is known now
+    if (own == 0 && seg > 0 && lane == 0)
+        __hip_atomic_store(seg_rows + seg - 1, kSegAll | (unsigned long long)(uint32_t)before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    rows = before + sum;
+    return true;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Means.  The product is formed transposed, columns x output rows: A holds 16 columns of the rows (lane (g, c): column 32 w + 2 c + parity,
+// contraction index (g, i) = row 32 ks + 16 (i / 4) + 4 g + i % 4 of the window), B the 0/1 membership of the same rows (column c: output row 16 ot + c).
+// Wavefront w takes columns 32 w .. 32 w + 31 in two tiles, even and odd: a lane ends up with eight neighbouring columns of one output row.
+struct ColumnOps {
+    bf16x8f_t x[4][2];
+};
+__device__ __forceinline__ void column_step(const CompressLds &s, int wave, int g, int c, int ks, bf16x8f_t &even, bf16x8f_t &odd) {
+    uint32_t d[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        d[i] = *reinterpret_cast<const uint32_t *>(s.rows + (32 * ks + 16 * (i >> 2) + 4 * g + (i & 3)) * kKeyRowBytes + 64 * wave + 4 * c);
+    even = __builtin_bit_cast(bf16x8f_t, make_uint4(pack_lo(d[0], d[1]), pack_lo(d[2], d[3]), pack_lo(d[4], d[5]), pack_lo(d[6], d[7])));
+    odd = __builtin_bit_cast(bf16x8f_t, make_uint4(pack_hi(d[0], d[1]), pack_hi(d[2], d[3]), pack_hi(d[4], d[5]), pack_hi(d[6], d[7])));
+}
+__device__ __forceinline__ void column_operands(const CompressLds &s, int wave, int g, int c, int nks, ColumnOps &o) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+        if (ks < nks) column_step(s, wave, g, c, ks, o.x[ks][0], o.x[ks][1]);
+}
+// out_a, out_b: output row of the lane's rows, -1 for none, counted from the first of `tiles` tiles
+__device__ __forceinline__ void file_membership(CompressLds &s, int out_a, int out_b, int tiles, int lane) {
+    for (int t = 0; t < tiles; ++t) {
+        const bool a = out_a >= 0 && (out_a >> 4) == t, b = out_b >= 0 && (out_b >> 4) == t;
+        s.hot[t][lane] = a ? (uint16_t)(1u << (out_a & 15)) : (uint16_t)0;
+        s.hot[t][64 + lane] = b ? (uint16_t)(1u << (out_b & 15)) : (uint16_t)0;
+        const uint64_t ma = ballot64(a), mb = ballot64(b);
+        if (lane == 0)
+            s.tile_steps[t] = (((uint32_t)ma != 0u) ? 1 : 0) | (((ma >> 32) != 0ull) ? 2 : 0) | (((uint32_t)mb != 0u) ? 4 : 0) | (((mb >> 32) != 0ull) ? 8 : 0);
+    }
+}
+// the lane's bit of its rows, turned to bit 14 of either half of a word: bf16 2.0.  (The sums are twice what they stand for, exactly.)
+__device__ __forceinline__ bf16x8f_t membership_operand(const uint16_t *hot, int ks, int c, int g) {
+    uint32_t aw[4];
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2) {
+        const uint2 w = *reinterpret_cast<const uint2 *>(hot + 32 * ks + 16 * h2 + 4 * g);
+        aw[2 * h2] = __builtin_amdgcn_alignbit(w.x, w.x, (uint32_t)(c + 18)) & 0x40004000u;
+        aw[2 * h2 + 1] = __builtin_amdgcn_alignbit(w.y, w.y, (uint32_t)(c + 18)) & 0x40004000u;
+    }
+    return __builtin_bit_cast(bf16x8f_t, make_uint4(aw[0], aw[1], aw[2], aw[3]));
+}
+__device__ __forceinline__ bf16x8f_t ones_operand() {
+    return __builtin_bit_cast(bf16x8f_t, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+}
+// a zero row times an infinity is not a number: sums that are not finite are taken again without the other clusters' rows
+__device__ __forceinline__ bool all_finite(const floatx4_t &a, const floatx4_t &b) {
+    float z = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z = fmaf(a[i], 0.f, fmaf(b[i], 0.f, z));
+    return z == 0.f;
+}
+// eight columns of one output row, from twice the sums and twice the size: 1/size is exact for powers of two, 1 ulp otherwise; a row of
+// size 1 is passed on unchanged
+__device__ __forceinline__ void scale_mean(float (&v)[8], const floatx4_t &even, const floatx4_t &odd, float size2) {
+    const float inv = (size2 > 3.f) ? __builtin_amdgcn_rcpf(size2) : 0.5f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[2 * i] = even[i] * inv; v[2 * i + 1] = odd[i] * inv; }
+}
+template <typename TO>
+__device__ __forceinline__ void store_mean(TO *row, const floatx4_t &even, const floatx4_t &odd, float size2, int wave, int g) {
+    float v[8];
+    scale_mean(v, even, odd, size2);
+    TO *at = row + 32 * wave + 8 * g;
+    if constexpr (sizeof(TO) == 2) {
+        store16_stream(at, make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])));
+    } else {
+        store16_stream(at, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
+        store16_stream(at + 4, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])));
+    }
+}
+// to row c of sixteen at `rows` (uniform), written through (sc1) to where another XCD's loads find it
+template <typename TO>
+__device__ __forceinline__ void store_mean_through(TO *rows, int c, const floatx4_t &even, const floatx4_t &odd, float size2, int wave, int g) {
+    constexpr int kThrough = 16;
+    float v[8];
+    scale_mean(v, even, odd, size2);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(rows, (short)0, 16 * kFastD * (int)sizeof(TO), 0x00020000);
+    const int off = (c * kFastD + 32 * wave + 8 * g) * (int)sizeof(TO);
+    if constexpr (sizeof(TO) == 2) {
+        const u32x4_t t = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+        __builtin_amdgcn_raw_buffer_store_b128(t, rs, off, 0, kThrough);
+    } else {
+        const u32x4_t t0 = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+        const u32x4_t t1 = {__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])};
+        __builtin_amdgcn_raw_buffer_store_b128(t0, rs, off, 0, kThrough);
+        __builtin_amdgcn_raw_buffer_store_b128(t1, rs, off + 16, 0, kThrough);
+    }
+}
+// the same sums member by member from memory, rows [0, rows) at X with output rows given by `member` (rare: see all_finite)
+template <typename F>
+__device__ __forceinline__ void sums_by_member(const bf16_t *X, int64_t stride_n, int rows, F member, int wave, int g, floatx4_t &even, floatx4_t &odd) {
+    even = odd = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int r = 0; r < rows; ++r) {
+        if (member(r)) {
+            float x[8];
+            load8(X + (int64_t)r * stride_n + 32 * wave + 8 * g, x);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { even[i] += 2.f * x[2 * i]; odd[i] += 2.f * x[2 * i + 1]; }
+        }
+    }
+}
+
+// Everything derived from the lane number is recomputed from phase to phase instead of being carried in registers across the kernel (they
+// spilled): the optimiser cannot see through the empty asm statement.
+__device__ __forceinline__ int fresh_lane() {
+    int lane = threadIdx.x & (kWave - 1);
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+// The same for the kernel's arguments: read again where a phase needs them, instead of being held in a hundred scalar registers (and their spills).
+typedef const __attribute__((address_space(4))) GscParams ConstParams;
+__device__ __forceinline__ ConstParams *fresh_params() {
+    ConstParams *p = (ConstParams *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+#define SC_FRESH_PARAMS ConstParams &p = *fresh_params()
+#define SC_FRESH_LANE                     \
+    const int lane = fresh_lane();        \
+    [[maybe_unused]] const int g = lane >> 4, c = lane & 15
+
+// COUNT: a probe of the budget search.  Only the number of rows is wanted: no values are read and nothing is merged.
+template <typename TO, bool COUNT>
+__global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams p) {
+    __shared__ __attribute__((aligned(16))) CompressLds s;
+    // Slots in order, (sequence, head) fastest: every workgroup waits for earlier ones only, and with a multiple of eight
+    // heads the windows of a head stay on one XCD.  Long chunks are decided ahead of everything else, by ahead_per_head workgroups per
+    // head that wait for nothing: a window waits for the rows of all before it, and a long chunk in between, which takes twice as long, would hold up
+    // those of half the chip (8 heads x 131072, a quarter of the windows long: 225 us, decided ahead 165).
+    const int n_bh = p.B * p.Hkv;
+    const int ahead_wgs = COUNT ? 0 : p.ahead_wgs;
+    const bool ahead = (int)blockIdx.x < ahead_wgs;
+    const unsigned id = ahead ? blockIdx.x : blockIdx.x - (unsigned)ahead_wgs;
+    const int place = (int)(id / (unsigned)n_bh), bh_i = (int)(id - (unsigned)place * (unsigned)n_bh);
+    const int b = bh_i / p.Hkv, h = bh_i - b * p.Hkv;
+    const int64_t bh = bh_i;
+    // (through the constant address space: scalar loads, which do not queue behind the vector loads of other wavefronts)
+    typedef int i32x8_t __attribute__((ext_vector_type(8)));
+    struct Window { int slot, first, rows, flags; };
+    auto take_window = [&](int at, Pair64 *delim) {
+        SC_FRESH_PARAMS;
+        const i32x8_t wd = *reinterpret_cast<const __attribute__((address_space(4))) i32x8_t *>((uintptr_t)(p.windows + (int64_t)b * p.win_slots + at));
+        if (delim) {
+            delim->a = ((uint64_t)(uint32_t)wd[5] << 32) | (uint32_t)wd[4];
+            delim->b = ((uint64_t)(uint32_t)wd[7] << 32) | (uint32_t)wd[6];
+        }
+        return Window{at, wd[0], wd[1], wd[2]};
+    };
+    // the `at`-th long chunk of the sequence, if it has as many
+    auto take_long = [&](int at, Window &w) {
+        SC_FRESH_PARAMS;
+        const int lane = fresh_lane(), S = p.slots_per_segment, segments = p.win_slots / S;
+        const int32_t *count = p.long_count + (int64_t)b * segments;
+        for (int s0 = 0; s0 < segments; s0 += kWave) {
+            const int mine = s0 + lane < segments ? count[s0 + lane] : 0;
             int incl = mine;
 #pragma unroll
             for (int d = 1; d < kWave; d <<= 1) {
                 const int up = __shfl_up(incl, d, kWave);
                 if (lane >= d) incl += up;
             }
-            basev = base_rows + before + m0 + incl - mine;
-            if (m0 + nch == M && lane == nch) p.comp_lens[bh] = (!base_bad && basev <= p.cap) ? basev : -1;
-        } else {
-            basev = (lane <= nch) ? rowbase_bh[m0 + lane] : 0;
+            const uint64_t behind = ballot64(incl > at);
+            if (behind != 0ull) {
+                const int l = first_bit(behind), k = at - __builtin_amdgcn_readlane(incl - mine, l);
+                w = take_window((s0 + l) * S + uniform((int)p.longs[(int64_t)b * segments + s0 + l].slot[k]), nullptr);
+                return true;
+            }
+            at -= __builtin_amdgcn_readlane(incl, kWave - 1);
         }
-        int idx = 0;
-        while (idx < nch) {
-            const int src0 = to.at(idx);
-            const int64_t out0 = __builtin_amdgcn_readlane(basev, idx);
-            int idx_hi = idx + 1;
-            if (to.rows(idx) <= kWin) {
-                int R = 0;
-                idx_hi = idx;
-                while (idx_hi < nch) {
-                    const int rr = to.rows(idx_hi);
-                    if (R + rr > kWin) break;
-                    R += rr;
-                    idx_hi += 1;
+        return false;
+    };
+    [[maybe_unused]] int next_long = place;
+    Window win, next;
+    Pair64 D = {0ull, 0ull};
+    if (!ahead) {
+        win = take_window(place, &D);
+        if (win.rows <= 0) return;
+    } else {
+        if (!take_long(next_long, win)) return;
+        D.a = D.b = 0ull;
+    }
+    const int &slot = win.slot, &w0 = win.first, &R = win.rows, &flags = win.flags;
+    const int tid = threadIdx.x, wave = uniform(tid / kWave);
+    const bf16_t *Kbh = reinterpret_cast<const bf16_t *>(p.K) + b * p.stride_b + h * p.stride_h;
+    const bf16_t *Vbh = reinterpret_cast<const bf16_t *>(p.V) + b * p.stride_b + h * p.stride_h;
+    const float tau = p.tau_dev ? *p.tau_dev : p.tau;
+    // the window's rows are known: tell the windows behind it
+    auto publish = [&](int rows, int lane) {      // one wavefront
+        SC_FRESH_PARAMS;
+        if (lane == 0) {
+            if constexpr (COUNT) p.win_count[bh * p.win_slots + slot] = rows;
+            else {
+                const int S = p.slots_per_segment;
+                uint32_t *pub = p.published + bh * p.win_slots;
+                unsigned long long *seg_rows = p.seg_rows + bh * (p.win_slots / S);
+                __hip_atomic_store(pub + slot, kPubRows | (uint32_t)rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(seg_rows + slot / S, (unsigned long long)(uint32_t)rows - (1ull << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    };
+    // first output row of the window, for all wavefronts (between two barriers)
+    auto find_base = [&](int rows) {      // one wavefront
+        SC_FRESH_LANE;
+        SC_FRESH_PARAMS;
+        const int S = p.slots_per_segment;
+        const int64_t cap = p.cap;
+        uint32_t *pub = p.published + bh * p.win_slots;
+        unsigned long long *seg_rows = p.seg_rows + bh * (p.win_slots / S);
+        int before = 0, polls = p.polls;
+        const bool ok = rows_before(pub, seg_rows, S, slot, ((p.B * p.Hkv) & 7) == 0, polls, lane, before);
+        bool bad;
+        const int held = gsc_base_rows(p, bh, bad);
+        if (lane == 0) {
+            const int64_t total = (int64_t)held + before + rows;
+            if (flags & kWinLast) {
+                // comp_lens is -1 in the end if any window of the head gave up, whatever the order
+                __hip_atomic_store(p.comp_lens + bh, (!bad && ok && total <= cap) ? (int32_t)total : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                if (__hip_atomic_load(p.gave_up + bh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+                    __hip_atomic_store(p.comp_lens + bh, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (!ok) {
+                __hip_atomic_store(p.gave_up + bh, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __hip_atomic_store(p.comp_lens + bh, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            s.base_ok = ok ? 1 : 0;
+            s.base_lo = (int)min((int64_t)held + before, (int64_t)0x7FFFFFFF);      // (beyond any capacity: nothing is written)
+        }
+    };
+
+    const int decider = (place + bh_i) & (kWinWaves - 1);
+    if (!ahead && !(flags & kWinLong)) {
+        {
+            SC_FRESH_LANE;
+            RowRegs xk;
+            load_rows(xk, Kbh, p.stride_n, w0 + 32 * wave, min(32, R - 32 * wave), g, c);
+            if (tid == 0) s.any_unsure = 0;
+            file_norms(s, xk, R - 32 * wave, wave, g, c);
+            park_rows(s, xk, wave, g, c);
+        }
+        __syncthreads();
+        const bool odd = uniform(*reinterpret_cast<const int *>(s.odd_norms)) != 0;
+        // the values, on their way while the rows are decided.  (Requested with the keys they delay those of the windows behind, and with
+        // them everything that waits for those windows' rows.)
+        [[maybe_unused]] RowRegs xv;
+        if constexpr (!COUNT) {
+            SC_FRESH_LANE;
+            load_rows(xv, Vbh, p.stride_n, w0 + 32 * wave, min(32, R - 32 * wave), g, c);
+        }
+        // wavefront w: column tiles 7 - w and w, nine tiles of the upper triangle; those of other chunks are left out
+#pragma unroll 1
+        for (int jj = 0; jj < 2; ++jj) {
+            const int J = jj == 0 ? 7 - wave : wave;
+            if (16 * J < R) {
+                SC_FRESH_LANE;
+                const uint64_t da = D.a & bits_below(min(16 * J, 64)), db = D.b & bits_below(max(16 * J - 64, 0));
+                const int lo = db != 0ull ? 65 + last_bit(db) : (da != 0ull ? 1 + last_bit(da) : 0);      // first row of the chunk of row 16 J
+                gram_column(s, J, lo >> 4, R, tau, odd, g, c);
+            }
+        }
+        __syncthreads();
+        [[maybe_unused]] ColumnOps kk;
+        const int nks = (R + 31) >> 5;
+        if (wave == decider) {
+            SC_FRESH_LANE;
+            // rows [lo, r) of the lane's rows' chunks; a delimiter is a chunk of its own
+            const uint64_t below = bits_below(lane);
+            const uint64_t da = D.a & below, db = D.b & below;
+            const int lo_a = da != 0ull ? 1 + last_bit(da) : 0;
+            const int lo_b = db != 0ull ? 65 + last_bit(db) : (D.a != 0ull ? 1 + last_bit(D.a) : 0);
+            const bool delim_a = (D.a >> lane) & 1ull, delim_b = (D.b >> lane) & 1ull;
+            const bool open_a = lane < R, open_b = 64 + lane < R;
+            const uint64_t before_a = (delim_a || !open_a) ? 0ull : below & ~bits_below(lo_a);
+            const uint64_t before_b0 = (delim_b || !open_b) ? 0ull : ~bits_below(min(lo_b, 64));
+            const uint64_t before_b1 = (delim_b || !open_b) ? 0ull : below & ~bits_below(max(lo_b - 64, 0));
+            Words y, u;
+            y.a = row_word(s.yes, lane, 0) & before_a;
+            y.b0 = row_word(s.yes, 64 + lane, 0) & before_b0;
+            y.b1 = row_word(s.yes, 64 + lane, 1) & before_b1;
+            u.a = u.b0 = u.b1 = 0ull;
+            if (uniform(s.any_unsure) != 0) {
+                u.a = row_word(s.unsure, lane, 0) & before_a;
+                u.b0 = row_word(s.unsure, 64 + lane, 0) & before_b0;
+                u.b1 = row_word(s.unsure, 64 + lane, 1) & before_b1;
+            }
+            Decision d;
+            if (!first_fit_fixed_point(s, y, u, open_a, open_b, tau, lane, wave, d)) {
+                // chunk ranges: up to the first delimiter from the row on
+                const uint64_t ea = D.a & ~below, eb = D.b & ~below;
+                const int hi_a = ea != 0ull ? first_bit(ea) : (D.b != 0ull ? 64 + first_bit(D.b) : R);
+                const int hi_b = eb != 0ull ? 64 + first_bit(eb) : R;
+                const int la = delim_a ? lane : lo_a, ha = delim_a ? lane + 1 : hi_a;
+                const int lb = delim_b ? 64 + lane : lo_b, hb = delim_b ? 65 + lane : hi_b;
+                const Pair64 ra = {bits_below(min(ha, 64)) & ~bits_below(min(la, 64)), bits_below(max(ha - 64, 0)) & ~bits_below(max(la - 64, 0))};
+                const Pair64 rb = {bits_below(min(hb, 64)) & ~bits_below(min(lb, 64)), bits_below(max(hb - 64, 0)) & ~bits_below(max(lb - 64, 0))};
+                const Pair64 all = {bits_below(min(R, 64)), bits_below(max(R - 64, 0))};
+                first_fit_by_seed(s, y, u, all, ra, rb, tau, lane, wave, d);
+            }
+            const int nseed = __popcll(d.seeds.a) + __popcll(d.seeds.b);
+            publish(nseed, lane);
+            if constexpr (!COUNT) {
+                const int out_a = open_a ? rows_below(d.seeds, d.seed_a) : -1, out_b = open_b ? rows_below(d.seeds, d.seed_b) : -1;
+                SC_FRESH_PARAMS;
+                if (p.cluster_id) {
+                    int32_t *cid = p.cluster_id + bh * p.N_max + w0;
+                    if (open_a) cid[lane] = delim_a ? -1 : out_a - rows_below(d.seeds, lo_a);
+                    if (open_b) cid[64 + lane] = delim_b ? -1 : out_b - rows_below(d.seeds, lo_b);
+                }
+                file_membership(s, out_a, out_b, (nseed + 15) >> 4, lane);
+                if (lane == 0) s.nseed = nseed;
+                column_operands(s, wave, g, c, nks, kk);
+            }
+            decided(s, lane);
+        } else {
+            SC_FRESH_LANE;
+            if constexpr (!COUNT) column_operands(s, wave, g, c, nks, kk);
+            settle_until_decided(s, tau, lane, wave, nullptr, 0, nullptr);
+        }
+        if constexpr (!COUNT) {
+            // everybody has the keys: the values take their place
+            SC_FRESH_LANE;
+            const int nseed = uniform(s.nseed);
+            park_rows(s, xv, wave, g, c);
+            if (wave == ((decider + 1) & (kWinWaves - 1))) find_base(nseed);
+            __syncthreads();
+            if (uniform(s.base_ok) == 0) return;
+            ColumnOps vv;
+            column_operands(s, wave, g, c, nks, vv);
+            const int64_t base = uniform(s.base_lo);
+            const bool odd_keys = uniform(s.any_unsure) != 0;      // (a key that is not finite has no usable norm)
+            SC_FRESH_PARAMS;
+            const int64_t cap = p.cap;
+            TO *Kat = reinterpret_cast<TO *>(p.Kc) + (bh * cap + base) * kFastD, *Vat = reinterpret_cast<TO *>(p.Vc) + (bh * cap + base) * kFastD;
+            int32_t *counts = p.counts + bh * cap;
+            for (int ot = 0; 16 * ot < nseed; ++ot) {
+                floatx4_t ke = {0.f, 0.f, 0.f, 0.f}, ko = ke, ve = ke, vo = ke, cn = ke;
+                const int steps = uniform(s.tile_steps[ot]);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    if ((steps >> ks) & 1) {
+                        const bf16x8f_t mem = membership_operand(s.hot[ot], ks, c, g);
+                        ke = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk.x[ks][0], mem, ke, 0, 0, 0);
+                        ko = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk.x[ks][1], mem, ko, 0, 0, 0);
+                        ve = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv.x[ks][0], mem, ve, 0, 0, 0);
+                        vo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv.x[ks][1], mem, vo, 0, 0, 0);
+                        cn = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_operand(), mem, cn, 0, 0, 0);
+                    }
+                }
+                const int o = 16 * ot + c;
+                if (ballot64(!all_finite(ve, vo) || (odd_keys && !all_finite(ke, ko))) != 0ull) {
+                    auto member = [&](int r) { return ((s.hot[ot][r] >> c) & 1) != 0; };
+                    sums_by_member(Kbh + (int64_t)w0 * p.stride_n, p.stride_n, R, member, wave, g, ke, ko);
+                    sums_by_member(Vbh + (int64_t)w0 * p.stride_n, p.stride_n, R, member, wave, g, ve, vo);
+                }
+                if (o < nseed && base + o < cap) {
+                    store_mean<TO>(Kat + o * kFastD, ke, ko, cn[0], wave, g);
+                    store_mean<TO>(Vat + o * kFastD, ve, vo, cn[0], wave, g);
+                    if (wave == 0 && g == 0) counts[base + o] = (int)(0.5f * cn[0] + 0.5f);
                 }
             }
-            const int n_out = __builtin_amdgcn_readlane(basev, idx_hi) - (int)out0;
-            for (int o0 = 0; o0 < n_out; o0 += 16) {
-                uint4 kk[4][NP], vv[4][NP];
+        }
+        return;
+    }
+
+    // ---------------- one chunk longer than a window: blocks of 128 rows.  Seeds are listed in the workspace (row and reciprocal norm); a block's rows
+    // are first compared with the seeds of the blocks before, 64 at a time, sixteen per wavefront, then among themselves.
+    if (COUNT || ahead) {
+    RowRegs x;
+    {
+        SC_FRESH_LANE;
+        load_rows<0>(x, Kbh, p.stride_n, w0 + 32 * wave, min(32, R - 32 * wave), g, c);
+    }
+    for (;;) {
+    SC_FRESH_PARAMS;
+    // (the next one is looked up and its first rows are requested while this one is worked on)
+    bool more = false;
+    if (ahead) {
+        next_long += p.ahead_per_head;
+        more = take_long(next_long, next);
+    }
+    const int start = w0, l = R;
+    const bool closed = (flags & kWinClosed) != 0;
+    int32_t *seed_rows = p.seedrow + bh * p.N_max + start;
+    int32_t *seed_rinv = p.stmp + bh * p.N_max + start;
+    int32_t *cid = p.cid + bh * p.N_max + start;
+    const bf16_t *Kch = Kbh + (int64_t)start * p.stride_n;
+    // The first sixteen stay at hand: their keys in registers (the A operand of the comparison), their sums over the keys in accumulators.  If there are
+    // no more, their means wait in the workspace, and the keys need not be read again.
+    int nseeds = 0;
+    bf16x8f_t carried[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int o = o0 + 4 * k + g;
-                    const bool ok = o < n_out && out0 + o < cap;
-                    const uint4 *ks = reinterpret_cast<const uint4 *>(ktmp_c + ((int64_t)src0 + (ok ? o : 0)) * kFastD);
-                    const uint4 *vs = reinterpret_cast<const uint4 *>(vtmp_c + ((int64_t)src0 + (ok ? o : 0)) * kFastD);
+    for (int ks = 0; ks < 4; ++ks) carried[ks] = __builtin_bit_cast(bf16x8f_t, make_uint4(0u, 0u, 0u, 0u));
+    [[maybe_unused]] floatx4_t ke = {0.f, 0.f, 0.f, 0.f}, ko = ke, cn = ke;
+#pragma unroll 1
+    for (int rb = 0; rb < l; rb += kWinRows) {
+        const int Rb = min(kWinRows, l - rb), nx = rb + kWinRows;
+        {
+            SC_FRESH_LANE;
+            if (tid == 0) s.any_unsure = 0;
+            file_norms(s, x, Rb - 32 * wave, wave, g, c);
+            park_rows(s, x, wave, g, c);
+            // on its way while this block is worked on
+            if (nx < l) load_rows<0>(x, Kch, p.stride_n, nx + 32 * wave, min(32, l - nx - 32 * wave), g, c);
+            else if (more) load_rows<0>(x, Kbh, p.stride_n, next.first + 32 * wave, min(32, next.rows - 32 * wave), g, c);
+        }
+        __syncthreads();
+        const bool odd = uniform(*reinterpret_cast<const int *>(s.odd_norms)) != 0;
+        Pair64 open = {bits_below(min(Rb, 64)), bits_below(max(Rb - 64, 0))};      // (the deciding wavefront's)
+        int my_a = -1, my_b = -1;      // cluster of the lane's rows
+        bool any_open = true;
+#pragma unroll 1
+        for (int s0 = 0; s0 < nseeds && any_open; s0 += 16 * kWinWaves) {
+            SC_FRESH_LANE;
+            // (one group of sixteen: its row tiles are shared out)
+            const bool shared = nseeds - s0 <= 16;
+            const int first = s0 + (shared ? 0 : 16 * wave), ns = min(16, nseeds - first);
+            if (ns > 0) {
+                bf16x8f_t a[4];
+                floatx4_t rs;
+                if (first == 0) {
 #pragma unroll
-                    for (int q = 0; q < NP; ++q) {
-                        kk[k][q] = ok ? load16_stream(ks + q) : make_uint4(0, 0, 0, 0);
-                        vv[k][q] = ok ? load16_stream(vs + q) : make_uint4(0, 0, 0, 0);
+                    for (int ks = 0; ks < 4; ++ks) a[ks] = carried[ks];
+                    rs = *reinterpret_cast<const floatx4_t *>(s.seed_rinv + 4 * g);
+                } else {
+                    const int srow = (c < ns) ? __hip_atomic_load(seed_rows + first + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+                    const bf16_t *sp = Kch + (int64_t)srow * p.stride_n + 8 * g;
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+                        a[ks] = __builtin_bit_cast(bf16x8f_t, (c < ns) ? *reinterpret_cast<const uint4 *>(sp + 32 * ks) : make_uint4(0u, 0u, 0u, 0u));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        rs[i] = (4 * g + i < ns) ? __int_as_float(__hip_atomic_load(seed_rinv + first + 4 * g + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0.f;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) rs[i] = (4 * g + i < ns) ? rs[i] : 0.f;
+                const float rsum = (rs[0] + rs[1]) + (rs[2] + rs[3]);      // not a number if one of them is
+                const bool odd_seed = ballot64(!(rsum == rsum)) != 0ull;
+                const int J_step = shared ? kWinWaves : 1;
+                for (int J = shared ? wave : 0; 16 * J < Rb; J += J_step) {
+                    floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) {
+                        const uint4 v = *reinterpret_cast<const uint4 *>(s.rows + (16 * J + c) * kKeyRowBytes + (32 * ks + 8 * g) * 2);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks], __builtin_bit_cast(bf16x8f_t, v), acc, 0, 0, 0);
+                    }
+                    float hn, wn;
+                    column_bounds(s.rinv[16 * J + c], 16 * J + c < Rb, tau, hn, wn);
+                    Nibbles n = threshold_nibbles(acc, rs, hn);
+                    uint32_t ub = 0u;
+                    if (odd_seed || odd || ballot64(n.least <= __float_as_uint(wn)) != 0ull) ub = unsure_nibble(n, wn);
+                    const uint32_t yb = n.yes;
+                    const uint32_t both = or_rows((yb << (4 * g)) | (ub << (16 + 4 * g)));
+                    const uint32_t valid = (1u << ns) - 1u;
+                    if (g == 0) {
+                        reinterpret_cast<uint16_t *>(s.yes[16 * J + c])[shared ? 0 : wave] = (uint16_t)(both & valid);
+                        reinterpret_cast<uint16_t *>(s.unsure[16 * J + c])[shared ? 0 : wave] = (uint16_t)((both >> 16) & valid);
+                    }
+                }
+            }
+            __syncthreads();
+            if (wave == decider) {
+                const bool open_a = (open.a >> lane) & 1ull, open_b = (open.b >> lane) & 1ull;
+                const uint64_t there = bits_below(min(64, nseeds - s0));      // (groups that do not exist have filed nothing)
+                uint64_t ya = open_a ? row_word(s.yes, lane, 0) & there : 0ull, ua = open_a ? row_word(s.unsure, lane, 0) & there : 0ull;
+                uint64_t yb = open_b ? row_word(s.yes, 64 + lane, 0) & there : 0ull, ub = open_b ? row_word(s.unsure, 64 + lane, 0) & there : 0ull;
+                if (lane == 0) s.first_seed = s0;
+                // first fit over these seeds; a pair inside the band is settled in fp64 when it is the first candidate of its row
+                for (;;) {
+                    const int fa = (ya | ua) != 0ull ? first_bit(ya | ua) : 0, fb = (yb | ub) != 0ull ? first_bit(yb | ub) : 0;
+                    Pair64 ask;
+                    ask.a = ballot64((ua >> fa) & 1ull);
+                    ask.b = ballot64((ub >> fb) & 1ull);
+                    if ((ask.a | ask.b) == 0ull) break;
+                    const Pair64 above = settle_pairs(s, ask, fa, fb, tau, lane, wave, Kch, p.stride_n, seed_rows);
+                    if ((ask.a >> lane) & 1ull) {
+                        ua &= ~(1ull << fa);
+                        if ((above.a >> lane) & 1ull) ya |= 1ull << fa;
+                    }
+                    if ((ask.b >> lane) & 1ull) {
+                        ub &= ~(1ull << fb);
+                        if ((above.b >> lane) & 1ull) yb |= 1ull << fb;
+                    }
+                }
+                if (ya != 0ull) my_a = s0 + first_bit(ya);
+                if (yb != 0ull) my_b = s0 + first_bit(yb);
+                open.a &= ~ballot64(ya != 0ull);
+                open.b &= ~ballot64(yb != 0ull);
+                if (lane == 0) s.open = (open.a | open.b) != 0ull ? 1 : 0;
+                decided(s, lane);
+            } else {
+                settle_until_decided(s, tau, lane, wave, Kch, p.stride_n, seed_rows);
+            }
+            any_open = uniform(s.open) != 0;      // (the words are read: the next seeds' may come)
+        }
+        if (any_open) {
+#pragma unroll 1
+            for (int jj = 0; jj < 2; ++jj) {
+                const int J = jj == 0 ? 7 - wave : wave;
+                SC_FRESH_LANE;
+                if (16 * J < Rb) gram_column(s, J, 0, Rb, tau, odd, g, c);
+            }
+            __syncthreads();
+        }
+        if (wave == decider) {
+            SC_FRESH_LANE;
+            int now = nseeds;
+            if (any_open) {
+                // the rows still open are decided among themselves; the new seeds continue the chunk's numbering
+                const bool open_a = (open.a >> lane) & 1ull, open_b = (open.b >> lane) & 1ull;
+                const uint64_t below = bits_below(lane);
+                Words y, u;
+                y.a = open_a ? row_word(s.yes, lane, 0) & below & open.a : 0ull;
+                y.b0 = open_b ? row_word(s.yes, 64 + lane, 0) & open.a : 0ull;
+                y.b1 = open_b ? row_word(s.yes, 64 + lane, 1) & below & open.b : 0ull;
+                u.a = u.b0 = u.b1 = 0ull;
+                if (uniform(s.any_unsure) != 0) {
+                    u.a = open_a ? row_word(s.unsure, lane, 0) & below & open.a : 0ull;
+                    u.b0 = open_b ? row_word(s.unsure, 64 + lane, 0) & open.a : 0ull;
+                    u.b1 = open_b ? row_word(s.unsure, 64 + lane, 1) & below & open.b : 0ull;
+                }
+                Decision d;
+                if (!first_fit_fixed_point(s, y, u, open_a, open_b, tau, lane, wave, d)) {
+                    const Pair64 all = {~0ull, ~0ull};
+                    first_fit_by_seed(s, y, u, open, all, all, tau, lane, wave, d);
+                }
+                if (open_a) my_a = nseeds + rows_below(d.seeds, d.seed_a);
+                if (open_b) my_b = nseeds + rows_below(d.seeds, d.seed_b);
+                // seed list of the chunk, filed by the new seeds themselves
+                if ((d.seeds.a >> lane) & 1ull) {
+                    __hip_atomic_store(seed_rows + my_a, rb + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(seed_rinv + my_a, __float_as_int(s.rinv[lane]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (my_a < 16) {
+                        s.seed_rinv[my_a] = s.rinv[lane];
+                        s.seed_row[my_a] = rb + lane;
+                    }
+                }
+                if ((d.seeds.b >> lane) & 1ull) {
+                    __hip_atomic_store(seed_rows + my_b, rb + 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(seed_rinv + my_b, __float_as_int(s.rinv[64 + lane]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (my_b < 16) {
+                        s.seed_rinv[my_b] = s.rinv[64 + lane];
+                        s.seed_row[my_b] = rb + 64 + lane;
+                    }
+                }
+                now = nseeds + __popcll(d.seeds.a) + __popcll(d.seeds.b);
+            }
+            // cluster of every row: the caller's output, and what the sweeps for the means read back
+            if (lane < Rb) __hip_atomic_store(cid + rb + lane, my_a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (64 + lane < Rb) __hip_atomic_store(cid + rb + 64 + lane, my_b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 0) s.nseed = now;
+            if constexpr (!COUNT) file_membership(s, (lane < Rb) ? my_a : -1, (64 + lane < Rb) ? my_b : -1, 1, lane);
+            if (nx >= l) publish(now + (closed ? 1 : 0), lane);
+            // seeds and clusters are where others read them: seeds beyond the sixteenth in the next block, clusters in the workgroup of the window's slot
+            if (now > 16 || nx >= l) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            decided(s, lane);
+        } else {
+            settle_until_decided(s, tau, fresh_lane(), wave, nullptr, 0, nullptr);
+        }
+        const int known = nseeds;
+        nseeds = uniform(s.nseed);
+        SC_FRESH_LANE;
+        if (known < 16 && nseeds > known) {
+            const bool fresh = c >= known && c < nseeds;
+            const int row = fresh ? s.seed_row[c] - rb : 0;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(s.rows + row * kKeyRowBytes + (32 * ks + 8 * g) * 2);
+                if (fresh) carried[ks] = __builtin_bit_cast(bf16x8f_t, v);
+            }
+        }
+        if constexpr (!COUNT) {
+            const int steps = uniform(s.tile_steps[0]);
+#pragma unroll 1
+            for (int ks = 0; ks < 4; ++ks) {
+                if ((steps >> ks) & 1) {
+                    bf16x8f_t even, odds;
+                    column_step(s, wave, g, c, ks, even, odds);
+                    const bf16x8f_t mem = membership_operand(s.hot[0], ks, c, g);
+                    ke = __builtin_amdgcn_mfma_f32_16x16x32_bf16(even, mem, ke, 0, 0, 0);
+                    ko = __builtin_amdgcn_mfma_f32_16x16x32_bf16(odds, mem, ko, 0, 0, 0);
+                    cn = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_operand(), mem, cn, 0, 0, 0);
+                }
+            }
+        }
+        __syncthreads();      // the next block overwrites the parked keys and the words
+    }
+    if constexpr (COUNT) return;
+    else {
+        uint32_t *pub = p.published + bh * p.win_slots;
+        if (nseeds <= 16) {
+            SC_FRESH_LANE;
+            TO *key_means = reinterpret_cast<TO *>(p.rows_ws) + bh * p.N_max * kFastD;
+            if (ballot64(!all_finite(ke, ko)) != 0ull)
+                sums_by_member(Kch, p.stride_n, l, [&](int r) { return __hip_atomic_load(cid + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == c; }, wave, g, ke, ko);
+            if (c < nseeds) store_mean_through<TO>(key_means + (int64_t)(start + kMeansAt) * kFastD, c, ke, ko, cn[0], wave, g);
+        }
+        if (closed && tid == 0 && p.cluster_id) p.cluster_id[bh * p.N_max + start + l] = -1;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) __hip_atomic_store(pub + slot, kPubReady | kPubRows | (uint32_t)(nseeds + (closed ? 1 : 0)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!more) return;
+        win = next;
+    }
+    }
+    }
+
+    // ---------------- means of a long chunk
+    if constexpr (!COUNT) {
+        SC_FRESH_PARAMS;
+        const int64_t cap = p.cap;
+        TO *Kout = reinterpret_cast<TO *>(p.Kc) + bh * cap * kFastD, *Vout = reinterpret_cast<TO *>(p.Vc) + bh * cap * kFastD;
+        int32_t *counts = p.counts + bh * cap;
+        TO *key_means = reinterpret_cast<TO *>(p.rows_ws) + bh * p.N_max * kFastD;
+        const int start = w0, l = R;
+        const bool closed = (flags & kWinClosed) != 0;
+        const int32_t *cid = p.cid + bh * p.N_max + start;
+        const bf16_t *Kch = Kbh + (int64_t)start * p.stride_n;
+        // the values of the first block are on their way while the place is looked up
+        const bf16_t *Vch = Vbh + (int64_t)start * p.stride_n;
+        SC_FRESH_LANE;
+        RowRegs x;
+        load_rows(x, Vch, p.stride_n, 32 * wave, min(32, l - 32 * wave), g, c);
+        if (wave == decider) {      // what the workgroup that has decided the chunk has left
+            const bool one_xcd = ((p.B * p.Hkv) & 7) == 0;
+            u32x16_t w;
+            int polls = p.polls;
+            for (int look = 0;; ++look) {
+                load_words(w, p.published + bh * p.win_slots + slot, one_xcd && look % kVectorEvery != kVectorEvery - 1, lane);
+                if ((w[0] & kPubReady) != 0u || --polls < 0) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (lane == 0) s.nseed = (w[0] & kPubReady) != 0u ? (int)(w[0] & kPubValue) : -1;
+        }
+        int oa = -1, ob = -1;      // clusters of the block's rows
+        auto request_clusters = [&](int rb) {
+            oa = ob = -1;
+            if (wave == decider) {
+                if (rb + lane < l) oa = __hip_atomic_load(cid + rb + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (rb + 64 + lane < l) ob = __hip_atomic_load(cid + rb + 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        };
+        request_clusters(0);
+        __syncthreads();
+        const int rows = uniform(s.nseed), nseeds = rows - (closed ? 1 : 0);
+        // The place is looked up when the first sums are there: the windows just before are being decided meanwhile.
+        int64_t base = -1;
+        auto look_up = [&]() {
+            if (wave == decider) find_base(rows);
+            __syncthreads();
+            base = uniform(s.base_lo);
+            return uniform(s.base_ok) != 0;
+        };
+        if (rows < 0) {      // gave up waiting
+            if (wave == decider && lane == 0) {
+                __hip_atomic_store(p.gave_up + bh, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __hip_atomic_store(p.comp_lens + bh, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            return;
+        }
+        // kTiles tiles of sixteen clusters per sweep over the chunk: values, then keys
+        constexpr int kTiles = 2;
+        auto finish = [&](const bf16_t *X, TO *out, int o0, floatx4_t even, floatx4_t odd, const floatx4_t &n, bool sizes) {
+            const int o = o0 + c;
+            if (ballot64(!all_finite(even, odd)) != 0ull) {
+                auto member = [&](int r) { return __hip_atomic_load(cid + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == o; };
+                sums_by_member(X, p.stride_n, l, member, wave, g, even, odd);
+            }
+            if (o < nseeds && base + o < cap) {
+                store_mean<TO>(out + (base + o) * kFastD, even, odd, n[0], wave, g);
+                if (sizes && wave == 0 && g == 0) counts[base + o] = (int)(0.5f * n[0] + 0.5f);
+            }
+        };
+        const bool keys_done = nseeds <= 16;
+        bool first = true;
+#pragma unroll 1
+        for (int src = 0; src < (keys_done ? 1 : 2); ++src) {
+            const bf16_t *Xch = src == 0 ? Vch : Kch;
+#pragma unroll 1
+            for (int o0 = 0; o0 < nseeds; o0 += 16 * kTiles) {
+                floatx4_t ev[kTiles], od[kTiles], sz[kTiles];
+#pragma unroll
+                for (int t = 0; t < kTiles; ++t) ev[t] = od[t] = sz[t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+                if (!first) {
+                    load_rows(x, Xch, p.stride_n, 32 * wave, min(32, l - 32 * wave), g, c);
+                    request_clusters(0);
+                }
+                first = false;
+#pragma unroll 1
+                for (int rb = 0; rb < l; rb += kWinRows) {
+                    const int Rb = min(kWinRows, l - rb);
+                    __syncthreads();      // the block before has been read
+                    park_rows(s, x, wave, g, c);
+                    if (wave == decider) file_membership(s, oa - o0, ob - o0, kTiles, lane);
+                    const int nx = rb + kWinRows;
+                    if (nx < l) {      // on their way while this block is worked on
+                        load_rows(x, Xch, p.stride_n, nx + 32 * wave, min(32, l - nx - 32 * wave), g, c);
+                        request_clusters(nx);
+                    }
+                    __syncthreads();
+                    int steps[kTiles];
+#pragma unroll
+                    for (int t = 0; t < kTiles; ++t) steps[t] = uniform(s.tile_steps[t]);
+#pragma unroll 1
+                    for (int ks = 0; 32 * ks < Rb; ++ks) {
+                        bf16x8f_t even, odd;
+                        column_step(s, wave, g, c, ks, even, odd);
+#pragma unroll
+                        for (int t = 0; t < kTiles; ++t) {
+                            if ((steps[t] >> ks) & 1) {
+                                const bf16x8f_t mem = membership_operand(s.hot[t], ks, c, g);
+                                ev[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(even, mem, ev[t], 0, 0, 0);
+                                od[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(odd, mem, od[t], 0, 0, 0);
+                                sz[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_operand(), mem, sz[t], 0, 0, 0);
+                            }
+                        }
+                    }
+                }
+                if (base < 0) {
+                    if (!look_up()) return;
+                    if (keys_done) {
+                        // sixteen lanes a row
+                        constexpr int kPieces = (int)sizeof(TO) * kFastD / 256;
+                        const int o = tid >> 4;
+                        if (o < nseeds && base + o < cap) {
+                            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(key_means + (int64_t)(start + kMeansAt) * kFastD, (short)0, 16 * kFastD * (int)sizeof(TO), 0x00020000);
+#pragma unroll
+                            for (int e = 0; e < kPieces; ++e) {
+                                const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, o * kFastD * (int)sizeof(TO) + 16 * (16 * e + (tid & 15)), 0, 16);
+                                store16_stream(reinterpret_cast<char *>(Kout + (base + o) * kFastD) + 16 * (16 * e + (tid & 15)), make_uint4(v.x, v.y, v.z, v.w));
+                            }
+                        }
                     }
                 }
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int o = o0 + 4 * k + g;
-                    if (o < n_out && out0 + o < cap) {
-                        uint4 *kd = reinterpret_cast<uint4 *>(Kc_c + (out0 + o) * kFastD);
-                        uint4 *vd = reinterpret_cast<uint4 *>(Vc_c + (out0 + o) * kFastD);
-#pragma unroll
-                        for (int q = 0; q < NP; ++q) { store16_stream(kd + q, kk[k][q]); store16_stream(vd + q, vv[k][q]); }
-                    }
-                }
+                for (int t = 0; t < kTiles; ++t)
+                    if (o0 + 16 * t < nseeds) finish(Xch, src == 0 ? Vout : Kout, o0 + 16 * t, ev[t], od[t], sz[t], src == 0);
             }
-            for (int o = lane; o < n_out; o += kWave)
-                if (out0 + o < cap) counts_bh[out0 + o] = stmp_bh[src0 + o];
-            idx = idx_hi;
+        }
+        if (closed && base + nseeds < cap && tid < 16) {
+            // the closing delimiter is the output row behind: a copy with size 1
+            float kv[8], vv[8];
+            load8(Kbh + (int64_t)(start + l) * p.stride_n + 8 * c, kv);
+            load8(Vbh + (int64_t)(start + l) * p.stride_n + 8 * c, vv);
+            store8(Kout + (base + nseeds) * kFastD + 8 * c, kv);
+            store8(Vout + (base + nseeds) * kFastD + 8 * c, vv);
+            if (tid == 0) counts[base + nseeds] = 1;
         }
     }
 }
 
 // ------------------------------------------------------------------------------------------------
-hipError_t launch_gsc_fast(const GscParams &p, hipStream_t stream) {
-    // Single-wave workgroups, each looping over the tasks x, x + grid_x, ... of its (sequence, head).  A
-    // workgroup that takes one task is faster than one that walks several, and the host cannot know how many
-    // tasks there are: with chunks of a few dozen tokens, about one per 21 tokens per chunk of the task.  A
-    // small call gets a workgroup per expected task; a large one, where the many workgroups that find no task
-    // (a microsecond of one wave slot each) would cost more than the walking, one per two.  Shorter chunks
-    // make the workgroups loop, longer ones leave more of them without a task.
-    const int max_tasks = (p.N_max + 1 + p.chunks_per_item - 1) / p.chunks_per_item;
-    int gx = tuning().gsc_grid_x;
-    if (gx <= 0) {
-        const int64_t rows_in_call = (int64_t)p.B * p.Hkv * p.N_max;
-        const int tokens_per_wg = 21 * p.chunks_per_item * (rows_in_call <= (int64_t(1) << 19) ? 1 : 2);
-        gx = max(16, p.N_max / tokens_per_wg);
+// count: rows of every (sequence, head) after a counting probe, and what the budget search does with them
+__global__ __launch_bounds__(256) void gsc_count_kernel(GscParams p) {
+    __shared__ int s_sum[4];
+    const int64_t bh = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int32_t *cnt = p.win_count + bh * p.win_slots;
+    int sum = 0;
+    for (int i = tid; i < p.win_slots; i += 256) sum += cnt[i];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kWave);
+    if (lane == 0) s_sum[wave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        bool bad;
+        const int64_t total = (int64_t)gsc_base_rows(p, bh, bad) + s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+        const int rows = (p.num_chunks[bh / p.Hkv] > 0 && !bad && total <= p.cap) ? (int)total : -1;
+        p.comp_lens[bh] = rows;
+        if (p.budget) budget_probe_arrive(p.budget, rows, (unsigned int)(p.B * p.Hkv));
     }
-    gx = max(1, min(max_tasks, gx));
-    GscParams pc = p;
-    pc.grid_x = gx;
-    const dim3 grid2((unsigned)(2 * gx * p.Hkv * p.B));   // two passes over the tasks: long ones first
-    const dim3 grid1((unsigned)(gx * p.Hkv * p.B));
-    if (p.count_only) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, true>), grid2, dim3(kFastTaskThreads), 0, stream, pc);
-    else if (p.out_is_bf16) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, false>), grid2, dim3(kFastTaskThreads), 0, stream, pc);
-    else hipLaunchKernelGGL((gsc_compress_kernel<float, false>), grid2, dim3(kFastTaskThreads), 0, stream, pc);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (p.count_only) return launch_gsc_scan(p, stream);   // adds up the counts: comp_lens, and nothing else is wanted
-    // Up to 32k tokens the relocation adds up the cluster counts before its task itself (one round of loads
-    // per 2048 chunks; a sequence that is all delimiters costs sixteen rounds per workgroup, 0.8 ms per call);
-    // longer sequences get the scan kernel, which does the sum once per (sequence, head) whatever the
-    // number of chunks.
-    const bool inline_prefix = p.N_max <= kInlinePrefixTokens;
-    if (!inline_prefix) {
-        e = launch_gsc_scan(p, stream);
+}
+
+// ------------------------------------------------------------------------------------------------
+hipError_t launch_gsc_fast(const GscParams &p0, bool planned, hipStream_t stream) {
+    GscParams p = p0;
+    const int segments = (p.N_max + kSegRows - 1) / kSegRows;
+    p.slots_per_segment = gsc_slots_per_segment(p.N_max, p.max_chunks);
+    p.win_slots = segments * p.slots_per_segment;
+    // the workspace has two arrays of rows, 256 bytes or more per token and head each: means of long chunks at rows of their own in the one, everything
+    // else in the other (at most 1024 + 16 slots per 1024 tokens)
+    const size_t bh = (size_t)p.B * p.Hkv;
+    p.seg_rows = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(p.rows_ws) + align_up(bh * (size_t)p.N_max * kFastD * (p.out_is_bf16 ? 2 : 4), 256)) + kSegFront;
+    p.windows = reinterpret_cast<GscWindow *>(reinterpret_cast<char *>(p.seg_rows - kSegFront) + align_up((bh * (size_t)segments + kSegFront) * 8, sizeof(GscWindow)));
+    p.published = reinterpret_cast<uint32_t *>(p.windows + (size_t)p.B * p.win_slots);
+    p.win_count = reinterpret_cast<int32_t *>(p.published + bh * (size_t)p.win_slots);
+    p.longs = reinterpret_cast<GscLongs *>(p.win_count + bh * (size_t)p.win_slots);
+    p.gave_up = p.rowbase;
+    p.long_count = reinterpret_cast<int32_t *>(p.longs + (size_t)segments * p.B);
+    // Half of what is resident together, the rest goes to windows (a quarter or three quarters: the same within 1 %); where there are no long
+    // chunks, all of them leave within a microsecond.  (One for every 512 tokens instead: a long-tailed call of 8 heads x 4000 took
+    // 41 us against 32, a call without long chunks 1 us less.)
+    const size_t longest = (size_t)p.N_max / (kWinRows + 1) + 1;
+    p.ahead_per_head = p.N_max < kWinRows ? 0 : (int)max((size_t)1, min(longest, 512 / bh));
+    p.ahead_wgs = (int)(bh * p.ahead_per_head);
+    if (!planned) {
+        hipLaunchKernelGGL(gsc_plan_kernel, dim3((unsigned)(segments * p.B)), dim3(kWave), 0, stream, p);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    {
-        if (inline_prefix) {
-            if (p.base_lens) {
-                if (p.out_is_bf16) hipLaunchKernelGGL((gsc_relocate_kernel<bf16_t, true, true>), grid1, dim3(kFastTaskThreads), 0, stream, pc);
-                else hipLaunchKernelGGL((gsc_relocate_kernel<float, true, true>), grid1, dim3(kFastTaskThreads), 0, stream, pc);
-            } else {
-                if (p.out_is_bf16) hipLaunchKernelGGL((gsc_relocate_kernel<bf16_t, true, false>), grid1, dim3(kFastTaskThreads), 0, stream, pc);
-                else hipLaunchKernelGGL((gsc_relocate_kernel<float, true, false>), grid1, dim3(kFastTaskThreads), 0, stream, pc);
-            }
-        } else {
-            if (p.out_is_bf16) hipLaunchKernelGGL((gsc_relocate_kernel<bf16_t, false, false>), grid1, dim3(kFastTaskThreads), 0, stream, pc);
-            else hipLaunchKernelGGL((gsc_relocate_kernel<float, false, false>), grid1, dim3(kFastTaskThreads), 0, stream, pc);
-        }
-        e = hipGetLastError();
-    }
-    return e;
+    const dim3 grid((unsigned)((size_t)p.win_slots * bh + (p.count_only ? 0 : p.ahead_wgs)));
+    if (p.count_only) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, true>), grid, dim3(kWinThreads), 0, stream, p);
+    else if (p.out_is_bf16) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, false>), grid, dim3(kWinThreads), 0, stream, p);
+    else hipLaunchKernelGGL((gsc_compress_kernel<float, false>), grid, dim3(kWinThreads), 0, stream, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !p.count_only) return e;
+    hipLaunchKernelGGL(gsc_count_kernel, dim3((unsigned)bh), dim3(256), 0, stream, p);
+    return hipGetLastError();
 }
 
 }  // namespace sc

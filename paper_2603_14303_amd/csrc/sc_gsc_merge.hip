@@ -259,10 +259,7 @@ __global__ __launch_bounds__(256) void gsc_scan_kernel(GscParams p) {
     const int64_t bh = (int64_t)b * p.Hkv + h;
     const int M = p.num_chunks[b];
     if (M <= 0) {
-        if (tid == 0) {
-            p.comp_lens[bh] = -1;
-            if (p.budget) budget_probe_arrive(p.budget, -1, (unsigned int)(p.B * p.Hkv));
-        }
+        if (tid == 0) p.comp_lens[bh] = -1;
         return;
     }
     const int32_t *pcount_bh = p.pcount + bh * ((int64_t)p.N_max + 1);
@@ -305,9 +302,7 @@ __global__ __launch_bounds__(256) void gsc_scan_kernel(GscParams p) {
     }
     if (tid == 0) {
         rowbase_bh[M] = running;
-        const int rows = (!base_bad && running <= p.cap) ? running : -1;
-        p.comp_lens[bh] = rows;
-        if (p.budget) budget_probe_arrive(p.budget, rows, (unsigned int)(p.B * p.Hkv));
+        p.comp_lens[bh] = (!base_bad && running <= p.cap) ? running : -1;
     }
 }
 
@@ -507,13 +502,8 @@ size_t gsc_merge_workspace_bytes(int B, int Hkv, int N_max, int d, int out_elem_
     bytes += align_up(bh * ((size_t)N_max + 1) * 4, 256);    // pcount
     bytes += align_up(bh * ((size_t)N_max + 2) * 4, 256);    // rowbase
     bytes += align_up(bh * (size_t)N_max * 4, 256);          // stmp
-    bytes += 2 * align_up(bh * (size_t)N_max * (size_t)d * (size_t)out_elem_bytes, 256);   // ktmp, vtmp: provisional rows of the output type
+    bytes += 2 * align_up(bh * (size_t)N_max * (size_t)d * (size_t)out_elem_bytes, 256);   // (the fast path uses a small part of it)
     return bytes;
-}
-
-hipError_t launch_gsc_scan(const GscParams &p, hipStream_t stream) {
-    hipLaunchKernelGGL(gsc_scan_kernel, dim3(p.Hkv, p.B), dim3(256), 0, stream, p);
-    return hipGetLastError();
 }
 
 template <typename T, int D>
@@ -537,9 +527,9 @@ static hipError_t launch_typed(const GscParams &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// (the fast path addresses a window of rows with 32-bit byte offsets: 64 rows of stride_n elements)
+// (the fast path addresses the rows of a wavefront with 32-bit byte offsets, and publishes numbers of rows in 30 bits)
 bool gsc_merge_takes_fast_path(const GscMergeArgs &a) {
-    return a.in_dtype == DType::BF16 && a.d == 128 && tuning().gsc_fast_path && a.stride_n <= (int64_t(1) << 22);
+    return a.in_dtype == DType::BF16 && a.d == 128 && tuning().gsc_fast_path && a.stride_n <= (int64_t(1) << 22) && a.N_max < (1 << 30);
 }
 
 hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
@@ -580,21 +570,15 @@ hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
     w += align_up(bh * ((size_t)a.N_max + 2) * 4, 256);
     p.stmp = reinterpret_cast<int32_t *>(w);
     w += align_up(bh * (size_t)a.N_max * 4, 256);
-    p.ktmp = w;
-    w += align_up(bh * (size_t)a.N_max * (size_t)a.d * (a.out_dtype == DType::BF16 ? 2 : 4), 256);
-    p.vtmp = w;
+    p.rows_ws = w;
     p.cid = a.cluster_id ? a.cluster_id : ws_cid;
     p.cluster_id = a.cluster_id;
 
     if (gsc_merge_takes_fast_path(a)) {
         if (a.count_only) p.budget = reinterpret_cast<BudgetState *>(a.budget_state);
-        // Two chunks per task pack fuller windows and halve the workgroups; a call so small that every window
-        // finds a free wave slot at once (a stretch of tokens appended during decoding) is faster with one,
-        // because no window then waits behind another in its workgroup (256 tokens, 8 heads: 19 against 23 us).
-        const int auto_chunks = ((int64_t)a.B * a.Hkv * a.N_max <= 32768) ? 1 : 2;
-        const int want = tuning().gsc_chunks_per_task > 0 ? tuning().gsc_chunks_per_task : auto_chunks;
-        p.chunks_per_item = max(1, min(kMaxChunksPerItem, want));
-        return launch_gsc_fast(p, stream);
+        p.max_chunks = tuning().gsc_chunks_per_task;
+        p.polls = tuning().gsc_polls;
+        return launch_gsc_fast(p, a.planned, stream);
     }
 
     if (a.in_dtype == DType::BF16) {

@@ -45,7 +45,7 @@ __device__ __forceinline__ void budget_bracket_step(BudgetState *st, long long s
     if (st->rows_out) *st->rows_out = st->rows_lo;
 }
 
-// A counting probe ends in the scan kernel, one workgroup per (sequence, head); with a search attached each
+// A counting probe ends in a kernel that adds up its rows, one workgroup per (sequence, head); with a search attached each
 // of them adds its row count to the state and the last one to arrive moves the bracket, so no further
 // launch is needed between two probes.  rows < 0: the head overflowed (or has no valid chunking).  One thread.
 __device__ __forceinline__ void budget_probe_arrive(BudgetState *st, int rows, unsigned int n_heads) {
@@ -62,6 +62,9 @@ __device__ __forceinline__ void budget_probe_arrive(BudgetState *st, int rows, u
         budget_bracket_step(st, sum, bad);
     }
 }
+
+struct GscWindow;
+struct GscLongs;
 
 struct GscParams {
     const void *K, *V;
@@ -83,24 +86,34 @@ struct GscParams {
     int32_t *seedrow;     // [B, Hkv, N_max]   seed positions of a chunk that spans several blocks
     int32_t *pcount;      // [B, Hkv, N_max + 1] clusters per chunk (+ flag bit 30)
     int32_t *rowbase;     // [B, Hkv, N_max + 2] first output row of every chunk; without a scan kernel, generic path: clusters of every item
-    void *ktmp;           // [B, Hkv, N_max, d] merged keys at provisional rows (fast path)
-    void *vtmp;           // [B, Hkv, N_max, d] merged values at provisional rows (fast path)
-    int32_t *stmp;        // [B, Hkv, N_max]   cluster sizes at provisional rows (fast path)
-    int count_only;       // fast path: cluster and count only (per-chunk cluster counts and comp_lens); no values are read, no rows written
-    int chunks_per_item;
+    int32_t *stmp;        // [B, Hkv, N_max]   fast path: reciprocal norms of the seeds of a chunk that spans several blocks
+    void *rows_ws;        // [B, Hkv, N_max, d] twice, in the output type: the fast path lays out the arrays below in it
+    GscWindow *windows;   // [B, win_slots]
+    uint32_t *published;  // [B, Hkv, win_slots] rows of a window, for the windows behind it
+    unsigned long long *seg_rows;   // [B, Hkv, segments] rows of a segment's windows
+    int32_t *win_count;   // [B, Hkv, win_slots] rows of a window, counting probes
+    GscLongs *longs;      // [B, segments] slots of long chunks
+    int32_t *long_count;  // [B, segments]
+    int ahead_per_head, ahead_wgs;  // workgroups that decide long chunks first: per (sequence, head), in all
+    int32_t *gave_up;     // [B, Hkv]          a window's workgroup has stopped waiting for the ones before it
+    int slots_per_segment, win_slots;   // windows per kSegRows rows / per sequence that there is room for
+    int max_chunks;       // chunks per window, <= 0: as many as fit
+    int polls;            // looks at the windows before before a workgroup gives up
+    int count_only;       // fast path: cluster and count only (comp_lens); no values are read, no rows written
+    int chunks_per_item;  // generic path
     int short_wgs[2];     // generic path: workgroups per (sequence, head) where short chunks make items of 8 / of 16 or 32, 0: they don't (see gsc_item_shape)
-    int grid_x;           // fast path: workgroups per pass and (sequence, head) of the compress kernel
 };
 
 // rows already present in the outputs of (sequence, head) bh; an overflowed or impossible state counts as
 // a full cache, so that nothing more is written and the new length is filed as -1
-__device__ __forceinline__ int gsc_base_rows(const GscParams &p, int64_t bh, bool &bad) {
+template <typename P>
+__device__ __forceinline__ int gsc_base_rows(const P &p, int64_t bh, bool &bad) {
     const int raw = p.base_lens ? p.base_lens[bh] : 0;
     bad = raw < 0 || raw > p.cap;
     return bad ? p.cap : raw;
 }
 
-hipError_t launch_gsc_scan(const GscParams &p, hipStream_t stream);
-hipError_t launch_gsc_fast(const GscParams &p, hipStream_t stream);
+// planned: the windows of these offsets are in the workspace already (and nothing has been published since)
+hipError_t launch_gsc_fast(const GscParams &p, bool planned, hipStream_t stream);
 
 }  // namespace sc

@@ -32,7 +32,8 @@ struct GscMergeArgs {
     const int32_t *base_lens = nullptr;   // append mode: rows already in the outputs, [B, Hkv]
     const float *tau_dev = nullptr;       // threshold in device memory (overrides tau)
     bool count_only = false;              // only comp_lens is produced (bf16 / d = 128 fast path; elsewhere the full merge runs)
-    void *budget_state = nullptr;         // counting probe of the budget search: its scan kernel also moves the bracket (fast path only)
+    void *budget_state = nullptr;         // counting probe of the budget search: its last kernel also moves the bracket (fast path only)
+    bool planned = false;                 // an earlier call has cut the same offsets into windows in this workspace and not merged since (fast path only)
     void *ws;
 };
 // out_elem_bytes: element size of the merged rows the call will write (4 sizes it for either output type)
@@ -116,8 +117,9 @@ struct Tuning {
     int decode_poll_budget = 1 << 20;   // polls (about 0.3 us each) of the folding workgroup before it gives up; negative: give up at once (host-driven test of the failure path)
     int decode_mfma_min_group = 9;  // query heads per KV head from which single-row decode runs on the multi-row kernel (9 = never)
     int gsc_chunks_per_item = 0;    // generic path: chunks handled by one workgroup work item; <= 0 picks it from the rows of the call
-    int gsc_grid_x = 0;             // workgroups per pass and (sequence, KV head); <= 0 picks it from the sequence length
-    int gsc_chunks_per_task = 0;    // fast path: chunks handled by one single-wave workgroup; <= 0: 2, or 1 for a call of a few thousand tokens
+    int gsc_grid_x = 0;             // generic path: workgroups per (sequence, KV head); <= 0 picks it from the sequence length
+    int gsc_chunks_per_task = 0;    // fast path: chunks a window holds at most; <= 0: as many as fit
+    int gsc_polls = 1 << 20;        // fast path: looks (about 1 us each) at the windows before before a workgroup gives up; negative: give up at once if a look does not find them
     int gsc_fast_path = 1;          // 0 forces the generic kernels even for bf16 / d = 128
     int global_polls = 1 << 20;     // sc_gsc_merge_global: looks (about 0.5 us each) at rows another block decides before the ordered pass takes over
     int multi_block_rows = 0;       // query rows per workgroup of sc_multi_attn: 32 or 128; anything else picks it from the shape of the call

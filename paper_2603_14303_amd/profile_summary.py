@@ -101,7 +101,7 @@ def main():
          "compressed_rows %d" % j1["config"]["compressed_rows"],
          "fetch_scale %.5f" % ff, "write_scale %.5f" % wf]
     total = {}
-    for key, pats in (("gsc_compress", ("gsc_compress_kernel",)), ("gsc_scan", ("gsc_scan_kernel",)), ("gsc_relocate", ("gsc_relocate_kernel",)),
+    for key, pats in (("gsc_compress", ("gsc_compress_kernel",)), ("gsc_plan", ("gsc_plan_kernel",)),
                       ("decode", ("decode_bf16_kernel",)), ("decode_mfma", ("multi_wave_kernel",)), ("decode_mfma_combine", ("multi_attn_combine_kernel",)),
                       ("segment", ("segment_kernel",))):
         f = [(n, v) for (k, c), (n, v) in F.items() if c == "FETCH_SIZE" and all(p in k for p in pats)]
@@ -113,7 +113,7 @@ def main():
         t.append("%s_write_kib_raw %.1f   # %d dispatches" % (key, wvv, wn))
         total[key] = (fv * ff + wvv * wf) * 1024.0
         t.append("%s_bytes %d" % (key, total[key]))
-    gm = sum(total.get(k, 0.0) for k in ("gsc_compress", "gsc_scan", "gsc_relocate"))
+    gm = sum(total.get(k, 0.0) for k in ("gsc_compress", "gsc_plan"))
     t.append("gsc_merge_bytes %d   # all kernels of the call; algorithmic bytes %d" % (gm, j1["roofline"]["algorithmic_bytes"]))
     dk = total.get("decode", 0.0) or (total.get("decode_mfma", 0.0) + total.get("decode_mfma_combine", 0.0))
     t.append("decode_bytes %d   # algorithmic bytes %d" % (dk, j1["roofline_decode"]["algorithmic_bytes"]))

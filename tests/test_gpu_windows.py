@@ -1,0 +1,134 @@
+"""The edges of the bf16 / d = 128 compression: chunk lengths around the 128 rows of a window (and twice that), windows
+of more chunks than a wavefront has lanes, sequences that end just before and after the 1024 rows of a planning segment,
+long chunks with more clusters than their key means are kept for (16), head counts that do and do not tie a head to one
+XCD (a multiple of 8), non-finite values, and the bound on the waits.  Indices, sizes and lengths must equal the oracle's
+bit for bit; fp32 means within 1e-3 (fp32 sums of at most a few thousand bf16 terms: ~1e-5)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2603_14303_amd import binding as sc
+from paper_2603_14303_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import gpu_common as g
+
+D = 128
+GAPS = {
+    "window": [126, 127, 128, 129, 130],            # chunk lengths that just fit and just do not fit
+    "two windows": [255, 256, 257, 128, 384, 385],
+    "every row": [1],                               # 128 chunks in one window
+    "pairs": [1, 2, 2, 1, 3],                       # more than 64 chunks in a window
+    "long": [700, 3, 150, 40, 1025, 129, 1],        # several long chunks, across planning segments
+    "none": [],                                     # one chunk
+}
+
+
+def _case(seed, gaps, lens, heads, centres):
+    rng = np.random.default_rng(seed)
+    B, N = len(lens), max(lens)
+    mask = np.zeros((B, N), np.uint8)
+    K = np.zeros((B, heads, N, D), np.float32)
+    V = np.zeros_like(K)
+    for b, n in enumerate(lens):
+        if gaps:
+            p = np.cumsum(np.roll(np.resize(gaps, n), b)) - 1
+            mask[b, p[p < n]] = 1
+        for h in range(heads):
+            c = rng.standard_normal((centres, D))
+            K[b, h, :n] = c[rng.integers(0, centres, n)] + 0.1 * rng.standard_normal((n, D))
+            V[b, h, :n] = rng.standard_normal((n, D))
+    return mask, wl.round_to_bf16(K), wl.round_to_bf16(V)
+
+
+def _merge(mask, K, V, lens, tau, out_dtype=torch.float32):
+    off, nch, sl = g.check_segment(mask, np.array(lens, np.int32))
+    out = sc.sc_gsc_merge(g.to_device(K, True), g.to_device(V, True), off, nch, tau, seq_lens=sl, out_dtype=out_dtype,
+                          want_cluster_id=True)
+    torch.cuda.synchronize()
+    return out
+
+
+def _check_head(out, b, h, r, n):
+    Kc, Vc, counts, clens, cid = out
+    rows = r["n_rows"]
+    assert int(clens[b, h]) == rows, (b, h, int(clens[b, h]), rows)
+    assert np.array_equal(cid[b, h, :n].cpu().numpy(), r["cid"]), (b, h)
+    assert np.array_equal(counts[b, h, :rows].cpu().numpy(), r["counts"][:rows]), (b, h)
+    for got, ref in ((Kc, r["Kc"]), (Vc, r["Vc"])):
+        got, ref = got[b, h, :rows].float().cpu().numpy(), ref[:rows]
+        finite = np.isfinite(ref)
+        assert np.array_equal(np.isfinite(got), finite) and np.array_equal(np.isnan(got), np.isnan(ref)), (b, h)
+        assert np.array_equal(np.isposinf(got), np.isposinf(ref)), (b, h)
+        assert g.rowwise_err(np.where(finite, got, 0), np.where(finite, ref, 0)) <= 1e-3, (b, h)
+
+
+@pytest.mark.parametrize("per_window", [0, 1])
+@pytest.mark.parametrize("layout", list(GAPS))
+@pytest.mark.parametrize("lens,heads", [((1023, 1025), 3), ((2047, 2050, 1, 0), 2), ((3000,), 8)])
+def test_edges(layout, lens, heads, per_window):
+    mask, K, V = _case(7 + len(layout), GAPS[layout], lens, heads, 40)
+    tau = 0.6
+    old = sc.tune_get("gsc_chunks_per_task")
+    sc.tune_set("gsc_chunks_per_task", per_window)
+    try:
+        out = _merge(mask, K, V, lens, tau)
+        half = _merge(mask, K, V, lens, tau, torch.bfloat16)
+    finally:
+        sc.tune_set("gsc_chunks_per_task", old)
+    compared = 0
+    for b, n in enumerate(lens):
+        if n == 0:
+            assert (out[3][b] == 0).all() and (half[3][b] == 0).all()
+            continue
+        o = oracle.segment(mask[b], n)
+        for h in range(heads):
+            r = oracle.compress_head(K[b, h, :n], V[b, h, :n], o, tau)
+            if r["chunk_margin"].min() <= 1e-9:
+                continue                                            # a coin toss in fp64 itself
+            compared += 1
+            _check_head(out, b, h, r, n)
+            rows = r["n_rows"]
+            for i in (0, 1):                                        # bf16 rows are the RNE rounding of the fp32 ones
+                assert torch.equal(half[i][b, h, :rows], out[i][b, h, :rows].to(torch.bfloat16)), (b, h)
+    assert compared >= heads
+
+
+@pytest.mark.parametrize("layout", ["window", "pairs", "long"])
+def test_values_that_are_not_finite_stay_in_their_cluster(layout):
+    lens, heads, tau = (1500,), 2, 0.6
+    mask, K, V = _case(50, GAPS[layout], lens, heads, 6)
+    for i, x in enumerate((np.inf, np.nan, -np.inf)):
+        V[0, 0, 40 + 400 * i, 5 * i] = x
+        V[0, 1, 1499 - i, 127] = x
+    out = _merge(mask, K, V, lens, tau)
+    o = oracle.segment(mask[0], lens[0])
+    for h in range(heads):
+        r = oracle.compress_head(K[0, h], V[0, h], o, tau)
+        assert r["chunk_margin"].min() > 1e-9 and not np.isfinite(r["Vc"][:r["n_rows"]]).all()
+        _check_head(out, 0, h, r, lens[0])
+
+
+def test_a_wait_that_is_given_up_is_reported():
+    """No waiting at all: every head is either complete and right or reported by a length of -1, and every call ends."""
+    lens, heads, tau = (3000, 2500), 4, 0.6
+    mask, K, V = _case(60, GAPS["long"] + [9, 17, 40] * 40, lens, heads, 10)
+    old = sc.tune_get("gsc_polls")
+    sc.tune_set("gsc_polls", -1)
+    try:
+        out = _merge(mask, K, V, lens, tau)
+    finally:
+        sc.tune_set("gsc_polls", old)
+    again = _merge(mask, K, V, lens, tau)
+    assert (again[3] > 0).all()
+    for b, n in enumerate(lens):
+        o = oracle.segment(mask[b], n)
+        for h in range(heads):
+            r = oracle.compress_head(K[b, h, :n], V[b, h, :n], o, tau)
+            assert r["chunk_margin"].min() > 1e-9
+            _check_head(again, b, h, r, n)
+            if int(out[3][b, h]) != -1:
+                _check_head(out, b, h, r, n)
