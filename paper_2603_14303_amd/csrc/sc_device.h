@@ -14,14 +14,6 @@ constexpr int kWave = 64;
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
-// round-to-nearest-even; NaN stays NaN
-__device__ __forceinline__ uint32_t f32_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-
 // ------------------------------------------------------------------ 8-element row pieces
 // Every kernel gives a lane 8 consecutive elements of a row (16 B of bf16, 32 B of fp32), so a row
 // of d elements is covered by d/8 neighbouring lanes with fully coalesced 16-byte accesses.
@@ -93,15 +85,6 @@ __device__ __forceinline__ float row_allreduce_sum(float x) {
     if (LPR == 16) x += dpp<kDppMirror>(x);
     return x;
 }
-template <int LPR>
-__device__ __forceinline__ float row_allreduce_max(float x) {
-    x = fmaxf(x, dpp<kDppQuadXor1>(x));
-    x = fmaxf(x, dpp<kDppQuadXor2>(x));
-    x = fmaxf(x, dpp<kDppHalfMirror>(x));
-    if (LPR == 16) x = fmaxf(x, dpp<kDppMirror>(x));
-    return x;
-}
-
 // "Transposed" reduction: every lane holds LPR partial sums p[0..LPR); lane c of each LPR-lane
 // group ends up with the group-wide total of p[c].  Costs ~2*LPR adds instead of LPR*log2(LPR).
 template <int LPR>

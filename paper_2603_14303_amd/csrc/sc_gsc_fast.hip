@@ -85,9 +85,6 @@ __device__ __forceinline__ uint64_t bits_below(int x) {   // bits [0, x), 0 <= x
 }
 __device__ __forceinline__ int last_bit(uint64_t m) { return 63 - __clzll((long long)m); }      // m != 0
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
-    return ((uint64_t)(uint32_t)uniform((int)(uint32_t)(x >> 32)) << 32) | (uint32_t)uniform((int)(uint32_t)x);
-}
 __device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {   // position of the k-th set bit, 0 <= k < popcount(m)
     int pos = 0;
 #pragma unroll

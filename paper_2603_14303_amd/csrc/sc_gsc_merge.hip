@@ -273,7 +273,7 @@ __global__ __launch_bounds__(256) void gsc_scan_kernel(GscParams p) {
 #pragma unroll
         for (int k = 0; k < kItems; ++k) {
             const int m = base + tid * kItems + k;
-            v[k] = (m < M) ? (pcount_bh[m] & kPcountMask) + ((m < M - 1) ? 1 : 0) : 0;
+            v[k] = (m < M) ? pcount_bh[m] + ((m < M - 1) ? 1 : 0) : 0;
             sum += v[k];
         }
         int incl = sum;
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
             // every chunk of the items before is closed by a delimiter: its rows are its clusters and one more
             int part = 0;
             for (int i = summed_to + tid; i < item; i += kGscThreads) part += rowbase_bh[i] + C;
-            const int mine = (lane < nch) ? (pcount_bh[m0 + lane] & kPcountMask) + ((m0 + lane < M - 1) ? 1 : 0) : 0;
+            const int mine = (lane < nch) ? pcount_bh[m0 + lane] + ((m0 + lane < M - 1) ? 1 : 0) : 0;
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d, kWave);
             if (lane == 0) s_sum[wave] = part;

@@ -9,7 +9,6 @@ constexpr int kGscThreads = 256;
 constexpr int kMaxChunksPerItem = 32;
 constexpr int kInlinePrefixTokens = 32768;   // up to here the last kernel adds the cluster counts up itself: a launch less
 constexpr float kBand = 1e-4f;   // fp32 cosine error for d <= 128 is < 2e-5; inside the band -> fp64
-constexpr int kPcountMask = (1 << 30) - 1;   // low bits of a pcount entry: clusters of the chunk
 
 // State of the threshold search of sc_gsc_merge_budget (device memory, behind the merge workspace).
 struct BudgetState {
@@ -84,7 +83,7 @@ struct GscParams {
     int32_t *cid;         // [B, Hkv, N_max]   cluster index of every token (caller's buffer or workspace)
     int32_t *cluster_id;  // the caller's buffer, or NULL if not requested
     int32_t *seedrow;     // [B, Hkv, N_max]   seed positions of a chunk that spans several blocks
-    int32_t *pcount;      // [B, Hkv, N_max + 1] clusters per chunk (+ flag bit 30)
+    int32_t *pcount;      // [B, Hkv, N_max + 1] generic path: clusters per chunk
     int32_t *rowbase;     // [B, Hkv, N_max + 2] first output row of every chunk; without a scan kernel, generic path: clusters of every item
     int32_t *stmp;        // [B, Hkv, N_max]   fast path: reciprocal norms of the seeds of a chunk that spans several blocks
     void *rows_ws;        // [B, Hkv, N_max, d] twice, in the output type: the fast path lays out the arrays below in it
