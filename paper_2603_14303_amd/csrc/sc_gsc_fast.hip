@@ -1498,7 +1498,7 @@ hipError_t launch_gsc_fast(const GscParams &p0, bool planned, hipStream_t stream
     p.long_count = reinterpret_cast<int32_t *>(p.longs + (size_t)segments * p.B);
     // Half of what is resident together, the rest goes to windows (a quarter or three quarters: the same within 1 %); where there are no long
     // chunks, all of them leave within a microsecond.  (One for every 512 tokens instead: a long-tailed call of 8 heads x 4000 took
-    // 41 us against 32, a call without long chunks 1 us less.)
+    // 41 us against 32.)
     const size_t longest = (size_t)p.N_max / (kWinRows + 1) + 1;
     p.ahead_per_head = p.N_max < kWinRows ? 0 : (int)max((size_t)1, min(longest, 512 / bh));
     p.ahead_wgs = (int)(bh * p.ahead_per_head);
