@@ -735,7 +735,8 @@ __device__ __forceinline__ void file_membership(CompressLds &s, int out_a, int o
             s.tile_steps[t] = (((uint32_t)ma != 0u) ? 1 : 0) | (((ma >> 32) != 0ull) ? 2 : 0) | (((uint32_t)mb != 0u) ? 4 : 0) | (((mb >> 32) != 0ull) ? 8 : 0);
     }
 }
-// the lane's bit of its rows, turned to bit 14 of either half of a word: bf16 2.0.  (The sums are twice what they stand for, exactly.)
+// the lane's bit of its rows, turned to bit 14 of either half of a word: bf16 2.0.  (The sums are twice what they stand for, exactly, as long as
+// they are finite; see all_finite.)
 __device__ __forceinline__ bf16x8f_t membership_operand(const uint16_t *hot, int ks, int c, int g) {
     uint32_t aw[4];
 #pragma unroll
@@ -749,24 +750,25 @@ __device__ __forceinline__ bf16x8f_t membership_operand(const uint16_t *hot, int
 __device__ __forceinline__ bf16x8f_t ones_operand() {
     return __builtin_bit_cast(bf16x8f_t, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
 }
-// a zero row times an infinity is not a number: sums that are not finite are taken again without the other clusters' rows
+// A zero row times an infinity is not a number, and twice a sum of 2^127 or more is an infinity: sums that are not finite are taken again,
+// once instead of twice and without the other clusters' rows.
 __device__ __forceinline__ bool all_finite(const floatx4_t &a, const floatx4_t &b) {
     float z = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) z = fmaf(a[i], 0.f, fmaf(b[i], 0.f, z));
     return z == 0.f;
 }
-// eight columns of one output row, from twice the sums and twice the size: 1/size is exact for powers of two, 1 ulp otherwise; a row of
-// size 1 is passed on unchanged
-__device__ __forceinline__ void scale_mean(float (&v)[8], const floatx4_t &even, const floatx4_t &odd, float size2) {
-    const float inv = (size2 > 3.f) ? __builtin_amdgcn_rcpf(size2) : 0.5f;
+// what twice the sums are multiplied with, from twice the size: 1/size is exact for powers of two, 1 ulp otherwise; a row of size 1 is passed
+// on unchanged.  (Sums taken once: twice that.)
+__device__ __forceinline__ float mean_scale(float size2) { return (size2 > 3.f) ? __builtin_amdgcn_rcpf(size2) : 0.5f; }
+__device__ __forceinline__ void scale_mean(float (&v)[8], const floatx4_t &even, const floatx4_t &odd, float scale) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { v[2 * i] = even[i] * inv; v[2 * i + 1] = odd[i] * inv; }
+    for (int i = 0; i < 4; ++i) { v[2 * i] = even[i] * scale; v[2 * i + 1] = odd[i] * scale; }
 }
 template <typename TO>
-__device__ __forceinline__ void store_mean(TO *row, const floatx4_t &even, const floatx4_t &odd, float size2, int wave, int g) {
+__device__ __forceinline__ void store_mean(TO *row, const floatx4_t &even, const floatx4_t &odd, float scale, int wave, int g) {
     float v[8];
-    scale_mean(v, even, odd, size2);
+    scale_mean(v, even, odd, scale);
     TO *at = row + 32 * wave + 8 * g;
     if constexpr (sizeof(TO) == 2) {
         store16_stream(at, make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])));
@@ -777,10 +779,10 @@ __device__ __forceinline__ void store_mean(TO *row, const floatx4_t &even, const
 }
 // to row c of sixteen at `rows` (uniform), written through (sc1) to where another XCD's loads find it
 template <typename TO>
-__device__ __forceinline__ void store_mean_through(TO *rows, int c, const floatx4_t &even, const floatx4_t &odd, float size2, int wave, int g) {
+__device__ __forceinline__ void store_mean_through(TO *rows, int c, const floatx4_t &even, const floatx4_t &odd, float scale, int wave, int g) {
     constexpr int kThrough = 16;
     float v[8];
-    scale_mean(v, even, odd, size2);
+    scale_mean(v, even, odd, scale);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(rows, (short)0, 16 * kFastD * (int)sizeof(TO), 0x00020000);
     const int off = (c * kFastD + 32 * wave + 8 * g) * (int)sizeof(TO);
     if constexpr (sizeof(TO) == 2) {
@@ -793,7 +795,7 @@ __device__ __forceinline__ void store_mean_through(TO *rows, int c, const floatx
         __builtin_amdgcn_raw_buffer_store_b128(t1, rs, off + 16, 0, kThrough);
     }
 }
-// the same sums member by member from memory, rows [0, rows) at X with output rows given by `member` (rare: see all_finite)
+// the sums, once, member by member from memory, rows [0, rows) at X with output rows given by `member` (rare: see all_finite)
 template <typename F>
 __device__ __forceinline__ void sums_by_member(const bf16_t *X, int64_t stride_n, int rows, F member, int wave, int g, floatx4_t &even, floatx4_t &odd) {
     even = odd = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -803,7 +805,7 @@ __device__ __forceinline__ void sums_by_member(const bf16_t *X, int64_t stride_n
             float x[8];
             load8(X + (int64_t)r * stride_n + 32 * wave + 8 * g, x);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { even[i] += 2.f * x[2 * i]; odd[i] += 2.f * x[2 * i + 1]; }
+            for (int i = 0; i < 4; ++i) { even[i] += x[2 * i]; odd[i] += x[2 * i + 1]; }
         }
     }
 }
@@ -1056,14 +1058,16 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                     }
                 }
                 const int o = 16 * ot + c;
+                float scale = mean_scale(cn[0]);
                 if (ballot64(!all_finite(ve, vo) || (odd_keys && !all_finite(ke, ko))) != 0ull) {
+                    scale *= 2.f;
                     auto member = [&](int r) { return ((s.hot[ot][r] >> c) & 1) != 0; };
                     sums_by_member(Kbh + (int64_t)w0 * p.stride_n, p.stride_n, R, member, wave, g, ke, ko);
                     sums_by_member(Vbh + (int64_t)w0 * p.stride_n, p.stride_n, R, member, wave, g, ve, vo);
                 }
                 if (o < nseed && base + o < cap) {
-                    store_mean<TO>(Kat + o * kFastD, ke, ko, cn[0], wave, g);
-                    store_mean<TO>(Vat + o * kFastD, ve, vo, cn[0], wave, g);
+                    store_mean<TO>(Kat + o * kFastD, ke, ko, scale, wave, g);
+                    store_mean<TO>(Vat + o * kFastD, ve, vo, scale, wave, g);
                     if (wave == 0 && g == 0) counts[base + o] = (int)(0.5f * cn[0] + 0.5f);
                 }
             }
@@ -1299,9 +1303,12 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         if (nseeds <= 16) {
             SC_FRESH_LANE;
             TO *key_means = reinterpret_cast<TO *>(p.rows_ws) + bh * p.N_max * kFastD;
-            if (ballot64(!all_finite(ke, ko)) != 0ull)
+            float scale = mean_scale(cn[0]);
+            if (ballot64(!all_finite(ke, ko)) != 0ull) {
+                scale *= 2.f;
                 sums_by_member(Kch, p.stride_n, l, [&](int r) { return __hip_atomic_load(cid + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == c; }, wave, g, ke, ko);
-            if (c < nseeds) store_mean_through<TO>(key_means + (int64_t)(start + kMeansAt) * kFastD, c, ke, ko, cn[0], wave, g);
+            }
+            if (c < nseeds) store_mean_through<TO>(key_means + (int64_t)(start + kMeansAt) * kFastD, c, ke, ko, scale, wave, g);
         }
         if (closed && tid == 0 && p.cluster_id) p.cluster_id[bh * p.N_max + start + l] = -1;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1371,12 +1378,14 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         constexpr int kTiles = 2;
         auto finish = [&](const bf16_t *X, TO *out, int o0, floatx4_t even, floatx4_t odd, const floatx4_t &n, bool sizes) {
             const int o = o0 + c;
+            float scale = mean_scale(n[0]);
             if (ballot64(!all_finite(even, odd)) != 0ull) {
+                scale *= 2.f;
                 auto member = [&](int r) { return __hip_atomic_load(cid + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == o; };
                 sums_by_member(X, p.stride_n, l, member, wave, g, even, odd);
             }
             if (o < nseeds && base + o < cap) {
-                store_mean<TO>(out + (base + o) * kFastD, even, odd, n[0], wave, g);
+                store_mean<TO>(out + (base + o) * kFastD, even, odd, scale, wave, g);
                 if (sizes && wave == 0 && g == 0) counts[base + o] = (int)(0.5f * n[0] + 0.5f);
             }
         };

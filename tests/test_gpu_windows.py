@@ -1,7 +1,7 @@
 """The edges of the bf16 / d = 128 compression: chunk lengths around the 128 rows of a window (and twice that), windows
 of more chunks than a wavefront has lanes, sequences that end just before and after the 1024 rows of a planning segment,
 long chunks with more clusters than their key means are kept for (16), head counts that do and do not tie a head to one
-XCD (a multiple of 8), non-finite values, and the bound on the waits.  Indices, sizes and lengths must equal the oracle's
+XCD (a multiple of 8), non-finite and very large values, and the bound on the waits.  Indices, sizes and lengths must equal the oracle's
 bit for bit; fp32 means within 1e-3 (fp32 sums of at most a few thousand bf16 terms: ~1e-5)."""
 import numpy as np
 import pytest
@@ -110,6 +110,44 @@ def test_values_that_are_not_finite_stay_in_their_cluster(layout):
         r = oracle.compress_head(K[0, h], V[0, h], o, tau)
         assert r["chunk_margin"].min() > 1e-9 and not np.isfinite(r["Vc"][:r["n_rows"]]).all()
         _check_head(out, 0, h, r, lens[0])
+
+
+@pytest.mark.parametrize("centres", [6, 40])                       # up to sixteen clusters in a long chunk, and more
+@pytest.mark.parametrize("layout", ["window", "pairs", "long"])
+def test_values_near_the_largest_finite_one(layout, centres):
+    """Every third cluster or delimiter is scaled until its sums lie up to 2^128, and some rows of size 1 hold the largest bf16
+    value itself: means must stay finite and as exact as others (keys and values, the cosines are not changed by the scale)."""
+    n, heads, tau = 1500, 2, 0.6
+    mask, K, V = _case(70 + centres, GAPS[layout], (n,), heads, centres)
+    K, V = np.clip(K, -3.875, 3.875), np.clip(V, -3.875, 3.875)
+    top = float(torch.finfo(torch.bfloat16).max)
+    o = oracle.segment(mask[0], n)
+    expected = []
+    for h in range(heads):
+        r = oracle.compress_head(K[0, h], V[0, h], o, tau)
+        assert r["chunk_margin"].min() > 1e-9
+        chunk = np.searchsorted(o, np.arange(n), side="right") - 1
+        group = np.unique(chunk * (n + 1) + np.where(r["cid"] < 0, n, r["cid"]), return_inverse=True)[1]
+        scale = np.exp2(126 - np.ceil(np.log2(np.bincount(group))))[group]
+        scaled = group % 3 == 0
+        assert scaled.any() and not scaled.all()
+        for x in (K, V):
+            x[0, h, scaled] *= scale[scaled, None].astype(np.float32)
+            assert np.abs(x[0, h]).max() >= 2.0 ** 127
+        single = np.flatnonzero((np.bincount(group)[group] == 1) & ~scaled)
+        V[0, h, single[::2], 3] = top
+        V[0, h, single[1::2], 64] = -top
+        expected.append(oracle.compress_head(K[0, h], V[0, h], o, tau))
+        assert np.isfinite(expected[h]["Kc"]).all() and np.isfinite(expected[h]["Vc"]).all()
+    out = _merge(mask, K, V, (n,), tau)
+    half = _merge(mask, K, V, (n,), tau, torch.bfloat16)
+    for h in range(heads):
+        r = expected[h]
+        _check_head(out, 0, h, r, n)
+        alone = np.flatnonzero(r["counts"][:r["n_rows"]] == 1)
+        for i, name in ((0, "Kc"), (1, "Vc")):
+            assert np.array_equal(out[i][0, h].cpu().numpy()[alone].astype(np.float64), r[name][alone]), (h, name)
+            assert torch.equal(half[i][0, h, :r["n_rows"]], out[i][0, h, :r["n_rows"]].to(torch.bfloat16)), (h, name)
 
 
 def test_a_wait_that_is_given_up_is_reported():
