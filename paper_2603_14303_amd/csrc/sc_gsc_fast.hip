@@ -24,6 +24,7 @@
 // 8 x 131072 178 -> 165, 32 sequences x 8 heads x 4096 327 -> 265; tau inside the band, 4 layers x 8 x 32768: 291 -> 190 a layer.
 #include "sc_device.h"
 #include "sc_gsc_params.h"
+#include "sc_gsc_words.h"
 #include "sc_host.h"
 
 namespace sc {
@@ -59,14 +60,8 @@ constexpr int kWinLong = 1;      // one chunk with more than kWinRows rows
 constexpr int kWinLast = 2;      // the last window of its sequence
 constexpr int kWinClosed = 4;    // kWinLong: a delimiter follows
 
-// What a window's workgroup publishes as soon as it knows it: one word per (sequence, head) and slot with the number of rows
-// (kPubReady: a long chunk, and the clusters of its rows have arrived), and the rows added to a 64-bit word per (sequence, head) and
-// segment: rows of its windows in the low half, windows that have not added theirs in the high half; once all before are known
-// too, it holds kSegAll and the rows up to its end instead.
-constexpr uint32_t kPubRows = 1u << 30, kPubReady = 1u << 31;
-constexpr uint32_t kPubValue = (1u << 30) - 1u;
-constexpr unsigned long long kSegAll = 1ull << 63;
-constexpr int kSegFront = 8;                   // words before the segment words: they are read eight at a time, down to the first
+// What a window's workgroup publishes as soon as it knows it: its rows, in its own word and added to those of its segment (sc_gsc_words.h).
+constexpr int kSegFront = 8;                   // room before the segments' words: those of eight are read at a time, down to the first
 
 // Windows that can start in `rows` consecutive rows: two neighbours hold more than kWinRows rows together.  An odd number: the last slots of
 // every segment stay empty, and workgroups go to the shader engines in turn (with sixteen slots two of four engines got half
@@ -273,7 +268,7 @@ __global__ __launch_bounds__(kWave) void gsc_plan_kernel(GscParams p) {
             p.published[at + k] = 0u;
             if (p.count_only) p.win_count[at + k] = 0;
         }
-        if ((lane & 15) == 0) p.seg_rows[(bh0 + h) * segments + seg] = (unsigned long long)used << 32;
+        if ((lane & 15) == 0) p.segments[(bh0 + h) * segments + seg] = GscSegment{segment_start(used), 0u};
     }
     if (seg == 0)
         for (int h = lane; h < p.Hkv; h += kWave) p.gave_up[bh0 + h] = 0;
@@ -649,7 +644,7 @@ __device__ __forceinline__ void load_words(u32x16_t &w, const void *at, bool sca
         for (int k = 0; k < 16; ++k) w[k] = (uint32_t)__builtin_amdgcn_readlane((int)v, k);
     }
 }
-__device__ __forceinline__ bool rows_before(const uint32_t *published, unsigned long long *seg_rows, int S, int slot, bool one_xcd, int &polls, int lane, int &rows) {
+__device__ __forceinline__ bool rows_before(const uint32_t *published, GscSegment *segments, int bits, int S, int slot, bool one_xcd, int &polls, int lane, int &rows) {
     const int seg = slot / S, own = slot - seg * S;
     int sum = 0, look = 0;
     auto again = [&]() {
@@ -681,16 +676,16 @@ __device__ __forceinline__ bool rows_before(const uint32_t *published, unsigned 
     for (int top = seg; !known && top > 0; top -= 8) {      // segments top - 8 .. top - 1
         u32x16_t w;
         for (;;) {
-            load_words(w, seg_rows + top - 8, one_xcd && look % kVectorEvery != kVectorEvery - 1, lane);
+            load_words(w, segments + top - 8, one_xcd && look % kVectorEvery != kVectorEvery - 1, lane);
             bool there = true;
             int part = 0;
             known = false;
 #pragma unroll
             for (int k = 7; k >= 0; --k) {
                 if (!known && top - 8 + k >= 0) {
-                    there = there && ((w[2 * k + 1] >> 31) != 0u || w[2 * k + 1] == 0u);
-                    part += (int)w[2 * k];
-                    known = (w[2 * k + 1] >> 31) != 0u;
+                    known = (w[2 * k + 1] & kPubRows) != 0u;
+                    there = there && (known || segment_complete(w[2 * k], bits));
+                    part += known ? (int)(w[2 * k + 1] & kPubValue) : segment_rows(w[2 * k], bits);
                 }
             }
             if (there) { before += part; break; }
@@ -699,7 +694,7 @@ __device__ __forceinline__ bool rows_before(const uint32_t *published, unsigned 
     }
     // the end of the segment before is known now
     if (own == 0 && seg > 0 && lane == 0)
-        __hip_atomic_store(seg_rows + seg - 1, kSegAll | (unsigned long long)(uint32_t)before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&segments[seg - 1].upto, kPubRows | (uint32_t)before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     rows = before + sum;
     return true;
 }
@@ -902,9 +897,9 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             else {
                 const int S = p.slots_per_segment;
                 uint32_t *pub = p.published + bh * p.win_slots;
-                unsigned long long *seg_rows = p.seg_rows + bh * (p.win_slots / S);
+                GscSegment *segments = p.segments + bh * (p.win_slots / S);
                 __hip_atomic_store(pub + slot, kPubRows | (uint32_t)rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_add(seg_rows + slot / S, (unsigned long long)(uint32_t)rows - (1ull << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(&segments[slot / S].part, segment_added(rows, p.seg_bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     };
@@ -915,9 +910,9 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         const int S = p.slots_per_segment;
         const int64_t cap = p.cap;
         uint32_t *pub = p.published + bh * p.win_slots;
-        unsigned long long *seg_rows = p.seg_rows + bh * (p.win_slots / S);
+        GscSegment *segments = p.segments + bh * (p.win_slots / S);
         int before = 0, polls = p.polls;
-        const bool ok = rows_before(pub, seg_rows, S, slot, ((p.B * p.Hkv) & 7) == 0, polls, lane, before);
+        const bool ok = rows_before(pub, segments, p.seg_bits, S, slot, ((p.B * p.Hkv) & 7) == 0, polls, lane, before);
         bool bad;
         const int held = gsc_base_rows(p, bh, bad);
         if (lane == 0) {
@@ -1490,16 +1485,20 @@ __global__ __launch_bounds__(256) void gsc_count_kernel(GscParams p) {
 }
 
 // ------------------------------------------------------------------------------------------------
+bool gsc_fast_holds(int N_max) { return segment_holds(gsc_slots_per_segment(N_max, 0), N_max); }
+
 hipError_t launch_gsc_fast(const GscParams &p0, bool planned, hipStream_t stream) {
     GscParams p = p0;
     const int segments = (p.N_max + kSegRows - 1) / kSegRows;
+    if (!segment_holds(gsc_slots_per_segment(p.N_max, p.max_chunks), p.N_max)) p.max_chunks = 0;
     p.slots_per_segment = gsc_slots_per_segment(p.N_max, p.max_chunks);
+    p.seg_bits = segment_bits(p.slots_per_segment);
     p.win_slots = segments * p.slots_per_segment;
     // the workspace has two arrays of rows, 256 bytes or more per token and head each: means of long chunks at rows of their own in the one, everything
     // else in the other (at most 1024 + 16 slots per 1024 tokens)
     const size_t bh = (size_t)p.B * p.Hkv;
-    p.seg_rows = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(p.rows_ws) + align_up(bh * (size_t)p.N_max * kFastD * (p.out_is_bf16 ? 2 : 4), 256)) + kSegFront;
-    p.windows = reinterpret_cast<GscWindow *>(reinterpret_cast<char *>(p.seg_rows - kSegFront) + align_up((bh * (size_t)segments + kSegFront) * 8, sizeof(GscWindow)));
+    p.segments = reinterpret_cast<GscSegment *>(reinterpret_cast<char *>(p.rows_ws) + align_up(bh * (size_t)p.N_max * kFastD * (p.out_is_bf16 ? 2 : 4), 256)) + kSegFront;
+    p.windows = reinterpret_cast<GscWindow *>(reinterpret_cast<char *>(p.segments - kSegFront) + align_up((bh * (size_t)segments + kSegFront) * sizeof(GscSegment), sizeof(GscWindow)));
     p.published = reinterpret_cast<uint32_t *>(p.windows + (size_t)p.B * p.win_slots);
     p.win_count = reinterpret_cast<int32_t *>(p.published + bh * (size_t)p.win_slots);
     p.longs = reinterpret_cast<GscLongs *>(p.win_count + bh * (size_t)p.win_slots);

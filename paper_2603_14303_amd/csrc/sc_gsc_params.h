@@ -64,6 +64,7 @@ __device__ __forceinline__ void budget_probe_arrive(BudgetState *st, int rows, u
 
 struct GscWindow;
 struct GscLongs;
+struct GscSegment;
 
 struct GscParams {
     const void *K, *V;
@@ -89,12 +90,13 @@ struct GscParams {
     void *rows_ws;        // [B, Hkv, N_max, d] twice, in the output type: the fast path lays out the arrays below in it
     GscWindow *windows;   // [B, win_slots]
     uint32_t *published;  // [B, Hkv, win_slots] rows of a window, for the windows behind it
-    unsigned long long *seg_rows;   // [B, Hkv, segments] rows of a segment's windows
+    GscSegment *segments; // [B, Hkv, segments] rows of a segment's windows
     int32_t *win_count;   // [B, Hkv, win_slots] rows of a window, counting probes
     GscLongs *longs;      // [B, segments] slots of long chunks
     int32_t *long_count;  // [B, segments]
     int ahead_per_head, ahead_wgs;  // workgroups that decide long chunks first: per (sequence, head), in all
     int32_t *gave_up;     // [B, Hkv]          a window's workgroup has stopped waiting for the ones before it
+    int seg_bits;         // of a segment's word that count windows
     int slots_per_segment, win_slots;   // windows per kSegRows rows / per sequence that there is room for
     int max_chunks;       // chunks per window, <= 0: as many as fit
     int polls;            // looks at the windows before before a workgroup gives up
@@ -112,6 +114,7 @@ __device__ __forceinline__ int gsc_base_rows(const P &p, int64_t bh, bool &bad) 
     return bad ? p.cap : raw;
 }
 
+bool gsc_fast_holds(int N_max);   // sequences of that many tokens fit its words
 // planned: the windows of these offsets are in the workspace already (and nothing has been published since)
 hipError_t launch_gsc_fast(const GscParams &p, bool planned, hipStream_t stream);
 
