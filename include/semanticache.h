@@ -380,8 +380,9 @@ sc_status sc_stream_read_probe(const void *src, size_t bytes, void *sink, void *
  *   "gsc_fast_path"        0 forces the generic kernels even for bf16 / d = 128
  *   "gsc_chunks_per_task"  fast path: chunks that a window of 128 rows holds at most; <= 0 (the default) = as
  *                          many as fit
- *   "gsc_polls"            fast path: looks of a window at the row counts before it until it gives up and
- *                          comp_lens becomes -1 (default 2^20, a second or so); negative: give up at the first
+ *   "gsc_polls"            fast path: looks of a window at the row counts before it until it leaves its rows to the
+ *                          workgroups of those counts (default 2^16, some 0.05 s; -1: at the first that does not
+ *                          find them, below: without looking; the outcome is the same)
  *   "gsc_chunks_per_item"  generic path: chunks per work item; <= 0 = chosen from B * Hkv * N_max and
  *                          from the mean chunk length of the sequence
  *   "gsc_grid_x"           generic path: workgroups per pass and (sequence, KV head); <= 0 = chosen from N_max

@@ -265,13 +265,13 @@ __global__ __launch_bounds__(kWave) void gsc_plan_kernel(GscParams p) {
     for (int h = lane >> 4; h < p.Hkv; h += 4) {
         const int64_t at = (bh0 + h) * slots + (int64_t)seg * S;
         for (int k = lane & 15; k < S; k += 16) {
-            p.published[at + k] = 0u;
+            p.published[at + k] = k < used ? 0u : kPubRows;
             if (p.count_only) p.win_count[at + k] = 0;
         }
         if ((lane & 15) == 0) p.segments[(bh0 + h) * segments + seg] = GscSegment{segment_start(used), 0u};
     }
     if (seg == 0)
-        for (int h = lane; h < p.Hkv; h += kWave) p.gave_up[bh0 + h] = 0;
+        for (int h = lane; h < p.Hkv; h += kWave) p.head_state[bh0 + h] = 0u;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -298,6 +298,7 @@ struct CompressLds {
     unsigned char odd_norms[kWinWaves];  // wavefront w's rows hold one without a usable norm
     int pairs, first_seed;               // pairs the deciding wavefront wants settled (0: it has decided); seed that the list counts from
     int nseed, open;                     // outcome: seeds; a long chunk: rows still open
+    int any_left, left_from, left_slot;  // windows of the head were left; where the search for them goes on, and the one found
 };
 static_assert(sizeof(CompressLds) <= 39680, "four workgroups per compute unit");
 
@@ -629,11 +630,14 @@ __device__ __forceinline__ int rows_below(const Pair64 &set, int row) {      // 
 
 // ------------------------------------------------------------------------------------------------
 // Rows before a window: those of the windows before it in its segment, and of the segments before.  Workgroups are dispatched in slot order, so the
-// ones waited for are running or done; the wait is bounded all the same.
+// ones waited for are running or done, but for other calls: every XCD dispatches for itself, and with the heads of two calls spread over XCDs
+// each call's next window can find an XCD full of the other's that wait.  A long chunk can take seconds to decide, too.  So the wait is
+// bounded, and a window whose workgroup stops waiting is left to others (next_left).
 // One wavefront asks through the scalar cache (glc: past it, from L2): a vector load would queue behind the rows that the compute unit's other
 // wavefronts have asked for, 3 us where this takes less than one.  Where the windows of a head are spread over XCDs (their number is no multiple
 // of eight), and every kVectorEvery-th time elsewhere, the look goes the other way, for words that another XCD's stores have changed in memory.
 constexpr int kVectorEvery = 8;
+constexpr int kSettledPolls = 1 << 20;       // where everything that is asked for has been published already
 typedef uint32_t u32x16_t __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ void load_words(u32x16_t &w, const void *at, bool scalar, int lane) {      // `at`: uniform
     if (scalar) {
@@ -890,7 +894,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
     const bf16_t *Vbh = reinterpret_cast<const bf16_t *>(p.V) + b * p.stride_b + h * p.stride_h;
     const float tau = p.tau_dev ? *p.tau_dev : p.tau;
     // the window's rows are known: tell the windows behind it
-    auto publish = [&](int rows, int lane) {      // one wavefront
+    auto publish = [&](int rows, bool is_long, int lane) {      // one wavefront
         SC_FRESH_PARAMS;
         if (lane == 0) {
             if constexpr (COUNT) p.win_count[bh * p.win_slots + slot] = rows;
@@ -898,34 +902,36 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                 const int S = p.slots_per_segment;
                 uint32_t *pub = p.published + bh * p.win_slots;
                 GscSegment *segments = p.segments + bh * (p.win_slots / S);
-                __hip_atomic_store(pub + slot, kPubRows | (uint32_t)rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (is_long) __hip_atomic_fetch_or(pub + slot, kPubRows | (uint32_t)rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (its slot's workgroup may have left it)
+                else __hip_atomic_store(pub + slot, kPubRows | (uint32_t)rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_fetch_add(&segments[slot / S].part, segment_added(rows, p.seg_bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     };
-    // first output row of the window, for all wavefronts (between two barriers)
-    auto find_base = [&](int rows) {      // one wavefront
+    // First output row of the window, for all wavefronts (between two barriers).  left: somebody else's window, the rows before are published; should
+    // they not arrive all the same, the head ends with a length of -1.
+    auto find_base = [&](int rows, bool left) {      // one wavefront
         SC_FRESH_LANE;
         SC_FRESH_PARAMS;
         const int S = p.slots_per_segment;
         const int64_t cap = p.cap;
         uint32_t *pub = p.published + bh * p.win_slots;
         GscSegment *segments = p.segments + bh * (p.win_slots / S);
-        int before = 0, polls = p.polls;
-        const bool ok = rows_before(pub, segments, p.seg_bits, S, slot, ((p.B * p.Hkv) & 7) == 0, polls, lane, before);
+        int before = 0, polls = left ? kSettledPolls : p.polls;
+        const bool ok = polls >= -1 && rows_before(pub, segments, p.seg_bits, S, slot, ((p.B * p.Hkv) & 7) == 0, polls, lane, before);
         bool bad;
         const int held = gsc_base_rows(p, bh, bad);
         if (lane == 0) {
             const int64_t total = (int64_t)held + before + rows;
-            if (flags & kWinLast) {
-                // comp_lens is -1 in the end if any window of the head gave up, whatever the order
-                __hip_atomic_store(p.comp_lens + bh, (!bad && ok && total <= cap) ? (int32_t)total : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (ok && (flags & kWinLast)) {
+                // (-1 in the end if the rows before any window of the head did not arrive, whatever the order)
+                __hip_atomic_store(p.comp_lens + bh, (!bad && total <= cap) ? (int32_t)total : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                if (__hip_atomic_load(p.gave_up + bh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+                if ((__hip_atomic_load(p.head_state + bh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kHeadFailed) != 0u)
                     __hip_atomic_store(p.comp_lens + bh, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (!ok) {
-                __hip_atomic_store(p.gave_up + bh, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!ok && left) {
+                __hip_atomic_fetch_or(p.head_state + bh, kHeadFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __hip_atomic_store(p.comp_lens + bh, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -934,7 +940,75 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         }
     };
 
+    // Windows that were left.  Their workgroups have filed what the merged rows need (whole chunks: the output row of every row, in the workspace),
+    // marked them in their words and set kHeadLeft; then they search, and so does every workgroup of the head that finds kHeadLeft set after
+    // what it has published has arrived.  A search takes the slots in order up to the first whose rows are not published, clears the marks that it finds
+    // (a long chunk's not before its clusters have arrived, too) and finishes those windows.  So the last of the windows before a left one to publish
+    // finds it, if no other has, and every window is finished once, by a workgroup that finds the rows of all before it published.  (The look costs
+    // 0.2 to 1 %: 8 heads x 32768 49.1 us and 49.3, x 131072 165.0 and 166.9.  The value that the addition to the segment's rows can return
+    // would say the same, but its returning form costs 1.5 to 2 %.)
+    // The next window to finish goes to `win`, its rows to s.nseed; false: none.  For all wavefronts.
+    [[maybe_unused]] auto next_left = [&](bool mark) {
+        __syncthreads();
+        if (threadIdx.x < kWave) {
+            SC_FRESH_PARAMS;
+            const int lane = fresh_lane(), slots = p.win_slots;
+            uint32_t *pub = p.published + bh * slots;
+            if (mark) {
+                if (lane == 0) __hip_atomic_fetch_or(pub + win.slot, kPubLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                if (lane == 0) __hip_atomic_fetch_or(p.head_state + bh, kHeadLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            int found = -1, k0 = uniform(s.left_from);
+            uint32_t word = 0u;
+            for (; k0 < slots; k0 += kWave) {
+                uint32_t w = kPubRows;
+                bool mine = false;
+                if (k0 + lane < slots) {
+                    w = __hip_atomic_load(pub + k0 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    mine = (w & kPubLeft) != 0u && ((w & kPubReady) != 0u || (p.windows[(int64_t)b * slots + k0 + lane].flags & kWinLong) == 0);
+                }
+                const uint64_t missing = ballot64((w & kPubRows) == 0u);
+                uint64_t marked = ballot64(mine);
+                if (missing != 0ull) marked &= bits_below(first_bit(missing));
+                for (; marked != 0ull && found < 0; marked &= marked - 1ull) {
+                    const int at = k0 + first_bit(marked);
+                    if (lane == 0) word = __hip_atomic_fetch_and(pub + at, ~kPubLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    word = (uint32_t)uniform((int)word);
+                    if ((word & kPubLeft) != 0u) found = at;
+                }
+                if (found >= 0 || missing != 0ull) break;
+            }
+            if (lane == 0) {
+                s.left_slot = found;
+                s.left_from = k0;
+                s.nseed = (int)(word & kPubValue);
+            }
+        }
+        __syncthreads();
+        const int at = uniform(s.left_slot);
+        if (at >= 0) win = take_window(at, nullptr);
+        return at >= 0;
+    };
+    // Last of all: were windows of the head left?  The wavefront that has published looks, once that has arrived.  For all wavefronts.
+    [[maybe_unused]] auto any_left = [&](bool looks) {
+        if (looks) {
+            SC_FRESH_PARAMS;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const uint32_t state = __hip_atomic_load(p.head_state + bh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (fresh_lane() == 0) {
+                s.any_left = (state & kHeadLeft) != 0u ? 1 : 0;
+                s.left_from = 0;
+            }
+        }
+        __syncthreads();
+        return uniform(s.any_left) != 0;
+    };
+
     const int decider = (place + bh_i) & (kWinWaves - 1);
+    [[maybe_unused]] bool own = true;      // the merged rows of a long chunk: of this slot's; else of windows that were left
+    [[maybe_unused]] bool mark = false;    // and this one is the first of them
     if (!ahead && !(flags & kWinLong)) {
         {
             SC_FRESH_LANE;
@@ -1003,7 +1077,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                 first_fit_by_seed(s, y, u, all, ra, rb, tau, lane, wave, d);
             }
             const int nseed = __popcll(d.seeds.a) + __popcll(d.seeds.b);
-            publish(nseed, lane);
+            publish(nseed, false, lane);
             if constexpr (!COUNT) {
                 const int out_a = open_a ? rows_below(d.seeds, d.seed_a) : -1, out_b = open_b ? rows_below(d.seeds, d.seed_b) : -1;
                 SC_FRESH_PARAMS;
@@ -1027,52 +1101,69 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             SC_FRESH_LANE;
             const int nseed = uniform(s.nseed);
             park_rows(s, xv, wave, g, c);
-            if (wave == ((decider + 1) & (kWinWaves - 1))) find_base(nseed);
+            if (wave == ((decider + 1) & (kWinWaves - 1))) find_base(nseed, false);
             __syncthreads();
-            if (uniform(s.base_ok) == 0) return;
-            ColumnOps vv;
-            column_operands(s, wave, g, c, nks, vv);
-            const int64_t base = uniform(s.base_lo);
-            const bool odd_keys = uniform(s.any_unsure) != 0;      // (a key that is not finite has no usable norm)
-            SC_FRESH_PARAMS;
-            const int64_t cap = p.cap;
-            TO *Kat = reinterpret_cast<TO *>(p.Kc) + (bh * cap + base) * kFastD, *Vat = reinterpret_cast<TO *>(p.Vc) + (bh * cap + base) * kFastD;
-            int32_t *counts = p.counts + bh * cap;
-            for (int ot = 0; 16 * ot < nseed; ++ot) {
-                floatx4_t ke = {0.f, 0.f, 0.f, 0.f}, ko = ke, ve = ke, vo = ke, cn = ke;
-                const int steps = uniform(s.tile_steps[ot]);
+            if (uniform(s.base_ok) != 0) {
+                ColumnOps vv;
+                column_operands(s, wave, g, c, nks, vv);
+                const int64_t base = uniform(s.base_lo);
+                const bool odd_keys = uniform(s.any_unsure) != 0;      // (a key that is not finite has no usable norm)
+                SC_FRESH_PARAMS;
+                const int64_t cap = p.cap;
+                TO *Kat = reinterpret_cast<TO *>(p.Kc) + (bh * cap + base) * kFastD, *Vat = reinterpret_cast<TO *>(p.Vc) + (bh * cap + base) * kFastD;
+                int32_t *counts = p.counts + bh * cap;
+                for (int ot = 0; 16 * ot < nseed; ++ot) {
+                    floatx4_t ke = {0.f, 0.f, 0.f, 0.f}, ko = ke, ve = ke, vo = ke, cn = ke;
+                    const int steps = uniform(s.tile_steps[ot]);
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    if ((steps >> ks) & 1) {
-                        const bf16x8f_t mem = membership_operand(s.hot[ot], ks, c, g);
-                        ke = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk.x[ks][0], mem, ke, 0, 0, 0);
-                        ko = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk.x[ks][1], mem, ko, 0, 0, 0);
-                        ve = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv.x[ks][0], mem, ve, 0, 0, 0);
-                        vo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv.x[ks][1], mem, vo, 0, 0, 0);
-                        cn = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_operand(), mem, cn, 0, 0, 0);
+                    for (int ks = 0; ks < 4; ++ks) {
+                        if ((steps >> ks) & 1) {
+                            const bf16x8f_t mem = membership_operand(s.hot[ot], ks, c, g);
+                            ke = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk.x[ks][0], mem, ke, 0, 0, 0);
+                            ko = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk.x[ks][1], mem, ko, 0, 0, 0);
+                            ve = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv.x[ks][0], mem, ve, 0, 0, 0);
+                            vo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv.x[ks][1], mem, vo, 0, 0, 0);
+                            cn = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_operand(), mem, cn, 0, 0, 0);
+                        }
+                    }
+                    const int o = 16 * ot + c;
+                    float scale = mean_scale(cn[0]);
+                    if (ballot64(!all_finite(ve, vo) || (odd_keys && !all_finite(ke, ko))) != 0ull) {
+                        scale *= 2.f;
+                        auto member = [&](int r) { return ((s.hot[ot][r] >> c) & 1) != 0; };
+                        sums_by_member(Kbh + (int64_t)w0 * p.stride_n, p.stride_n, R, member, wave, g, ke, ko);
+                        sums_by_member(Vbh + (int64_t)w0 * p.stride_n, p.stride_n, R, member, wave, g, ve, vo);
+                    }
+                    if (o < nseed && base + o < cap) {
+                        store_mean<TO>(Kat + o * kFastD, ke, ko, scale, wave, g);
+                        store_mean<TO>(Vat + o * kFastD, ve, vo, scale, wave, g);
+                        if (wave == 0 && g == 0) counts[base + o] = (int)(0.5f * cn[0] + 0.5f);
                     }
                 }
-                const int o = 16 * ot + c;
-                float scale = mean_scale(cn[0]);
-                if (ballot64(!all_finite(ve, vo) || (odd_keys && !all_finite(ke, ko))) != 0ull) {
-                    scale *= 2.f;
-                    auto member = [&](int r) { return ((s.hot[ot][r] >> c) & 1) != 0; };
-                    sums_by_member(Kbh + (int64_t)w0 * p.stride_n, p.stride_n, R, member, wave, g, ke, ko);
-                    sums_by_member(Vbh + (int64_t)w0 * p.stride_n, p.stride_n, R, member, wave, g, ve, vo);
+                if ((flags & kWinLast) || !any_left(wave == decider)) return;      // (nobody waits for the last one's rows)
+            } else {
+                // left to others, who need the output row of every row
+                SC_FRESH_PARAMS;
+                if (tid < R) {
+                    int out = -1;
+                    for (int t = 0; 16 * t < nseed; ++t)
+                        if (s.hot[t][tid] != 0) out = 16 * t + __ffs((int)s.hot[t][tid]) - 1;
+                    __hip_atomic_store(p.stmp + bh * p.N_max + w0 + tid, out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-                if (o < nseed && base + o < cap) {
-                    store_mean<TO>(Kat + o * kFastD, ke, ko, scale, wave, g);
-                    store_mean<TO>(Vat + o * kFastD, ve, vo, scale, wave, g);
-                    if (wave == 0 && g == 0) counts[base + o] = (int)(0.5f * cn[0] + 0.5f);
-                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                if (tid == 0) s.left_from = 0;
+                mark = true;
             }
+            own = false;
+        } else {
+            return;
         }
-        return;
     }
 
     // ---------------- one chunk longer than a window: blocks of 128 rows.  Seeds are listed in the workspace (row and reciprocal norm); a block's rows
     // are first compared with the seeds of the blocks before, 64 at a time, sixteen per wavefront, then among themselves.
-    if (COUNT || ahead) {
+    else if (COUNT || ahead) {
+    own = false;
     RowRegs x;
     {
         SC_FRESH_LANE;
@@ -1098,7 +1189,8 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
     bf16x8f_t carried[4];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) carried[ks] = __builtin_bit_cast(bf16x8f_t, make_uint4(0u, 0u, 0u, 0u));
-    [[maybe_unused]] floatx4_t ke = {0.f, 0.f, 0.f, 0.f}, ko = ke, cn = ke;
+    [[maybe_unused]] floatx4_t ke = {0.f, 0.f, 0.f, 0.f}, ko = ke;
+    [[maybe_unused]] int members = 0;      // rows of cluster c among those that the lane's operands have held
 #pragma unroll 1
     for (int rb = 0; rb < l; rb += kWinRows) {
         const int Rb = min(kWinRows, l - rb), nx = rb + kWinRows;
@@ -1257,7 +1349,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             if (64 + lane < Rb) __hip_atomic_store(cid + rb + 64 + lane, my_b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (lane == 0) s.nseed = now;
             if constexpr (!COUNT) file_membership(s, (lane < Rb) ? my_a : -1, (64 + lane < Rb) ? my_b : -1, 1, lane);
-            if (nx >= l) publish(now + (closed ? 1 : 0), lane);
+            if (nx >= l) publish(now + (closed ? 1 : 0), true, lane);
             // seeds and clusters are where others read them: seeds beyond the sixteenth in the next block, clusters in the workgroup of the window's slot
             if (now > 16 || nx >= l) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             decided(s, lane);
@@ -1286,7 +1378,8 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                     const bf16x8f_t mem = membership_operand(s.hot[0], ks, c, g);
                     ke = __builtin_amdgcn_mfma_f32_16x16x32_bf16(even, mem, ke, 0, 0, 0);
                     ko = __builtin_amdgcn_mfma_f32_16x16x32_bf16(odds, mem, ko, 0, 0, 0);
-                    cn = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_operand(), mem, cn, 0, 0, 0);
+                    const uint4 bits = __builtin_bit_cast(uint4, mem);
+                    members += __popc(bits.x) + __popc(bits.y) + __popc(bits.z) + __popc(bits.w);
                 }
             }
         }
@@ -1298,7 +1391,9 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         if (nseeds <= 16) {
             SC_FRESH_LANE;
             TO *key_means = reinterpret_cast<TO *>(p.rows_ws) + bh * p.N_max * kFastD;
-            float scale = mean_scale(cn[0]);
+            members += __shfl_xor(members, 16, kWave);
+            members += __shfl_xor(members, 32, kWave);
+            float scale = mean_scale(2.f * (float)members);
             if (ballot64(!all_finite(ke, ko)) != 0ull) {
                 scale *= 2.f;
                 sums_by_member(Kch, p.stride_n, l, [&](int r) { return __hip_atomic_load(cid + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == c; }, wave, g, ke, ko);
@@ -1308,15 +1403,23 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         if (closed && tid == 0 && p.cluster_id) p.cluster_id[bh * p.N_max + start + l] = -1;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) __hip_atomic_store(pub + slot, kPubReady | kPubRows | (uint32_t)(nseeds + (closed ? 1 : 0)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!more) return;
-        win = next;
+        if (tid == 0) __hip_atomic_fetch_or(pub + slot, kPubReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!uniform(more ? 1 : 0)) break;
+        win = Window{uniform(next.slot), uniform(next.first), uniform(next.rows), uniform(next.flags)};
     }
+    }
+    if constexpr (!COUNT) {
+        if (!any_left(wave == 0)) return;      // (the rows arrived before the clusters were announced)
     }
     }
 
-    // ---------------- means of a long chunk
+    // ---------------- means of a long chunk, and of windows that were left
     if constexpr (!COUNT) {
+    for (;;) {
+        if (!own && !next_left(mark)) return;
+        mark = false;
+        win = Window{uniform(win.slot), uniform(win.first), uniform(win.rows), uniform(win.flags)};
+        own = uniform(own ? 1 : 0) != 0;
         SC_FRESH_PARAMS;
         const int64_t cap = p.cap;
         TO *Kout = reinterpret_cast<TO *>(p.Kc) + bh * cap * kFastD, *Vout = reinterpret_cast<TO *>(p.Vc) + bh * cap * kFastD;
@@ -1324,18 +1427,20 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         TO *key_means = reinterpret_cast<TO *>(p.rows_ws) + bh * p.N_max * kFastD;
         const int start = w0, l = R;
         const bool closed = (flags & kWinClosed) != 0;
-        const int32_t *cid = p.cid + bh * p.N_max + start;
+        // (cluster of every row; a window of whole chunks: the output row)
+        const int32_t *cid = ((flags & kWinLong) ? p.cid : p.stmp) + bh * p.N_max + start;
         const bf16_t *Kch = Kbh + (int64_t)start * p.stride_n;
         // the values of the first block are on their way while the place is looked up
         const bf16_t *Vch = Vbh + (int64_t)start * p.stride_n;
         SC_FRESH_LANE;
         RowRegs x;
         load_rows(x, Vch, p.stride_n, 32 * wave, min(32, l - 32 * wave), g, c);
-        if (wave == decider) {      // what the workgroup that has decided the chunk has left
+        if (own && wave == decider) {      // what the workgroup that has decided the chunk has left
             const bool one_xcd = ((p.B * p.Hkv) & 7) == 0;
             u32x16_t w;
             int polls = p.polls;
-            for (int look = 0;; ++look) {
+            w[0] = 0u;
+            for (int look = 0; polls >= -1; ++look) {
                 load_words(w, p.published + bh * p.win_slots + slot, one_xcd && look % kVectorEvery != kVectorEvery - 1, lane);
                 if ((w[0] & kPubReady) != 0u || --polls < 0) break;
                 __builtin_amdgcn_s_sleep(1);
@@ -1356,19 +1461,12 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         // The place is looked up when the first sums are there: the windows just before are being decided meanwhile.
         int64_t base = -1;
         auto look_up = [&]() {
-            if (wave == decider) find_base(rows);
+            if (wave == decider) find_base(rows, !own);
             __syncthreads();
             base = uniform(s.base_lo);
             return uniform(s.base_ok) != 0;
         };
-        if (rows < 0) {      // gave up waiting
-            if (wave == decider && lane == 0) {
-                __hip_atomic_store(p.gave_up + bh, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __hip_atomic_store(p.comp_lens + bh, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            return;
-        }
+        bool ok = rows >= 0;
         // kTiles tiles of sixteen clusters per sweep over the chunk: values, then keys
         constexpr int kTiles = 2;
         auto finish = [&](const bf16_t *X, TO *out, int o0, floatx4_t even, floatx4_t odd, const floatx4_t &n, bool sizes) {
@@ -1384,10 +1482,10 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                 if (sizes && wave == 0 && g == 0) counts[base + o] = (int)(0.5f * n[0] + 0.5f);
             }
         };
-        const bool keys_done = nseeds <= 16;
+        const bool keys_done = (flags & kWinLong) != 0 && nseeds <= 16;
         bool first = true;
 #pragma unroll 1
-        for (int src = 0; src < (keys_done ? 1 : 2); ++src) {
+        for (int src = 0; ok && src < (keys_done ? 1 : 2); ++src) {
             const bf16_t *Xch = src == 0 ? Vch : Kch;
 #pragma unroll 1
             for (int o0 = 0; o0 < nseeds; o0 += 16 * kTiles) {
@@ -1430,7 +1528,8 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                     }
                 }
                 if (base < 0) {
-                    if (!look_up()) return;
+                    ok = look_up();
+                    if (!ok) break;
                     if (keys_done) {
                         // sixteen lanes a row
                         constexpr int kPieces = (int)sizeof(TO) * kFastD / 256;
@@ -1450,7 +1549,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                     if (o0 + 16 * t < nseeds) finish(Xch, src == 0 ? Vout : Kout, o0 + 16 * t, ev[t], od[t], sz[t], src == 0);
             }
         }
-        if (closed && base + nseeds < cap && tid < 16) {
+        if (ok && closed && base + nseeds < cap && tid < 16) {
             // the closing delimiter is the output row behind: a copy with size 1
             float kv[8], vv[8];
             load8(Kbh + (int64_t)(start + l) * p.stride_n + 8 * c, kv);
@@ -1459,6 +1558,14 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             store8(Vout + (base + nseeds) * kFastD + 8 * c, vv);
             if (tid == 0) counts[base + nseeds] = 1;
         }
+        if (own) {
+            if (ok) return;
+            // left to others; its clusters are, or will be, in the workspace
+            own = false;
+            mark = true;
+            if (tid == 0) s.left_from = 0;
+        }
+    }
     }
 }
 
@@ -1502,7 +1609,7 @@ hipError_t launch_gsc_fast(const GscParams &p0, bool planned, hipStream_t stream
     p.published = reinterpret_cast<uint32_t *>(p.windows + (size_t)p.B * p.win_slots);
     p.win_count = reinterpret_cast<int32_t *>(p.published + bh * (size_t)p.win_slots);
     p.longs = reinterpret_cast<GscLongs *>(p.win_count + bh * (size_t)p.win_slots);
-    p.gave_up = p.rowbase;
+    p.head_state = reinterpret_cast<uint32_t *>(p.rowbase);
     p.long_count = reinterpret_cast<int32_t *>(p.longs + (size_t)segments * p.B);
     // Half of what is resident together, the rest goes to windows (a quarter or three quarters: the same within 1 %); where there are no long
     // chunks, all of them leave within a microsecond.  (One for every 512 tokens instead: a long-tailed call of 8 heads x 4000 took

@@ -527,7 +527,7 @@ static hipError_t launch_typed(const GscParams &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// (the fast path addresses the rows of a wavefront with 32-bit byte offsets, and publishes the rows of a segment in 26 bits)
+// (the fast path addresses the rows of a wavefront with 32-bit byte offsets, and publishes the rows of a segment in 27 bits)
 bool gsc_merge_takes_fast_path(const GscMergeArgs &a) {
     return a.in_dtype == DType::BF16 && a.d == 128 && tuning().gsc_fast_path && a.stride_n <= (int64_t(1) << 22) && gsc_fast_holds(a.N_max);
 }

@@ -86,7 +86,7 @@ struct GscParams {
     int32_t *seedrow;     // [B, Hkv, N_max]   seed positions of a chunk that spans several blocks
     int32_t *pcount;      // [B, Hkv, N_max + 1] generic path: clusters per chunk
     int32_t *rowbase;     // [B, Hkv, N_max + 2] first output row of every chunk; without a scan kernel, generic path: clusters of every item
-    int32_t *stmp;        // [B, Hkv, N_max]   fast path: reciprocal norms of the seeds of a chunk that spans several blocks
+    int32_t *stmp;        // [B, Hkv, N_max]   fast path: reciprocal norms of the seeds of a chunk that spans several blocks; output row of every row of a window left to others
     void *rows_ws;        // [B, Hkv, N_max, d] twice, in the output type: the fast path lays out the arrays below in it
     GscWindow *windows;   // [B, win_slots]
     uint32_t *published;  // [B, Hkv, win_slots] rows of a window, for the windows behind it
@@ -95,11 +95,11 @@ struct GscParams {
     GscLongs *longs;      // [B, segments] slots of long chunks
     int32_t *long_count;  // [B, segments]
     int ahead_per_head, ahead_wgs;  // workgroups that decide long chunks first: per (sequence, head), in all
-    int32_t *gave_up;     // [B, Hkv]          a window's workgroup has stopped waiting for the ones before it
+    uint32_t *head_state; // [B, Hkv]          whether windows were left to others
     int seg_bits;         // of a segment's word that count windows
     int slots_per_segment, win_slots;   // windows per kSegRows rows / per sequence that there is room for
     int max_chunks;       // chunks per window, <= 0: as many as fit
-    int polls;            // looks at the windows before before a workgroup gives up
+    int polls;            // looks at the windows before until a workgroup leaves its own to others
     int count_only;       // fast path: cluster and count only (comp_lens); no values are read, no rows written
     int chunks_per_item;  // generic path
     int short_wgs[2];     // generic path: workgroups per (sequence, head) where short chunks make items of 8 / of 16 or 32, 0: they don't (see gsc_item_shape)

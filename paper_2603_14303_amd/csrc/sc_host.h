@@ -119,7 +119,7 @@ struct Tuning {
     int gsc_chunks_per_item = 0;    // generic path: chunks handled by one workgroup work item; <= 0 picks it from the rows of the call
     int gsc_grid_x = 0;             // generic path: workgroups per (sequence, KV head); <= 0 picks it from the sequence length
     int gsc_chunks_per_task = 0;    // fast path: chunks a window holds at most; <= 0: as many as fit
-    int gsc_polls = 1 << 20;        // fast path: looks (about 1 us each) at the windows before before a workgroup gives up; negative: give up at once if a look does not find them
+    int gsc_polls = 1 << 16;        // fast path: looks (about 1 us each) at the windows before until a workgroup leaves its own to others; -1: at the first look that does not find them, below: without looking
     int gsc_fast_path = 1;          // 0 forces the generic kernels even for bf16 / d = 128
     int global_polls = 1 << 20;     // sc_gsc_merge_global: looks (about 0.5 us each) at rows another block decides before the ordered pass takes over
     int multi_block_rows = 0;       // query rows per workgroup of sc_multi_attn: 32 or 128; anything else picks it from the shape of the call

@@ -1,7 +1,7 @@
 """The edges of the bf16 / d = 128 compression: chunk lengths around the 128 rows of a window (and twice that), windows
 of more chunks than a wavefront has lanes, sequences that end just before and after the 1024 rows of a planning segment,
 long chunks with more clusters than their key means are kept for (16), head counts that do and do not tie a head to one
-XCD (a multiple of 8), non-finite and very large values, and the bound on the waits.  Indices, sizes and lengths must equal the oracle's
+XCD (a multiple of 8), non-finite and very large values, and workgroups that stop waiting.  Indices, sizes and lengths must equal the oracle's
 bit for bit; fp32 means within 1e-3 (fp32 sums of at most a few thousand bf16 terms: ~1e-5)."""
 import numpy as np
 import pytest
@@ -170,3 +170,106 @@ def test_a_wait_that_is_given_up_is_reported():
             _check_head(again, b, h, r, n)
             if int(out[3][b, h]) != -1:
                 _check_head(out, b, h, r, n)
+
+
+@pytest.fixture
+def polls():
+    old = sc.tune_get("gsc_polls")
+    yield lambda n: sc.tune_set("gsc_polls", n)
+    sc.tune_set("gsc_polls", old)
+
+
+def _same(a, b, lens):
+    """Every output of two calls, rows and tokens that exist, bit for bit."""
+    assert torch.equal(a[3], b[3])
+    for i, n in enumerate(lens):
+        assert torch.equal(a[4][i, :, :n], b[4][i, :, :n])
+        for h in range(a[3].shape[1]):
+            rows = int(a[3][i, h])
+            assert all(torch.equal(a[j][i, h, :rows], b[j][i, h, :rows]) for j in range(3)), (i, h)
+
+
+@pytest.mark.parametrize("looks", [-2, -1, 0, 5])                    # -2: every window and long chunk is left to others
+@pytest.mark.parametrize("layout", ["window", "every row", "long", "none", "mixed"])
+@pytest.mark.parametrize("lens,heads,centres", [((3000, 2500), 4, 10), ((1100, 1, 0), 3, 40), ((4500,), 8, 25)])
+def test_windows_that_stop_waiting_are_finished(polls, layout, lens, heads, centres, looks):
+    """The same cache, whoever writes it: with few looks, or none, windows are finished by the workgroups that complete their segments."""
+    gaps = {**GAPS, "mixed": GAPS["long"] + [9, 17, 40] * 40}[layout]
+    mask, K, V = _case(60 + centres, gaps, lens, heads, centres)
+    tau = 0.6
+    want = _merge(mask, K, V, lens, tau)
+    half = _merge(mask, K, V, lens, tau, torch.bfloat16)
+    polls(looks)
+    for _ in range(2):
+        _same(_merge(mask, K, V, lens, tau), want, lens)
+        _same(_merge(mask, K, V, lens, tau, torch.bfloat16), half, lens)
+    compared = 0
+    for b, n in enumerate(lens):
+        if n < 128:
+            continue
+        o = oracle.segment(mask[b], n)
+        for h in range(heads):
+            r = oracle.compress_head(K[b, h, :n], V[b, h, :n], o, tau)
+            if r["chunk_margin"].min() > 1e-9:
+                compared += 1
+                _check_head(want, b, h, r, n)
+    assert compared >= heads
+
+
+@pytest.mark.parametrize("looks", [-2, 100])
+def test_a_long_chunk_takes_longer_than_anybody_waits(polls, looks):
+    """Two thousand rows that hardly merge in one chunk, and windows behind it that stop waiting long before it is decided."""
+    n, heads, tau = 4200, 2, 0.9
+    mask, K, V = _case(90, [2100, 30, 12, 60, 700, 5], (n,), heads, n)
+    polls(looks)
+    out = _merge(mask, K, V, (n,), tau)
+    o = oracle.segment(mask[0], n)
+    for h in range(heads):
+        r = oracle.compress_head(K[0, h], V[0, h], o, tau)
+        assert r["chunk_margin"].min() > 1e-9 and r["n_rows"] > 0.8 * n
+        _check_head(out, 0, h, r, n)
+
+
+def test_windows_left_behind_a_cache_that_is_too_small_or_appended_to(polls):
+    """Capacity and append, every window left: lengths and rows as with waiting; rows beyond the capacity stay untouched."""
+    n, heads, tau = 2600, 3, 0.6
+    mask, K, V = _case(95, GAPS["long"] + [9, 17, 40] * 20, (n,), heads, 10)
+    off, nch, _ = g.check_segment(mask, np.array([n], np.int32))
+    Kd, Vd = g.to_device(K, True), g.to_device(V, True)
+    full = int(_merge(mask, K, V, (n,), tau)[3].max())
+    results = []
+    for looks in (1 << 20, -2):
+        polls(looks)
+        for cap, base in ((full // 2, None), (2 * full, [[0, full // 3, full]]), (full, [[1, 0, -1]])):
+            Kc = torch.full((1, heads, cap, D), -7.0, device="cuda")
+            Vc, counts = Kc.clone(), torch.full((1, heads, cap), -7, dtype=torch.int32, device="cuda")
+            clens = torch.full((1, heads), -7, dtype=torch.int32, device="cuda")
+            lens = None if base is None else torch.tensor(base, dtype=torch.int32, device="cuda")
+            sc.sc_gsc_merge(Kd, Vd, off, nch, tau, cap=cap, out_dtype=torch.float32, Kc=Kc, Vc=Vc, counts=counts, comp_lens=clens, base_lens=lens)
+            torch.cuda.synchronize()
+            results.append((Kc, Vc, counts, clens))
+    for a, b in zip(results[:3], results[3:]):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def test_two_calls_at_once(polls):
+    """Two streams, heads that no XCD has to itself: windows of either call can hold up those of the other until they stop waiting."""
+    n, heads, tau = 20000, 3, 0.6
+    calls = []
+    for seed in (97, 98):
+        mask, K, V = _case(seed, [9, 17, 40, 24, 200], (n,), heads, 10)
+        off, nch, _ = g.check_segment(mask, np.array([n], np.int32))
+        args = (g.to_device(K, True), g.to_device(V, True), off, nch, tau)
+        calls.append((args, sc.sc_gsc_merge(*args, want_cluster_id=True), torch.cuda.Stream(),
+                      sc.gsc_merge_workspace(1, heads, n, D, "cuda")))
+    torch.cuda.synchronize()
+    for looks in (1 << 10, 4):
+        polls(looks)
+        got = []
+        for _ in range(5):
+            for args, _, stream, ws in calls:
+                with torch.cuda.stream(stream):
+                    got.append(sc.sc_gsc_merge(*args, want_cluster_id=True, workspace=ws))
+        torch.cuda.synchronize()
+        for i, out in enumerate(got):
+            _same(out, calls[i % 2][1], (n,))

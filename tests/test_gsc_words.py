@@ -16,7 +16,7 @@ int main() {
     // slots of a segment, and the largest number of tokens that its words hold
     for (int slots : {1, 2, 3, 15, 16, 17, 31, 32, 1025}) {
         const int bits = segment_bits(slots);
-        const long long most = (1ll << (31 - bits)) - 1;
+        const long long most = std::min((1ll << (32 - bits)) - 1, (long long)kPubValue);
         wrong += !segment_holds(slots, most) + segment_holds(slots, most + 1) + ((1 << bits) <= slots) + (bits > 1 && (1 << (bits - 1)) > slots);
         for (int windows = 0; windows <= std::min(slots, 5); ++windows) {
             std::vector<int> rows;
