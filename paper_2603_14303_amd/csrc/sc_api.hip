@@ -173,6 +173,7 @@ static sc_status gsc_check_and_fill(const void *K, const void *V, sc_dtype in_dt
     a.Kc = Kc; a.Vc = Vc; a.out_dtype = static_cast<DType>(out_dtype); a.cap = cap;
     a.counts = counts; a.comp_lens = comp_lens; a.cluster_id = cluster_id; a.ws = ws;
     a.base_lens = append ? base_lens : nullptr;
+    a.tune = tuning();
     return SC_OK;
 }
 

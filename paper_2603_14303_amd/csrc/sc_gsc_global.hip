@@ -797,7 +797,7 @@ __global__ void glob_one_chunk_kernel(const int32_t *seq_lens, int B, int N_max,
 // ------------------------------------------------------------------------------------------------
 static bool glob_fast_ok(const GscMergeArgs &a) {
     return a.in_dtype == DType::BF16 && a.d == kGlD && a.N_max <= 32768 && a.stride_n % 8 == 0 && a.stride_n * 2 * kGlBlock < (1ll << 31) &&
-           tuning().gsc_fast_path != 0;
+           a.tune.gsc_fast_path != 0;
 }
 static size_t glob_head_bytes(int N_max) {   // upper bound of what launch_gsc_global lays out per (sequence, head)
     const size_t nbp = (size_t)(N_max + kGlBlock - 1) / kGlBlock, npad = nbp * kGlBlock, nseg = (nbp + kGlSegment - 1) / kGlSegment;
@@ -855,7 +855,7 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     p.tany = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * p.nseg * 8 * BH, 256);
     p.tuns = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * p.nseg * 8 * BH, 256);
     p.state = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * 16 * BH, 256);
-    p.polls = tuning().global_polls;
+    p.polls = a.tune.global_polls;
 
     hipLaunchKernelGGL(glob_norms_kernel, dim3((unsigned)(npad / 16), (unsigned)BH), dim3(256), 0, stream, p);
     hipError_t e = hipGetLastError();

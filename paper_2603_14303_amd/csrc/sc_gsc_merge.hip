@@ -507,10 +507,10 @@ size_t gsc_merge_workspace_bytes(int B, int Hkv, int N_max, int d, int out_elem_
 }
 
 template <typename T, int D>
-static hipError_t launch_typed(const GscParams &p, hipStream_t stream) {
+static hipError_t launch_typed(const GscParams &p, int grid_x, hipStream_t stream) {
     const int max_items = (p.N_max + 1 + p.chunks_per_item - 1) / p.chunks_per_item;
     const int heads = p.B * p.Hkv;
-    const int gx = max(1, min(max_items, tuning().gsc_grid_x > 0 ? tuning().gsc_grid_x : gsc_item_workgroups(heads, p.N_max, p.chunks_per_item)));
+    const int gx = max(1, min(max_items, grid_x > 0 ? grid_x : gsc_item_workgroups(heads, p.N_max, p.chunks_per_item)));
     const int per_layer = min(heads, 1 << kGridHeadsLog2);
     const dim3 grid(per_layer, min(gx, 65535), (heads + per_layer - 1) / per_layer);
     hipLaunchKernelGGL((gsc_assign_kernel<T, D>), grid, dim3(kGscThreads), 0, stream, p);
@@ -529,7 +529,7 @@ static hipError_t launch_typed(const GscParams &p, hipStream_t stream) {
 
 // (the fast path addresses the rows of a wavefront with 32-bit byte offsets, and publishes the rows of a segment in 27 bits)
 bool gsc_merge_takes_fast_path(const GscMergeArgs &a) {
-    return a.in_dtype == DType::BF16 && a.d == 128 && tuning().gsc_fast_path && a.stride_n <= (int64_t(1) << 22) && gsc_fast_holds(a.N_max);
+    return a.in_dtype == DType::BF16 && a.d == 128 && a.tune.gsc_fast_path && a.stride_n <= (int64_t(1) << 22) && gsc_fast_holds(a.N_max);
 }
 
 hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
@@ -553,8 +553,8 @@ hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
     // offsets, the prefix and the barriers of an item among eight (us, 4 / 8 / 16 chunks: 2 heads x 1024 x 64 f32
     // 30 / 33 / 45; 8 x 8192 x 128 f32 72 / 77 / 117; 8 x 32768 x 64 bf16 179 / 156 / 181).
     const int auto_item = ((int64_t)a.B * a.Hkv * a.N_max <= (int64_t(1) << 16)) ? 4 : 8;
-    p.chunks_per_item = max(1, min(kMaxChunksPerItem, tuning().gsc_chunks_per_item > 0 ? tuning().gsc_chunks_per_item : auto_item));
-    const bool fixed = tuning().gsc_chunks_per_item > 0 || tuning().gsc_grid_x > 0;
+    p.chunks_per_item = max(1, min(kMaxChunksPerItem, a.tune.gsc_chunks_per_item > 0 ? a.tune.gsc_chunks_per_item : auto_item));
+    const bool fixed = a.tune.gsc_chunks_per_item > 0 || a.tune.gsc_grid_x > 0;
     p.short_wgs[0] = fixed ? 0 : max(1, gsc_item_workgroups(a.B * a.Hkv, p.N_max, 8));
     p.short_wgs[1] = fixed ? 0 : max(1, gsc_item_workgroups(a.B * a.Hkv, p.N_max, 16));
 
@@ -576,15 +576,15 @@ hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
 
     if (gsc_merge_takes_fast_path(a)) {
         if (a.count_only) p.budget = reinterpret_cast<BudgetState *>(a.budget_state);
-        p.max_chunks = tuning().gsc_chunks_per_task;
-        p.polls = tuning().gsc_polls;
+        p.max_chunks = a.tune.gsc_chunks_per_task;
+        p.polls = a.tune.gsc_polls;
         return launch_gsc_fast(p, a.planned, stream);
     }
 
     if (a.in_dtype == DType::BF16) {
-        return a.d == 128 ? launch_typed<bf16_t, 128>(p, stream) : launch_typed<bf16_t, 64>(p, stream);
+        return a.d == 128 ? launch_typed<bf16_t, 128>(p, a.tune.gsc_grid_x, stream) : launch_typed<bf16_t, 64>(p, a.tune.gsc_grid_x, stream);
     }
-    return a.d == 128 ? launch_typed<float, 128>(p, stream) : launch_typed<float, 64>(p, stream);
+    return a.d == 128 ? launch_typed<float, 128>(p, a.tune.gsc_grid_x, stream) : launch_typed<float, 64>(p, a.tune.gsc_grid_x, stream);
 }
 
 }  // namespace sc

@@ -10,6 +10,24 @@ enum class DType : int { F32 = 0, BF16 = 1 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// tuning knobs, set through sc_tune_set and read by the launchers; a merge call takes a copy, so that all its launches go by the same ones
+struct Tuning {
+    int decode_max_splits = 0;      // split-K workgroups per (sequence, KV head); <= 0 picks it from B*Hkv
+    int decode_min_rows = 192;      // rows of the merged cache a split should at least get
+    int decode_local_handover = 1;  // 0: split partials always go through memory, also when a head's splits share an XCC
+    int decode_poll_budget = 1 << 20;   // polls (about 0.3 us each) of the folding workgroup before it gives up; negative: give up at once (host-driven test of the failure path)
+    int decode_mfma_min_group = 9;  // query heads per KV head from which single-row decode runs on the multi-row kernel (9 = never)
+    int gsc_chunks_per_item = 0;    // generic path: chunks handled by one workgroup work item; <= 0 picks it from the rows of the call
+    int gsc_grid_x = 0;             // generic path: workgroups per (sequence, KV head); <= 0 picks it from the sequence length
+    int gsc_chunks_per_task = 0;    // fast path: chunks a window holds at most; <= 0: as many as fit
+    int gsc_polls = 1 << 16;        // fast path: looks (about 1 us each) at the windows before until a workgroup leaves its own to others; -1: at the first look that does not find them, below: without looking
+    int gsc_fast_path = 1;          // 0 forces the generic kernels even for bf16 / d = 128
+    int global_polls = 1 << 20;     // sc_gsc_merge_global: looks (about 0.5 us each) at rows another block decides before the ordered pass takes over
+    int multi_block_rows = 0;       // query rows per workgroup of sc_multi_attn: 32 or 128; anything else picks it from the shape of the call
+    int multi_target_wgs = 256;     // compute units the split count of sc_multi_attn reckons with
+};
+Tuning &tuning();
+
 // ---- sc_segment
 hipError_t launch_segment(const uint8_t *mask, int64_t mask_stride_b, const int32_t *seq_lens, int B, int n_max,
                           int32_t *offsets, int64_t offsets_stride_b, int offsets_cap, int32_t *num_chunks,
@@ -30,6 +48,7 @@ struct GscMergeArgs {
     int cap;
     int32_t *counts, *comp_lens, *cluster_id;
     const int32_t *base_lens = nullptr;   // append mode: rows already in the outputs, [B, Hkv]
+    Tuning tune;                          // the knobs when the call was made
     const float *tau_dev = nullptr;       // threshold in device memory (overrides tau)
     bool count_only = false;              // only comp_lens is produced (bf16 / d = 128 fast path; elsewhere the full merge runs)
     void *budget_state = nullptr;         // counting probe of the budget search: its last kernel also moves the bracket (fast path only)
@@ -108,23 +127,5 @@ hipError_t launch_multi_fast(const MultiArgs &a, hipStream_t stream);
 
 // ---- measuring aid: streaming read of a buffer
 hipError_t launch_stream_read_probe(const void *src, size_t bytes, void *sink, hipStream_t stream);
-
-// tuning knobs (read by the launchers; set through sc_tune_set)
-struct Tuning {
-    int decode_max_splits = 0;      // split-K workgroups per (sequence, KV head); <= 0 picks it from B*Hkv
-    int decode_min_rows = 192;      // rows of the merged cache a split should at least get
-    int decode_local_handover = 1;  // 0: split partials always go through memory, also when a head's splits share an XCC
-    int decode_poll_budget = 1 << 20;   // polls (about 0.3 us each) of the folding workgroup before it gives up; negative: give up at once (host-driven test of the failure path)
-    int decode_mfma_min_group = 9;  // query heads per KV head from which single-row decode runs on the multi-row kernel (9 = never)
-    int gsc_chunks_per_item = 0;    // generic path: chunks handled by one workgroup work item; <= 0 picks it from the rows of the call
-    int gsc_grid_x = 0;             // generic path: workgroups per (sequence, KV head); <= 0 picks it from the sequence length
-    int gsc_chunks_per_task = 0;    // fast path: chunks a window holds at most; <= 0: as many as fit
-    int gsc_polls = 1 << 16;        // fast path: looks (about 1 us each) at the windows before until a workgroup leaves its own to others; -1: at the first look that does not find them, below: without looking
-    int gsc_fast_path = 1;          // 0 forces the generic kernels even for bf16 / d = 128
-    int global_polls = 1 << 20;     // sc_gsc_merge_global: looks (about 0.5 us each) at rows another block decides before the ordered pass takes over
-    int multi_block_rows = 0;       // query rows per workgroup of sc_multi_attn: 32 or 128; anything else picks it from the shape of the call
-    int multi_target_wgs = 256;     // compute units the split count of sc_multi_attn reckons with
-};
-Tuning &tuning();
 
 }  // namespace sc

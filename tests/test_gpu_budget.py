@@ -1,6 +1,8 @@
 """GPU parity for sc_gsc_merge_budget: the bisection on the device must probe the thresholds the oracle's
 bisection probes (every probe's row count is an integer the two sides agree on exactly), end on the
 same fp32 threshold, and leave the merged cache of that threshold in the outputs."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -110,3 +112,47 @@ def test_budget_search_replays_from_a_graph():
             r = int(eager[3][0, h])
             assert torch.equal(out[0][0, h, :r], eager[0][0, h, :r]) and torch.equal(out[2][0, h, :r], eager[2][0, h, :r])
         del scratch
+
+
+def test_knobs_that_change_during_the_search():
+    """A search is many launches that share one layout of the workspace: all go by the knobs of the moment the call was made."""
+    w = wl.get_workload("layer32k")
+    case = build_case(w, 0.7, n_max=3000, heads=2, exclude_near=False)
+    K, V = g.to_device(case["K"], True), g.to_device(case["V"], True)
+    off, nch, sl = g.run_segment(case["mask"], case["seq_lens"])
+    budget = int(0.3 * 2 * int(case["seq_lens"][0]))
+
+    def search():
+        return sc.sc_gsc_merge_budget(K, V, off, nch, budget, -1.01, 1.0, 12, seq_lens=sl, out_dtype=torch.float32, want_cluster_id=True)
+
+    want = search()
+    torch.cuda.synchronize()
+    old = {k: sc.tune_get(k) for k in ("gsc_chunks_per_task", "gsc_polls", "gsc_fast_path")}
+    stop = threading.Event()
+
+    def turn():
+        i = 0
+        while not stop.is_set():
+            sc.tune_set("gsc_chunks_per_task", i % 4)
+            sc.tune_set("gsc_polls", 1 << (i % 20))
+            sc.tune_set("gsc_fast_path", int(i % 5 != 0))
+            i += 1
+
+    t = threading.Thread(target=turn)
+    t.start()
+    try:
+        got = [search() for _ in range(40)]
+    finally:
+        stop.set()
+        t.join()
+        for k, v in old.items():
+            sc.tune_set(k, v)
+    torch.cuda.synchronize()
+    for out in got:
+        assert out[5].item() == want[5].item() and out[6].item() == want[6].item()
+        assert torch.equal(out[3], want[3]) and torch.equal(out[4], want[4])
+        for h in range(2):
+            rows = int(want[3][0, h])
+            assert torch.equal(out[2][0, h, :rows], want[2][0, h, :rows])
+            for i in (0, 1):        # fp32 means of bf16 rows, summed in another order where another path was taken
+                assert torch.allclose(out[i][0, h, :rows], want[i][0, h, :rows], rtol=1e-5, atol=1e-5)
