@@ -38,6 +38,7 @@ constexpr int kFastD = 128;
 constexpr int kWinWaves = 4;
 constexpr int kWinThreads = kWinWaves * kWave;
 constexpr int kWinRows = 128;            // rows of a window
+constexpr int kAheadWgs = 512;           // workgroups that decide long chunks ahead of the windows (one per head if there are more heads)
 constexpr int kSegRows = 1024;           // rows of a sequence whose chunks one wavefront of the plan kernel packs
 constexpr float kFastBand = 1e-4f;       // fp32 cosine error for d = 128 is < 2e-5; inside the band -> fp64
 
@@ -1592,12 +1593,18 @@ __global__ __launch_bounds__(256) void gsc_count_kernel(GscParams p) {
 }
 
 // ------------------------------------------------------------------------------------------------
-bool gsc_fast_holds(int N_max) { return segment_holds(gsc_slots_per_segment(N_max, 0), N_max); }
+static int segments_of(int n_max) { return (n_max + kSegRows - 1) / kSegRows; }
+// a workgroup of the compress kernel for every slot and those ahead: fewer than 2^32 threads in a launch, and the rows of a segment in its word
+static bool fast_holds(int heads, int n_max, int max_chunks) {
+    const int S = gsc_slots_per_segment(n_max, max_chunks);
+    return segment_holds(S, n_max) && ((int64_t)segments_of(n_max) * S * heads + max(heads, kAheadWgs)) * kWinThreads < (int64_t(1) << 32);
+}
+bool gsc_fast_holds(int heads, int N_max) { return fast_holds(heads, N_max, 0); }
 
 hipError_t launch_gsc_fast(const GscParams &p0, bool planned, hipStream_t stream) {
     GscParams p = p0;
-    const int segments = (p.N_max + kSegRows - 1) / kSegRows;
-    if (!segment_holds(gsc_slots_per_segment(p.N_max, p.max_chunks), p.N_max)) p.max_chunks = 0;
+    const int segments = segments_of(p.N_max);
+    if (!fast_holds(p.B * p.Hkv, p.N_max, p.max_chunks)) p.max_chunks = 0;
     p.slots_per_segment = gsc_slots_per_segment(p.N_max, p.max_chunks);
     p.seg_bits = segment_bits(p.slots_per_segment);
     p.win_slots = segments * p.slots_per_segment;
@@ -1615,7 +1622,7 @@ hipError_t launch_gsc_fast(const GscParams &p0, bool planned, hipStream_t stream
     // chunks, all of them leave within a microsecond.  (One for every 512 tokens instead: a long-tailed call of 8 heads x 4000 took
     // 41 us against 32.)
     const size_t longest = (size_t)p.N_max / (kWinRows + 1) + 1;
-    p.ahead_per_head = p.N_max < kWinRows ? 0 : (int)max((size_t)1, min(longest, 512 / bh));
+    p.ahead_per_head = p.N_max < kWinRows ? 0 : (int)max((size_t)1, min(longest, kAheadWgs / bh));
     p.ahead_wgs = (int)(bh * p.ahead_per_head);
     if (!planned) {
         hipLaunchKernelGGL(gsc_plan_kernel, dim3((unsigned)(segments * p.B)), dim3(kWave), 0, stream, p);

@@ -527,9 +527,10 @@ static hipError_t launch_typed(const GscParams &p, int grid_x, hipStream_t strea
     return hipGetLastError();
 }
 
-// (the fast path addresses the rows of a wavefront with 32-bit byte offsets, and publishes the rows of a segment in 27 bits)
+// (the fast path addresses the rows of a wavefront with 32-bit byte offsets, publishes the rows of a segment in 27 bits, and launches a
+// workgroup for every window there is room for, which millions of heads of a few tokens can make too many)
 bool gsc_merge_takes_fast_path(const GscMergeArgs &a) {
-    return a.in_dtype == DType::BF16 && a.d == 128 && a.tune.gsc_fast_path && a.stride_n <= (int64_t(1) << 22) && gsc_fast_holds(a.N_max);
+    return a.in_dtype == DType::BF16 && a.d == 128 && a.tune.gsc_fast_path && a.stride_n <= (int64_t(1) << 22) && gsc_fast_holds(a.B * a.Hkv, a.N_max);
 }
 
 hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {

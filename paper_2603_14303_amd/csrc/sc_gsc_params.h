@@ -114,7 +114,7 @@ __device__ __forceinline__ int gsc_base_rows(const P &p, int64_t bh, bool &bad) 
     return bad ? p.cap : raw;
 }
 
-bool gsc_fast_holds(int N_max);   // sequences of that many tokens fit its words
+bool gsc_fast_holds(int heads, int N_max);   // they fit its words and its launch
 // planned: the windows of these offsets are in the workspace already (and nothing has been published since)
 hipError_t launch_gsc_fast(const GscParams &p, bool planned, hipStream_t stream);
 

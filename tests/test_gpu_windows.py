@@ -273,3 +273,18 @@ def test_two_calls_at_once(polls):
         torch.cuda.synchronize()
         for i, out in enumerate(got):
             _same(out, calls[i % 2][1], (n,))
+
+
+def test_more_windows_than_one_launch_can_have():
+    """Six million heads of two tokens: a workgroup for each window there is room for would be more than 2^32 threads."""
+    B, heads, tau = 65535, 90, 0.6
+    gen = torch.Generator(device="cuda").manual_seed(99)
+    K = torch.randn((B, heads, 2, D), generator=gen, device="cuda", dtype=torch.bfloat16)
+    K[:, ::2, 1] = K[:, ::2, 0]                                     # every other head has two tokens alike, the others two that have nothing in common
+    off, nch = sc.sc_segment(torch.zeros((B, 2), dtype=torch.uint8, device="cuda"))
+    Kc, Vc, counts, clens, _ = sc.sc_gsc_merge(K, K, off, nch, tau)
+    torch.cuda.synchronize()
+    assert (clens[:, ::2] == 1).all() and (clens[:, 1::2] == 2).all()
+    assert (counts[:, ::2, 0] == 2).all() and (counts[:, 1::2] == 1).all()
+    for x in (Kc, Vc):
+        assert torch.equal(x[:, ::2, 0], K[:, ::2, 0]) and torch.equal(x[:, 1::2], K[:, 1::2])
