@@ -55,7 +55,7 @@ def test_workspace_queries(lib):
     b = lib.sc_gsc_merge_workspace_bytes(4, 8, 32768, 128)
     assert a > 0 and a % 256 == 0 and b >= 4 * a - 4096
     assert lib.sc_gsc_merge_workspace_bytes(0, 8, 32768, 128) == 0
-    # sized for one output type: fp32 is the general size, bf16 halves the provisional rows
+    # sized for one output type: fp32 is the general size, bf16 halves its two arrays of rows
     assert lib.sc_gsc_merge_workspace_bytes_for(1, 8, 32768, 128, 0) == a
     half = lib.sc_gsc_merge_workspace_bytes_for(1, 8, 32768, 128, 1)
     assert half % 256 == 0 and a - half == 2 * 8 * 32768 * 128 * 2

@@ -86,9 +86,9 @@ def _cut_after_delimiter(mask_row, n, frac):
 
 @pytest.mark.parametrize("name,n,tau,frac", [
     ("tiny", 1024, 0.7, 0.5),              # fp32, d = 64: generic kernels (their scan adds the old length)
-    ("layer32k", 4096 + 37, 0.7, 0.4),     # bf16 fast path, relocation adds the old length itself
+    ("layer32k", 4096 + 37, 0.7, 0.4),     # bf16 fast path, every window adds the old length itself
     ("layer32k", 3000, 0.9745, 0.9),       # short stretch behind a long prefix
-    ("long128k", 70000, 0.7, 0.3),         # stretch beyond 32k tokens: fast path with the scan kernel
+    ("long128k", 70000, 0.7, 0.3),         # stretch beyond 32k tokens
 ])
 def test_append_gives_the_rows_of_one_call_over_the_whole_sequence(name, n, tau, frac):
     w = wl.get_workload(name)

@@ -107,8 +107,8 @@ def test_random_structures(bf16, d, seed):
 
 @pytest.mark.parametrize("bf16,d,seed", [(True, 128, 300), (False, 64, 301)])
 def test_thousands_of_short_chunks(bf16, d, seed):
-    """A delimiter every few tokens: more chunks than one round of the relocation's count sum holds (2048)
-    and more tasks than the compress grid has workgroups per head, on a ragged batch."""
+    """A delimiter every few tokens: windows of some thirty chunks (64 are planned at a time), and on the
+    generic path more items than its grid has workgroups per head, on a ragged batch."""
     rng = np.random.default_rng(seed)
     B, H, N = 2, 2, 24576
     lens = np.array([N, 15001], np.int32)
