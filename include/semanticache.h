@@ -105,13 +105,14 @@ sc_status sc_segment(const uint8_t *mask, int64_t mask_stride_b, const int32_t *
  * order of their seeds, then the chunk's closing delimiter with size 1.  Rows of size 1 (delimiters,
  * unmerged tokens) carry the values of their input row unchanged (widened exactly if out_dtype is
  * wider); the one liberty taken is that a negative zero may come out as a positive zero.
- * Inputs are expected to be finite: the sums run on matrix cores over groups of neighbouring chunks
- * with 0/1 weights, so a NaN or Inf element can turn the same column of other rows of its group into
- * NaN.  The clustering decisions themselves treat NaN similarities as "not above tau".
+ * An element that is not finite shows in its own column of its own cluster's row and nowhere else, and
+ * its key resembles no other (a similarity that is not a number is "not above tau").  Sums are fp32: a
+ * cluster whose sum in a column passes the largest finite fp32 value gets an infinity there.
  * With bf16 inputs, bf16 or fp32 outputs and d = 128 the call runs two kernels (the sequences are cut
  * into windows of whole chunks; every window is clustered, merged and written to its final rows, whose
- * place it learns from the row counts that the windows before it publish); other combinations run a
- * generic three-kernel path with the same results.
+ * place it learns from the row counts that the windows before it publish); other combinations, sequences
+ * of 2^27 tokens or more and calls of millions of heads run a generic three-kernel path with the same
+ * results.
  *
  *   K, V            device [B, Hkv, N_max, d] of in_dtype, addressed as
  *                   base + b*stride_b + h*stride_h + n*stride_n (+ e), strides in ELEMENTS;

@@ -4,7 +4,7 @@
 // not say how a budget becomes the threshold tau of Alg. 1.  The number of rows N'(tau) grows with tau
 // (a higher bar merges less), so the largest tau that still meets the budget is found by bisection.
 // Every probe is the clustering half of sc_gsc_merge (counts only); the threshold lives in device memory.
-// A probe ends in the scan kernel, whose workgroups (one per sequence and head) add up their row counts;
+// A probe ends in the count kernel, whose workgroups (one per sequence and head) add up their row counts;
 // the last of them to arrive moves the bracket and writes the next threshold (where a probe is a complete
 // merge, outside the bf16 / d = 128 path, a small kernel after it does that from the merged lengths).  The
 // whole search is a fixed sequence of launches on the caller's stream with no host synchronisation.  The
@@ -62,7 +62,7 @@ hipError_t launch_gsc_budget(GscMergeArgs a, long long budget_rows, float tau_lo
     const bool counting = gsc_merge_takes_fast_path(a);
     for (int it = 0; it <= iterations; ++it) {     // `iterations` probes, then the launch at the result
         // a probe only needs the row counts: clustering without reading the values, without the merge and
-        // without writing rows, and its scan kernel moves the bracket itself (where the fast path runs;
+        // without writing rows, and its count kernel moves the bracket itself (where the fast path runs;
         // elsewhere a probe is a full merge followed by the update kernel, like the final launch)
         const bool probe = it < iterations;
         a.count_only = probe;

@@ -146,7 +146,7 @@ __device__ __forceinline__ int lane_gather(int x, int src_lane) {
 
 __device__ __forceinline__ uint64_t ballot64(bool pred) { return __builtin_amdgcn_ballot_w64(pred); }
 // 16 bytes that are read (written) once by this launch and not again soon: the non-temporal hint keeps
-// them from displacing lines that are (provisional rows, partials, offsets)
+// them from displacing lines that are (partials, offsets, published counts)
 typedef unsigned int stream_u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load16_stream(const void *p) {
     const stream_u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const stream_u32x4_t *>(p));

@@ -16,12 +16,14 @@
 // A chunk longer than a window runs over several 128-row blocks, its seeds re-read through L2, and its values are read once more for
 // the means.
 //
-// Bounds: the bytes of K, V and the merged rows where chunks are short (8 heads x 131072 tokens, bf16: 537 MB in, a third of
-// it out), fp64 pairs where tau lies inside the band of the similarities, the chain of blocks in long chunks.  Up to a few
-// hundred workgroups it is one window's chain: rows in, Gram product, decisions, the rows before, means, rows out, 20 us in all.
+// Bounds: a window's chain (rows in, Gram product, decisions, the rows before, means, rows out), some 13 us with all places of the chip
+// taken, and the bytes of K, V and the merged rows next (8 heads x 131072 tokens, bf16: 537 MB in, a tenth of it out); fp64
+// pairs where tau lies inside the band of the similarities, the chain of blocks in long chunks.  Up to a few hundred workgroups it is one
+// window's chain alone.
 // Merged rows that are written once, to their final place, and a decision by one wavefront with the pairs shared by four, against
-// provisional rows that a second launch moves, and one wavefront per 64-row task: 8 heads x 32768 54.5 us -> 48.8,
-// 8 x 131072 178 -> 165, 32 sequences x 8 heads x 4096 327 -> 265; tau inside the band, 4 layers x 8 x 32768: 291 -> 190 a layer.
+// provisional rows that a second launch moves, and one wavefront per 64-row task (us per call with its sc_segment): 8 heads x 32768
+// 54.5 -> 49.1, 8 x 131072 178 -> 167, 32 sequences of 8192 to 16384 x 4 heads, tau inside the band, 326 -> 267, 4 x 8 x 32768, tau
+// inside the band, 290 -> 194.
 #include "sc_device.h"
 #include "sc_gsc_params.h"
 #include "sc_gsc_words.h"
