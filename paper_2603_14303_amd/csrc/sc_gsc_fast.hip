@@ -22,8 +22,8 @@
 // window's chain alone.
 // Merged rows that are written once, to their final place, and a decision by one wavefront with the pairs shared by four, against
 // provisional rows that a second launch moves, and one wavefront per 64-row task (us per call with its sc_segment): 8 heads x 32768
-// 54.5 -> 49.1, 8 x 131072 178 -> 167, 32 sequences of 8192 to 16384 x 4 heads, tau inside the band, 326 -> 267, 4 x 8 x 32768, tau
-// inside the band, 290 -> 194.
+// 54.5 -> 49.5, 8 x 131072 178 -> 168, 32 sequences of 8192 to 16384 x 4 heads, tau inside the band, 326 -> 267, 4 x 8 x 32768, tau
+// inside the band, 290 -> 196.
 #include "sc_device.h"
 #include "sc_gsc_params.h"
 #include "sc_gsc_words.h"
@@ -948,7 +948,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
     // what it has published has arrived.  A search takes the slots in order up to the first whose rows are not published, clears the marks that it finds
     // (a long chunk's not before its clusters have arrived, too) and finishes those windows.  So the last of the windows before a left one to publish
     // finds it, if no other has, and every window is finished once, by a workgroup that finds the rows of all before it published.  (The look costs
-    // 0.2 to 1 %: 8 heads x 32768 49.1 us and 49.3, x 131072 165.0 and 166.9.  The value that the addition to the segment's rows can return
+    // 0.4 to 1 %: 8 heads x 32768 49.3 us and 49.5, x 131072 166.5 and 168.3.  The value that the addition to the segment's rows can return
     // would say the same, but its returning form costs 1.5 to 2 %.)
     // The next window to finish goes to `win`, its rows to s.nseed; false: none.  For all wavefronts.
     [[maybe_unused]] auto next_left = [&](bool mark) {

@@ -101,8 +101,9 @@ def test_edges(layout, lens, heads, per_window):
 @pytest.mark.parametrize("centres", [6, 40])                       # up to sixteen clusters in a long chunk, and more
 @pytest.mark.parametrize("keys", [False, True])
 @pytest.mark.parametrize("layout", ["window", "pairs", "long"])
-def test_values_that_are_not_finite_stay_in_their_cluster(layout, keys, centres):
-    """A key that is not finite resembles nothing: its row is a cluster of its own, and its neighbours' sums are theirs alone."""
+@pytest.mark.parametrize("fast", [1, 0])
+def test_values_that_are_not_finite_stay_in_their_cluster(fast, layout, keys, centres):
+    """A key that is not finite resembles nothing: its row is a cluster of its own, and its neighbours' sums are theirs alone; on the generic path, too."""
     lens, heads, tau = (1500,), 2, 0.6
     mask, K, V = _case(50 if centres == 6 else 51, GAPS[layout], lens, heads, centres)
     for i, x in enumerate((np.inf, np.nan, -np.inf)):
@@ -111,7 +112,12 @@ def test_values_that_are_not_finite_stay_in_their_cluster(layout, keys, centres)
         if keys:
             K[0, 0, 60 + 400 * i, 3 * i] = x
             K[0, 1, 1490 - i, 100] = x
-    out = _merge(mask, K, V, lens, tau)
+    old = sc.tune_get("gsc_fast_path")
+    sc.tune_set("gsc_fast_path", fast)
+    try:
+        out = _merge(mask, K, V, lens, tau)
+    finally:
+        sc.tune_set("gsc_fast_path", old)
     o = oracle.segment(mask[0], lens[0])
     for h in range(heads):
         r = oracle.compress_head(K[0, h], V[0, h], o, tau)
