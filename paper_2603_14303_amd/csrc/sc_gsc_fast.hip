@@ -41,6 +41,7 @@ constexpr int kWinWaves = 4;
 constexpr int kWinThreads = kWinWaves * kWave;
 constexpr int kWinRows = 128;            // rows of a window
 constexpr int kAheadWgs = 512;           // workgroups that decide long chunks ahead of the windows (one per head if there are more heads)
+constexpr int kAheadProbes = 1536;       // the same in a counting probe, where nobody waits for anybody (512: long-tailed chunks 558 us instead of 514, 768 to 3072 within 2 %)
 constexpr int kSegRows = 1024;           // rows of a sequence whose chunks one wavefront of the plan kernel packs
 constexpr float kFastBand = 1e-4f;       // fp32 cosine error for d = 128 is < 2e-5; inside the band -> fp64
 
@@ -99,7 +100,9 @@ __device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {   // position of
 // neighbouring wavefronts meet at the first chunk that starts in the later one's rows.  Slots that are left over are
 // filed as empty, and what the windows' workgroups will publish is cleared: the workspace may hold anything.
 // Bound by its chain: two trips to memory and the walk.
-__global__ __launch_bounds__(kWave) void gsc_plan_kernel(GscParams p) {
+// start: the budget search that begins with this plan, if any.
+template <typename... Start>
+__global__ __launch_bounds__(kWave) void gsc_plan_kernel(GscParams p, Start... start) {
     constexpr int kSpan = kSegRows + kWinRows;       // rows whose delimiters the walk can ask for
     constexpr int kLook = 8;
     __shared__ uint32_t s_bits[kWave];               // (kSpan / 32 + 5 <= 64 words)
@@ -114,6 +117,9 @@ __global__ __launch_bounds__(kWave) void gsc_plan_kernel(GscParams p) {
     GscWindow *win = p.windows + (int64_t)b * slots + (int64_t)seg * S;
     const int seg0 = seg * kSegRows;
     s_bits[lane] = 0u;
+    if constexpr (sizeof...(Start) != 0) {
+        if (blockIdx.x == 0 && lane == 0) budget_begin(start...);
+    }
     if (lane == 0) s_off[kLook * kWave] = 0x7FFFFFFF;
     int used = 0, n_long = 0;
     GscLongs *longs = p.longs + (int64_t)b * (slots / S) + seg;
@@ -269,7 +275,10 @@ __global__ __launch_bounds__(kWave) void gsc_plan_kernel(GscParams p) {
         const int64_t at = (bh0 + h) * slots + (int64_t)seg * S;
         for (int k = lane & 15; k < S; k += 16) {
             p.published[at + k] = k < used ? 0u : kPubRows;
-            if (p.count_only) p.win_count[at + k] = 0;
+            if (p.count_only && k >= used) {
+                uint4 *none = reinterpret_cast<uint4 *>(p.win_count + (at + k) * kProbeWords);
+                none[0] = none[1] = make_uint4(0u, 0u, 0u, 0u);
+            }
         }
         if ((lane & 15) == 0) p.segments[(bh0 + h) * segments + seg] = GscSegment{segment_start(used), 0u};
     }
@@ -470,6 +479,20 @@ __device__ __forceinline__ uint64_t row_word(const uint32_t (*words)[4], int row
     return *reinterpret_cast<const uint64_t *>(&words[row][2 * half]);
 }
 
+__device__ __forceinline__ void wave_handover() {   // LDS traffic of one wavefront executes in order: only the compiler must not reorder
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+// a pair of rows, one sixteenth of either in each lane of sixteen
+__device__ __forceinline__ bool settle_one(const uint4 &a, const uint4 &b, float tau) {
+    double dot = 0.0, sa = 0.0, sb = 0.0;
+    cosine_sums_f64(a, b, dot, sa, sb);
+    dot = row_allreduce_sum(dot);
+    sa = row_allreduce_sum(sa);
+    sb = row_allreduce_sum(sb);
+    return cosine_exceeds_f64(dot, sa, sb, tau);
+}
 // Pairs of s.list, `n` of them, by the whole workgroup: row, and partner (another row of the window, or with a chunk's seed rows given the
 // number of a carried seed, whose key is fetched from memory).  A pair takes the 16 lanes of a row, so sixteen are settled
 // at once: the chain of a pair is long, and a threshold inside the band of the similarities asks for many.
@@ -487,13 +510,7 @@ __device__ __forceinline__ void settle_share(CompressLds &s, int n, float tau, i
         } else {
             a = *reinterpret_cast<const uint4 *>(s.rows + i * kKeyRowBytes + 16 * c);
         }
-        const uint4 bb = *reinterpret_cast<const uint4 *>(s.rows + j * kKeyRowBytes + 16 * c);
-        double dot = 0.0, sa = 0.0, sb = 0.0;
-        cosine_sums_f64(a, bb, dot, sa, sb);
-        dot = row_allreduce_sum(dot);
-        sa = row_allreduce_sum(sa);
-        sb = row_allreduce_sum(sb);
-        const bool above = cosine_exceeds_f64(dot, sa, sb, tau);
+        const bool above = settle_one(a, *reinterpret_cast<const uint4 *>(s.rows + j * kKeyRowBytes + 16 * c), tau);
         if (c == 0 && e < n) s.above[e] = above ? 1u : 0u;
     }
 }
@@ -513,6 +530,31 @@ __device__ __forceinline__ Pair64 settle_pairs(CompressLds &s, const Pair64 &tod
     Pair64 r;
     r.a = ballot64(in_a && s.above[min(at_a, kWinRows - 1)] != 0u);
     r.b = ballot64(in_b && s.above[min(at_b, kWinRows - 1)] != 0u);
+    return r;
+}
+// The same by one wavefront for itself (a probe's four wavefronts decide at thresholds of their own), with the rows from memory: the window's
+// keys are at Kwin.  list: room for 2 * kWinRows words in LDS.
+__device__ __forceinline__ Pair64 settle_alone(uint32_t *list, const bf16_t *Kwin, int64_t stride_n, const Pair64 &todo, int other_a, int other_b, float tau, int lane) {
+    const int g = lane >> 4, c = lane & 15;
+    uint32_t *above = list + kWinRows;
+    const int n_a = __popcll(todo.a), n = n_a + __popcll(todo.b);
+    const bool in_a = (todo.a >> lane) & 1ull, in_b = (todo.b >> lane) & 1ull;
+    const int at_a = __popcll(todo.a & bits_below(lane)), at_b = n_a + __popcll(todo.b & bits_below(lane));
+    if (in_a) list[at_a] = ((uint32_t)other_a << 8) | (uint32_t)lane;
+    if (in_b) list[at_b] = ((uint32_t)other_b << 8) | (uint32_t)(64 + lane);
+    wave_handover();
+    for (int e0 = 0; e0 < n; e0 += 4) {
+        const int e = e0 + g;
+        const uint32_t w = list[min(e, n - 1)];
+        const bool yes = settle_one(*reinterpret_cast<const uint4 *>(Kwin + (int64_t)(w >> 8) * stride_n + 8 * c),
+                                    *reinterpret_cast<const uint4 *>(Kwin + (int64_t)(w & 0xFFu) * stride_n + 8 * c), tau);
+        if (c == 0 && e < n) above[e] = yes ? 1u : 0u;
+    }
+    wave_handover();
+    Pair64 r;
+    r.a = ballot64(in_a && above[min(at_a, kWinRows - 1)] != 0u);
+    r.b = ballot64(in_b && above[min(at_b, kWinRows - 1)] != 0u);
+    wave_handover();
     return r;
 }
 // the other wavefronts, until the deciding one is done
@@ -547,7 +589,9 @@ struct Decision {
 // the later row joins: the first such pair of every row is settled in fp64 and the fixed point is taken
 // again.  Returns false, with nothing decided but the settled pairs, if the set has not settled after a few applications of F or
 // pairs keep turning up: the caller then takes the seeds one at a time.
-__device__ __forceinline__ bool first_fit_fixed_point(CompressLds &s, Words &y, Words &u, bool open_a, bool open_b, float tau, int lane, int wave, Decision &d) {
+// settle(set, other_a, other_b): for every row of the set the pair with the partner given for it; the rows whose pair is above tau.
+template <typename Settle>
+__device__ __forceinline__ bool first_fit_fixed_point(Settle settle, Words &y, Words &u, bool open_a, bool open_b, int lane, Decision &d) {
     for (int pass = 0; pass < 8; ++pass) {
         Pair64 S;
         S.a = ballot64(open_a && y.a == 0ull);
@@ -579,7 +623,7 @@ __device__ __forceinline__ bool first_fit_fixed_point(CompressLds &s, Words &y, 
         }
         const int oa = doubt_a != 0ull ? first_bit(doubt_a) : 0;
         const int ob = doubt_b0 != 0ull ? first_bit(doubt_b0) : (doubt_b1 != 0ull ? 64 + first_bit(doubt_b1) : 0);
-        const Pair64 above = settle_pairs(s, doubtful, oa, ob, tau, lane, wave, nullptr, 0, nullptr);
+        const Pair64 above = settle(doubtful, oa, ob);
         if ((doubtful.a >> lane) & 1ull) {
             u.a &= ~(1ull << oa);
             if ((above.a >> lane) & 1ull) y.a |= 1ull << oa;
@@ -596,7 +640,8 @@ __device__ __forceinline__ bool first_fit_fixed_point(CompressLds &s, Words &y, 
 
 // The literal loop: per round every chunk takes its first open row as its next seed, and the open rows with that bit set join it
 // (chunks never interact, so their loops run side by side; inside a chunk the order is exactly Alg. 1's).  ra, rb: the chunk's rows for the lane's rows.
-__device__ __forceinline__ void first_fit_by_seed(CompressLds &s, Words &y, Words &u, Pair64 todo, const Pair64 &ra, const Pair64 &rb, float tau, int lane, int wave, Decision &d) {
+template <typename Settle>
+__device__ __forceinline__ void first_fit_by_seed(Settle settle, Words &y, Words &u, Pair64 todo, const Pair64 &ra, const Pair64 &rb, int lane, Decision &d) {
     d.seeds.a = d.seeds.b = 0ull;
     d.seed_a = d.seed_b = -1;
     while ((todo.a | todo.b) != 0ull) {
@@ -613,7 +658,7 @@ __device__ __forceinline__ void first_fit_by_seed(CompressLds &s, Words &y, Word
         ask.a = ballot64(cand_a && ((u.a >> (sa & 63)) & 1ull));
         ask.b = ballot64(cand_b && (((sb < 64 ? u.b0 : u.b1) >> (sb & 63)) & 1ull));
         if ((ask.a | ask.b) != 0ull) {
-            const Pair64 above = settle_pairs(s, ask, sa & 127, sb & 127, tau, lane, wave, nullptr, 0, nullptr);
+            const Pair64 above = settle(ask, sa & 127, sb & 127);
             yes_a = yes_a || ((above.a >> lane) & 1ull);
             yes_b = yes_b || ((above.b >> lane) & 1ull);
         }
@@ -626,6 +671,50 @@ __device__ __forceinline__ void first_fit_by_seed(CompressLds &s, Words &y, Word
         todo.a &= ~(new_a | got_a);
         todo.b &= ~(new_b | got_b);
     }
+}
+// The lane's two rows of a window of whole chunks: where their chunks start; a delimiter is a chunk of its own.
+struct RowChunks {
+    int lo_a, lo_b;
+    bool delim_a, delim_b, open_a, open_b;
+    __device__ __forceinline__ RowChunks(const Pair64 &D, int R, int lane) {
+        const uint64_t below = bits_below(lane), da = D.a & below, db = D.b & below;
+        lo_a = da != 0ull ? 1 + last_bit(da) : 0;
+        lo_b = db != 0ull ? 65 + last_bit(db) : (D.a != 0ull ? 1 + last_bit(D.a) : 0);
+        delim_a = (D.a >> lane) & 1ull;
+        delim_b = (D.b >> lane) & 1ull;
+        open_a = lane < R;
+        open_b = 64 + lane < R;
+    }
+};
+// Alg. 1 in a window of whole chunks (delimiters D, R rows) from its bit matrices
+template <typename Settle>
+__device__ __forceinline__ void decide_window(const RowChunks &r, const uint32_t (*yes)[4], const uint32_t (*unsure)[4], const int &any_unsure, const Pair64 &D, int R,
+                                              int lane, Settle settle, Decision &d) {
+    const uint64_t below = bits_below(lane);
+    const uint64_t before_a = (r.delim_a || !r.open_a) ? 0ull : below & ~bits_below(r.lo_a);
+    const uint64_t before_b0 = (r.delim_b || !r.open_b) ? 0ull : ~bits_below(min(r.lo_b, 64));
+    const uint64_t before_b1 = (r.delim_b || !r.open_b) ? 0ull : below & ~bits_below(max(r.lo_b - 64, 0));
+    Words y, u;
+    y.a = row_word(yes, lane, 0) & before_a;
+    y.b0 = row_word(yes, 64 + lane, 0) & before_b0;
+    y.b1 = row_word(yes, 64 + lane, 1) & before_b1;
+    u.a = u.b0 = u.b1 = 0ull;
+    if (uniform(any_unsure) != 0) {
+        u.a = row_word(unsure, lane, 0) & before_a;
+        u.b0 = row_word(unsure, 64 + lane, 0) & before_b0;
+        u.b1 = row_word(unsure, 64 + lane, 1) & before_b1;
+    }
+    if (first_fit_fixed_point(settle, y, u, r.open_a, r.open_b, lane, d)) return;
+    // chunk ranges: up to the first delimiter from the row on
+    const uint64_t ea = D.a & ~below, eb = D.b & ~below;
+    const int hi_a = ea != 0ull ? first_bit(ea) : (D.b != 0ull ? 64 + first_bit(D.b) : R);
+    const int hi_b = eb != 0ull ? 64 + first_bit(eb) : R;
+    const int la = r.delim_a ? lane : r.lo_a, ha = r.delim_a ? lane + 1 : hi_a;
+    const int lb = r.delim_b ? 64 + lane : r.lo_b, hb = r.delim_b ? 65 + lane : hi_b;
+    const Pair64 ra = {bits_below(min(ha, 64)) & ~bits_below(min(la, 64)), bits_below(max(ha - 64, 0)) & ~bits_below(max(la - 64, 0))};
+    const Pair64 rb = {bits_below(min(hb, 64)) & ~bits_below(min(lb, 64)), bits_below(max(hb - 64, 0)) & ~bits_below(max(lb - 64, 0))};
+    const Pair64 all = {bits_below(min(R, 64)), bits_below(max(R - 64, 0))};
+    first_fit_by_seed(settle, y, u, all, ra, rb, lane, d);
 }
 __device__ __forceinline__ int rows_below(const Pair64 &set, int row) {      // rows of the set before `row` (0..128)
     return __popcll(set.a & bits_below(min(row, 64))) + __popcll(set.b & bits_below(max(row - 64, 0)));
@@ -831,7 +920,106 @@ __device__ __forceinline__ ConstParams *fresh_params() {
     const int lane = fresh_lane();        \
     [[maybe_unused]] const int g = lane >> 4, c = lane & 15
 
-// COUNT: a probe of the budget search.  Only the number of rows is wanted: no values are read and nothing is merged.
+// ------------------------------------------------------------------------------------------------
+// A probe of the budget search: the rows of a window at up to seven thresholds from one reading of its keys.  The cosines of its Gram
+// matrix stay in registers (five pairs of tiles per wavefront); once all are there, bit matrices of all thresholds take the place of the
+// keys in LDS, and every wavefront decides at one or two of them by itself.
+struct ProbeWords {
+    uint32_t yes[kProbeWords][kWinRows][4], unsure[kProbeWords][kWinRows][4];
+};
+static_assert(sizeof(ProbeWords) <= kWinRows * kKeyRowBytes, "in place of the keys");
+
+// OR over the four 16-lane rows, same lane position, of four values: row g gets the one of v[g]
+__device__ __forceinline__ uint32_t or_rows_transposed(const uint32_t (&v)[4]) {
+    auto r = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+    const uint32_t x = r[0] | r[1];
+    r = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+    const uint32_t z = r[0] | r[1];
+    r = __builtin_amdgcn_permlane16_swap(x, z, false, false);
+    return r[0] | r[1];
+}
+constexpr int kProbePairs = 5;      // pairs of row tiles of a wavefront's two column tiles, 7 - wave and wave: (9 - wave) / 2 and wave / 2 + 1
+struct ProbeTiles {
+    floatx4_t cosine[kProbePairs][2];
+    uint32_t live;                  // bit q: pair q lies in the window and holds pairs of one chunk
+};
+__device__ __forceinline__ void probe_pair(int q, int wave, int &J, int &I2) {      // column tile and pair of row tiles
+    const int n0 = (9 - wave) >> 1;
+    J = q < n0 ? 7 - wave : wave;
+    I2 = q < n0 ? q : q - n0;
+}
+__device__ __forceinline__ void probe_products(const CompressLds &s, const Pair64 &D, int R, int wave, int g, int c, ProbeTiles &t) {
+    t.live = 0u;
+#pragma unroll
+    for (int q = 0; q < kProbePairs; ++q) {
+        int J, I2;
+        probe_pair(q, wave, J, I2);
+        const uint64_t da = D.a & bits_below(min(16 * J, 64)), db = D.b & bits_below(max(16 * J - 64, 0));
+        const int lo = db != 0ull ? 65 + last_bit(db) : (da != 0ull ? 1 + last_bit(da) : 0);      // first row of the chunk of row 16 J
+        if (16 * J >= R || I2 < (lo >> 5)) continue;
+        t.live |= 1u << q;
+        floatx4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int col = (32 * ks + 8 * g) * 2;
+            const bf16x8f_t b = __builtin_bit_cast(bf16x8f_t, *reinterpret_cast<const uint4 *>(s.rows + (16 * J + c) * kKeyRowBytes + col));
+            const char *at = s.rows + (32 * I2 + c) * kKeyRowBytes + col;
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8f_t, *reinterpret_cast<const uint4 *>(at)), b, acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8f_t, *reinterpret_cast<const uint4 *>(at + 16 * kKeyRowBytes)), b, acc1, 0, 0, 0);
+        }
+        // (two roundings more than the band's other users have: a few 2^-24 of a cosine, the band is 1e-4.)  Rows that do not exist have a
+        // reciprocal norm of zero; a norm that is not usable makes all its cosines not a number.
+        const floatx4_t rm0 = *reinterpret_cast<const floatx4_t *>(s.rinv + 32 * I2 + 4 * g), rm1 = *reinterpret_cast<const floatx4_t *>(s.rinv + 32 * I2 + 16 + 4 * g);
+        const float rn = s.rinv[16 * J + c];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            t.cosine[q][0][i] = acc0[i] * (rm0[i] * rn);
+            t.cosine[q][1][i] = acc1[i] * (rm1[i] * rn);
+        }
+    }
+}
+// The wavefront's tiles at four thresholds: words of threshold k to yes[k] and unsure[k], all four at once.  A subtraction and a shift of
+// its sign bit (v_alignbit) per pair and threshold, and half a minimum that tells whether any pair came near.
+__device__ __forceinline__ void probe_words(const ProbeTiles &t, const float (&tau)[kWinWaves], bool odd, int wave, int g, int c, uint32_t (*yes)[4], uint32_t (*unsure)[4]) {
+#pragma unroll
+    for (int q = 0; q < kProbePairs; ++q) {
+        if (((t.live >> q) & 1u) == 0u) continue;
+        int J, I2;
+        probe_pair(q, wave, J, I2);
+        uint32_t y[kWinWaves], u[kWinWaves];
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < kWinWaves; ++k) {
+            float diff[8], least = 1.f;
+            uint32_t n0 = 0u, n1 = 0u;
+#pragma unroll
+            for (int i = 3; i >= 0; --i) {
+                diff[i] = tau[k] - t.cosine[q][0][i];
+                diff[4 + i] = tau[k] - t.cosine[q][1][i];
+                n0 = __builtin_amdgcn_alignbit(n0, __float_as_uint(diff[i]), 31);      // (n0 << 1) | sign bit
+                n1 = __builtin_amdgcn_alignbit(n1, __float_as_uint(diff[4 + i]), 31);
+                least = fminf(least, fminf(fabsf(diff[i]), fabsf(diff[4 + i])));
+            }
+            u[k] = 0u;
+            y[k] = (n0 | (n1 << 16)) << (4 * g);
+            if (odd || ballot64(least <= kFastBand) != 0ull) {      // (a minimum passes over what is not a number)
+                uint32_t near = 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    near |= !(fabsf(diff[i]) > kFastBand) ? 1u << i : 0u;
+                    near |= !(fabsf(diff[4 + i]) > kFastBand) ? 65536u << i : 0u;
+                }
+                u[k] = near << (4 * g);
+                any = true;
+            }
+        }
+        const uint32_t yy = or_rows_transposed(y), uu = any ? or_rows_transposed(u) : 0u;
+        yes[16 * J + c][I2] = yy & ~uu;
+        unsure[16 * J + c][I2] = uu;
+    }
+}
+
+// COUNT: a probe of the budget search.  Only the numbers of rows are wanted: no values are read and nothing is merged.
 template <typename TO, bool COUNT>
 __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams p) {
     __shared__ __attribute__((aligned(16))) CompressLds s;
@@ -839,8 +1027,10 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
     // heads the windows of a head stay on one XCD.  Long chunks are decided ahead of everything else, by ahead_per_head workgroups per
     // head that wait for nothing: a window waits for the rows of all before it, and a long chunk in between, which takes twice as long, would hold up
     // those of half the chip (8 heads x 131072, a quarter of the windows long: 225 us, decided ahead 165).
+    // (A probe's work ahead is a long chunk at one threshold.)
     const int n_bh = p.B * p.Hkv;
-    const int ahead_wgs = COUNT ? 0 : p.ahead_wgs;
+    const int ahead_wgs = p.ahead_wgs;
+    [[maybe_unused]] const int nodes = COUNT ? (1 << p.probe_levels) - 1 : 1;
     const bool ahead = (int)blockIdx.x < ahead_wgs;
     const unsigned id = ahead ? blockIdx.x : blockIdx.x - (unsigned)ahead_wgs;
     const int place = (int)(id / (unsigned)n_bh), bh_i = (int)(id - (unsigned)place * (unsigned)n_bh);
@@ -881,26 +1071,32 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         }
         return false;
     };
-    [[maybe_unused]] int next_long = place;
+    int next_long = place;
     Window win, next;
     Pair64 D = {0ull, 0ull};
     if (!ahead) {
         win = take_window(place, &D);
-        if (win.rows <= 0) return;
+        if (win.rows <= 0 || (COUNT && (win.flags & kWinLong) != 0)) return;
     } else {
-        if (!take_long(next_long, win)) return;
+        if (!take_long(next_long / nodes, win)) return;
         D.a = D.b = 0ull;
     }
     const int &slot = win.slot, &w0 = win.first, &R = win.rows, &flags = win.flags;
     const int tid = threadIdx.x, wave = uniform(tid / kWave);
     const bf16_t *Kbh = reinterpret_cast<const bf16_t *>(p.K) + b * p.stride_b + h * p.stride_h;
     const bf16_t *Vbh = reinterpret_cast<const bf16_t *>(p.V) + b * p.stride_b + h * p.stride_h;
-    const float tau = p.tau_dev ? *p.tau_dev : p.tau;
+    float tau = p.tau_dev ? *p.tau_dev : p.tau;
+    [[maybe_unused]] float tau_lo = 0.f, tau_hi = 0.f;      // the search's bracket
+    if constexpr (COUNT) {
+        tau_lo = p.budget->lo;
+        tau_hi = p.budget->hi;
+        if (ahead) tau = budget_node_tau(tau_lo, tau_hi, 1 + next_long % nodes);
+    }
     // the window's rows are known: tell the windows behind it
     auto publish = [&](int rows, bool is_long, int lane) {      // one wavefront
         SC_FRESH_PARAMS;
         if (lane == 0) {
-            if constexpr (COUNT) p.win_count[bh * p.win_slots + slot] = rows;
+            if constexpr (COUNT) p.win_count[(bh * p.win_slots + slot) * kProbeWords + next_long % nodes] = rows;      // (a long chunk)
             else {
                 const int S = p.slots_per_segment;
                 uint32_t *pub = p.published + bh * p.win_slots;
@@ -1023,10 +1219,35 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         }
         __syncthreads();
         const bool odd = uniform(*reinterpret_cast<const int *>(s.odd_norms)) != 0;
+        if constexpr (COUNT) {
+            SC_FRESH_LANE;
+            ProbeTiles tiles;
+            probe_products(s, D, R, wave, g, c, tiles);
+            const RowChunks rows(D, R, lane);
+            __syncthreads();      // the keys have been read
+            ProbeWords &words = *reinterpret_cast<ProbeWords *>(s.rows);
+            for (int t0 = 0; t0 < nodes; t0 += kWinWaves) {
+                float taus[kWinWaves];
+#pragma unroll
+                for (int k = 0; k < kWinWaves; ++k) taus[k] = budget_node_tau(tau_lo, tau_hi, min(t0 + k, nodes - 1) + 1);
+                // (lane group g files the words of threshold t0 + g)
+                probe_words(tiles, taus, odd, wave, g, c, words.yes[t0 + g], words.unsure[t0 + g]);
+            }
+            __syncthreads();
+            for (int t = wave; t < nodes; t += kWinWaves) {
+                const float mine = budget_node_tau(tau_lo, tau_hi, t + 1);
+                uint32_t *list = (wave < 2 ? &s.yes[0][0] : &s.unsure[0][0]) + (wave & 1) * 2 * kWinRows;
+                Decision d;
+                decide_window(rows, words.yes[t], words.unsure[t], 1, D, R, lane,
+                              [&](const Pair64 &ask, int oa, int ob) { return settle_alone(list, Kbh + (int64_t)w0 * p.stride_n, p.stride_n, ask, oa, ob, mine, lane); }, d);
+                if (lane == 0) p.win_count[(bh * p.win_slots + slot) * kProbeWords + t] = __popcll(d.seeds.a) + __popcll(d.seeds.b);
+            }
+            return;
+        } else {
         // the values, on their way while the rows are decided.  (Requested with the keys they delay those of the windows behind, and with
         // them everything that waits for those windows' rows.)
-        [[maybe_unused]] RowRegs xv;
-        if constexpr (!COUNT) {
+        RowRegs xv;
+        {
             SC_FRESH_LANE;
             load_rows(xv, Vbh, p.stride_n, w0 + 32 * wave, min(32, R - 32 * wave), g, c);
         }
@@ -1042,52 +1263,24 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             }
         }
         __syncthreads();
-        [[maybe_unused]] ColumnOps kk;
+        ColumnOps kk;
         const int nks = (R + 31) >> 5;
         if (wave == decider) {
             SC_FRESH_LANE;
-            // rows [lo, r) of the lane's rows' chunks; a delimiter is a chunk of its own
-            const uint64_t below = bits_below(lane);
-            const uint64_t da = D.a & below, db = D.b & below;
-            const int lo_a = da != 0ull ? 1 + last_bit(da) : 0;
-            const int lo_b = db != 0ull ? 65 + last_bit(db) : (D.a != 0ull ? 1 + last_bit(D.a) : 0);
-            const bool delim_a = (D.a >> lane) & 1ull, delim_b = (D.b >> lane) & 1ull;
-            const bool open_a = lane < R, open_b = 64 + lane < R;
-            const uint64_t before_a = (delim_a || !open_a) ? 0ull : below & ~bits_below(lo_a);
-            const uint64_t before_b0 = (delim_b || !open_b) ? 0ull : ~bits_below(min(lo_b, 64));
-            const uint64_t before_b1 = (delim_b || !open_b) ? 0ull : below & ~bits_below(max(lo_b - 64, 0));
-            Words y, u;
-            y.a = row_word(s.yes, lane, 0) & before_a;
-            y.b0 = row_word(s.yes, 64 + lane, 0) & before_b0;
-            y.b1 = row_word(s.yes, 64 + lane, 1) & before_b1;
-            u.a = u.b0 = u.b1 = 0ull;
-            if (uniform(s.any_unsure) != 0) {
-                u.a = row_word(s.unsure, lane, 0) & before_a;
-                u.b0 = row_word(s.unsure, 64 + lane, 0) & before_b0;
-                u.b1 = row_word(s.unsure, 64 + lane, 1) & before_b1;
-            }
+            const RowChunks rows(D, R, lane);
+            const bool open_a = rows.open_a, open_b = rows.open_b;
             Decision d;
-            if (!first_fit_fixed_point(s, y, u, open_a, open_b, tau, lane, wave, d)) {
-                // chunk ranges: up to the first delimiter from the row on
-                const uint64_t ea = D.a & ~below, eb = D.b & ~below;
-                const int hi_a = ea != 0ull ? first_bit(ea) : (D.b != 0ull ? 64 + first_bit(D.b) : R);
-                const int hi_b = eb != 0ull ? 64 + first_bit(eb) : R;
-                const int la = delim_a ? lane : lo_a, ha = delim_a ? lane + 1 : hi_a;
-                const int lb = delim_b ? 64 + lane : lo_b, hb = delim_b ? 65 + lane : hi_b;
-                const Pair64 ra = {bits_below(min(ha, 64)) & ~bits_below(min(la, 64)), bits_below(max(ha - 64, 0)) & ~bits_below(max(la - 64, 0))};
-                const Pair64 rb = {bits_below(min(hb, 64)) & ~bits_below(min(lb, 64)), bits_below(max(hb - 64, 0)) & ~bits_below(max(lb - 64, 0))};
-                const Pair64 all = {bits_below(min(R, 64)), bits_below(max(R - 64, 0))};
-                first_fit_by_seed(s, y, u, all, ra, rb, tau, lane, wave, d);
-            }
+            decide_window(rows, s.yes, s.unsure, s.any_unsure, D, R, lane,
+                          [&](const Pair64 &ask, int oa, int ob) { return settle_pairs(s, ask, oa, ob, tau, lane, wave, nullptr, 0, nullptr); }, d);
             const int nseed = __popcll(d.seeds.a) + __popcll(d.seeds.b);
             publish(nseed, false, lane);
-            if constexpr (!COUNT) {
+            {
                 const int out_a = open_a ? rows_below(d.seeds, d.seed_a) : -1, out_b = open_b ? rows_below(d.seeds, d.seed_b) : -1;
                 SC_FRESH_PARAMS;
                 if (p.cluster_id) {
                     int32_t *cid = p.cluster_id + bh * p.N_max + w0;
-                    if (open_a) cid[lane] = delim_a ? -1 : out_a - rows_below(d.seeds, lo_a);
-                    if (open_b) cid[64 + lane] = delim_b ? -1 : out_b - rows_below(d.seeds, lo_b);
+                    if (open_a) cid[lane] = rows.delim_a ? -1 : out_a - rows_below(d.seeds, rows.lo_a);
+                    if (open_b) cid[64 + lane] = rows.delim_b ? -1 : out_b - rows_below(d.seeds, rows.lo_b);
                 }
                 file_membership(s, out_a, out_b, (nseed + 15) >> 4, lane);
                 if (lane == 0) s.nseed = nseed;
@@ -1096,10 +1289,10 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             decided(s, lane);
         } else {
             SC_FRESH_LANE;
-            if constexpr (!COUNT) column_operands(s, wave, g, c, nks, kk);
+            column_operands(s, wave, g, c, nks, kk);
             settle_until_decided(s, tau, lane, wave, nullptr, 0, nullptr);
         }
-        if constexpr (!COUNT) {
+        {
             // everybody has the keys: the values take their place
             SC_FRESH_LANE;
             const int nseed = uniform(s.nseed);
@@ -1158,14 +1351,13 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                 mark = true;
             }
             own = false;
-        } else {
-            return;
+        }
         }
     }
 
     // ---------------- one chunk longer than a window: blocks of 128 rows.  Seeds are listed in the workspace (row and reciprocal norm); a block's rows
     // are first compared with the seeds of the blocks before, 64 at a time, sixteen per wavefront, then among themselves.
-    else if (COUNT || ahead) {
+    else if (ahead) {
     own = false;
     RowRegs x;
     {
@@ -1175,15 +1367,17 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
     for (;;) {
     SC_FRESH_PARAMS;
     // (the next one is looked up and its first rows are requested while this one is worked on)
-    bool more = false;
-    if (ahead) {
-        next_long += p.ahead_per_head;
-        more = take_long(next_long, next);
-    }
+    const int after = next_long + p.ahead_per_head;
+    const bool more = take_long(after / nodes, next);
     const int start = w0, l = R;
     const bool closed = (flags & kWinClosed) != 0;
     int32_t *seed_rows = p.seedrow + bh * p.N_max + start;
     int32_t *seed_rinv = p.stmp + bh * p.N_max + start;
+    if constexpr (COUNT) {      // the chunk is decided at several thresholds at once: a list for each, where the means of a merge would go
+        const int64_t lists = (int64_t)n_bh * kProbeWords * p.N_max;
+        seed_rows = reinterpret_cast<int32_t *>(p.rows_ws) + (bh * kProbeWords + next_long % nodes) * p.N_max + start;
+        seed_rinv = seed_rows + lists;
+    }
     int32_t *cid = p.cid + bh * p.N_max + start;
     const bf16_t *Kch = Kbh + (int64_t)start * p.stride_n;
     // The first sixteen stay at hand: their keys in registers (the A operand of the comparison), their sums over the keys in accumulators.  If there are
@@ -1322,9 +1516,10 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                     u.b1 = open_b ? row_word(s.unsure, 64 + lane, 1) & below & open.b : 0ull;
                 }
                 Decision d;
-                if (!first_fit_fixed_point(s, y, u, open_a, open_b, tau, lane, wave, d)) {
+                auto settle = [&](const Pair64 &ask, int oa, int ob) { return settle_pairs(s, ask, oa, ob, tau, lane, wave, nullptr, 0, nullptr); };
+                if (!first_fit_fixed_point(settle, y, u, open_a, open_b, lane, d)) {
                     const Pair64 all = {~0ull, ~0ull};
-                    first_fit_by_seed(s, y, u, open, all, all, tau, lane, wave, d);
+                    first_fit_by_seed(settle, y, u, open, all, all, lane, d);
                 }
                 if (open_a) my_a = nseeds + rows_below(d.seeds, d.seed_a);
                 if (open_b) my_b = nseeds + rows_below(d.seeds, d.seed_b);
@@ -1348,8 +1543,8 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                 now = nseeds + __popcll(d.seeds.a) + __popcll(d.seeds.b);
             }
             // cluster of every row: the caller's output, and what the sweeps for the means read back
-            if (lane < Rb) __hip_atomic_store(cid + rb + lane, my_a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (64 + lane < Rb) __hip_atomic_store(cid + rb + 64 + lane, my_b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!COUNT && lane < Rb) __hip_atomic_store(cid + rb + lane, my_a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!COUNT && 64 + lane < Rb) __hip_atomic_store(cid + rb + 64 + lane, my_b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (lane == 0) s.nseed = now;
             if constexpr (!COUNT) file_membership(s, (lane < Rb) ? my_a : -1, (64 + lane < Rb) ? my_b : -1, 1, lane);
             if (nx >= l) publish(now + (closed ? 1 : 0), true, lane);
@@ -1388,8 +1583,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         }
         __syncthreads();      // the next block overwrites the parked keys and the words
     }
-    if constexpr (COUNT) return;
-    else {
+    if constexpr (!COUNT) {
         uint32_t *pub = p.published + bh * p.win_slots;
         if (nseeds <= 16) {
             SC_FRESH_LANE;
@@ -1407,9 +1601,11 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) __hip_atomic_fetch_or(pub + slot, kPubReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!uniform(more ? 1 : 0)) break;
-        win = Window{uniform(next.slot), uniform(next.first), uniform(next.rows), uniform(next.flags)};
     }
+    if (!uniform(more ? 1 : 0)) break;
+    win = Window{uniform(next.slot), uniform(next.first), uniform(next.rows), uniform(next.flags)};
+    next_long = after;
+    if constexpr (COUNT) tau = budget_node_tau(tau_lo, tau_hi, 1 + next_long % nodes);
     }
     if constexpr (!COUNT) {
         if (!any_left(wave == 0)) return;      // (the rows arrived before the clusters were announced)
@@ -1573,24 +1769,37 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
 }
 
 // ------------------------------------------------------------------------------------------------
-// count: rows of every (sequence, head) after a counting probe, and what the budget search does with them
-__global__ __launch_bounds__(256) void gsc_count_kernel(GscParams p) {
-    __shared__ int s_sum[4];
+// count: rows of every (sequence, head) at each threshold of a counting probe, and what the budget search does with them.  Two threads a window,
+// 512 windows at a time: one trip to memory for a sequence of 32768 tokens, and a kernel of little else.
+constexpr int kCountThreads = 1024;
+__global__ __launch_bounds__(kCountThreads) void gsc_count_kernel(GscParams p) {
+    constexpr int kWaves = kCountThreads / kWave;
+    static_assert(kProbeWords == 8 && kWaves == 16, "two threads a window; two wavefronts a lane in the last sum");
+    __shared__ __attribute__((aligned(16))) int s_sum[kWaves][kProbeWords];
     const int64_t bh = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int32_t *cnt = p.win_count + bh * p.win_slots;
-    int sum = 0;
-    for (int i = tid; i < p.win_slots; i += 256) sum += cnt[i];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid / kWave), half = tid & 1;
+    const int4 *cnt = reinterpret_cast<const int4 *>(p.win_count + bh * p.win_slots * kProbeWords) + half;
+    int4 sum = make_int4(0, 0, 0, 0);
+    for (int i = tid >> 1; i < p.win_slots; i += 2 * (kCountThreads / 2)) {
+        const int j = i + kCountThreads / 2;
+        const int4 x = cnt[2 * (int64_t)i], y = j < p.win_slots ? cnt[2 * (int64_t)j] : make_int4(0, 0, 0, 0);
+        sum.x += x.x + y.x; sum.y += x.y + y.y; sum.z += x.z + y.z; sum.w += x.w + y.w;
+    }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kWave);
-    if (lane == 0) s_sum[wave] = sum;
+    for (int d = 32; d >= 2; d >>= 1) {
+        sum.x += __shfl_xor(sum.x, d, kWave); sum.y += __shfl_xor(sum.y, d, kWave);
+        sum.z += __shfl_xor(sum.z, d, kWave); sum.w += __shfl_xor(sum.w, d, kWave);
+    }
+    if (lane < 2) *reinterpret_cast<int4 *>(&s_sum[wave][4 * half]) = sum;
     __syncthreads();
-    if (tid == 0) {
+    if (wave == 0) {
+        int at = s_sum[lane / kProbeWords][lane & (kProbeWords - 1)] + s_sum[lane / kProbeWords + 8][lane & (kProbeWords - 1)];
+#pragma unroll
+        for (int d = 32; d >= kProbeWords; d >>= 1) at += __shfl_xor(at, d, kWave);
         bool bad;
-        const int64_t total = (int64_t)gsc_base_rows(p, bh, bad) + s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+        const int64_t total = (int64_t)gsc_base_rows(p, bh, bad) + at;
         const int rows = (p.num_chunks[bh / p.Hkv] > 0 && !bad && total <= p.cap) ? (int)total : -1;
-        p.comp_lens[bh] = rows;
-        if (p.budget) budget_probe_arrive(p.budget, rows, (unsigned int)(p.B * p.Hkv));
+        budget_probe_arrive(p.budget, rows, lane, p.probe_levels, (unsigned int)(p.B * p.Hkv));      // (lane t: threshold t; the eighth sum is of words that nobody asks for)
     }
 }
 
@@ -1603,7 +1812,7 @@ static bool fast_holds(int heads, int n_max, int max_chunks) {
 }
 bool gsc_fast_holds(int heads, int N_max) { return fast_holds(heads, N_max, 0); }
 
-hipError_t launch_gsc_fast(const GscParams &p0, bool planned, hipStream_t stream) {
+hipError_t launch_gsc_fast(const GscParams &p0, bool planned, const BudgetStart *start, hipStream_t stream) {
     GscParams p = p0;
     const int segments = segments_of(p.N_max);
     if (!fast_holds(p.B * p.Hkv, p.N_max, p.max_chunks)) p.max_chunks = 0;
@@ -1616,28 +1825,30 @@ hipError_t launch_gsc_fast(const GscParams &p0, bool planned, hipStream_t stream
     p.segments = reinterpret_cast<GscSegment *>(reinterpret_cast<char *>(p.rows_ws) + align_up(bh * (size_t)p.N_max * kFastD * (p.out_is_bf16 ? 2 : 4), 256)) + kSegFront;
     p.windows = reinterpret_cast<GscWindow *>(reinterpret_cast<char *>(p.segments - kSegFront) + align_up((bh * (size_t)segments + kSegFront) * sizeof(GscSegment), sizeof(GscWindow)));
     p.published = reinterpret_cast<uint32_t *>(p.windows + (size_t)p.B * p.win_slots);
-    p.win_count = reinterpret_cast<int32_t *>(p.published + bh * (size_t)p.win_slots);
-    p.longs = reinterpret_cast<GscLongs *>(p.win_count + bh * (size_t)p.win_slots);
+    p.win_count = reinterpret_cast<int32_t *>(p.published + align_up(bh * (size_t)p.win_slots, 8));
+    p.longs = reinterpret_cast<GscLongs *>(p.win_count + bh * (size_t)p.win_slots * kProbeWords);
     p.head_state = reinterpret_cast<uint32_t *>(p.rowbase);
     p.long_count = reinterpret_cast<int32_t *>(p.longs + (size_t)segments * p.B);
     // Half of what is resident together, the rest goes to windows (a quarter or three quarters: the same within 1 %); where there are no long
     // chunks, all of them leave within a microsecond.  (One for every 512 tokens instead: a long-tailed call of 8 heads x 4000 took
     // 41 us against 32.)
-    const size_t longest = (size_t)p.N_max / (kWinRows + 1) + 1;
-    p.ahead_per_head = p.N_max < kWinRows ? 0 : (int)max((size_t)1, min(longest, kAheadWgs / bh));
+    const size_t longest = ((size_t)p.N_max / (kWinRows + 1) + 1) * (p.count_only ? (size_t(1) << p.probe_levels) - 1 : 1);
+    p.ahead_per_head = p.N_max < kWinRows ? 0 : (int)max((size_t)1, min(longest, (size_t)(p.count_only ? kAheadProbes : kAheadWgs) / bh));
     p.ahead_wgs = (int)(bh * p.ahead_per_head);
     if (!planned) {
-        hipLaunchKernelGGL(gsc_plan_kernel, dim3((unsigned)(segments * p.B)), dim3(kWave), 0, stream, p);
+        const dim3 grid((unsigned)(segments * p.B));
+        if (start) hipLaunchKernelGGL((gsc_plan_kernel<BudgetStart>), grid, dim3(kWave), 0, stream, p, *start);
+        else hipLaunchKernelGGL((gsc_plan_kernel<>), grid, dim3(kWave), 0, stream, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const dim3 grid((unsigned)((size_t)p.win_slots * bh + (p.count_only ? 0 : p.ahead_wgs)));
+    const dim3 grid((unsigned)((size_t)p.win_slots * bh + p.ahead_wgs));
     if (p.count_only) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, true>), grid, dim3(kWinThreads), 0, stream, p);
     else if (p.out_is_bf16) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, false>), grid, dim3(kWinThreads), 0, stream, p);
     else hipLaunchKernelGGL((gsc_compress_kernel<float, false>), grid, dim3(kWinThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p.count_only) return e;
-    hipLaunchKernelGGL(gsc_count_kernel, dim3((unsigned)bh), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL(gsc_count_kernel, dim3((unsigned)bh), dim3(kCountThreads), 0, stream, p);
     return hipGetLastError();
 }
 

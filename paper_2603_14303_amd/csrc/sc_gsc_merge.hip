@@ -549,6 +549,7 @@ hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
     p.base_lens = a.base_lens;
     p.count_only = a.count_only ? 1 : 0;
     p.budget = nullptr;
+    p.probe_levels = a.probe_levels;
     // Generic path: a wavefront per chunk, so four chunks are one round of a workgroup.  Calls of up to 64k rows in
     // all are bound by the longest chain of chunks and take that; larger ones fill the chip anyway and share the
     // offsets, the prefix and the barriers of an item among eight (us, 4 / 8 / 16 chunks: 2 heads x 1024 x 64 f32
@@ -579,7 +580,7 @@ hipError_t launch_gsc_merge(const GscMergeArgs &a, hipStream_t stream) {
         if (a.count_only) p.budget = reinterpret_cast<BudgetState *>(a.budget_state);
         p.max_chunks = a.tune.gsc_chunks_per_task;
         p.polls = a.tune.gsc_polls;
-        return launch_gsc_fast(p, a.planned, stream);
+        return launch_gsc_fast(p, a.planned, a.budget_start, stream);
     }
 
     if (a.in_dtype == DType::BF16) {

@@ -10,6 +10,12 @@ constexpr int kMaxChunksPerItem = 32;
 constexpr int kInlinePrefixTokens = 32768;   // up to here the last kernel adds the cluster counts up itself: a launch less
 constexpr float kBand = 1e-4f;   // fp32 cosine error for d <= 128 is < 2e-5; inside the band -> fp64
 
+// A counting probe of the budget search counts the rows at every threshold that the next steps of the bisection may ask for: the
+// midpoint, the midpoints of its two halves, and so on, kProbeLevels deep.
+constexpr int kProbeLevels = 3;
+constexpr int kProbeNodes = (1 << kProbeLevels) - 1;
+constexpr int kProbeWords = kProbeNodes + 1;      // counts of a window, one unused
+
 // State of the threshold search of sc_gsc_merge_budget (device memory, behind the merge workspace).
 struct BudgetState {
     float tau;            // threshold of the next sc_gsc_merge launch
@@ -23,9 +29,46 @@ struct BudgetState {
     long long *rows_out;
     // a probe's (sequence, head) workgroups add up their rows here; the last of them moves the bracket
     unsigned int arrived;
-    int bad;
-    long long total;
+    unsigned int bad;                 // bit t: some head overflowed at threshold t
+    long long total[kProbeNodes];
 };
+
+// What a search starts from, and what starts it: the plan kernel of its first counting probe, or a kernel of its own.  One thread.
+struct BudgetStart {
+    BudgetState *state;
+    float lo, hi;
+    int iterations;
+    long long budget_rows;
+    float *tau_out;
+    long long *rows_out;
+};
+__device__ __forceinline__ void budget_begin(const BudgetStart &b) {
+    BudgetState *st = b.state;
+    st->lo = b.lo;
+    st->hi = b.hi;
+    st->step = 0;
+    st->rows_lo = -1;
+    st->tau = (b.iterations > 0) ? 0.5f * (b.lo + b.hi) : b.lo;   // no probe: the final launch runs at tau_lo
+    st->budget_rows = b.budget_rows;
+    st->iterations = b.iterations;
+    st->tau_out = b.tau_out;
+    st->rows_out = b.rows_out;
+    st->arrived = 0u;
+    st->bad = 0u;
+    for (int t = 0; t < kProbeNodes; ++t) st->total[t] = 0;
+}
+
+// The threshold of node `node` of the probes' tree (1: the midpoint, 2 j and 2 j + 1: the midpoints of the lower and the upper half that
+// node j makes), by the same fp32 midpoints as budget_bracket_step's.
+__host__ __device__ __forceinline__ float budget_node_tau(float lo, float hi, int node) {
+    int level = 0;
+    while ((node >> (level + 1)) != 0) ++level;
+    for (; level > 0; --level) {
+        const float mid = 0.5f * (lo + hi);
+        if ((node >> (level - 1)) & 1) lo = mid; else hi = mid;
+    }
+    return 0.5f * (lo + hi);
+}
 
 // after a probe at st->tau with `sum` rows in all (`bad`: some head overflowed its capacity, which counts
 // as over budget): move the bracket and choose the next threshold: another midpoint, or lo itself for the
@@ -44,21 +87,36 @@ __device__ __forceinline__ void budget_bracket_step(BudgetState *st, long long s
     if (st->rows_out) *st->rows_out = st->rows_lo;
 }
 
-// A counting probe ends in a kernel that adds up its rows, one workgroup per (sequence, head); with a search attached each
-// of them adds its row count to the state and the last one to arrive moves the bracket, so no further
-// launch is needed between two probes.  rows < 0: the head overflowed (or has no valid chunking).  One thread.
-__device__ __forceinline__ void budget_probe_arrive(BudgetState *st, int rows, unsigned int n_heads) {
-    if (rows >= 0) atomicAdd(reinterpret_cast<unsigned long long *>(&st->total), (unsigned long long)rows);
-    else atomicOr(&st->bad, 1);
+// A counting probe ends in a kernel that adds up its rows, one workgroup per (sequence, head): each of them adds its row counts (lane t: at
+// node t + 1 of the tree; rows < 0: the head overflowed, or has no valid chunking) to the state, and the last one to arrive goes down the tree and
+// moves the bracket `levels` times, so no further launch is needed between two probes.  One wavefront.
+__device__ __forceinline__ void budget_probe_arrive(BudgetState *st, int rows, int lane, int levels, unsigned int n_heads) {
+    const int nodes = (1 << levels) - 1;
+    if (lane < nodes) {
+        if (rows >= 0) atomicAdd(reinterpret_cast<unsigned long long *>(&st->total[lane]), (unsigned long long)rows);
+        else atomicOr(&st->bad, 1u << lane);
+    }
     __threadfence();
-    if (atomicAdd(&st->arrived, 1u) == n_heads - 1u) {
-        __threadfence();
-        const long long sum = (long long)atomicAdd(reinterpret_cast<unsigned long long *>(&st->total), 0ull);
-        const bool bad = atomicOr(&st->bad, 0) != 0;
-        st->total = 0;
-        st->bad = 0;
+    unsigned int before = 0u;
+    if (lane == 0) before = atomicAdd(&st->arrived, 1u);
+    if (__builtin_amdgcn_readfirstlane((int)before) != (int)(n_heads - 1u)) return;
+    __threadfence();
+    long long total = 0;
+    if (lane < nodes) {
+        total = (long long)atomicAdd(reinterpret_cast<unsigned long long *>(&st->total[lane]), 0ull);
+        st->total[lane] = 0;
+    }
+    const unsigned int bad = atomicOr(&st->bad, 0u);
+    if (lane == 0) {
+        st->bad = 0u;
         st->arrived = 0u;
-        budget_bracket_step(st, sum, bad);
+    }
+    for (int level = 0, node = 1; level < levels; ++level) {
+        const bool over = ((bad >> (node - 1)) & 1u) != 0u;
+        const long long sum = (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(total >> 32), node - 1) << 32) |
+                                          (unsigned)__builtin_amdgcn_readlane((int)total, node - 1));
+        if (lane == 0) budget_bracket_step(st, sum, over);
+        node = 2 * node + ((!over && sum <= st->budget_rows) ? 1 : 0);
     }
 }
 
@@ -91,7 +149,7 @@ struct GscParams {
     GscWindow *windows;   // [B, win_slots]
     uint32_t *published;  // [B, Hkv, win_slots] rows of a window, for the windows behind it
     GscSegment *segments; // [B, Hkv, segments] rows of a segment's windows
-    int32_t *win_count;   // [B, Hkv, win_slots] rows of a window, counting probes
+    int32_t *win_count;   // [B, Hkv, win_slots, kProbeWords] rows of a window at each threshold of a counting probe
     GscLongs *longs;      // [B, segments] slots of long chunks
     int32_t *long_count;  // [B, segments]
     int ahead_per_head, ahead_wgs;  // workgroups that decide long chunks first: per (sequence, head), in all
@@ -102,6 +160,7 @@ struct GscParams {
     int polls;            // looks at the windows before until a workgroup leaves its own to others
     int count_only;       // fast path: cluster and count only (comp_lens); no values are read, no rows written
     int chunks_per_item;  // generic path
+    int probe_levels;     // steps of the search that a counting probe decides
     int short_wgs[2];     // generic path: workgroups per (sequence, head) where short chunks make items of 8 / of 16 or 32, 0: they don't (see gsc_item_shape)
 };
 
@@ -116,6 +175,6 @@ __device__ __forceinline__ int gsc_base_rows(const P &p, int64_t bh, bool &bad) 
 
 bool gsc_fast_holds(int heads, int N_max);   // they fit its words and its launch
 // planned: the windows of these offsets are in the workspace already (and nothing has been published since)
-hipError_t launch_gsc_fast(const GscParams &p, bool planned, hipStream_t stream);
+hipError_t launch_gsc_fast(const GscParams &p, bool planned, const BudgetStart *start, hipStream_t stream);
 
 }  // namespace sc

@@ -52,6 +52,8 @@ struct GscMergeArgs {
     const float *tau_dev = nullptr;       // threshold in device memory (overrides tau)
     bool count_only = false;              // only comp_lens is produced (bf16 / d = 128 fast path; elsewhere the full merge runs)
     void *budget_state = nullptr;         // counting probe of the budget search: its last kernel also moves the bracket (fast path only)
+    const struct BudgetStart *budget_start = nullptr;   // the search that this probe's plan starts
+    int probe_levels = 1;                 // steps of the search that a counting probe decides
     bool planned = false;                 // an earlier call has cut the same offsets into windows in this workspace and not merged since (fast path only)
     void *ws;
 };

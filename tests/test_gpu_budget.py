@@ -156,3 +156,57 @@ def test_knobs_that_change_during_the_search():
             assert torch.equal(out[2][0, h, :rows], want[2][0, h, :rows])
             for i in (0, 1):        # fp32 means of bf16 rows, summed in another order where another path was taken
                 assert torch.allclose(out[i][0, h, :rows], want[i][0, h, :rows], rtol=1e-5, atol=1e-5)
+
+
+PROBE_GAPS = {
+    "short": [24, 3, 61, 40, 1, 17, 90],
+    "window": [126, 127, 128, 129, 130],            # chunk lengths that just fit a window and just do not fit
+    "every row": [1],
+    "long": [700, 3, 150, 40, 1025, 129, 1],        # a long chunk is counted at every threshold by a workgroup of its own
+    "none": [],
+}
+
+
+@pytest.mark.parametrize("layout", list(PROBE_GAPS))
+@pytest.mark.parametrize("lens,heads", [((1023, 1025), 3), ((2600, 1, 0), 8), ((100,), 1)])
+def test_every_threshold_of_a_probe_counts_exactly(layout, lens, heads):
+    """A probe counts at seven thresholds and the search goes down their tree: with the budget set to the rows at a threshold, and to one
+    row less, a count that is off by one anywhere on the way turns the search.  Bundles of keys at angles of their own, so that
+    thresholds of every size split clusters; a zero row and a key that is not finite among them (a norm that is not usable)."""
+    rng = np.random.default_rng(sum(lens) + 10 * heads + len(layout))
+    B, N = len(lens), max(lens)
+    mask = np.zeros((B, N), np.uint8)
+    K = np.zeros((B, heads, N, 128), np.float32)
+    for b, n in enumerate(lens):
+        if PROBE_GAPS[layout]:
+            p = np.cumsum(np.roll(np.resize(PROBE_GAPS[layout], n), b)) - 1
+            mask[b, p[p < n]] = 1
+        for h in range(heads):
+            c = rng.standard_normal((30, 128))
+            spread = rng.choice([0.05, 0.15, 0.5, 1.0], size=(n, 1))
+            K[b, h, :n] = c[rng.integers(0, 30, n)] + spread * rng.standard_normal((n, 128))
+    K[0, 0, lens[0] // 2] = 0.0
+    K[0, heads - 1, lens[0] // 3, 5] = np.inf
+    K = wl.round_to_bf16(K)
+    Kd = g.to_device(K, True)
+    off, nch, sl = g.run_segment(mask, np.array(lens, np.int32))
+    known = {}
+
+    def rows_at(tau):
+        if tau not in known:
+            known[tau] = int(sc.sc_gsc_merge(Kd, Kd, off, nch, float(tau), seq_lens=sl)[3].sum().item())
+        return known[tau]
+
+    lo, hi = -1.01, 1.0
+    mids = [(a + b) / 2 for a, b in ((lo, hi), (0.0, 1.0), (0.5, 1.0), (0.25, 0.5), (-0.5, 0.5), (0.75, 1.0), (0.9, 1.0))]
+    for iters in (1, 2, 3, 4, 6, 8):
+        for at in mids:
+            # the rows at the midpoint that the search comes nearest to `at` with
+            a, b = np.float32(lo), np.float32(hi)
+            for _ in range(iters):
+                mid = np.float32(0.5) * (a + b)
+                a, b = (mid, b) if mid <= at else (a, mid)
+            for budget in (rows_at(mid), rows_at(mid) - 1):
+                want, _ = oracle.tau_for_budget(rows_at, budget, lo, hi, iters)
+                out = sc.sc_gsc_merge_budget(Kd, Kd, off, nch, max(0, budget), lo, hi, iters, seq_lens=sl)
+                assert out[5].item() == want and int(out[6].item()) == rows_at(want), (iters, at, budget)
