@@ -261,8 +261,8 @@ sc_status sc_gsc_merge_append(const void *K, const void *V, sc_dtype in_dtype,
  * variant of the paper's chunking ablation (Sec. 3.4), for which the chunk-by-chunk kernels of
  * sc_gsc_merge are slow by construction; the result is what sc_segment on an all-zero mask followed by
  * sc_gsc_merge gives (same integers; sums in row order).  bf16 inputs with d = 128 and N_max <= 32768 run
- * a dedicated path (all pairwise comparisons on the matrix cores, a block-sequential resolution of the
- * seeds, a gather by cluster); other shapes are handed to sc_gsc_merge's kernels with one-chunk offsets.
+ * a dedicated path (pairwise comparisons on the matrix cores, in stages where a sequence is long, seeds decided
+ * by all blocks at once, a gather by cluster); other shapes are handed to sc_gsc_merge's kernels with one-chunk offsets.
  * Arguments, layouts, overflow behaviour (comp_lens = -1) and errors as for sc_gsc_merge, without offsets /
  * num_chunks;  ws: sc_gsc_merge_global_workspace_bytes(B, Hkv, N_max, d) bytes (about N_max^2 / 8 bytes
  * per (sequence, KV head) on the dedicated path: 1.1 GB for 8 heads of 32768 tokens).

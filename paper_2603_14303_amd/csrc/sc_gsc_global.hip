@@ -6,16 +6,19 @@
 // it; a row joins the EARLIEST seed it resembles) but every similarity it can ask for is known in
 // advance, so the work is split into a dense part and a sparse one:
 //   norms    reciprocal norms of all rows.
-//   pairs    all pairwise comparisons "Sim(i, j) > tau" for i < j on the matrix cores
+//   pairs    pairwise comparisons "Sim(i, j) > tau" on the matrix cores
 //            (v_mfma_f32_16x16x32_bf16, 64 x 64 rows per product block): one 64-bit word per (row j,
 //            block of 64 earlier rows), "surely above" and "inside the +-1e-4 band" (decided later in
 //            fp64).  Only blocks that hold such a pair are written; a bit per block says which.
 //   decide   which rows are seeds and which seed every row joins, all blocks of 64 rows at once.
-//   number   one workgroup per (sequence, head) numbers the clusters and their members in row order.
+//   rank, slots, place   number the clusters and their members in row order.
 //   sum      one 16-lane group per cluster adds up its members' keys and values in row order (fp32),
 //            scales by 1/size and writes the output row: Eq. 3.
-// 8 heads x 32768 tokens, tau 0.7, us per call: 2550 with every word written, read back into candidate lists and resolved
-// block by block in order (pairs 1370, lists 307, resolve 762, sum 107); now 1060 (pairs 948, decide 14, number 92, sum 42).
+// A row needs comparing with SEEDS only, and one row in six is one where merging pays.  Long sequences are therefore taken in stages of 4096 rows
+// or a multiple: all pairs inside the stages (one launch), then stage by stage the rows of a stage against the seeds of the stages before, listed without
+// gaps, and the decisions of the stage.  8 heads x 32768 tokens, us per call: tau 0.7 1020 with all pairs, 600 in four stages of 8192 rows (pairs inside them 275,
+// with the seeds 46 + 90 + 102, decide 4 x 18); tau 0.979, half the rows seeds, 1045 and 900.  What that costs where every row is a seed
+// (tau 1: 1100 and 1330) buys nothing, so stages are only as short as one seed in three rows pays for.
 // Everything else (other element types, head dims, longer sequences) is handed to the ordinary kernels
 // of sc_gsc_merge with offsets that describe one chunk per sequence.
 #include "sc_device.h"
@@ -34,8 +37,8 @@ constexpr int kGlD = 128;
 constexpr int kGlBlock = 64;                    // rows per block
 constexpr int kGlTileRowBytes = 272;            // 256 B of keys + 16 B pad: conflict-free operand reads
 constexpr int kGlPairWaves = 4;                 // row blocks per workgroup of the pairs kernel
-constexpr int kGlNumberThreads = 1024;
-constexpr int kGlSegment = 64;                  // column blocks per work item of the pairs kernel
+constexpr int kGlSeedUnit = 8, kGlSeedShare = 4;   // with listed seeds: column blocks a work item is rounded up to; work items for a list of one row in so many
+constexpr int kGlWordBlocks = 64;               // column blocks per word of tile flags; stages are multiples of this
 constexpr int kGlLeader = 1 << 16;              // place of the first row of a cluster in a block
 
 struct GlobParams {
@@ -59,10 +62,15 @@ struct GlobParams {
     int32_t *join;                // [npad]: the seed row that a row belongs to (a seed: itself)
     int32_t *place;               // [npad]: place inside the own block's rows of the cluster, see glob_decide_block
     int32_t *lead, *order;        // [npad]
-    int polls;                    // looks at another block's rows before the number kernel takes over
-    int32_t *mbase, *csize;       // [nbp * 64 + 1], [nbp * 64]
-    int32_t *nclusters;           // [1]
+    int polls;                    // looks at another block's rows before the ordered pass takes over
+    int32_t *mbase, *csize;       // [nbp * 64 + 1], the last one: slots given out; [nbp * 64]
+    int32_t *nclusters;           // [1]; before the rank kernel: blocks whose wavefronts are through
+    int walk;                     // column blocks per work item of the pairs kernel: 8, 16 or 32
+    int stage_words, stage;       // words of tile flags of a stage; the stage of this launch
+    int32_t *seedlist;            // [npad]: the seeds of the stages before, in row order (the memory of `order`)
 };
+__device__ __forceinline__ int gl_stage_blocks(const GlobParams &p) { return p.stage_words * kGlWordBlocks; }
+__device__ __forceinline__ int gl_stage_start(const GlobParams &p, int J) { return J / gl_stage_blocks(p) * gl_stage_blocks(p); }      // first block of block J's stage
 
 __device__ __forceinline__ long long gl_col_base(int I, int nbp) {   // first word of column block I
     return 64ll * ((long long)I * nbp - (long long)I * (I - 1) / 2);
@@ -113,6 +121,7 @@ __global__ __launch_bounds__(256) void glob_norms_kernel(GlobParams p) {
         for (int e = 0; e < 8; ++e) nsq = fmaf(x[e], x[e], nsq);
     }
     nsq = row_allreduce_sum<16>(nsq);
+    if (row == 0 && c == 0) p.nclusters[bh] = p.mbase[(int64_t)bh * (p.nbp * 64 + 1) + p.nbp * 64] = 0;
     if (c == 0 && (row & 31) == 0) p.state[(int64_t)bh * p.nbp * 2 + row / 32] = 0ull;      // nothing decided yet
     if (c == 0)
         p.rinv[(int64_t)bh * p.nbp * 64 + row] = (row < n && nsq > 1e-30f && nsq < 1e30f) ? __frsqrt_rn(nsq) : __builtin_nanf("");
@@ -125,25 +134,36 @@ __global__ __launch_bounds__(256) void glob_norms_kernel(GlobParams p) {
 // the rows of block I pass through an LDS tile shared by the four wavefronts and are the A operand.  The
 // product tile leaves lane (g, c) with the dot products of row 16 Jt + c of block J and rows
 // 16 It + 4 g + i of block I: four bits of that row's word, completed by an OR over the lane groups.
+template <bool SEEDS>
 __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(GlobParams p) {
+    constexpr int kListTiles = kGlSeedUnit * kGlSeedShare;
     __shared__ __attribute__((aligned(16))) char s_tiles[2][kGlBlock * kGlTileRowBytes];      // two tiles: one worked on, one being filled
     __shared__ __attribute__((aligned(16))) float s_rinvs[2][kGlBlock];
     __shared__ int s_odd[2];      // a row of the tile has no usable norm
-    const int bh = blockIdx.y, b = bh / p.Hkv, h = bh - b * p.Hkv;
+    [[maybe_unused]] __shared__ unsigned short s_list[SEEDS ? kListTiles * kGlBlock : 1];      // rows of the seeds (n <= 32768)
+    [[maybe_unused]] __shared__ int s_part[kGlPairWaves];
+    const int bh = (int)blockIdx.x % (p.B * p.Hkv), b = bh / p.Hkv, h = bh - b * p.Hkv;
     const int n = gl_seq_len(p, b);
     const int nb = (n + kGlBlock - 1) / kGlBlock;
     const int njg = (nb + kGlPairWaves - 1) / kGlPairWaves;
-    // Work item = (group JG of four row blocks, segment of kGlSegment column blocks): the walks over the column
-    // blocks have about the same length whatever the row.  Groups 16 q .. 16 q + 15 have q + 1 segments each
-    // (kGlSegment = 64 column blocks = 16 groups), so 8 q (q + 1) items come before group 16 q.
+    // Work item = (group JG of four row blocks, segment of p.walk column blocks): short walks of about the same length, so that the
+    // triangle of one stage fills the chip.  Within a stage, groups per_seg q .. per_seg (q + 1) - 1 have q + 1 segments each, so
+    // per_seg q (q + 1) / 2 items come before them.  With the seeds of the stages before: an equal share of the list for each of `walks` items, as
+    // many as give them a unit of eight column blocks if one row in four is a seed.
+    const int stage_blocks = gl_stage_blocks(p), x = (int)blockIdx.x / (p.B * p.Hkv);
+    [[maybe_unused]] const int walks = p.stage * stage_blocks / kListTiles;
     int JG, seg;
-    {
-        const int x = (int)gridDim.x - 1 - (int)blockIdx.x;      // the longest rows first
+    if constexpr (SEEDS) {
+        JG = p.stage * (stage_blocks / kGlPairWaves) + x / walks;
+        seg = x % walks;
+    } else {
+        const int per_seg = p.walk / kGlPairWaves;      // groups of row blocks to a segment
+        const int stage_segs = stage_blocks / p.walk, items = per_seg * stage_segs * (stage_segs + 1) / 2, st = x / items, y = x - st * items;
         int q = 0;
-        while (8 * (q + 1) * (q + 2) <= x) ++q;
-        const int rem = x - 8 * q * (q + 1);
-        JG = 16 * q + rem / (q + 1);
-        seg = rem % (q + 1);
+        while (per_seg * (q + 1) * (q + 2) / 2 <= y) ++q;
+        const int rem = y - per_seg * q * (q + 1) / 2;
+        JG = per_seg * (st * stage_segs + q) + rem / (q + 1);
+        seg = st * stage_segs + rem % (q + 1);
     }
     if (JG >= njg) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -154,6 +174,60 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
     const bf16_t *Kbh = p.K + b * p.stride_b + h * p.stride_h;
     const float *rinv_bh = p.rinv + (int64_t)bh * p.nbp * 64;
     const int sb = (int)p.stride_n * 2;      // bytes between rows
+    auto flags8 = [&](unsigned long long *words) { return reinterpret_cast<unsigned char *>(words + ((int64_t)bh * p.nbp + J) * p.nseg); };      // of 8 blocks
+    int I_first, I_last;
+    [[maybe_unused]] int ns = 0;      // seeds of this walk
+    if constexpr (SEEDS) {
+        const unsigned long long *st = p.state + (int64_t)bh * p.nbp * 2;
+        const int J0 = p.stage * stage_blocks;
+        uint64_t mask[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int I = 2 * tid + q;
+            const unsigned long long w0 = I < J0 ? st[2 * I] : 0ull, w1 = I < J0 ? st[2 * I + 1] : 0ull;
+            mask[q] = (w0 >> 32) | (w1 & 0xFFFFFFFF00000000ull);
+        }
+        const int mine = __popcll(mask[0]) + __popcll(mask[1]);
+        int incl = mine;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int up = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += up;
+        }
+        if (lane == kWave - 1) s_part[wave] = incl;
+        __syncthreads();
+        int at = incl - mine, total = 0;
+#pragma unroll
+        for (int w = 0; w < kGlPairWaves; ++w) {
+            if (w < wave) at += s_part[w];
+            total += s_part[w];
+        }
+        // units of eight tiles: `units` hold seeds, `per` of them are this walk's; the flags of the others are cleared
+        const int units = (total + kGlSeedUnit * kGlBlock - 1) / (kGlSeedUnit * kGlBlock), per = (units + walks - 1) / walks;      // per <= kGlSeedShare
+        if (active)
+            for (int q = units + seg + walks * lane; q < J0 / kGlSeedUnit; q += walks * kWave) flags8(p.tany)[q] = flags8(p.tuns)[q] = 0;
+        const int first = seg * per * kGlSeedUnit * kGlBlock, most = per * kGlSeedUnit * kGlBlock;
+        ns = min(total - first, most);
+        if (ns <= 0) return;
+        at -= first;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (at + 64 <= 0 || at >= most) { at += __popcll(mask[q]); continue; }
+            for (uint64_t m = mask[q]; m != 0ull; m &= m - 1ull, ++at)
+                if (at >= 0 && at < most) s_list[at] = (unsigned short)((2 * tid + q) * kGlBlock + first_bit(m));
+        }
+        __syncthreads();
+        if (JG == p.stage * (stage_blocks / kGlPairWaves)) {      // for the rows that join one of them
+            int32_t *list = p.seedlist + (int64_t)bh * p.nbp * kGlBlock + first;
+            for (int i = tid; i < ns; i += kGlPairWaves * kWave) list[i] = s_list[i];
+        }
+        I_first = seg * per * kGlSeedUnit;
+        I_last = I_first + (ns + kGlBlock - 1) / kGlBlock - 1;
+    } else {
+        I_first = seg * p.walk;
+        I_last = min(min(JG * kGlPairWaves + kGlPairWaves - 1, nb - 1), I_first + p.walk - 1);
+        if (I_first > I_last) return;
+    }
     // rows of block J as B operands, through a descriptor that ends after the sequence's last row
     uint4 bq[4][4];
     float hn[4], wn[4], ln[4];
@@ -178,14 +252,22 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
         }
     }
     bad_j = ballot64(bad_j) != 0ull;
-    const int I_first = seg * kGlSegment;
-    const int I_last = min(min(JG * kGlPairWaves + kGlPairWaves - 1, nb - 1), I_first + kGlSegment - 1);
-    if (I_first > I_last) return;
     // the tile of block I: thread t brings rows t / 16 + 16 r, piece t % 16
     const int lrow = tid >> 4, lc = tid & 15;
-    uint4 pre[4];
-    float pre_r = 0.f;
-    auto fetch = [&](int I) {
+    uint4 pre_a[4], pre_b[4];      // two tiles on their way
+    float pre_ra = 0.f, pre_rb = 0.f;
+    auto fetch = [&](int I, uint4 (&pre)[4], float &pre_r) {
+        if (I > I_last) return;
+        if constexpr (SEEDS) {
+            const int at = (I - I_first) * kGlBlock;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = at + lrow + 16 * r;
+                pre[r] = k < ns ? *reinterpret_cast<const uint4 *>(Kbh + (int64_t)s_list[k] * p.stride_n + 8 * lc) : make_uint4(0u, 0u, 0u, 0u);
+            }
+            if (tid < kGlBlock) pre_r = at + tid < ns ? rinv_bh[s_list[at + tid]] : 0.f;
+            return;
+        }
         const int rows_i = min(kGlBlock, n - I * kGlBlock);
         const auto src = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(Kbh + (int64_t)I * kGlBlock * p.stride_n), (short)0,
                                                            rows_i > 0 ? (rows_i - 1) * sb + kGlD * 2 : 0, 0x00020000);
@@ -196,7 +278,8 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
         }
         if (tid < kGlBlock) pre_r = rinv_bh[I * kGlBlock + tid];
     };
-    auto park = [&](int I) {
+    auto park = [&](int I, const uint4 (&pre)[4], float pre_r) {
+        if (I > I_last) return;
         char *t = s_tiles[I & 1];
 #pragma unroll
         for (int r = 0; r < 4; ++r) *reinterpret_cast<uint4 *>(t + (lrow + 16 * r) * kGlTileRowBytes + 16 * lc) = pre[r];
@@ -206,47 +289,59 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
             if (lane == 0) s_odd[I & 1] = odd ? 1 : 0;
         }
     };
-    uint64_t any_bits = 0ull, uns_bits = 0ull;      // of this segment's column blocks
-    fetch(I_first);
-    park(I_first);
-    if (I_first < I_last) fetch(I_first + 1);
-    for (int I = I_first; I <= I_last; ++I) {
+    uint32_t any_bits = 0u, uns_bits = 0u;      // of this walk's column blocks
+    auto work = [&](int I, uint4 (&pre)[4], float &pre_r) {
         __syncthreads();          // tile I is complete; everybody is done with tile I - 1, whose buffer takes tile I + 1 now
-        if (I < I_last) {
-            park(I + 1);
-            if (I + 1 < I_last) fetch(I + 2);      // on its way while this tile is worked on
-        }
+        park(I + 1, pre, pre_r);
+        fetch(I + 3, pre, pre_r);      // on its way while this tile and the next are worked on
         const char *s_tile = s_tiles[I & 1];
         const float *s_rinv = s_rinvs[I & 1];
-        if (!active || I > J) continue;    // wave-uniform
+        if (!active || (!SEEDS && I > J)) return;    // wave-uniform
         const bool odd = bad_j || __builtin_amdgcn_readfirstlane(s_odd[I & 1]) != 0;
         uint32_t yl[4], yh[4], ul[4], uh[4];
 #pragma unroll
         for (int Jt = 0; Jt < 4; ++Jt) yl[Jt] = yh[Jt] = ul[Jt] = uh[Jt] = 0u;
-        bool touched = odd;
+        // sim(m, n) > t  <=>  dot * rinv_m > t * norm_n.  Hardly any tile holds a pair that comes near: one multiply-add
+        // and half a maximum per pair tell.  All products of the tile are asked for before the first answer is looked at, so that the
+        // matrix cores go on while the vector unit compares.
+        gl_float4 acc[4][4];
+        uint64_t near[4];
+        float top[4];
+        uint4 a[4];
+        gl_float4 rm;
+        auto operand = [&](int step) { return *reinterpret_cast<const uint4 *>(s_tile + (16 * (step >> 2) + c) * kGlTileRowBytes + (32 * (step & 3) + 8 * g) * 2); };
+        auto compare = [&](int It, int Jt) {
+            if (Jt == 0) rm = *reinterpret_cast<const gl_float4 *>(s_rinv + 16 * It + 4 * g);
+            const float t0 = fmaf(acc[It][Jt][0], rm[0], -ln[Jt]), t1 = fmaf(acc[It][Jt][1], rm[1], -ln[Jt]);
+            const float t2 = fmaf(acc[It][Jt][2], rm[2], -ln[Jt]), t3 = fmaf(acc[It][Jt][3], rm[3], -ln[Jt]);
+            top[It] = (Jt == 0) ? fmaxf(t0, t1) : fmaxf(fmaxf(top[It], t0), t1);
+            top[It] = fmaxf(fmaxf(top[It], t2), t3);
+        };
+#pragma unroll
+        for (int step = 0; step < 3; ++step) a[step] = operand(step);
+#pragma unroll
+        for (int step = 0; step < 16; ++step) {
+            if (step + 3 < 16) a[(step + 3) & 3] = operand(step + 3);
+#pragma unroll
+            for (int Jt = 0; Jt < 4; ++Jt) {
+                if (step % 4 == 0) acc[step >> 2][Jt] = gl_float4{0.f, 0.f, 0.f, 0.f};
+                acc[step >> 2][Jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(gl_bf16x8, a[step & 3]), __builtin_bit_cast(gl_bf16x8, bq[Jt][step & 3]),
+                                                                             acc[step >> 2][Jt], 0, 0, 0);
+            }
+            if (step >= 4) compare((step >> 2) - 1, step & 3);
+            __builtin_amdgcn_sched_barrier(0);      // the order of issue stays as written
+        }
+#pragma unroll
+        for (int Jt = 0; Jt < 4; ++Jt) compare(3, Jt);
+        const uint64_t all_near = odd ? ~0ull : 0ull;
+#pragma unroll
+        for (int It = 0; It < 4; ++It) near[It] = ballot64(top[It] >= 0.f) | all_near;
+        const bool touched = (near[0] | near[1] | near[2] | near[3]) != 0ull;
+        if (!touched && (SEEDS || I != J)) return;
 #pragma unroll
         for (int It = 0; It < 4; ++It) {
-            gl_float4 acc[4];
-#pragma unroll
-            for (int Jt = 0; Jt < 4; ++Jt) acc[Jt] = gl_float4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const uint4 a = *reinterpret_cast<const uint4 *>(s_tile + (16 * It + c) * kGlTileRowBytes + (32 * ks + 8 * g) * 2);
-#pragma unroll
-                for (int Jt = 0; Jt < 4; ++Jt)
-                    acc[Jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(gl_bf16x8, a),
-                                                                      __builtin_bit_cast(gl_bf16x8, bq[Jt][ks]), acc[Jt], 0, 0, 0);
-            }
+            if (near[It] == 0ull) continue;
             const gl_float4 rm = *reinterpret_cast<const gl_float4 *>(s_rinv + 16 * It + 4 * g);
-            // sim(m, n) > t  <=>  dot * rinv_m > t * norm_n.  Hardly any tile holds a pair that comes near: one multiply-add
-            // and half a maximum per pair tell.
-            float top = fmaf(acc[0][0], rm[0], -ln[0]);
-#pragma unroll
-            for (int Jt = 0; Jt < 4; ++Jt)
-#pragma unroll
-                for (int i = (Jt == 0) ? 1 : 0; i < 4; ++i) top = fmaxf(top, fmaf(acc[Jt][i], rm[i], -ln[Jt]));
-            if (!odd && ballot64(top >= 0.f) == 0ull) continue;
-            touched = true;
             // dd = (tau + band) * norm_n - dot * rinv_m is negative for a sure yes and at most 2 * band * norm_n inside the
             // band: the sign bit of dd is shifted into a nibble, an unsigned minimum over the bit patterns keeps the smallest
             // non-negative dd (negative values compare as huge).  Only if some lane saw a value inside the band, or a row
@@ -260,7 +355,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
                 uint32_t nib = 0u, dmin = 0x7F800000u;
 #pragma unroll
                 for (int i = 3; i >= 0; --i) {
-                    const uint32_t dd = __float_as_uint(fmaf(-acc[Jt][i], rm[i], hn[Jt]));
+                    const uint32_t dd = __float_as_uint(fmaf(-acc[It][Jt][i], rm[i], hn[Jt]));
                     nib = __builtin_amdgcn_alignbit(nib, dd, 31);      // (nib << 1) | sign bit
                     dmin = min(dmin, dd);
                 }
@@ -273,7 +368,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
                     uint32_t y4 = 0u, u4 = 0u;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float dd = fmaf(-acc[Jt][i], rm[i], hn[Jt]);
+                        const float dd = fmaf(-acc[It][Jt][i], rm[i], hn[Jt]);
                         const bool yes = dd < 0.f;
                         const bool unsure = !yes && !(dd > wn[Jt]);
                         y4 |= yes ? (1u << i) : 0u;
@@ -288,7 +383,6 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
                 if (It < 2) yl[Jt] |= yn[Jt] << sh; else yh[Jt] |= yn[Jt] << sh;
             }
         }
-        if (!touched && I != J) continue;
         // complete the words over the four lane groups; lane 16 Jt + c keeps the words of row 16 Jt + c
         uint32_t myl = 0u, myh = 0u, mul = 0u, muh = 0u;
 #pragma unroll
@@ -298,17 +392,29 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
             if (g == Jt) { myl = a0; myh = a1; mul = b0; muh = b1; }
         }
         if (J * kGlBlock + lane >= n) myl = myh = mul = muh = 0u;      // no such row
+        if constexpr (SEEDS) {      // no such seed
+            const uint64_t there = gl_bits_below(min(kGlBlock, ns - (I - I_first) * kGlBlock));
+            myl &= (uint32_t)there; mul &= (uint32_t)there;
+            myh &= (uint32_t)(there >> 32); muh &= (uint32_t)(there >> 32);
+        }
         const long long w = (long long)bh * p.tri + gl_col_base(I, p.nbp) + (long long)(J - I) * kGlBlock + lane;
         const bool any = ballot64((myl | myh | mul | muh) != 0u) != 0ull, any_u = ballot64((mul | muh) != 0u) != 0ull;
-        if (any || I == J) p.Y[w] = ((unsigned long long)myh << 32) | myl;      // a block's own words are always read
-        if (any_u || I == J) p.U[w] = ((unsigned long long)muh << 32) | mul;
-        any_bits |= any ? 1ull << (I & 63) : 0ull;
-        uns_bits |= any_u ? 1ull << (I & 63) : 0ull;
+        if (any || (!SEEDS && I == J)) p.Y[w] = ((unsigned long long)myh << 32) | myl;      // a block's own words are always read
+        if (any_u || (!SEEDS && I == J)) p.U[w] = ((unsigned long long)muh << 32) | mul;
+        any_bits |= any ? 1u << (I - I_first) : 0u;
+        uns_bits |= any_u ? 1u << (I - I_first) : 0u;
+    };
+    fetch(I_first, pre_a, pre_ra);
+    park(I_first, pre_a, pre_ra);
+    fetch(I_first + 1, pre_b, pre_rb);
+    fetch(I_first + 2, pre_a, pre_ra);
+    for (int I = I_first; I <= I_last; I += 2) {
+        work(I, pre_b, pre_rb);
+        if (I + 1 <= I_last) work(I + 1, pre_a, pre_ra);
     }
-    if (active && lane == 0) {      // (a segment is the 64 column blocks of one word)
-        const int64_t at = ((int64_t)bh * p.nbp + J) * p.nseg + seg;
-        p.tany[at] = any_bits;
-        p.tuns[at] = uns_bits;
+    if (active && lane < kListTiles / 8 && I_first + 8 * lane <= (SEEDS ? I_last : I_first + p.walk - 1)) {
+        flags8(p.tany)[I_first / 8 + lane] = (unsigned char)(any_bits >> (8 * lane));
+        flags8(p.tuns)[I_first / 8 + lane] = (unsigned char)(uns_bits >> (8 * lane));
     }
 }
 
@@ -323,7 +429,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
 // the members of a cluster mostly sit close together, so a block hardly ever waits for one that waits itself, and
 // the rounds are a few microseconds for all blocks instead of 1.4 us for each of them in turn.
 //
-// Waiting is bounded (p.polls looks in all); blocks that are left undecided are finished in order by one wavefront of the number kernel.
+// Waiting is bounded (p.polls looks in all); blocks that are left undecided are finished in order by the last wavefront of the head.
 // Blocks are dispatched in row order, so the ones waited for are running or done, and giving up never pays: with 4096 looks
 // (2 ms) the last blocks of a long chain did (8 heads x 32768 rows that drift by 0.4, tau 0.8: 3.6 ms, 3.1 with patience), and all of
 // them where many pairs need fp64 (2 heads x 2048 zero rows: 872 ms, 79 with patience).
@@ -349,10 +455,10 @@ __device__ __forceinline__ void gl_publish(unsigned long long *st, int J, GlobBl
     k.published = k.decided;
 }
 
-// One candidate word (64 earlier rows from `first_row` on; decided / seeds: what is known about them) for every lane with
+// One candidate word (64 earlier rows from `first_row` on, or the rows of `list`; decided / seeds: what is known about them) for every lane with
 // `open`: follows the candidates as far as they are known.  Lanes that find their seed join k.decided; returns the lanes that
 // wait for an undecided row.  uw loses the bits that fp64 has turned down.
-__device__ __forceinline__ uint64_t gl_follow(const GlobParams &p, const bf16_t *Kbh, uint64_t yw, uint64_t &uw, int first_row, uint64_t decided,
+__device__ __forceinline__ uint64_t gl_follow(const GlobParams &p, const bf16_t *Kbh, uint64_t yw, uint64_t &uw, int first_row, const int32_t *list, uint64_t decided,
                                               uint64_t seeds, bool open, int j0, int lane, GlobBlock &k) {
     for (;;) {
         const bool undecided = open && ((k.decided >> lane) & 1ull) == 0ull;
@@ -360,18 +466,18 @@ __device__ __forceinline__ uint64_t gl_follow(const GlobParams &p, const bf16_t 
         const int f = (c != 0ull) ? first_bit(c) : 0;
         const bool known = c != 0ull && ((decided >> f) & 1ull) != 0ull;
         const bool sure = known && ((yw >> f) & 1ull) != 0ull;
-        if (sure) k.target = first_row + f;
+        if (sure) k.target = list ? list[f] : first_row + f;
         k.decided |= ballot64(sure);
         uint64_t ask = ballot64(known && !sure);
         if (ask == 0ull) return ballot64(c != 0ull && !known);
         while (ask != 0ull) {
             const int r = __builtin_amdgcn_readfirstlane(first_bit(ask));
             ask &= ask - 1ull;
-            const int fr = __builtin_amdgcn_readlane(f, r);
-            const bool ok = gl_cosine_exceeds_f64(Kbh + (int64_t)(first_row + fr) * p.stride_n, Kbh + (int64_t)(j0 + r) * p.stride_n, p.tau, lane);
+            const int fr = __builtin_amdgcn_readlane(f, r), row = list ? __builtin_amdgcn_readfirstlane(list[fr]) : first_row + fr;
+            const bool ok = gl_cosine_exceeds_f64(Kbh + (int64_t)row * p.stride_n, Kbh + (int64_t)(j0 + r) * p.stride_n, p.tau, lane);
             if (ok) k.decided |= 1ull << r;
             if (lane == r) {
-                if (ok) k.target = first_row + fr;
+                if (ok) k.target = row;
                 else uw &= ~(1ull << fr);
             }
         }
@@ -388,7 +494,7 @@ __device__ __forceinline__ void gl_own_block(const GlobParams &p, const bf16_t *
     for (;;) {
         const uint64_t before = k.decided;
         if ((cleared & ~before) == 0ull) return;
-        gl_follow(p, Kbh, y, u, j0, k.decided, k.seeds, open, j0, lane, k);
+        gl_follow(p, Kbh, y, u, j0, nullptr, k.decided, k.seeds, open, j0, lane, k);
         auto candidates = [&]() { return (open && ((k.decided >> lane) & 1ull) == 0ull) ? (y | u) & ~(k.decided & ~k.seeds) : 0ull; };
         // no candidate left that is a seed or may become one: a seed itself
         const uint64_t more = ballot64(open && ((k.decided >> lane) & 1ull) == 0ull && candidates() == 0ull);
@@ -426,6 +532,9 @@ __device__ __forceinline__ bool glob_decide_block(const GlobParams &p, int bh, c
     const unsigned long long *Y = p.Y + (long long)bh * p.tri, *U = p.U + (long long)bh * p.tri;
     const unsigned long long *any_row = p.tany + ((int64_t)bh * p.nbp + J) * p.nseg, *uns_row = p.tuns + ((int64_t)bh * p.nbp + J) * p.nseg;
     unsigned long long *st = p.state + (int64_t)bh * p.nbp * 2;
+    // words of tiles before the stage's first block are of 64 seeds each, whose rows are listed
+    const int J0 = gl_stage_start(p, J);
+    const int32_t *seedlist = p.seedlist + (int64_t)bh * npad;
     int32_t *join = p.join + (int64_t)bh * npad + j0, *place = p.place + (int64_t)bh * npad + j0;
     GlobBlock k;
     gl_load_state(st, J, k.decided, k.seeds);
@@ -492,12 +601,14 @@ __device__ __forceinline__ bool glob_decide_block(const GlobParams &p, int bh, c
 #pragma unroll
             for (int q = 0; q < kBatch; ++q) {
                 dec[q] = sds[q] = 0ull;
-                if (tile[q] >= 0) gl_load_state(st, tile[q], dec[q], sds[q]);
+                if (tile[q] >= J0) gl_load_state(st, tile[q], dec[q], sds[q]);
+                else if (tile[q] >= 0) dec[q] = sds[q] = ~0ull;
             }
 #pragma unroll
             for (int q = 0; q < kBatch; ++q) {
                 if (tile[q] < 0 || gave_up) continue;
-                uint64_t waiting = gl_follow(p, Kbh, yw[q], uw[q], tile[q] * kGlBlock, dec[q], sds[q], valid && has_cross, j0, lane, k);
+                const int32_t *list = tile[q] < J0 ? seedlist + tile[q] * kGlBlock : nullptr;
+                uint64_t waiting = gl_follow(p, Kbh, yw[q], uw[q], tile[q] * kGlBlock, list, dec[q], sds[q], valid && has_cross, j0, lane, k);
                 while (waiting != 0ull) {
                     // rows that have just joined may settle others of the block, which other blocks may be waiting for
                     if (k.decided != settled) {
@@ -508,7 +619,7 @@ __device__ __forceinline__ bool glob_decide_block(const GlobParams &p, int bh, c
                     if (--polls < 0) { gave_up = true; break; }
                     __builtin_amdgcn_s_sleep(4);
                     gl_load_state(st, tile[q], dec[q], sds[q]);
-                    waiting = gl_follow(p, Kbh, yw[q], uw[q], tile[q] * kGlBlock, dec[q], sds[q], valid && has_cross, j0, lane, k);
+                    waiting = gl_follow(p, Kbh, yw[q], uw[q], tile[q] * kGlBlock, list, dec[q], sds[q], valid && has_cross, j0, lane, k);
                 }
             }
             if (kept) break;      // (the block's own rows follow below)
@@ -540,194 +651,199 @@ __device__ __forceinline__ bool glob_decide_block(const GlobParams &p, int bh, c
     return true;
 }
 
+// Blocks [first, last) that were left undecided, in order; every block before them is decided, so nothing is waited for.  One wavefront.
+__device__ __forceinline__ void gl_finish_blocks(const GlobParams &p, int bh, const bf16_t *Kbh, int n, int first, int last, int lane) {
+    const unsigned long long *st = p.state + (int64_t)bh * p.nbp * 2;
+    for (int J = first; J < last; ++J) {
+        uint64_t dec, sds;
+        gl_load_state(st, J, dec, sds);
+        if (dec == gl_bits_below(min(kGlBlock, n - J * kGlBlock))) continue;
+        glob_decide_block(p, bh, Kbh, n, J, lane, 0);
+        __threadfence();                                   // the next block's wavefront-wide loads see it
+    }
+}
+
 __global__ __launch_bounds__(kWave) void glob_decide_kernel(GlobParams p) {
-    const int n_bh = p.B * p.Hkv;
-    const int J = (int)blockIdx.x / n_bh, bh = (int)blockIdx.x - J * n_bh;      // row order; with a multiple of 8 heads a head stays on one XCD
+    const int n_bh = p.B * p.Hkv, lane = threadIdx.x;
+    const int at = (int)blockIdx.x / n_bh, bh = (int)blockIdx.x - at * n_bh;      // row order; with a multiple of 8 heads a head stays on one XCD
     const int b = bh / p.Hkv, h = bh - b * p.Hkv;
     const int n = __builtin_amdgcn_readfirstlane(gl_seq_len(p, b));
+    const int first = p.stage * gl_stage_blocks(p), J = first + at;
     if (J * kGlBlock >= n) return;
-    glob_decide_block(p, bh, p.K + b * p.stride_b + h * p.stride_h, n, J, threadIdx.x, p.polls);
+    const bf16_t *Kbh = p.K + b * p.stride_b + h * p.stride_h;
+    const bool done = glob_decide_block(p, bh, Kbh, n, J, lane, p.polls);
+    // What follows needs all seeds of this stage: the last wavefront to come through decides what others have left undecided.
+    const int last = min(first + gl_stage_blocks(p), (n + kGlBlock - 1) / kGlBlock);
+    if (!done) __threadfence();      // the seeds that some of its rows have joined
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    int before = 0;
+    if (lane == 0) before = __hip_atomic_fetch_add(p.nclusters + bh, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(before) != last - 1) return;
+    bool open = false;
+    for (int q = first + lane; q < last; q += kWave) {
+        const unsigned long long *st = p.state + (int64_t)bh * p.nbp * 2 + 2 * q;
+        const uint32_t d0 = (uint32_t)__hip_atomic_load(st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), d1 = (uint32_t)__hip_atomic_load(st + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t want = gl_bits_below(min(kGlBlock, n - q * kGlBlock));
+        open = open || d0 != (uint32_t)want || d1 != (uint32_t)(want >> 32);
+    }
+    if (ballot64(open) == 0ull) return;
+    __threadfence();
+    gl_finish_blocks(p, bh, Kbh, n, first, last, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
-// number: one workgroup per (sequence, head).  Clusters are numbered in seed order and their members in row order: every row gets
-// its cluster, the first row of a cluster in a block takes the next slots of that cluster for all its rows there (one
-// wavefront, in block order: LDS additions of one wavefront execute in order and nothing waits for their results but
-// the stores), sizes become first slots, rows go to their slots.
-__global__ __launch_bounds__(kGlNumberThreads) void glob_number_kernel(GlobParams p) {
-    extern __shared__ unsigned int s_size2[];       // members filed per cluster, two 16-bit fields a word (n <= 32768); later first slots
+// Clusters are numbered in seed order and their members in row order.
+//   rank    a workgroup per kGlRankRows rows: the cluster of every row and its place among the rows of that cluster here; how many rows of these each
+//           cluster has.
+//   slots   a thread per cluster: sums over the workgroups of rank, the cluster's size and where its members go (space taken in any order).
+//   place   a thread per row: its slot.
+// (One workgroup per head did all of it before: 86 us for 8 heads x 32768 rows whatever the chip had free.)
+constexpr int kGlRankRows = 2048, kGlRankThreads = 512;
+
+__device__ __forceinline__ uint64_t gl_seed_mask(const unsigned long long *st, int I) {
+    return (st[2 * I] >> 32) | (st[2 * I + 1] & 0xFFFFFFFF00000000ull);
+}
+// rows of each cluster in every part of kGlRankRows rows, later in the parts before: 16-bit fields, two to a word.  (In the memory of U: nobody reads that
+// any more, and its 256 nbp (nbp + 1) bytes per head hold them for every length.)
+__device__ __forceinline__ unsigned int *gl_part_sizes(const GlobParams &p, int bh, int part) {
+    return reinterpret_cast<unsigned int *>(p.U + (long long)bh * p.tri) + (int64_t)part * (p.nbp * kGlBlock / 2);
+}
+
+__global__ __launch_bounds__(kGlRankThreads) void glob_rank_kernel(GlobParams p) {
+    extern __shared__ unsigned int s_size2[];       // rows filed per cluster, two 16-bit fields a word
     __shared__ unsigned long long s_mask[512];      // seeds of every block
     __shared__ int s_pref[512];                     // clusters before block J
-    __shared__ int s_scan[kGlNumberThreads];
-    __shared__ int s_undecided;
-    const int bh = blockIdx.x, b = bh / p.Hkv, h = bh - b * p.Hkv;
-    const int n = __builtin_amdgcn_readfirstlane(gl_seq_len(p, b));
-    const int nb = (n + kGlBlock - 1) / kGlBlock;
-    const int npad = p.nbp * kGlBlock;
+    __shared__ int s_scan[kGlRankThreads / kWave];
+    __shared__ int s_lead[kGlRankRows];
+    const int bh = (int)blockIdx.x % (p.B * p.Hkv), part = (int)blockIdx.x / (p.B * p.Hkv);
+    const int n = __builtin_amdgcn_readfirstlane(gl_seq_len(p, bh / p.Hkv));
+    const int first = part * kGlRankRows;
+    if (first >= n && part > 0) return;      // (the first one reports, too)
+    const int nb = (n + kGlBlock - 1) / kGlBlock, npad = p.nbp * kGlBlock;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const unsigned long long *st = p.state + (int64_t)bh * p.nbp * 2;
     const int32_t *join = p.join + (int64_t)bh * npad, *place = p.place + (int64_t)bh * npad;
-    int32_t *lead = p.lead + (int64_t)bh * npad, *order = p.order + (int64_t)bh * npad;
-    int32_t *cid_out = p.cluster_id ? p.cluster_id + (int64_t)bh * p.N_max : nullptr;
-    unsigned short *s_size = reinterpret_cast<unsigned short *>(s_size2);
-    if (tid == 0) s_undecided = 0;
-    for (int i = tid; i < npad / 2; i += kGlNumberThreads) s_size2[i] = 0u;
-    __syncthreads();
-    {
-        bool open = false;
-        if (tid < 2 * nb) {
-            const int rows = n - tid * 32;
-            const uint32_t want = rows <= 0 ? 0u : (rows >= 32 ? 0xFFFFFFFFu : (1u << rows) - 1u);
-            open = ((uint32_t)st[tid] & want) != want;
-        }
-        if (open) s_undecided = 1;
-    }
-    __syncthreads();
-    if (s_undecided != 0) {      // (2 * nb <= 1024 words: one look each)
-        if (wave == 0) {
-            const bf16_t *Kbh = p.K + b * p.stride_b + h * p.stride_h;
-            for (int J = 0; J < nb; ++J) {
-                uint64_t dec, sds;
-                gl_load_state(st, J, dec, sds);
-                const uint64_t all = gl_bits_below(min(kGlBlock, n - J * kGlBlock));
-                if (dec == all) continue;
-                glob_decide_block(p, bh, Kbh, n, J, lane, 0);      // every earlier row is decided: nothing to wait for
-                __threadfence();                                   // the next block's wavefront-wide loads see it
-            }
-        }
-        __threadfence();
-        __syncthreads();
-    }
-    // ---- clusters before every block
-    int mine = 0;
-    if (tid < 512) {
-        uint64_t m = 0ull;
-        if (tid < nb) {
-            const unsigned long long w0 = __hip_atomic_load(st + 2 * tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned long long w1 = __hip_atomic_load(st + 2 * tid + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            m = (w0 >> 32) | (w1 & 0xFFFFFFFF00000000ull);
-        }
-        s_mask[tid] = m;
-        mine = __popcll(m);
-    }
-    // exclusive sum over the workgroup; total in the last entry
-    auto scan = [&](int x) {
-        int incl = x;
+    constexpr int kPer = kGlRankRows / kGlRankThreads;
+    int t[kPer], pl[kPer];
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int up = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += up;
-        }
-        if (lane == kWave - 1) s_scan[wave] = incl;
-        __syncthreads();
-        int before = 0;
-        for (int w = 0; w < wave; ++w) before += s_scan[w];
-        return before + incl - x;
-    };
-    const int pref = scan(mine);
-    if (tid < 512) s_pref[tid] = pref;
-    int P = 0;
-    for (int w = 0; w < kGlNumberThreads / kWave; ++w) P += s_scan[w];
+    for (int q = 0; q < kPer; ++q) {
+        const int j = first + q * kGlRankThreads + tid;
+        t[q] = j < n ? join[j] : 0;
+        pl[q] = j < n ? place[j] : 0;
+    }
+    // ---- clusters before every block (512 at most)
+    const uint64_t m = tid < nb ? gl_seed_mask(p.state + (int64_t)bh * p.nbp * 2, tid) : 0ull;
+    const int mine = __popcll(m);
+    int incl = mine;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int up = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += up;
+    }
+    if (lane == kWave - 1) s_scan[wave] = incl;
+    s_mask[tid] = m;
     __syncthreads();
-    // ---- the cluster of every row
-    constexpr int kPer = 32;             // 1024 threads x 32 = 32768 clusters at most
-    auto cluster_of = [&](int seed_row) { return s_pref[seed_row >> 6] + (int)__popcll(s_mask[seed_row >> 6] & gl_bits_below(seed_row & 63)); };
-    for (int j0 = tid; j0 < n; j0 += 8 * kGlNumberThreads) {
-        int t[8], pl[8];
+    int before = 0, P = 0;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int j = j0 + q * kGlNumberThreads;
-            t[q] = j < n ? join[j] : 0;
-            pl[q] = j < n ? place[j] : 0;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int j = j0 + q * kGlNumberThreads;
-            if (j < n) {
-                const int c = cluster_of(t[q]);
-                if (cid_out) cid_out[j] = c;
-                lead[j] = (pl[q] & kGlLeader) ? c | ((pl[q] & 0x7F) << 16) : -1;
-            }
-        }
+    for (int w = 0; w < kGlRankThreads / kWave; ++w) {
+        if (w < wave) before += s_scan[w];
+        P += s_scan[w];
+    }
+    s_pref[tid] = before + incl - mine;
+    for (int i = tid; i < (P + 1) / 2; i += kGlRankThreads) s_size2[i] = 0u;
+    if (part == 0 && tid == 0) {
+        p.nclusters[bh] = P;
+        p.comp_lens[bh] = (P <= p.cap) ? P : -1;
     }
     __syncthreads();
-    // ---- slots inside the clusters, in row order
+    // ---- the cluster of every row; the first rows of a cluster in a block file all its rows there
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int j = first + q * kGlRankThreads + tid;
+        t[q] = s_pref[t[q] >> 6] + (int)__popcll(s_mask[t[q] >> 6] & gl_bits_below(t[q] & 63));
+        if (p.cluster_id && j < n) p.cluster_id[(int64_t)bh * p.N_max + j] = t[q];
+        s_lead[q * kGlRankThreads + tid] = (j < n && (pl[q] & kGlLeader)) ? t[q] | ((pl[q] & 0x7F) << 16) : -1;
+    }
+    __syncthreads();
+    // ---- places in row order: one wavefront, block by block (LDS additions of one wavefront execute in order)
     if (wave == 0) {
         constexpr int kAhead = 8;
-        int v[kAhead], w[kAhead];
-        auto get = [&](int J0, int (&x)[kAhead]) {
-#pragma unroll
-            for (int q = 0; q < kAhead; ++q) {
-                const int j = (J0 + q) * kGlBlock + lane;
-                x[q] = j < n ? lead[j] : -1;
-            }
-        };
-        get(0, v);
-        for (int J0 = 0; J0 < nb; J0 += kAhead) {
-            get(J0 + kAhead, w);
+        for (int J0 = 0; J0 < kGlRankRows / kGlBlock && first + J0 * kGlBlock < n; J0 += kAhead) {
+            int v[kAhead];
             unsigned int old[kAhead];
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) v[q] = s_lead[(J0 + q) * kGlBlock + lane];
 #pragma unroll
             for (int q = 0; q < kAhead; ++q)
                 if (v[q] >= 0) old[q] = atomicAdd(&s_size2[(v[q] & 0xFFFF) >> 1], (unsigned)(v[q] >> 16) << (16 * (v[q] & 1)));
 #pragma unroll
             for (int q = 0; q < kAhead; ++q)
-                if (v[q] >= 0) lead[(J0 + q) * kGlBlock + lane] = (int)((old[q] >> (16 * (v[q] & 1))) & 0xFFFFu);
-#pragma unroll
-            for (int q = 0; q < kAhead; ++q) v[q] = w[q];
+                if (v[q] >= 0) s_lead[(J0 + q) * kGlBlock + lane] = (int)((old[q] >> (16 * (v[q] & 1))) & 0xFFFFu);
         }
     }
     __syncthreads();
-    // ---- cluster sizes -> first slot of every cluster; sizes and length to the outputs
-    {
-        const int per = (P + kGlNumberThreads - 1) / kGlNumberThreads;
-        int local[kPer];
-        int sum = 0;
+    int32_t *lead = p.lead + (int64_t)bh * npad;
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int c = tid * per + q;
-            local[q] = (q < per && c < P) ? (int)s_size[c] : 0;
-            sum += local[q];
-        }
-        int run = scan(sum);
-        int32_t *mbase = p.mbase + (int64_t)bh * (npad + 1), *csize = p.csize + (int64_t)bh * npad;
-        int32_t *counts_bh = p.counts + (int64_t)bh * p.cap;
+    for (int q = 0; q < kPer; ++q) {
+        const int i = q * kGlRankThreads + tid, j = first + i;
+        const int at = (pl[q] & kGlLeader) ? s_lead[i] : s_lead[(i & ~63) + (pl[q] >> 8)] + (pl[q] & 0x7F);
+        if (j < n) lead[j] = t[q] | (at << 16);
+    }
+    unsigned int *sizes = gl_part_sizes(p, bh, part);
+    for (int i = tid; i < (P + 1) / 2; i += kGlRankThreads) sizes[i] = s_size2[i];
+}
+
+__global__ __launch_bounds__(256) void glob_slots_kernel(GlobParams p) {
+    __shared__ int s_scan[4];
+    __shared__ int s_base;
+    const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int n = gl_seq_len(p, bh / p.Hkv), P = p.nclusters[bh], npad = p.nbp * kGlBlock;
+    if ((int)blockIdx.x * 512 >= P) return;
+    const int c = ((int)blockIdx.x * 256 + tid) * 2;      // two clusters a thread
+    unsigned int sum = 0u;      // (n <= 32768: the fields do not spill over)
+    if (c < P)
+        for (int part = 0; part * kGlRankRows < n; part += 4) {
+            unsigned int x[4];
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int c = tid * per + q;
-            if (q < per && c < P) {
-                mbase[c] = run;
-                csize[c] = local[q];
-                if (c < p.cap) counts_bh[c] = local[q];
-                s_size[c] = (unsigned short)run;      // n <= 32768: a slot index fits 16 bits
-                run += local[q];
+            for (int q = 0; q < 4; ++q) x[q] = (part + q) * kGlRankRows < n ? gl_part_sizes(p, bh, part + q)[c / 2] : 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if ((part + q) * kGlRankRows < n) gl_part_sizes(p, bh, part + q)[c / 2] = sum;
+                sum += x[q];
             }
         }
-        if (tid == 0) {
-            p.nclusters[bh] = P;
-            p.comp_lens[bh] = (P <= p.cap) ? P : -1;
-        }
+    const int s0 = (int)(sum & 0xFFFFu), s1 = (int)(sum >> 16);
+    int incl = s0 + s1;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int up = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += up;
     }
+    if (lane == kWave - 1) s_scan[wave] = incl;
     __syncthreads();
-    for (int j0 = tid; j0 < n; j0 += 8 * kGlNumberThreads) {
-        int t[8], pl[8], at[8];
+    int32_t *mbase = p.mbase + (int64_t)bh * (npad + 1);
+    if (tid == 0) s_base = atomicAdd(mbase + npad, s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3]);
+    __syncthreads();
+    int at = s_base + incl - s0 - s1;
+    for (int w = 0; w < wave; ++w) at += s_scan[w];
+    int32_t *csize = p.csize + (int64_t)bh * npad, *counts = p.counts + (int64_t)bh * p.cap;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int j = j0 + q * kGlNumberThreads;
-            t[q] = j < n ? join[j] : 0;
-            pl[q] = j < n ? place[j] : kGlLeader;
+    for (int q = 0; q < 2; ++q) {
+        if (c + q < P) {
+            mbase[c + q] = at;
+            csize[c + q] = q ? s1 : s0;
+            if (c + q < p.cap) counts[c + q] = q ? s1 : s0;
         }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int j = j0 + q * kGlNumberThreads;
-            at[q] = j < n ? lead[(pl[q] & kGlLeader) ? j : (j & ~63) + (pl[q] >> 8)] + ((pl[q] & kGlLeader) ? 0 : (pl[q] & 0x7F)) : 0;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int j = j0 + q * kGlNumberThreads;
-            if (j < n) order[(int)s_size[cluster_of(t[q])] + at[q]] = j;
-        }
+        at += s0;
     }
+}
+
+__global__ __launch_bounds__(256) void glob_place_kernel(GlobParams p) {
+    const int bh = blockIdx.y, j = (int)blockIdx.x * 256 + (int)threadIdx.x, npad = p.nbp * kGlBlock;
+    if (j >= gl_seq_len(p, bh / p.Hkv)) return;
+    const int v = p.lead[(int64_t)bh * npad + j], c = v & 0xFFFF;
+    const unsigned int before = gl_part_sizes(p, bh, j / kGlRankRows)[c / 2];
+    p.order[(int64_t)bh * npad + p.mbase[(int64_t)bh * (npad + 1) + c] + (int)((c & 1) ? before >> 16 : before & 0xFFFFu) + (v >> 16)] = j;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -800,7 +916,7 @@ static bool glob_fast_ok(const GscMergeArgs &a) {
            a.tune.gsc_fast_path != 0;
 }
 static size_t glob_head_bytes(int N_max) {   // upper bound of what launch_gsc_global lays out per (sequence, head)
-    const size_t nbp = (size_t)(N_max + kGlBlock - 1) / kGlBlock, npad = nbp * kGlBlock, nseg = (nbp + kGlSegment - 1) / kGlSegment;
+    const size_t nbp = (size_t)(N_max + kGlBlock - 1) / kGlBlock, npad = nbp * kGlBlock, nseg = (nbp + kGlWordBlocks - 1) / kGlWordBlocks;
     const size_t tri = 64 * nbp * (nbp + 1) / 2;
     return 6 * align_up(npad * 4, 256) + 2 * align_up(tri * 8, 256) + align_up((npad + 1) * 4, 256) + 2 * align_up(nbp * nseg * 8, 256) +
            align_up(nbp * 16, 256);
@@ -815,6 +931,23 @@ size_t gsc_global_workspace_bytes(int B, int Hkv, int N_max, int d) {
         fast = glob_head_bytes(N_max) * (size_t)B * Hkv + align_up((size_t)B * Hkv * 4, 256);
     }
     return glob_prefix_bytes(B) + (ordinary > fast ? ordinary : fast);
+}
+
+// Words of flags (of 64 column blocks) of a stage.  In us, with a seed in about three rows: all pairs at 1.16 PFLOP/s, and what a further stage's
+// two launches and the chain of its decisions cost.  (Us per call, stages of 4096 / 8192 / 16384 rows / one: 8 heads x 32768 647 / 664 / 815 / 1030,
+// with tau 0.9745 822 / 800 / 860 / 1044; 2 heads 397 / 316 / 304 / 360; 8 heads x 9000 218 / 216 / - / 185: numbering still in one workgroup per head.)
+static int glob_stage_words(size_t heads, int n, int nseg) {
+    const double all = (double)heads * n * n * 128 / 1.16e9, stage_cost = 26.0, seeds = 0.35;
+    int best = nseg;
+    double least = all;
+    for (int m = nseg - 1; m >= 1; --m) {
+        double own = 0.0;      // share of the pairs that lie within a stage
+        int stages = 0;
+        for (int s = 0; s < nseg; s += m, ++stages) own += (double)min(m, nseg - s) * min(m, nseg - s) / ((double)nseg * nseg);
+        const double cost = all * (own + seeds * (1.0 - own)) + stage_cost * (stages - 1);
+        if (cost < least) { least = cost; best = m; }
+    }
+    return best;
 }
 
 hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
@@ -851,7 +984,7 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     p.mbase = reinterpret_cast<int32_t *>(rest + o); o += align_up((npad + 1) * 4 * BH, 256);
     p.csize = reinterpret_cast<int32_t *>(rest + o); o += align_up(npad * 4 * BH, 256);
     p.nclusters = reinterpret_cast<int32_t *>(rest + o); o += align_up(4 * BH, 256);
-    p.nseg = (p.nbp + kGlSegment - 1) / kGlSegment;
+    p.nseg = (p.nbp + kGlWordBlocks - 1) / kGlWordBlocks;
     p.tany = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * p.nseg * 8 * BH, 256);
     p.tuns = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * p.nseg * 8 * BH, 256);
     p.state = reinterpret_cast<unsigned long long *>(rest + o); o += align_up((size_t)p.nbp * 16 * BH, 256);
@@ -860,15 +993,33 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     hipLaunchKernelGGL(glob_norms_kernel, dim3((unsigned)(npad / 16), (unsigned)BH), dim3(256), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int njg = (p.nbp + kGlPairWaves - 1) / kGlPairWaves;
-    int items = 0;      // see the kernel: group JG has JG / 16 + 1 segments
-    for (int jg = 0; jg < njg; ++jg) items += jg / 16 + 1;
-    hipLaunchKernelGGL(glob_pairs_kernel, dim3((unsigned)items, (unsigned)BH), dim3(kGlPairWaves * kWave), 0, stream, p);
+    p.seedlist = p.order;
+    p.stage_words = glob_stage_words(BH, a.N_max, p.nseg);
+    p.stage = 0;
+    const int M = p.stage_words, stages = (p.nseg + M - 1) / M;
+    // Length of a walk: the longest that leaves eight items for each of the 512 places (two workgroups on each of 256 CUs), so that the last ones do not
+    // matter.  (Us per call with 8 / 16 / 32 blocks: 8 heads x 32768 619 / 600 / 599; x 20000 367 / 372 / 411; x 3000 79 / 97 / 143.)
+    int items = 0;
+    for (p.walk = 32; p.walk >= 8; p.walk /= 2) {
+        const int stage_segs = M * kGlWordBlocks / p.walk;
+        items = p.walk / kGlPairWaves * stage_segs * (stage_segs + 1) / 2;
+        if ((size_t)stages * items * BH >= 4096 || p.walk == 8) break;
+    }
+    hipLaunchKernelGGL((glob_pairs_kernel<false>), dim3((unsigned)(stages * items * BH)), dim3(kGlPairWaves * kWave), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(glob_decide_kernel, dim3((unsigned)(p.nbp * BH)), dim3(kWave), 0, stream, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    for (p.stage = 0; p.stage < stages; ++p.stage) {
+        const int first = p.stage * M * kGlWordBlocks, blocks = min(M * kGlWordBlocks, p.nbp - first);
+        if (p.stage > 0) {
+            const int groups = (blocks + kGlPairWaves - 1) / kGlPairWaves;
+            hipLaunchKernelGGL((glob_pairs_kernel<true>), dim3((unsigned)(groups * (first / (kGlSeedUnit * kGlSeedShare)) * BH)), dim3(kGlPairWaves * kWave), 0, stream, p);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(glob_decide_kernel, dim3((unsigned)(blocks * BH)), dim3(kWave), 0, stream, p);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     const size_t dyn = npad * sizeof(unsigned short);
     if (dyn > 48 * 1024) {   // a host-side setting of the kernel (per device), not a stream operation
         int dev = 0;
@@ -879,12 +1030,18 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
         if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         std::lock_guard<std::mutex> lock(mu);
         if (!raised[dev]) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(glob_number_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(glob_rank_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
             if (e != hipSuccess) return e;
             raised[dev] = true;
         }
     }
-    hipLaunchKernelGGL(glob_number_kernel, dim3((unsigned)BH), dim3(kGlNumberThreads), dyn, stream, p);
+    hipLaunchKernelGGL(glob_rank_kernel, dim3((unsigned)((a.N_max + kGlRankRows - 1) / kGlRankRows * BH)), dim3(kGlRankThreads), dyn, stream, p);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(glob_slots_kernel, dim3((unsigned)((a.N_max + 511) / 512), (unsigned)BH), dim3(256), 0, stream, p);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(glob_place_kernel, dim3((unsigned)((a.N_max + 255) / 256), (unsigned)BH), dim3(256), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int max_clusters = a.N_max < a.cap ? a.N_max : a.cap;

@@ -216,3 +216,46 @@ def test_random_structures_as_one_chunk(seed):
             assert g.rowwise_err(Vc[b, h, :rows].cpu().numpy(), r["Vc"][:rows]) <= 1e-3
     assert compared >= (B * H + 1) // 2, (seed, compared)
     print("seed", seed, "compared", compared, "N", N, "tau", tau, "rows", clens.cpu().numpy().tolist())
+
+
+@pytest.mark.parametrize("tau,polls,drift", [(0.7, 1 << 20, 0.0), (0.9745, 1 << 20, 0.0), (0.9745, 0, 0.0), (0.8, 1 << 20, 0.4), (0.99875, 0, 0.05)])
+def test_sequences_long_enough_for_stages(tau, polls, drift):
+    # 8 heads x 12365 tokens are decided in stages: rows of the second are compared with the seeds of the first, listed without
+    # gaps (pairs decided in fp64 among them); one sequence ends inside the second stage's first blocks, one inside the first stage.
+    # Rows that drift: chains that a stage ends in the middle of; without patience every stage is finished by its last wavefront.
+    import oracle
+    rng = np.random.default_rng(int(1000 * tau) + polls % 7)
+    B, H, N, d = 2, 4, 12365, 128
+    lens = np.array([N, 5003] if drift else [8192 + 65, N], np.int32)
+    look = [(0, 1), (1, 2)]
+    if drift:
+        K = rng.standard_normal((B, H, N, d)).astype(np.float32)
+        for i in range(1, N):
+            K[:, :, i] = np.sqrt(1 - drift * drift) * K[:, :, i - 1] + drift * K[:, :, i]
+        K[:, :, 8190:8195] = 0.0
+    else:
+        centers = rng.standard_normal((B, H, N // 24, d)).astype(np.float32)
+        near = np.clip(np.arange(N) // 24 + rng.integers(-6, 7, size=N), 0, N // 24 - 1)
+        near[::97] = rng.integers(0, N // 24, size=len(near[::97]))      # some resemble rows of other stages
+        K = centers[:, :, near] + 0.15 * rng.standard_normal((B, H, N, d)).astype(np.float32)
+    K = _bf16_exact(K)
+    V = _bf16_exact(rng.standard_normal((B, H, N, d)))
+    old = sc.tune_get("global_polls")
+    try:
+        sc.tune_set("global_polls", polls)
+        Kc, Vc, counts, clens, cid = sc.sc_gsc_merge_global(g.to_device(K, True), g.to_device(V, True), tau, seq_lens=torch.from_numpy(lens).to(g.DEV),
+                                                            out_dtype=torch.float32, want_cluster_id=True)
+        torch.cuda.synchronize()
+    finally:
+        sc.tune_set("global_polls", old)
+    for b, h in look:
+        n = int(lens[b])
+        r = oracle.compress_head(K[b, h, :n], V[b, h, :n], np.array([0, n + 1], np.int32), tau)
+        assert r["chunk_margin"].min() > 1e-9
+        rows = r["n_rows"]
+        assert int(clens[b, h]) == rows
+        assert np.array_equal(cid[b, h, :n].cpu().numpy(), r["cid"])
+        assert np.array_equal(counts[b, h, :rows].cpu().numpy(), r["counts"][:rows])
+        assert g.rowwise_err(Kc[b, h, :rows].cpu().numpy(), r["Kc"][:rows]) <= 1e-3
+        assert g.rowwise_err(Vc[b, h, :rows].cpu().numpy(), r["Vc"][:rows]) <= 1e-3
+        print("b %d h %d: rows %d of %d" % (b, h, rows, n))
