@@ -16,9 +16,9 @@
 //            scales by 1/size and writes the output row: Eq. 3.
 // A row needs comparing with SEEDS only, and one row in six is one where merging pays.  Long sequences are therefore taken in stages of 4096 rows
 // or a multiple: all pairs inside the stages (one launch), then stage by stage the rows of a stage against the seeds of the stages before, listed without
-// gaps, and the decisions of the stage.  8 heads x 32768 tokens, us per call: tau 0.7 1020 with all pairs, 600 in four stages of 8192 rows (pairs inside them 275,
-// with the seeds 46 + 90 + 102, decide 4 x 18); tau 0.979, half the rows seeds, 1045 and 900.  What that costs where every row is a seed
-// (tau 1: 1100 and 1330) buys nothing, so stages are only as short as one seed in three rows pays for.
+// gaps, and the decisions of the stage.  8 heads x 32768 tokens, us per call: tau 0.7 1020 with all pairs, 576 in four stages of 8192 rows (pairs inside them 260,
+// with the seeds 46 + 78 + 90, decide 4 x 18); tau 0.979, half the rows seeds, 1045 and 853.  What that costs where every row is a seed
+// (tau 1: 1100 and 1140) buys nothing, so stages are only as short as one seed in three rows pays for.
 // Everything else (other element types, head dims, longer sequences) is handed to the ordinary kernels
 // of sc_gsc_merge with offsets that describe one chunk per sequence.
 #include "sc_device.h"
@@ -134,8 +134,11 @@ __global__ __launch_bounds__(256) void glob_norms_kernel(GlobParams p) {
 // the rows of block I pass through an LDS tile shared by the four wavefronts and are the A operand.  The
 // product tile leaves lane (g, c) with the dot products of row 16 Jt + c of block J and rows
 // 16 It + 4 g + i of block I: four bits of that row's word, completed by an OR over the lane groups.
+// Bound by the matrix cores, busy 55 % of the time, and the threshold step beside them.  Two quarters of a tile in registers at a time, so that three
+// workgroups share a compute unit: 8 heads x 32768 rows 606 us a call with all four and two workgroups, 576 so (x 1000 62 and 67: near the diagonal, where
+// every quarter holds a pair, they are formed twice).
 template <bool SEEDS>
-__global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(GlobParams p) {
+__global__ __launch_bounds__(kGlPairWaves *kWave, 3) void glob_pairs_kernel(GlobParams p) {
     constexpr int kListTiles = kGlSeedUnit * kGlSeedShare;
     __shared__ __attribute__((aligned(16))) char s_tiles[2][kGlBlock * kGlTileRowBytes];      // two tiles: one worked on, one being filled
     __shared__ __attribute__((aligned(16))) float s_rinvs[2][kGlBlock];
@@ -254,9 +257,9 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
     bad_j = ballot64(bad_j) != 0ull;
     // the tile of block I: thread t brings rows t / 16 + 16 r, piece t % 16
     const int lrow = tid >> 4, lc = tid & 15;
-    uint4 pre_a[4], pre_b[4];      // two tiles on their way
-    float pre_ra = 0.f, pre_rb = 0.f;
-    auto fetch = [&](int I, uint4 (&pre)[4], float &pre_r) {
+    uint4 pre[4];      // the next tile on its way
+    float pre_r = 0.f;
+    auto fetch = [&](int I) {
         if (I > I_last) return;
         if constexpr (SEEDS) {
             const int at = (I - I_first) * kGlBlock;
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
         }
         if (tid < kGlBlock) pre_r = rinv_bh[I * kGlBlock + tid];
     };
-    auto park = [&](int I, const uint4 (&pre)[4], float pre_r) {
+    auto park = [&](int I) {
         if (I > I_last) return;
         char *t = s_tiles[I & 1];
 #pragma unroll
@@ -290,10 +293,10 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
         }
     };
     uint32_t any_bits = 0u, uns_bits = 0u;      // of this walk's column blocks
-    auto work = [&](int I, uint4 (&pre)[4], float &pre_r) {
+    auto work = [&](int I) {
         __syncthreads();          // tile I is complete; everybody is done with tile I - 1, whose buffer takes tile I + 1 now
-        park(I + 1, pre, pre_r);
-        fetch(I + 3, pre, pre_r);      // on its way while this tile and the next are worked on
+        park(I + 1);
+        fetch(I + 2);      // on its way while this tile is worked on
         const char *s_tile = s_tiles[I & 1];
         const float *s_rinv = s_rinvs[I & 1];
         if (!active || (!SEEDS && I > J)) return;    // wave-uniform
@@ -302,46 +305,47 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
 #pragma unroll
         for (int Jt = 0; Jt < 4; ++Jt) yl[Jt] = yh[Jt] = ul[Jt] = uh[Jt] = 0u;
         // sim(m, n) > t  <=>  dot * rinv_m > t * norm_n.  Hardly any tile holds a pair that comes near: one multiply-add
-        // and half a maximum per pair tell.  All products of the tile are asked for before the first answer is looked at, so that the
-        // matrix cores go on while the vector unit compares.
-        gl_float4 acc[4][4];
-        uint64_t near[4];
+        // and half a maximum per pair tell, for one quarter of the tile while the products of the next are formed.  A quarter that does is formed again.
+        gl_float4 acc[2][4];
         float top[4];
         uint4 a[4];
         gl_float4 rm;
-        auto operand = [&](int step) { return *reinterpret_cast<const uint4 *>(s_tile + (16 * (step >> 2) + c) * kGlTileRowBytes + (32 * (step & 3) + 8 * g) * 2); };
+        auto operand = [&](int It, int ks) { return *reinterpret_cast<const uint4 *>(s_tile + (16 * It + c) * kGlTileRowBytes + (32 * ks + 8 * g) * 2); };
+        auto product = [&](gl_float4 (&x)[4], const uint4 &rows, int ks) {
+#pragma unroll
+            for (int Jt = 0; Jt < 4; ++Jt) {
+                if (ks == 0) x[Jt] = gl_float4{0.f, 0.f, 0.f, 0.f};
+                x[Jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(gl_bf16x8, rows), __builtin_bit_cast(gl_bf16x8, bq[Jt][ks]), x[Jt], 0, 0, 0);
+            }
+        };
         auto compare = [&](int It, int Jt) {
             if (Jt == 0) rm = *reinterpret_cast<const gl_float4 *>(s_rinv + 16 * It + 4 * g);
-            const float t0 = fmaf(acc[It][Jt][0], rm[0], -ln[Jt]), t1 = fmaf(acc[It][Jt][1], rm[1], -ln[Jt]);
-            const float t2 = fmaf(acc[It][Jt][2], rm[2], -ln[Jt]), t3 = fmaf(acc[It][Jt][3], rm[3], -ln[Jt]);
+            const gl_float4 &x = acc[It & 1][Jt];
+            const float t0 = fmaf(x[0], rm[0], -ln[Jt]), t1 = fmaf(x[1], rm[1], -ln[Jt]), t2 = fmaf(x[2], rm[2], -ln[Jt]), t3 = fmaf(x[3], rm[3], -ln[Jt]);
             top[It] = (Jt == 0) ? fmaxf(t0, t1) : fmaxf(fmaxf(top[It], t0), t1);
             top[It] = fmaxf(fmaxf(top[It], t2), t3);
         };
 #pragma unroll
-        for (int step = 0; step < 3; ++step) a[step] = operand(step);
+        for (int step = 0; step < 3; ++step) a[step] = operand(step >> 2, step & 3);
 #pragma unroll
         for (int step = 0; step < 16; ++step) {
-            if (step + 3 < 16) a[(step + 3) & 3] = operand(step + 3);
-#pragma unroll
-            for (int Jt = 0; Jt < 4; ++Jt) {
-                if (step % 4 == 0) acc[step >> 2][Jt] = gl_float4{0.f, 0.f, 0.f, 0.f};
-                acc[step >> 2][Jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(gl_bf16x8, a[step & 3]), __builtin_bit_cast(gl_bf16x8, bq[Jt][step & 3]),
-                                                                             acc[step >> 2][Jt], 0, 0, 0);
-            }
+            if (step + 3 < 16) a[(step + 3) & 3] = operand((step + 3) >> 2, (step + 3) & 3);
+            product(acc[(step >> 2) & 1], a[step & 3], step & 3);
             if (step >= 4) compare((step >> 2) - 1, step & 3);
             __builtin_amdgcn_sched_barrier(0);      // the order of issue stays as written
         }
 #pragma unroll
         for (int Jt = 0; Jt < 4; ++Jt) compare(3, Jt);
-        const uint64_t all_near = odd ? ~0ull : 0ull;
+        int near = odd ? 15 : 0;      // quarters with a pair that comes near
 #pragma unroll
-        for (int It = 0; It < 4; ++It) near[It] = ballot64(top[It] >= 0.f) | all_near;
-        const bool touched = (near[0] | near[1] | near[2] | near[3]) != 0ull;
-        if (!touched && (SEEDS || I != J)) return;
-#pragma unroll
+        for (int It = 0; It < 4; ++It) near |= ballot64(top[It] >= 0.f) != 0ull ? 1 << It : 0;
+        if (near == 0 && (SEEDS || I != J)) return;
         for (int It = 0; It < 4; ++It) {
-            if (near[It] == 0ull) continue;
-            const gl_float4 rm = *reinterpret_cast<const gl_float4 *>(s_rinv + 16 * It + 4 * g);
+            if (((near >> It) & 1) == 0) continue;
+            gl_float4 (&x)[4] = acc[0];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) product(x, operand(It, ks), ks);
+            rm = *reinterpret_cast<const gl_float4 *>(s_rinv + 16 * It + 4 * g);
             // dd = (tau + band) * norm_n - dot * rinv_m is negative for a sure yes and at most 2 * band * norm_n inside the
             // band: the sign bit of dd is shifted into a nibble, an unsigned minimum over the bit patterns keeps the smallest
             // non-negative dd (negative values compare as huge).  Only if some lane saw a value inside the band, or a row
@@ -355,7 +359,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
                 uint32_t nib = 0u, dmin = 0x7F800000u;
 #pragma unroll
                 for (int i = 3; i >= 0; --i) {
-                    const uint32_t dd = __float_as_uint(fmaf(-acc[It][Jt][i], rm[i], hn[Jt]));
+                    const uint32_t dd = __float_as_uint(fmaf(-x[Jt][i], rm[i], hn[Jt]));
                     nib = __builtin_amdgcn_alignbit(nib, dd, 31);      // (nib << 1) | sign bit
                     dmin = min(dmin, dd);
                 }
@@ -368,7 +372,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
                     uint32_t y4 = 0u, u4 = 0u;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float dd = fmaf(-acc[It][Jt][i], rm[i], hn[Jt]);
+                        const float dd = fmaf(-x[Jt][i], rm[i], hn[Jt]);
                         const bool yes = dd < 0.f;
                         const bool unsure = !yes && !(dd > wn[Jt]);
                         y4 |= yes ? (1u << i) : 0u;
@@ -404,14 +408,10 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 2) void glob_pairs_kernel(Glob
         any_bits |= any ? 1u << (I - I_first) : 0u;
         uns_bits |= any_u ? 1u << (I - I_first) : 0u;
     };
-    fetch(I_first, pre_a, pre_ra);
-    park(I_first, pre_a, pre_ra);
-    fetch(I_first + 1, pre_b, pre_rb);
-    fetch(I_first + 2, pre_a, pre_ra);
-    for (int I = I_first; I <= I_last; I += 2) {
-        work(I, pre_b, pre_rb);
-        if (I + 1 <= I_last) work(I + 1, pre_a, pre_ra);
-    }
+    fetch(I_first);
+    park(I_first);
+    fetch(I_first + 1);
+    for (int I = I_first; I <= I_last; ++I) work(I);
     if (active && lane < kListTiles / 8 && I_first + 8 * lane <= (SEEDS ? I_last : I_first + p.walk - 1)) {
         flags8(p.tany)[I_first / 8 + lane] = (unsigned char)(any_bits >> (8 * lane));
         flags8(p.tuns)[I_first / 8 + lane] = (unsigned char)(uns_bits >> (8 * lane));
@@ -997,7 +997,7 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     p.stage_words = glob_stage_words(BH, a.N_max, p.nseg);
     p.stage = 0;
     const int M = p.stage_words, stages = (p.nseg + M - 1) / M;
-    // Length of a walk: the longest that leaves eight items for each of the 512 places (two workgroups on each of 256 CUs), so that the last ones do not
+    // Length of a walk: the longest that leaves some five items for each of the 768 places (three workgroups on each of 256 CUs), so that the last ones do not
     // matter.  (Us per call with 8 / 16 / 32 blocks: 8 heads x 32768 619 / 600 / 599; x 20000 367 / 372 / 411; x 3000 79 / 97 / 143.)
     int items = 0;
     for (p.walk = 32; p.walk >= 8; p.walk /= 2) {
