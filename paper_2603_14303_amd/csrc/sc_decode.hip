@@ -190,6 +190,17 @@ __device__ __forceinline__ void file_failure(const DecParams &p, HeadSync *hs, i
     }
 }
 
+// One split has nothing to hand over: element e of query head hh of the group, sum a over denominator l.  (Through a partial of its own, as with
+// several splits, a head of 170 rows waited for a round trip to memory: 8 heads x 170 rows x 128 bf16 7.2 us, 5.4 so; 2 x 170 x 64 fp32 7.0 and 4.5.)
+template <int G, int D>
+__device__ __forceinline__ void store_alone(const DecParams &p, int b, int h, int hh, int e, float a, float m_log2, float l) {
+    const int64_t row = (int64_t)b * p.Hq + (int64_t)h * G + hh;
+    const float x = a * ((l > 0.f) ? 1.0f / l : 0.f);
+    if (p.o_is_bf16) reinterpret_cast<uint16_t *>(p.O)[row * D + e] = (uint16_t)pack_bf16x2(x, x);
+    else reinterpret_cast<float *>(p.O)[row * D + e] = x;
+    if (e == 0 && p.lse) p.lse[row] = (l > 0.f) ? (m_log2 + __log2f(l)) * kLn2 : -INFINITY;
+}
+
 constexpr int kPartPad = 4;   // floats after the D accumulators of a partial: m, l, 2 unused (keeps 16-byte rows)
 
 typedef unsigned int u32x4_dec_t __attribute__((ext_vector_type(4)));
@@ -528,21 +539,33 @@ __global__ __launch_bounds__(FastShape<G>::THREADS) void decode_bf16_kernel(DecP
         if (g == 0 && c < G) { s_m[wave][c] = m_run; s_l[wave][c] = lw; }
     }
     __syncthreads();
-    // ---- fold the waves, write this split's partial
-    float *part_bh = p.part + bh * (int64_t)p.max_splits * G * kStride;
-    for (int i = tid; i < G * D; i += THREADS) {
-        const int hh = i / D, e = i % D;
-        float mw = -INFINITY;
+    // ---- fold the waves
+    auto fold = [&](int hh, int e, float &mw, float &a, float &l) {
+        mw = -INFINITY;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) mw = fmaxf(mw, s_m[w][hh]);
         const float m_safe = (mw == -INFINITY) ? 0.f : mw;
-        float a = 0.f, l = 0.f;
+        a = l = 0.f;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
             const float f = fast_exp2(s_m[w][hh] - m_safe);
             a = fmaf(s_buf[(w * G + hh) * D + e], f, a);
             l = fmaf(s_l[w][hh], f, l);
         }
+    };
+    float mw, a, l;
+    if (__builtin_expect(S == 1, 0)) {
+        for (int i = tid; i < G * D; i += THREADS) {
+            fold(i / D, i % D, mw, a, l);
+            store_alone<G, D>(p, b, h, i / D, i % D, a, mw, l);
+        }
+        return;
+    }
+    // ---- write this split's partial
+    float *part_bh = p.part + bh * (int64_t)p.max_splits * G * kStride;
+    for (int i = tid; i < G * D; i += THREADS) {
+        const int hh = i / D, e = i % D;
+        fold(hh, e, mw, a, l);
         float *dst = part_bh + ((int64_t)split * G + hh) * kStride;
         store_partial(dst + e, a, local);
         if (e == 0) { store_partial(dst + D, mw, local); store_partial(dst + D + 1, l, local); }
@@ -709,21 +732,33 @@ __global__ __launch_bounds__(kDecThreads) void decode_generic_kernel(DecParams p
     }
     __syncthreads();
 
-    // ---- fold the waves, write this split's partial
-    float *part_bh = p.part + bh * (int64_t)p.max_splits * G * kStride;
-    for (int i = tid; i < G * D; i += kDecThreads) {
-        const int hh = i / D, e = i % D;
-        float mw = -INFINITY;
+    // ---- fold the waves
+    auto fold = [&](int hh, int e, float &mw, float &a, float &l) {
+        mw = -INFINITY;
 #pragma unroll
         for (int w = 0; w < kDecWaves; ++w) mw = fmaxf(mw, s_m[w][hh]);
         const float m_safe = (mw == -INFINITY) ? 0.f : mw;
-        float a = 0.f, l = 0.f;
+        a = l = 0.f;
 #pragma unroll
         for (int w = 0; w < kDecWaves; ++w) {
             const float f = fast_exp2(s_m[w][hh] - m_safe);
             a = fmaf(s_acc[w][hh][e], f, a);
             l = fmaf(s_l[w][hh], f, l);
         }
+    };
+    float mw, a, l;
+    if (__builtin_expect(S == 1, 0)) {
+        for (int i = tid; i < G * D; i += kDecThreads) {
+            fold(i / D, i % D, mw, a, l);
+            store_alone<G, D>(p, b, h, i / D, i % D, a, mw, l);
+        }
+        return;
+    }
+    // ---- write this split's partial
+    float *part_bh = p.part + bh * (int64_t)p.max_splits * G * kStride;
+    for (int i = tid; i < G * D; i += kDecThreads) {
+        const int hh = i / D, e = i % D;
+        fold(hh, e, mw, a, l);
         float *dst = part_bh + ((int64_t)split * G + hh) * kStride;
         store_partial(dst + e, a, local);
         if (e == 0) { store_partial(dst + D, mw, local); store_partial(dst + D + 1, l, local); }

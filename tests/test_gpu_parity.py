@@ -328,3 +328,33 @@ def test_generic_merge_short_chunks(H, n, gap):
         assert int(got[3][b, H - 1]) == 3 + ref["n_rows"]
         assert np.array_equal(got[4][b, H - 1].cpu().numpy(), ref["cid"])
         assert np.array_equal(got[2][b, H - 1, 3:3 + ref["n_rows"]].cpu().numpy(), ref["counts"][:ref["n_rows"]])
+
+
+@pytest.mark.parametrize("d,bf16,G,tail", [(128, True, 4, 0), (128, True, 7, 40), (64, True, 2, 0), (64, False, 1, 25), (128, False, 3, 0)])
+def test_heads_of_one_split(d, bf16, G, tail):
+    # heads that one workgroup takes alone store their outputs directly, beside heads of two splits in the same launch: no rows at
+    # all, one row, remainders of a step, the last count of one split and the first of two (192 rows each)
+    rng = np.random.default_rng(d + G)
+    rows = np.array([[0, 1], [17, 96], [191 - tail, 192 - tail], [193 - tail, 384]], np.int32)
+    B, H, cap = 4, 2, 400
+    Kc, Vc = (g.to_device(rng.standard_normal((B, H, cap, d)).astype(np.float32), bf16) for _ in range(2))
+    Q = g.to_device(rng.standard_normal((B, H * G, d)).astype(np.float32), bf16)
+    counts = torch.from_numpy(rng.integers(1, 30, size=(B, H, cap)).astype(np.int32)).to(g.DEV)
+    lens = torch.from_numpy(rows).to(g.DEV)
+    ws = sc.decode_attn_workspace(B, H * G, H, cap, d, g.DEV)
+    host = [x.float().cpu().numpy() for x in (Q, Kc, Vc)]
+    if tail:
+        Kt, Vt = (g.to_device(rng.standard_normal((B, H, tail, d)).astype(np.float32), bf16) for _ in range(2))
+        tl = torch.full((B,), tail, dtype=torch.int32, device=g.DEV)
+        O, lse = sc.sc_decode_attn(Q, Kc, Vc, counts, lens, want_lse=True, workspace=ws, Kt=Kt, Vt=Vt, tail_lens=tl)
+        want, want_lse = oracle.decode_attn_tail(*host, counts.cpu().numpy(), rows, Kt.float().cpu().numpy(), Vt.float().cpu().numpy(), tl.cpu().numpy())
+    else:
+        O, lse = sc.sc_decode_attn(Q, Kc, Vc, counts, lens, want_lse=True, workspace=ws)
+        want, want_lse = oracle.decode_attn(*host, counts.cpu().numpy(), rows)
+    torch.cuda.synchronize()
+    got, got_lse = O.float().cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64)
+    seen = np.isfinite(want_lse)
+    assert np.array_equal(np.isneginf(got_lse), np.isneginf(want_lse)) and (got[~seen] == 0).all()
+    # bf16: half an ulp of the stored result (2^-8 of it) is the larger part, fp32: sums of up to 400 terms
+    assert np.abs(got - want).max() <= (4e-3 if bf16 else 2e-5) * max(1.0, np.abs(want).max())
+    assert np.abs(got_lse[seen] - want_lse[seen]).max() <= 1e-3
