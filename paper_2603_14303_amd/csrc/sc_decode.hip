@@ -900,9 +900,11 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t stream) {
     p.poll_budget = tuning().decode_poll_budget;
     p.min_rows = max(1, tuning().decode_min_rows);
     // Splits per (sequence, KV head): enough workgroups to cover the 256 CUs about once; more splits
-    // only add partials to fold and tickets to take (both are serial tails of the kernel).
+    // only add partials to fold and tickets to take (both are serial tails of the kernel).  (A few heads with many rows, us for eight calls
+    // with up to 32 / 64 splits: 4 heads x 33000 rows 169 / 151, x 16000 122 / 110, x 6200 88 / 79; 1 head x 33000 151 / 122, x 8000 88 / 87,
+    // x 3000 the same, since a split gets decode_min_rows at least.)
     int splits = clamp_splits();
-    if (tuning().decode_max_splits <= 0) splits = max(2, min(32, 256 / max(1, a.B * a.Hkv)));
+    if (tuning().decode_max_splits <= 0) splits = max(2, min(kDecMaxSplits, 256 / max(1, a.B * a.Hkv)));
     // never more splits than the capacity can feed
     const int by_cap = (int)(((int64_t)a.cap + p.tail_cap + p.min_rows - 1) / p.min_rows);
     p.max_splits = max(1, min(splits, by_cap));

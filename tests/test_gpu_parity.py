@@ -358,3 +358,19 @@ def test_heads_of_one_split(d, bf16, G, tail):
     # bf16: half an ulp of the stored result (2^-8 of it) is the larger part, fp32: sums of up to 400 terms
     assert np.abs(got - want).max() <= (4e-3 if bf16 else 2e-5) * max(1.0, np.abs(want).max())
     assert np.abs(got_lse[seen] - want_lse[seen]).max() <= 1e-3
+
+
+@pytest.mark.parametrize("d,bf16,H,rows", [(128, True, 1, 12287), (128, True, 2, 20000), (64, False, 1, 12289), (128, False, 4, 6200)])
+def test_a_few_heads_with_many_rows_take_up_to_64_splits(d, bf16, H, rows):
+    rng = np.random.default_rng(rows)
+    G, cap = 3, rows + 5
+    Kc, Vc = (g.to_device(rng.standard_normal((1, H, cap, d)).astype(np.float32), bf16) for _ in range(2))
+    Q = g.to_device(rng.standard_normal((1, H * G, d)).astype(np.float32), bf16)
+    counts = rng.integers(1, 30, size=(1, H, cap)).astype(np.int32)
+    lens = np.full((1, H), rows, np.int32)
+    O, lse = sc.sc_decode_attn(Q, Kc, Vc, torch.from_numpy(counts).to(g.DEV), torch.from_numpy(lens).to(g.DEV), want_lse=True)
+    torch.cuda.synchronize()
+    want, want_lse = oracle.decode_attn(*[x.float().cpu().numpy() for x in (Q, Kc, Vc)], counts, lens)
+    # bf16: half an ulp of the stored result is the larger part; fp32: sums of 20000 terms
+    assert np.abs(O.float().cpu().numpy() - want).max() <= (4e-3 if bf16 else 2e-5) * max(1.0, np.abs(want).max())
+    assert np.abs(lse.cpu().numpy() - want_lse).max() <= 1e-3
