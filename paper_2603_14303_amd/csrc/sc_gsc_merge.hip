@@ -166,9 +166,9 @@ __device__ int gsc_chunk(const T *__restrict__ Kbh, int64_t stride_n, int start,
 // 16, 8 x 32768 x 64 f32, distance 1, takes 169 instead of 140 us and distance 2 118 instead of 104: not all of them are on the chip
 // at once, and the later ones start from the first item again.)
 static int gsc_item_workgroups(int heads, int N_max, int C) { return max(heads <= 8 ? 1024 / heads : min(128, 2048 / heads), N_max / (21 * C)); }
-__device__ __forceinline__ void gsc_item_shape(const GscParams &p, int M, int n, int &C, int &wgs) {
+__device__ __forceinline__ void gsc_item_shape(const GscParams &p, int M, int n, int launched, int &C, int &wgs) {
     C = p.chunks_per_item;
-    wgs = gridDim.y;
+    wgs = launched;
     if (p.short_wgs[0] == 0) return;
     const int64_t tokens = n, chunks = M;
     const bool dense = 2 * tokens < 5 * chunks;
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_assign_kernel(GscParams p) {
     int n = p.seq_lens ? p.seq_lens[b] : p.N_max;
     n = n < 0 ? 0 : (n > p.N_max ? p.N_max : n);
     int C, wgs;
-    gsc_item_shape(p, M, n, C, wgs);
+    gsc_item_shape(p, M, n, (int)gridDim.y, C, wgs);
     if ((int)blockIdx.y >= wgs) return;
     const int items = (M + C - 1) / C;
     const float tau = p.tau_dev ? *p.tau_dev : p.tau;
@@ -325,10 +325,16 @@ __device__ __forceinline__ void store_row8(void *base, int64_t elem_off, const f
 // x 32768 x 64 f32 with a delimiter per token, a call of items of eight took 323 us, 265 so.)
 constexpr int kMergeCidTile = 2048;
 constexpr int kMergeInFlight = 4;
+// APART: one workgroup adds up the keys, its neighbour the values, eight rows in flight each: in a call that leaves most of the chip idle the
+// largest cluster's trips to memory are the kernel's time, and there are workgroups to spare.  Whole call with its sc_segment, together / apart, us:
+// 2 heads x 1024 x 64 f32 35.0 / 31.6, 4 x 4000 51 / 43, 4 x 8000 53 / 45, 4 x 4000 x 64 bf16 65 / 55, 1 x 8000 64 / 53; even from 64k rows on
+// (4 x 16000 x 64 f32 58.5 / 59.5, x 128 70.6 / 70.5).  (Sixteen in flight: 310 registers, a wavefront per SIMD, 4 x 8000 53, 4 x 16000 82.)
+constexpr int kMergeInFlightApart = 8;
 
-template <typename T, int D, bool INLINE_PREFIX>
+template <typename T, int D, bool INLINE_PREFIX, bool APART>
 __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     constexpr int LPR = D / 8;
+    constexpr int kInFlight = APART ? kMergeInFlightApart : kMergeInFlight;
     constexpr int RPW = kWave / LPR;            // output rows a wave works on at once
     constexpr int kGroups = kGscThreads / LPR;  // output rows a workgroup works on at once
     __shared__ int s_off[kMaxChunksPerItem + 1];
@@ -343,6 +349,8 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     const int g = lane / LPR, c = lane % LPR;
     const int gsh = g * LPR;   // position of this group's bits inside a wave ballot
     const uint64_t gmask = (LPR == 16) ? 0xffffull : 0xffull;
+    const int first_item = APART ? (int)blockIdx.y >> 1 : (int)blockIdx.y;
+    const bool values = APART && (blockIdx.y & 1) != 0;      // this workgroup's rows
     const int M = p.num_chunks[b];
     const int64_t bh = bh_i;
     if (M <= 0) {
@@ -352,10 +360,10 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     int n = p.seq_lens ? p.seq_lens[b] : p.N_max;
     n = n < 0 ? 0 : (n > p.N_max ? p.N_max : n);
     int C, wgs;
-    gsc_item_shape(p, M, n, C, wgs);
-    if ((int)blockIdx.y >= wgs) return;
+    gsc_item_shape(p, M, n, APART ? (int)gridDim.y >> 1 : (int)gridDim.y, C, wgs);
+    if (first_item >= wgs) return;
     const int items = (M + C - 1) / C;
-    const T *Kbh = reinterpret_cast<const T *>(p.K) + b * p.stride_b + h * p.stride_h;
+    const T *Kbh = reinterpret_cast<const T *>(values ? p.V : p.K) + b * p.stride_b + h * p.stride_h;      // (APART: the rows that are added up)
     const T *Vbh = reinterpret_cast<const T *>(p.V) + b * p.stride_b + h * p.stride_h;
     const int32_t *off = p.offsets + (int64_t)b * p.offsets_stride_b;
     const int32_t *cid_bh = p.cid + bh * p.N_max;
@@ -365,7 +373,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     bool base_bad = false;
     int summed = INLINE_PREFIX ? gsc_base_rows(p, bh, base_bad) : 0, summed_to = 0;   // rows of the items [0, summed_to)
 
-    for (int item = blockIdx.y; item < items; item += wgs) {
+    for (int item = first_item; item < items; item += wgs) {
         const int m0 = item * C;
         const int nch = min(C, M - m0);
         __syncthreads();
@@ -394,7 +402,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
             if (wave == 0 && lane <= nch) {
                 const int base = summed + incl - mine;
                 s_base[lane] = base;
-                if (m0 + nch == M && lane == nch) p.comp_lens[bh] = (!base_bad && base <= p.cap) ? base : -1;
+                if (m0 + nch == M && lane == nch && !values) p.comp_lens[bh] = (!base_bad && base <= p.cap) ? base : -1;
             }
         }
         __syncthreads();
@@ -428,7 +436,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
                 // the delimiter that closes the chunk: copied unchanged, size 1
                 const int64_t src = (int64_t)(start + l) * p.stride_n + 8 * c;
                 load8(Kbh + src, ka);
-                load8(Vbh + src, va);
+                if constexpr (!APART) load8(Vbh + src, va);
                 size = 1;
             }
             for (int j0 = 0; j0 < lmax; j0 += kWave) {
@@ -441,32 +449,38 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
                     members |= ((ballot64(match) >> gsh) & gmask) << (LPR * k);
                 }
                 while (ballot64(members != 0ull) != 0ull) {
-                    int jj[kMergeInFlight];
-                    bool ok[kMergeInFlight];
-                    float kk[kMergeInFlight][8], vv[kMergeInFlight][8];
+                    int jj[kInFlight];
+                    bool ok[kInFlight];
+                    float kk[kInFlight][8], vv[kInFlight][8];
 #pragma unroll
-                    for (int u = 0; u < kMergeInFlight; ++u) {
+                    for (int u = 0; u < kInFlight; ++u) {
                         ok[u] = members != 0ull;
                         jj[u] = ok[u] ? first_bit(members) : 0;
                         members &= members - 1ull;
                     }
 #pragma unroll
-                    for (int u = 0; u < kMergeInFlight; ++u) {
+                    for (int u = 0; u < kInFlight; ++u) {
                         if (ok[u]) {
                             const int64_t src = (int64_t)(start + j0 + jj[u]) * p.stride_n + 8 * c;
                             load8(Kbh + src, kk[u]);
-                            load8(Vbh + src, vv[u]);
+                            if constexpr (!APART) load8(Vbh + src, vv[u]);
                         }
                     }
 #pragma unroll
-                    for (int u = 0; u < kMergeInFlight; ++u) {
+                    for (int u = 0; u < kInFlight; ++u) {
                         if (ok[u]) {
                             if (size == 0) {
 #pragma unroll
-                                for (int e = 0; e < 8; ++e) { ka[e] = kk[u][e]; va[e] = vv[u][e]; }
+                                for (int e = 0; e < 8; ++e) {
+                                    ka[e] = kk[u][e];
+                                    if constexpr (!APART) va[e] = vv[u][e];
+                                }
                             } else {
 #pragma unroll
-                                for (int e = 0; e < 8; ++e) { ka[e] += kk[u][e]; va[e] += vv[u][e]; }
+                                for (int e = 0; e < 8; ++e) {
+                                    ka[e] += kk[u][e];
+                                    if constexpr (!APART) va[e] += vv[u][e];
+                                }
                             }
                             size += 1;
                         }
@@ -476,18 +490,21 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
             if (size > 1) {
                 const float fs = (float)size;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) { ka[e] = ka[e] / fs; va[e] = va[e] / fs; }
+                for (int e = 0; e < 8; ++e) {
+                    ka[e] = ka[e] / fs;
+                    if constexpr (!APART) va[e] = va[e] / fs;
+                }
             }
             if (valid) {
                 const int64_t dst = ((int64_t)bh * p.cap + R) * D + 8 * c;
                 if (p.out_is_bf16) {
-                    store_row8<bf16_t>(p.Kc, dst, ka);
-                    store_row8<bf16_t>(p.Vc, dst, va);
+                    store_row8<bf16_t>(values ? p.Vc : p.Kc, dst, ka);
+                    if constexpr (!APART) store_row8<bf16_t>(p.Vc, dst, va);
                 } else {
-                    store_row8<float>(p.Kc, dst, ka);
-                    store_row8<float>(p.Vc, dst, va);
+                    store_row8<float>(values ? p.Vc : p.Kc, dst, ka);
+                    if constexpr (!APART) store_row8<float>(p.Vc, dst, va);
                 }
-                if (c == 0) counts_bh[R] = size;
+                if (c == 0 && !values) counts_bh[R] = size;
             }
         }
     }
@@ -506,6 +523,8 @@ size_t gsc_merge_workspace_bytes(int B, int Hkv, int N_max, int d, int out_elem_
     return bytes;
 }
 
+constexpr int64_t kMergeApartTokens = 49152;      // rows of all heads, see gsc_merge_kernel
+
 template <typename T, int D>
 static hipError_t launch_typed(const GscParams &p, int grid_x, hipStream_t stream) {
     const int max_items = (p.N_max + 1 + p.chunks_per_item - 1) / p.chunks_per_item;
@@ -517,13 +536,15 @@ static hipError_t launch_typed(const GscParams &p, int grid_x, hipStream_t strea
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (p.N_max <= kInlinePrefixTokens) {
-        hipLaunchKernelGGL((gsc_merge_kernel<T, D, true>), grid, dim3(kGscThreads), 0, stream, p);
+        const dim3 twice(grid.x, 2 * grid.y, grid.z);
+        if ((int64_t)heads * p.N_max <= kMergeApartTokens && twice.y <= 65535) hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, true>), twice, dim3(kGscThreads), 0, stream, p);
+        else hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, false>), grid, dim3(kGscThreads), 0, stream, p);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(gsc_scan_kernel, dim3(p.Hkv, p.B), dim3(256), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gsc_merge_kernel<T, D, false>), grid, dim3(kGscThreads), 0, stream, p);
+    hipLaunchKernelGGL((gsc_merge_kernel<T, D, false, false>), grid, dim3(kGscThreads), 0, stream, p);
     return hipGetLastError();
 }
 
