@@ -1,4 +1,4 @@
-"""Builds libsemanticache.so (HIP, gfx950) next to this file.
+"""Builds libsemanticache.so (HIP, gfx950) and _native.so (the argument marshalling of binding.py, C++) next to this file.
 
 Usage: python -m paper_2603_14303_amd.build [--force]
 """
@@ -13,6 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsemanticache.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["sc_api.hip", "sc_segment.hip", "sc_gsc_merge.hip", "sc_gsc_fast.hip", "sc_gsc_global.hip", "sc_decode.hip", "sc_multi.hip", "sc_budget.hip", "sc_probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -40,9 +41,26 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_native() -> None:
+    """_native.so against the torch that is installed; without torch there are no wrappers to speed up."""
+    try:
+        import torch
+        from torch.utils.cpp_extension import include_paths
+    except ImportError:
+        return
+    import sysconfig
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           *["-I" + i for i in include_paths()], "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "sc_binding.cpp"), "-o", tmp,
+           "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-L" + HERE, "-l:libsemanticache.so", "-Wl,-rpath,$ORIGIN"]
+    subprocess.check_call(cmd)
+    os.replace(tmp, NATIVE)
+
+
 def build(force: bool = True) -> str:
-    """Compile every HIP source for gfx950 and link the shared library.  Returns its path."""
-    if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in _deps()):
+    """Compile every HIP source for gfx950, link the shared library and build what binds it to Python.  Returns the library's path."""
+    if not force and all(os.path.exists(o) and all(os.path.getmtime(o) >= os.path.getmtime(d) for d in _deps()) for o in (LIB, NATIVE)):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=4) as ex:
@@ -50,6 +68,7 @@ def build(force: bool = True) -> str:
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, LIB)
+    _build_native()
     return LIB
 
 

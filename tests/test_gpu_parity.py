@@ -374,3 +374,36 @@ def test_a_few_heads_with_many_rows_take_up_to_64_splits(d, bf16, H, rows):
     # bf16: half an ulp of the stored result is the larger part; fp32: sums of 20000 terms
     assert np.abs(O.float().cpu().numpy() - want).max() <= (4e-3 if bf16 else 2e-5) * max(1.0, np.abs(want).max())
     assert np.abs(lse.cpu().numpy() - want_lse).max() <= 1e-3
+
+
+def test_calls_that_the_native_marshalling_leaves_to_the_wrappers():
+    # what _native does not take (-1) ends as it did before: in the general path or in its error; what it takes gives the same
+    rng = np.random.default_rng(9)
+    B, H, G, cap, d = 2, 2, 2, 70, 128
+    Kc, Vc = (g.to_device(rng.standard_normal((B, H, cap, d)).astype(np.float32), True) for _ in range(2))
+    Q = g.to_device(rng.standard_normal((B, H * G, d)).astype(np.float32), True)
+    counts = torch.ones((B, H, cap), dtype=torch.int32, device=g.DEV)
+    lens = torch.full((B, H), cap - 3, dtype=torch.int32, device=g.DEV)
+    ws = sc.decode_attn_workspace(B, H * G, H, cap, d, g.DEV)
+    want, _ = sc.sc_decode_attn(Q, Kc, Vc, counts, lens, workspace=ws)                      # allocates: the general path
+    O = torch.empty_like(Q)
+    stream = sc._stream()
+
+    def native(q=Q, o=O, kc=Kc, n=lens):
+        return sc._native.decode(q, kc, Vc, counts, n, 0.0, o, None, None, None, None, ws.ptr, ws.nbytes, stream)
+    assert native() == 0 and torch.equal(O, want)
+    sub = type("Sub", (torch.Tensor,), {})
+    for other in (Q.cpu(), Q.double(), Q[0], Q.transpose(0, 1), Q.as_subclass(sub), None, 3):
+        assert native(q=other) == -1
+    assert native(kc=Kc.transpose(2, 3)) == -1 and native(o=O.double()) == -1 and native(n=lens.cpu()) == -1
+    with pytest.raises(sc.SemantiCacheError, match="contiguous"):
+        sc.sc_decode_attn(Q, Kc.transpose(2, 3).contiguous().transpose(2, 3), Vc, counts, lens, O=O, workspace=ws)
+    with pytest.raises(sc.SemantiCacheError, match="dtype"):
+        sc.sc_decode_attn(Q, Kc, Vc, counts, lens, O=O.double(), workspace=ws)
+    small = sc.Workspace(256, g.DEV)
+    with pytest.raises(sc.SemantiCacheError, match="sc_decode_attn failed"):                # the library's own refusal
+        sc.sc_decode_attn(Q, Kc, Vc, counts, lens, O=O, workspace=small)
+    got, _ = sc.sc_decode_attn(Q.as_subclass(sub), Kc, Vc, counts, lens, O=O.zero_(), workspace=ws)
+    assert torch.equal(got, want)
+    got, _ = sc.sc_decode_attn(torch.nn.Parameter(Q), Kc, Vc, counts, lens, O=O.zero_(), workspace=ws)
+    assert torch.equal(got, want)
