@@ -371,7 +371,7 @@ sc_status sc_stream_read_probe(const void *src, size_t bytes, void *sink, void *
  * Launch-shape knobs for experiments (process-wide, not thread-safe; results never depend on them
  * beyond floating-point summation order).  Keys:
  *   "decode_max_splits"    split-K workgroups per (sequence, KV head); <= 0 = chosen from B*Hkv
- *   "decode_min_rows"      rows of the merged cache a split should at least get
+ *   "decode_min_rows"      rows of the merged cache a split should at least get; <= 0 (default) = chosen from the rows
  *   "decode_local_handover" 0: split partials always travel through memory, also where all splits of a
  *                          head share one XCC and could use its L2 (the default, 1)
  *   "decode_poll_budget"   polls of the folding workgroup before it gives up (default 2^20); negative:

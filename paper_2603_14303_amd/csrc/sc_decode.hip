@@ -75,8 +75,19 @@ struct DecParams {
     int poll_budget;      // polls of the folding workgroup before it gives up
 };
 
+// Splits of a head's rows, STEP of which its workgroups take at a time (every wavefront a wave-wide step).  Up to ALONE steps one workgroup is
+// done before several have handed their sums over; then a step for each of them, and from some 24 splits on two, since every further split is
+// more to fold.  (8 heads x 128 bf16, 32 calls, us with splits of at least 96 / 192 / 288 rows: 250 rows 231 / 258 / 205 (one split), 300 233 / 259 / 257,
+// 380 234 / 258 / 281, 760 233 / 261 / 290, 1500 244 / 271 / 298, 2100 283 / 300 / 327, 3000 284 / 279 / 306; 8 x 128 fp32, at least 64 / 192 rows:
+// 300 rows 299 / 429, 1000 348 / 507; 2 x 64 fp32, 128 / 192: 400 rows 282 / 367, 800 305 / 371.)
+constexpr int kOneStepSplits = 24;
+template <int STEP, int ALONE>
 __device__ __forceinline__ int splits_for(int rows, int max_splits, int min_rows) {
-    int s = (rows + min_rows - 1) / min_rows;
+    int s;
+    if (min_rows > 0) s = (rows + min_rows - 1) / min_rows;
+    else if (rows <= ALONE * STEP) s = 1;
+    else if (rows <= kOneStepSplits * STEP) s = (rows + STEP - 1) / STEP;
+    else s = (rows + 2 * STEP - 1) / (2 * STEP);
     return s < 1 ? 1 : (s > max_splits ? max_splits : s);
 }
 
@@ -356,7 +367,7 @@ __global__ __launch_bounds__(FastShape<G>::THREADS) void decode_bf16_kernel(DecP
     const unsigned long long epoch = __hip_atomic_load(&hs->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int rows_c = min(max(p.comp_lens[bh], 0), p.cap);
     const int rows_total = rows_c + (TAIL ? min(max(p.tail_lens[b], 0), p.tail_cap) : 0);
-    const int S = splits_for(rows_total, p.max_splits, p.min_rows);
+    const int S = splits_for<kRowsPerBlockStep, 3>(rows_total, p.max_splits, p.min_rows);
     if (split >= S) return;
     if (epoch == kEpochPoison) {   // an earlier call on this workspace failed: fail again, visibly
         if (split == S - 1) file_failure<G, D>(p, hs, b, h, tid, THREADS);
@@ -612,7 +623,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_generic_kernel(DecParams p
     const int rows_c = min(max(p.comp_lens[bh], 0), p.cap);
     // merged rows, then the uncompressed tail (if the call has one): a tail row is a cluster of one
     const int rows_total = rows_c + (p.Kt ? min(max(p.tail_lens[b], 0), p.tail_cap) : 0);
-    const int S = splits_for(rows_total, p.max_splits, p.min_rows);
+    const int S = splits_for<kRowsPerBlockStep, 2>(rows_total, p.max_splits, p.min_rows);
     if (split >= S) return;
     if (epoch == kEpochPoison) {   // an earlier call on this workspace failed: fail again, visibly
         if (split == S - 1) file_failure<G, D>(p, hs, b, h, tid, kDecThreads);
@@ -898,15 +909,16 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t stream) {
     // (split * B * Hkv + head) keeps every head on one XCC
     p.local = ((a.B * a.Hkv) % 8 == 0 && tuning().decode_local_handover) ? 1 : 0;
     p.poll_budget = tuning().decode_poll_budget;
-    p.min_rows = max(1, tuning().decode_min_rows);
+    p.min_rows = max(0, tuning().decode_min_rows);
     // Splits per (sequence, KV head): enough workgroups to cover the 256 CUs about once; more splits
     // only add partials to fold and tickets to take (both are serial tails of the kernel).  (A few heads with many rows, us for eight calls
     // with up to 32 / 64 splits: 4 heads x 33000 rows 169 / 151, x 16000 122 / 110, x 6200 88 / 79; 1 head x 33000 151 / 122, x 8000 88 / 87,
-    // x 3000 the same, since a split gets decode_min_rows at least.)
+    // x 3000 the same.)
     int splits = clamp_splits();
     if (tuning().decode_max_splits <= 0) splits = max(2, min(kDecMaxSplits, 256 / max(1, a.B * a.Hkv)));
     // never more splits than the capacity can feed
-    const int by_cap = (int)(((int64_t)a.cap + p.tail_cap + p.min_rows - 1) / p.min_rows);
+    const int least = p.min_rows > 0 ? p.min_rows : 64;      // (the smallest step)
+    const int by_cap = (int)(((int64_t)a.cap + p.tail_cap + least - 1) / least);
     p.max_splits = max(1, min(splits, by_cap));
     const int G = a.Hq / a.Hkv;
     if (a.kv_dtype == DType::BF16)

@@ -13,7 +13,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // tuning knobs, set through sc_tune_set and read by the launchers; a merge call takes a copy, so that all its launches go by the same ones
 struct Tuning {
     int decode_max_splits = 0;      // split-K workgroups per (sequence, KV head); <= 0 picks it from B*Hkv
-    int decode_min_rows = 192;      // rows of the merged cache a split should at least get
+    int decode_min_rows = 0;        // rows of the merged cache a split should at least get; <= 0 picks them from the rows
     int decode_local_handover = 1;  // 0: split partials always go through memory, also when a head's splits share an XCC
     int decode_poll_budget = 1 << 20;   // polls (about 0.3 us each) of the folding workgroup before it gives up; negative: give up at once (host-driven test of the failure path)
     int decode_mfma_min_group = 9;  // query heads per KV head from which single-row decode runs on the multi-row kernel (9 = never)

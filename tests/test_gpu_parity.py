@@ -332,11 +332,13 @@ def test_generic_merge_short_chunks(H, n, gap):
 
 @pytest.mark.parametrize("d,bf16,G,tail", [(128, True, 4, 0), (128, True, 7, 40), (64, True, 2, 0), (64, False, 1, 25), (128, False, 3, 0)])
 def test_heads_of_one_split(d, bf16, G, tail):
-    # heads that one workgroup takes alone store their outputs directly, beside heads of two splits in the same launch: no rows at
-    # all, one row, remainders of a step, the last count of one split and the first of two (192 rows each)
+    # heads that one workgroup takes alone store their outputs directly, beside heads of several splits in the same launch: no rows at
+    # all, one row, remainders of a step, the last count of one split and the first of two, of a step for every split and of two
     rng = np.random.default_rng(d + G)
-    rows = np.array([[0, 1], [17, 96], [191 - tail, 192 - tail], [193 - tail, 384]], np.int32)
-    B, H, cap = 4, 2, 400
+    step, alone = (96, 3) if bf16 and d == 128 else (8192 // d, 2)
+    rows = np.array([[0, 1], [17, step], [alone * step, alone * step + 1], [24 * step, 24 * step + 1]], np.int32)
+    rows = np.maximum(rows - np.where(rows > step, tail, 0), 0).astype(np.int32)
+    B, H, cap = 4, 2, 24 * step + 3
     Kc, Vc = (g.to_device(rng.standard_normal((B, H, cap, d)).astype(np.float32), bf16) for _ in range(2))
     Q = g.to_device(rng.standard_normal((B, H * G, d)).astype(np.float32), bf16)
     counts = torch.from_numpy(rng.integers(1, 30, size=(B, H, cap)).astype(np.int32)).to(g.DEV)
