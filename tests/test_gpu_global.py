@@ -259,3 +259,43 @@ def test_sequences_long_enough_for_stages(tau, polls, drift):
         assert g.rowwise_err(Kc[b, h, :rows].cpu().numpy(), r["Kc"][:rows]) <= 1e-3
         assert g.rowwise_err(Vc[b, h, :rows].cpu().numpy(), r["Vc"][:rows]) <= 1e-3
         print("b %d h %d: rows %d of %d" % (b, h, rows, n))
+
+
+def test_stages_in_a_captured_graph():
+    # the launches of a staged call, replayed on new keys with eager work in between, give what an eager call gives
+    gen = torch.Generator(g.DEV).manual_seed(4)
+    H, N, d = 8, 12365, 128
+    K = torch.empty((1, H, N, d), dtype=torch.bfloat16, device=g.DEV)
+    V = torch.empty_like(K)
+
+    def fill():
+        centers = torch.randn((H, 700, d), generator=gen, device=g.DEV)
+        pick = torch.randint(0, 700, (H, N), generator=gen, device=g.DEV)
+        K[0] = (torch.gather(centers, 1, pick[:, :, None].expand(-1, -1, d)) + 0.1 * torch.randn((H, N, d), generator=gen, device=g.DEV)).to(torch.bfloat16)
+        V.normal_(generator=gen)
+    fill()
+    lib = sc.load_library()
+    ws = sc.Workspace(lib.sc_gsc_merge_global_workspace_bytes(1, H, N, d), g.DEV)
+    Kc, Vc = torch.zeros((1, H, N, d), device=g.DEV), torch.zeros((1, H, N, d), device=g.DEV)
+    counts, lens = torch.zeros((1, H, N), dtype=torch.int32, device=g.DEV), torch.zeros((1, H), dtype=torch.int32, device=g.DEV)
+
+    def call():
+        st = lib.sc_gsc_merge_global(K.data_ptr(), V.data_ptr(), sc.SC_BF16, K.stride(0), K.stride(1), K.stride(2), None, 1, H, N, d, 0.9, Kc.data_ptr(),
+                                     Vc.data_ptr(), sc.SC_F32, N, counts.data_ptr(), lens.data_ptr(), None, ws.ptr, ws.nbytes, sc._stream())
+        assert st == sc.SC_OK
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(3):
+        fill()
+        want = sc.sc_gsc_merge_global(K, V, 0.9, out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(lens, want[3]) and (lens > 500).all()
+        for h in range(H):
+            r = int(lens[0, h])
+            assert torch.equal(counts[0, h, :r], want[2][0, h, :r])
+            assert torch.equal(Kc[0, h, :r], want[0][0, h, :r]) and torch.equal(Vc[0, h, :r], want[1][0, h, :r])
