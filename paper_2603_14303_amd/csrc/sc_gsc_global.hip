@@ -847,7 +847,9 @@ __global__ __launch_bounds__(256) void glob_place_kernel(GlobParams p) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// sum: Eq. 3.  16 lanes per cluster, members in row order.
+// sum: Eq. 3.  16 lanes per cluster, members in row order; keys and values in workgroups of their own, sixteen rows in flight: a cluster of a hundred
+// rows is the kernel's tail, its trips to memory are what that costs.  (Both in one, eight of each: 98 registers; 8 heads x 32768 44 us, 38 so;
+// the call at 8 x 5000 107 and 99, at 2 x 5000 79 and 72.)
 template <typename TO>
 __global__ __launch_bounds__(256) void glob_sum_kernel(GlobParams p) {
     const int bh = blockIdx.y, b = bh / p.Hkv, h = bh - b * p.Hkv;
@@ -855,36 +857,30 @@ __global__ __launch_bounds__(256) void glob_sum_kernel(GlobParams p) {
     const int P = min(p.nclusters[bh], p.cap);
     const int cl = blockIdx.x * 16 + threadIdx.x / 16, c = threadIdx.x % 16;
     if (cl >= P) return;
-    const bf16_t *Kbh = p.K + b * p.stride_b + h * p.stride_h + 8 * c;
-    const bf16_t *Vbh = p.V + b * p.stride_b + h * p.stride_h + 8 * c;
+    const bool values = blockIdx.z != 0;
+    const bf16_t *X = (values ? p.V : p.K) + b * p.stride_b + h * p.stride_h + 8 * c;
     const int32_t *order = p.order + (int64_t)bh * npad + p.mbase[(int64_t)bh * (npad + 1) + cl];
     const int size = p.csize[(int64_t)bh * npad + cl];
-    float ka[8], va[8];
+    float sum[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ka[e] = va[e] = 0.f;
+    for (int e = 0; e < 8; ++e) sum[e] = 0.f;
     const int first_lane = (threadIdx.x & (kWave - 1)) & ~15;
-    constexpr int kRows = 8;      // in flight: a cluster of a hundred rows is the kernel's tail, its trips to memory are what that costs
     for (int t0 = 0; t0 < size; t0 += 16) {
         const int members = min(16, size - t0);
         const int mine = (c < members) ? order[t0 + c] : 0;      // sixteen members in one load
-        for (int u0 = 0; u0 < members; u0 += kRows) {
-            uint4 kk[kRows], vv[kRows];
+        uint4 x[16];
 #pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                const int64_t row = __shfl(mine, first_lane + u0 + u, kWave);
-                if (u0 + u < members) {
-                    kk[u] = *reinterpret_cast<const uint4 *>(Kbh + row * p.stride_n);
-                    vv[u] = *reinterpret_cast<const uint4 *>(Vbh + row * p.stride_n);
-                }
-            }
+        for (int u = 0; u < 16; ++u) {
+            const int64_t row = __shfl(mine, first_lane + u, kWave);
+            if (u < members) x[u] = *reinterpret_cast<const uint4 *>(X + row * p.stride_n);
+        }
 #pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                if (u0 + u < members) {
+        for (int u = 0; u < 16; ++u) {
+            if (u < members) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        ka[2 * e] += bf16_lo(dword_of(kk[u], e)); ka[2 * e + 1] += bf16_hi(dword_of(kk[u], e));
-                        va[2 * e] += bf16_lo(dword_of(vv[u], e)); va[2 * e + 1] += bf16_hi(dword_of(vv[u], e));
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    sum[2 * e] += bf16_lo(dword_of(x[u], e));
+                    sum[2 * e + 1] += bf16_hi(dword_of(x[u], e));
                 }
             }
         }
@@ -892,11 +888,8 @@ __global__ __launch_bounds__(256) void glob_sum_kernel(GlobParams p) {
     // 1/size: a row of size 1 is passed on unchanged
     const float inv = (size > 1) ? 1.0f / (float)size : 1.0f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { ka[e] *= inv; va[e] *= inv; }
-    TO *Kc = reinterpret_cast<TO *>(p.Kc) + ((int64_t)bh * p.cap + cl) * kGlD + 8 * c;
-    TO *Vc = reinterpret_cast<TO *>(p.Vc) + ((int64_t)bh * p.cap + cl) * kGlD + 8 * c;
-    store8(Kc, ka);
-    store8(Vc, va);
+    for (int e = 0; e < 8; ++e) sum[e] *= inv;
+    store8(reinterpret_cast<TO *>(values ? p.Vc : p.Kc) + ((int64_t)bh * p.cap + cl) * kGlD + 8 * c, sum);
 }
 
 // one chunk per sequence in the offsets format of sc_segment: off = {0, n + 1}, one chunk
@@ -1045,7 +1038,7 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int max_clusters = a.N_max < a.cap ? a.N_max : a.cap;
-    const dim3 grid_sum((unsigned)((max_clusters + 15) / 16), (unsigned)BH);
+    const dim3 grid_sum((unsigned)((max_clusters + 15) / 16), (unsigned)BH, 2);
     if (p.out_is_bf16) hipLaunchKernelGGL((glob_sum_kernel<bf16_t>), grid_sum, dim3(256), 0, stream, p);
     else hipLaunchKernelGGL((glob_sum_kernel<float>), grid_sum, dim3(256), 0, stream, p);
     return hipGetLastError();
