@@ -672,18 +672,13 @@ __device__ __forceinline__ void first_fit_by_seed(Settle settle, Words &y, Words
         todo.b &= ~(new_b | got_b);
     }
 }
-// The lane's two rows of a window of whole chunks: where their chunks start; a delimiter is a chunk of its own.
+// Where the chunks of the lane's two rows of a window of whole chunks start.
 struct RowChunks {
     int lo_a, lo_b;
-    bool delim_a, delim_b, open_a, open_b;
-    __device__ __forceinline__ RowChunks(const Pair64 &D, int R, int lane) {
+    __device__ __forceinline__ RowChunks(const Pair64 &D, int lane) {
         const uint64_t below = bits_below(lane), da = D.a & below, db = D.b & below;
         lo_a = da != 0ull ? 1 + last_bit(da) : 0;
         lo_b = db != 0ull ? 65 + last_bit(db) : (D.a != 0ull ? 1 + last_bit(D.a) : 0);
-        delim_a = (D.a >> lane) & 1ull;
-        delim_b = (D.b >> lane) & 1ull;
-        open_a = lane < R;
-        open_b = 64 + lane < R;
     }
 };
 // Alg. 1 in a window of whole chunks (delimiters D, R rows) from its bit matrices
@@ -691,9 +686,11 @@ template <typename Settle>
 __device__ __forceinline__ void decide_window(const RowChunks &r, const uint32_t (*yes)[4], const uint32_t (*unsure)[4], const int &any_unsure, const Pair64 &D, int R,
                                               int lane, Settle settle, Decision &d) {
     const uint64_t below = bits_below(lane);
-    const uint64_t before_a = (r.delim_a || !r.open_a) ? 0ull : below & ~bits_below(r.lo_a);
-    const uint64_t before_b0 = (r.delim_b || !r.open_b) ? 0ull : ~bits_below(min(r.lo_b, 64));
-    const uint64_t before_b1 = (r.delim_b || !r.open_b) ? 0ull : below & ~bits_below(max(r.lo_b - 64, 0));
+    const bool delim_a = (D.a >> lane) & 1ull, delim_b = (D.b >> lane) & 1ull;      // a delimiter is a chunk of its own
+    const bool open_a = lane < R, open_b = 64 + lane < R;
+    const uint64_t before_a = (delim_a || !open_a) ? 0ull : below & ~bits_below(r.lo_a);
+    const uint64_t before_b0 = (delim_b || !open_b) ? 0ull : ~bits_below(min(r.lo_b, 64));
+    const uint64_t before_b1 = (delim_b || !open_b) ? 0ull : below & ~bits_below(max(r.lo_b - 64, 0));
     Words y, u;
     y.a = row_word(yes, lane, 0) & before_a;
     y.b0 = row_word(yes, 64 + lane, 0) & before_b0;
@@ -704,13 +701,13 @@ __device__ __forceinline__ void decide_window(const RowChunks &r, const uint32_t
         u.b0 = row_word(unsure, 64 + lane, 0) & before_b0;
         u.b1 = row_word(unsure, 64 + lane, 1) & before_b1;
     }
-    if (first_fit_fixed_point(settle, y, u, r.open_a, r.open_b, lane, d)) return;
+    if (first_fit_fixed_point(settle, y, u, open_a, open_b, lane, d)) return;
     // chunk ranges: up to the first delimiter from the row on
     const uint64_t ea = D.a & ~below, eb = D.b & ~below;
     const int hi_a = ea != 0ull ? first_bit(ea) : (D.b != 0ull ? 64 + first_bit(D.b) : R);
     const int hi_b = eb != 0ull ? 64 + first_bit(eb) : R;
-    const int la = r.delim_a ? lane : r.lo_a, ha = r.delim_a ? lane + 1 : hi_a;
-    const int lb = r.delim_b ? 64 + lane : r.lo_b, hb = r.delim_b ? 65 + lane : hi_b;
+    const int la = delim_a ? lane : r.lo_a, ha = delim_a ? lane + 1 : hi_a;
+    const int lb = delim_b ? 64 + lane : r.lo_b, hb = delim_b ? 65 + lane : hi_b;
     const Pair64 ra = {bits_below(min(ha, 64)) & ~bits_below(min(la, 64)), bits_below(max(ha - 64, 0)) & ~bits_below(max(la - 64, 0))};
     const Pair64 rb = {bits_below(min(hb, 64)) & ~bits_below(min(lb, 64)), bits_below(max(hb - 64, 0)) & ~bits_below(max(lb - 64, 0))};
     const Pair64 all = {bits_below(min(R, 64)), bits_below(max(R - 64, 0))};
@@ -1223,7 +1220,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             SC_FRESH_LANE;
             ProbeTiles tiles;
             probe_products(s, D, R, wave, g, c, tiles);
-            const RowChunks rows(D, R, lane);
+            const RowChunks rows(D, lane);
             __syncthreads();      // the keys have been read
             ProbeWords &words = *reinterpret_cast<ProbeWords *>(s.rows);
             for (int t0 = 0; t0 < nodes; t0 += kWinWaves) {
@@ -1267,8 +1264,9 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         const int nks = (R + 31) >> 5;
         if (wave == decider) {
             SC_FRESH_LANE;
-            const RowChunks rows(D, R, lane);
-            const bool open_a = rows.open_a, open_b = rows.open_b;
+            const RowChunks rows(D, lane);
+            const bool delim_a = (D.a >> lane) & 1ull, delim_b = (D.b >> lane) & 1ull;
+            const bool open_a = lane < R, open_b = 64 + lane < R;
             Decision d;
             decide_window(rows, s.yes, s.unsure, s.any_unsure, D, R, lane,
                           [&](const Pair64 &ask, int oa, int ob) { return settle_pairs(s, ask, oa, ob, tau, lane, wave, nullptr, 0, nullptr); }, d);
@@ -1279,8 +1277,8 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                 SC_FRESH_PARAMS;
                 if (p.cluster_id) {
                     int32_t *cid = p.cluster_id + bh * p.N_max + w0;
-                    if (open_a) cid[lane] = rows.delim_a ? -1 : out_a - rows_below(d.seeds, rows.lo_a);
-                    if (open_b) cid[64 + lane] = rows.delim_b ? -1 : out_b - rows_below(d.seeds, rows.lo_b);
+                    if (open_a) cid[lane] = delim_a ? -1 : out_a - rows_below(d.seeds, rows.lo_a);
+                    if (open_b) cid[64 + lane] = delim_b ? -1 : out_b - rows_below(d.seeds, rows.lo_b);
                 }
                 file_membership(s, out_a, out_b, (nseed + 15) >> 4, lane);
                 if (lane == 0) s.nseed = nseed;
