@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 try:
@@ -22,7 +23,7 @@ SC_OK = 0
 SC_F32, SC_BF16 = 0, 1
 
 _lib = None
-_native = None      # csrc/sc_binding.cpp: the wrappers' marshalling in C++, loaded with the library
+_native = None      # csrc/sc_binding.cpp: the wrappers' marshalling in C++, loaded with the library if it can be
 
 
 class SemantiCacheError(RuntimeError):
@@ -100,13 +101,24 @@ def load_library() -> ctypes.CDLL:
     lib.sc_gsc_merge_budget.argtypes = [vp, vp, i32, i64, i64, i64, vp, vp, i64, vp, i32, i32, i32, i32,
                                         i64, f32, f32, i32, vp, vp, i32, i32, vp, vp, vp, vp, vp, vp, sz, vp]
     if torch is not None:
-        try:
-            from . import _native as native
-        except ImportError as e:
-            raise SemantiCacheError("_native.so is not built; run `python -m paper_2603_14303_amd.build` (%s)" % e) from e
-        _native = native
+        _native = _load_native()
     _lib = lib
     return lib
+
+
+def _load_native():
+    """The module of csrc/sc_binding.cpp, or None with a warning: the wrappers make every call without it, at more host time."""
+    try:
+        from . import _native as native
+    except ImportError as e:
+        why = str(e)
+    else:
+        if native.torch_version == torch.__version__:
+            return native
+        why = "it was built for torch %s" % native.torch_version
+    warnings.warn("calls are marshalled in Python, _native is missing or built for another torch or Python (%s); "
+                  "`python -m paper_2603_14303_amd.build` builds it" % why, RuntimeWarning, stacklevel=3)
+    return None
 
 
 EXPORTED = [
@@ -131,7 +143,7 @@ def _check(status: int, what: str) -> None:
 
 # The wrappers below are called once per layer and generated token, and a decode call is 5 to 10 us of device time.  Calls whose outputs and
 # workspace are there already go through _native, which looks at the tensors in C++ and makes the call; whatever it does not take (status -1:
-# nothing has been done) goes on here, and so does everything else: outputs to allocate, errors to name.
+# nothing has been done) goes on here, and so does everything else: outputs to allocate, errors to name, a process without _native.
 # Host time of a decode call with a tail 9.7 -> 6.3 us, so that the GPU is not kept waiting: segment, merge and eight decode steps on 1024 fp32
 # tokens 92 -> 72 us, 32 decode calls of 170 rows 248 -> 195, 32 calls of eight query rows over 400 cache rows 381 -> 324.
 _DTYPE_CODES = {torch.float32: SC_F32, torch.bfloat16: SC_BF16} if torch is not None else {}
@@ -176,7 +188,7 @@ def tune_get(key: str) -> int:
 def sc_segment(mask, seq_lens=None, offsets=None, num_chunks=None):
     """mask u8 [B, N_max] (device) -> (offsets i32 [B, N_max + 2], num_chunks i32 [B])."""
     lib = load_library()
-    if mask.is_cuda and offsets is not None and num_chunks is not None:
+    if _native is not None and mask.is_cuda and offsets is not None and num_chunks is not None:
         st = _native.segment(mask, seq_lens, offsets, num_chunks, _stream())
         if st >= 0:
             _check(st, "sc_segment")
@@ -229,7 +241,7 @@ def sc_gsc_merge(K, V, offsets, num_chunks, tau: float, seq_lens=None, cap: Opti
     that Kc, Vc, counts already hold, and comp_lens (a different tensor) receives the new totals.
     """
     lib = load_library()
-    if K.is_cuda and cap is not None and Kc is not None and workspace is not None and not (want_cluster_id and cluster_id is None):
+    if _native is not None and K.is_cuda and cap is not None and Kc is not None and workspace is not None and not (want_cluster_id and cluster_id is None):
         st = _native.merge(K, V, offsets, num_chunks, tau, seq_lens, cap, Kc, Vc, counts, comp_lens, cluster_id, base_lens, workspace.ptr,
                            workspace.nbytes, _stream())
         if st >= 0:
@@ -295,7 +307,7 @@ def sc_decode_attn(Q, Kc, Vc, counts, comp_lens, scale: float = 0.0, O=None, lse
     rows of the uncompressed tail attend behind the merged rows, with size 1.
     """
     lib = load_library()
-    if Q.is_cuda and O is not None and workspace is not None and not (want_lse and lse is None):
+    if _native is not None and Q.is_cuda and O is not None and workspace is not None and not (want_lse and lse is None):
         st = _native.decode(Q, Kc, Vc, counts, comp_lens, scale, O, lse, Kt, Vt, tail_lens, workspace.ptr, workspace.nbytes, _stream())
         if st >= 0:
             _check(st, "sc_decode_attn" if Kt is None else "sc_decode_attn_tail")
@@ -361,7 +373,7 @@ def sc_multi_attn(Q, Kc, Vc, counts, comp_lens, scale: float = 0.0, O=None, lse=
     merged rows; with causal the last nq tail rows are the query rows' own tokens.
     """
     lib = load_library()
-    if Q.is_cuda and O is not None and workspace is not None and not (want_lse and lse is None):
+    if _native is not None and Q.is_cuda and O is not None and workspace is not None and not (want_lse and lse is None):
         st = _native.multi(Q, Kc, Vc, counts, comp_lens, scale, O, lse, Kt, Vt, tail_lens, causal, workspace.ptr, workspace.nbytes, _stream())
         if st >= 0:
             _check(st, "sc_multi_attn" if Kt is None else "sc_multi_attn_tail")

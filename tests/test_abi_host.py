@@ -28,6 +28,33 @@ def test_library_loads_without_torch(lib):
     subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
 
 
+@pytest.mark.parametrize("module", ["None", "types.SimpleNamespace(torch_version='0.0.0')"])
+def test_library_loads_without_its_native_marshalling(lib, module):
+    """_native missing, or built for another torch: the library loads with a warning and the wrappers do without it."""
+    code = ("import sys, types, warnings; import paper_2603_14303_amd as package\n"
+            "sys.modules['paper_2603_14303_amd._native'] = package._native = %s\n"
+            "if package._native is None: del package._native\n"
+            "from paper_2603_14303_amd import binding as sc\n"
+            "with warnings.catch_warnings(record=True) as seen:\n"
+            "    warnings.simplefilter('always'); lib = sc.load_library()\n"
+            "assert sc._native is None and [w.category for w in seen if '_native' in str(w.message)] == [RuntimeWarning]\n"
+            "assert lib.sc_decode_attn_workspace_bytes(1, 8, 2, 512, 128) > 0\n" % module)
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
+
+
+def test_build_knows_what_the_native_marshalling_was_built_for(lib, monkeypatch):
+    from paper_2603_14303_amd import build
+    import torch
+    assert build._native_is_current() and sc._native.torch_version == torch.__version__
+    monkeypatch.setattr(build, "_torch_version", lambda: "0.0.0")
+    assert not build._native_is_current()
+    # without torch there is nothing to build it for: the library alone decides whether anything is compiled
+    monkeypatch.setattr(build, "_torch_version", lambda: None)
+    monkeypatch.setattr(build, "NATIVE", os.path.join(ROOT, "no_such_file"))
+    monkeypatch.setattr(build, "_compile", lambda src: pytest.fail("compiled again"))
+    assert build.build(force=False) == build.LIB
+
+
 def _declared_symbols():
     text = open(os.path.join(ROOT, "include", "semanticache.h")).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
