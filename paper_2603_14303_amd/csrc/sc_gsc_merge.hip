@@ -325,16 +325,26 @@ __device__ __forceinline__ void store_row8(void *base, int64_t elem_off, const f
 // x 32768 x 64 f32 with a delimiter per token, a call of items of eight took 323 us, 265 so.)
 constexpr int kMergeCidTile = 2048;
 constexpr int kMergeInFlight = 4;
-// APART: one workgroup adds up the keys, its neighbour the values, eight rows in flight each: in a call that leaves most of the chip idle the
-// largest cluster's trips to memory are the kernel's time, and there are workgroups to spare.  Whole call with its sc_segment, together / apart, us:
-// 2 heads x 1024 x 64 f32 35.0 / 31.6, 4 x 4000 51 / 43, 4 x 8000 53 / 45, 4 x 4000 x 64 bf16 65 / 55, 1 x 8000 64 / 53; even from 64k rows on
-// (4 x 16000 x 64 f32 58.5 / 59.5, x 128 70.6 / 70.5).  (Sixteen in flight: 310 registers, a wavefront per SIMD, 4 x 8000 53, 4 x 16000 82.)
-constexpr int kMergeInFlightApart = 8;
+// TWICE: some items are split between two workgroups, one adds up the keys and the other the values, eight rows in flight each.  What that
+// shortens is the largest cluster's trips to memory, so an item is split where a chunk of it is long: of more than kSplitLong tokens, or of more than
+// kSplitLongRoom in a call whose items would fill half of the places on the chip (two workgroups on each of 256 CUs) otherwise.  Where chunks are short the
+// second workgroup would do the first one's barriers and look-ups once more for nothing, and where the chip is full it takes a place.  Whole call without
+// sc_segment, us, never split / every item split / by this rule (delimiters at a fixed distance, or at random every 24 tokens: "geom"):
+//   8 heads x 6000 x 64 f32   distance 1 25.5 / 36.0 / 25.2, 4 29.3 / 40.6 / 29.7, 24 18.8 / 23.8 / 19.7, 64 26.7 / 23.1 / 24.5, geom 48.9 / 46.1 / 48.3
+//   8 x 6000 x 128 f32        1 37.9 / 52.6 / 35.6, 4 47.8 / 63.6 / 47.8, 24 27.2 / 31.6 / 27.7, 64 43.0 / 34.8 / 35.8, geom 61.4 / 54.1 / 56.5
+//   4 x 12000 x 64 bf16       1 20.6 / 32.4 / 20.6, 4 29.1 / 42.0 / 30.0, 24 22.2 / 28.3 / 22.5, 64 34.1 / 30.4 / 31.6, geom 61.5 / 52.2 / 58.9
+//   1 x 8000 x 64 f32         1 12.1 / 15.3 / 12.4, 4 13.8 / 17.6 / 13.8, 24 17.2 / 15.9 / 16.9, 64 26.7 / 22.6 / 23.3, geom 46.3 / 38.2 / 38.6
+// (What is left where nothing is split, up to 4 % with d = 64, is the larger kernel's.)
+// The second workgroups come last, kSplitWorkgroups in all (as many as items are long: 4 x 12000 geom 59 with 512, 67 with 256; one for every item, 8 x
+// 2000 x 128 f32 with a delimiter every second token 17.2 instead of 16.8 us), and leave at once where chunks average less than kSplitMean tokens.
+// Even from 64k rows on (4 x 16000 x 64 f32 58.5 / 59.5).  (Sixteen in flight: 310 registers, a wavefront per SIMD, 4 x 8000 53, 4 x 16000 82.)
+constexpr int64_t kSplitTokens = 49152;      // rows of all heads
+constexpr int kSplitWorkgroups = 512, kSplitLong = 32, kSplitLongRoom = 20, kSplitMean = 12;
+constexpr int kMergeInFlightSplit = 8;
 
-template <typename T, int D, bool INLINE_PREFIX, bool APART>
+template <typename T, int D, bool INLINE_PREFIX, bool TWICE>
 __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     constexpr int LPR = D / 8;
-    constexpr int kInFlight = APART ? kMergeInFlightApart : kMergeInFlight;
     constexpr int RPW = kWave / LPR;            // output rows a wave works on at once
     constexpr int kGroups = kGscThreads / LPR;  // output rows a workgroup works on at once
     __shared__ int s_off[kMaxChunksPerItem + 1];
@@ -349,8 +359,9 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     const int g = lane / LPR, c = lane % LPR;
     const int gsh = g * LPR;   // position of this group's bits inside a wave ballot
     const uint64_t gmask = (LPR == 16) ? 0xffffull : 0xffull;
-    const int first_item = APART ? (int)blockIdx.y >> 1 : (int)blockIdx.y;
-    const bool values = APART && (blockIdx.y & 1) != 0;      // this workgroup's rows
+    const int seconds = TWICE ? p.split_wgs : 0, launched = (int)gridDim.y - seconds;
+    const bool values = TWICE && (int)blockIdx.y >= launched;      // a second workgroup
+    const int first_item = values ? (int)blockIdx.y - launched : (int)blockIdx.y;
     const int M = p.num_chunks[b];
     const int64_t bh = bh_i;
     if (M <= 0) {
@@ -360,10 +371,14 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     int n = p.seq_lens ? p.seq_lens[b] : p.N_max;
     n = n < 0 ? 0 : (n > p.N_max ? p.N_max : n);
     int C, wgs;
-    gsc_item_shape(p, M, n, APART ? (int)gridDim.y >> 1 : (int)gridDim.y, C, wgs);
-    if (first_item >= wgs) return;
+    gsc_item_shape(p, M, n, launched, C, wgs);
+    if (first_item >= (values ? seconds : wgs)) return;
     const int items = (M + C - 1) / C;
-    const T *Kbh = reinterpret_cast<const T *>(values ? p.V : p.K) + b * p.stride_b + h * p.stride_h;      // (APART: the rows that are added up)
+    const bool may_split = TWICE && n >= kSplitMean * (int64_t)M;
+    if (values && !may_split) return;
+    const int step = values ? seconds : wgs;
+    const int split_from = (2 * (int64_t)min(items, wgs) * (p.B * p.Hkv) <= kSplitWorkgroups) ? kSplitLongRoom : kSplitLong;
+    const T *Kbh = reinterpret_cast<const T *>(p.K) + b * p.stride_b + h * p.stride_h;
     const T *Vbh = reinterpret_cast<const T *>(p.V) + b * p.stride_b + h * p.stride_h;
     const int32_t *off = p.offsets + (int64_t)b * p.offsets_stride_b;
     const int32_t *cid_bh = p.cid + bh * p.N_max;
@@ -373,9 +388,14 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     bool base_bad = false;
     int summed = INLINE_PREFIX ? gsc_base_rows(p, bh, base_bad) : 0, summed_to = 0;   // rows of the items [0, summed_to)
 
-    for (int item = first_item; item < items; item += wgs) {
+    for (int item = first_item; item < items; item += step) {
         const int m0 = item * C;
         const int nch = min(C, M - m0);
+        bool split = false;      // the same for both workgroups
+        if constexpr (TWICE) {
+            split = may_split && ballot64(lane < nch && off[m0 + lane + 1] - off[m0 + lane] > split_from) != 0ull;
+            if (values && !split) continue;
+        }
         __syncthreads();
         if (tid <= nch) {
             s_off[tid] = off[m0 + tid];
@@ -413,100 +433,107 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
         const int R0 = __builtin_amdgcn_readfirstlane(s_base[0]);
         const int R1 = min(__builtin_amdgcn_readfirstlane(s_base[nch]), p.cap);
         // all loops below have wave-uniform trip counts; per-group differences are predicates
-        for (int Rw = R0 + wave * RPW; Rw < R1; Rw += kGroups) {
-            const int R = Rw + g;
-            const bool valid = R < R1;
-            // chunk of this output row: last idx with s_base[idx] <= R
-            int idx = 0;
-            for (int k = 1; k < nch; ++k) idx = (s_base[k] <= R) ? k : idx;
-            const int start = s_off[idx];
-            const int l = s_off[idx + 1] - 1 - start;
-            const int cl = R - s_base[idx];
-            const bool closed = (start + l) < n;   // chunk is followed by a delimiter
-            const int pc = s_base[idx + 1] - s_base[idx] - (closed ? 1 : 0);
-            const bool is_delim = valid && cl >= pc;
-            const int lscan = (valid && !is_delim) ? l : 0;
-            int lmax = 0;
+        auto merge_rows = [&](auto apart) {      // apart: the keys or the values only
+            constexpr bool APART = decltype(apart)::value;
+            constexpr int kInFlight = APART ? kMergeInFlightSplit : kMergeInFlight;
+            const T *Xbh = APART && values ? Vbh : Kbh;
+            for (int Rw = R0 + wave * RPW; Rw < R1; Rw += kGroups) {
+                const int R = Rw + g;
+                const bool valid = R < R1;
+                // chunk of this output row: last idx with s_base[idx] <= R
+                int idx = 0;
+                for (int k = 1; k < nch; ++k) idx = (s_base[k] <= R) ? k : idx;
+                const int start = s_off[idx];
+                const int l = s_off[idx + 1] - 1 - start;
+                const int cl = R - s_base[idx];
+                const bool closed = (start + l) < n;   // chunk is followed by a delimiter
+                const int pc = s_base[idx + 1] - s_base[idx] - (closed ? 1 : 0);
+                const bool is_delim = valid && cl >= pc;
+                const int lscan = (valid && !is_delim) ? l : 0;
+                int lmax = 0;
 #pragma unroll
-            for (int gg = 0; gg < RPW; ++gg) lmax = max(lmax, __builtin_amdgcn_readlane(lscan, gg * LPR));
+                for (int gg = 0; gg < RPW; ++gg) lmax = max(lmax, __builtin_amdgcn_readlane(lscan, gg * LPR));
 
-            float ka[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, va[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            int size = 0;
-            if (is_delim) {
-                // the delimiter that closes the chunk: copied unchanged, size 1
-                const int64_t src = (int64_t)(start + l) * p.stride_n + 8 * c;
-                load8(Kbh + src, ka);
-                if constexpr (!APART) load8(Vbh + src, va);
-                size = 1;
-            }
-            for (int j0 = 0; j0 < lmax; j0 += kWave) {
-                uint64_t members = 0ull;       // of rows j0 .. j0 + 63 of the chunk, the same for every lane of the group
-#pragma unroll
-                for (int k = 0; k < kWave / LPR; ++k) {
-                    const int j = j0 + LPR * k + c, t = start + j - t0;
-                    bool match = false;
-                    if (j < lscan) match = (t < kMergeCidTile ? s_cid[t] : cid_bh[start + j]) == cl;
-                    members |= ((ballot64(match) >> gsh) & gmask) << (LPR * k);
+                float ka[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, va[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                int size = 0;
+                if (is_delim) {
+                    // the delimiter that closes the chunk: copied unchanged, size 1
+                    const int64_t src = (int64_t)(start + l) * p.stride_n + 8 * c;
+                    load8(Xbh + src, ka);
+                    if constexpr (!APART) load8(Vbh + src, va);
+                    size = 1;
                 }
-                while (ballot64(members != 0ull) != 0ull) {
-                    int jj[kInFlight];
-                    bool ok[kInFlight];
-                    float kk[kInFlight][8], vv[kInFlight][8];
+                for (int j0 = 0; j0 < lmax; j0 += kWave) {
+                    uint64_t members = 0ull;       // of rows j0 .. j0 + 63 of the chunk, the same for every lane of the group
 #pragma unroll
-                    for (int u = 0; u < kInFlight; ++u) {
-                        ok[u] = members != 0ull;
-                        jj[u] = ok[u] ? first_bit(members) : 0;
-                        members &= members - 1ull;
+                    for (int k = 0; k < kWave / LPR; ++k) {
+                        const int j = j0 + LPR * k + c, t = start + j - t0;
+                        bool match = false;
+                        if (j < lscan) match = (t < kMergeCidTile ? s_cid[t] : cid_bh[start + j]) == cl;
+                        members |= ((ballot64(match) >> gsh) & gmask) << (LPR * k);
                     }
+                    while (ballot64(members != 0ull) != 0ull) {
+                        int jj[kInFlight];
+                        bool ok[kInFlight];
+                        float kk[kInFlight][8], vv[kInFlight][8];
 #pragma unroll
-                    for (int u = 0; u < kInFlight; ++u) {
-                        if (ok[u]) {
-                            const int64_t src = (int64_t)(start + j0 + jj[u]) * p.stride_n + 8 * c;
-                            load8(Kbh + src, kk[u]);
-                            if constexpr (!APART) load8(Vbh + src, vv[u]);
+                        for (int u = 0; u < kInFlight; ++u) {
+                            ok[u] = members != 0ull;
+                            jj[u] = ok[u] ? first_bit(members) : 0;
+                            members &= members - 1ull;
                         }
-                    }
 #pragma unroll
-                    for (int u = 0; u < kInFlight; ++u) {
-                        if (ok[u]) {
-                            if (size == 0) {
-#pragma unroll
-                                for (int e = 0; e < 8; ++e) {
-                                    ka[e] = kk[u][e];
-                                    if constexpr (!APART) va[e] = vv[u][e];
-                                }
-                            } else {
-#pragma unroll
-                                for (int e = 0; e < 8; ++e) {
-                                    ka[e] += kk[u][e];
-                                    if constexpr (!APART) va[e] += vv[u][e];
-                                }
+                        for (int u = 0; u < kInFlight; ++u) {
+                            if (ok[u]) {
+                                const int64_t src = (int64_t)(start + j0 + jj[u]) * p.stride_n + 8 * c;
+                                load8(Xbh + src, kk[u]);
+                                if constexpr (!APART) load8(Vbh + src, vv[u]);
                             }
-                            size += 1;
+                        }
+#pragma unroll
+                        for (int u = 0; u < kInFlight; ++u) {
+                            if (ok[u]) {
+                                if (size == 0) {
+#pragma unroll
+                                    for (int e = 0; e < 8; ++e) {
+                                        ka[e] = kk[u][e];
+                                        if constexpr (!APART) va[e] = vv[u][e];
+                                    }
+                                } else {
+#pragma unroll
+                                    for (int e = 0; e < 8; ++e) {
+                                        ka[e] += kk[u][e];
+                                        if constexpr (!APART) va[e] += vv[u][e];
+                                    }
+                                }
+                                size += 1;
+                            }
                         }
                     }
                 }
-            }
-            if (size > 1) {
-                const float fs = (float)size;
+                if (size > 1) {
+                    const float fs = (float)size;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    ka[e] = ka[e] / fs;
-                    if constexpr (!APART) va[e] = va[e] / fs;
+                    for (int e = 0; e < 8; ++e) {
+                        ka[e] = ka[e] / fs;
+                        if constexpr (!APART) va[e] = va[e] / fs;
+                    }
+                }
+                if (valid) {
+                    const int64_t dst = ((int64_t)bh * p.cap + R) * D + 8 * c;
+                    if (p.out_is_bf16) {
+                        store_row8<bf16_t>(APART && values ? p.Vc : p.Kc, dst, ka);
+                        if constexpr (!APART) store_row8<bf16_t>(p.Vc, dst, va);
+                    } else {
+                        store_row8<float>(APART && values ? p.Vc : p.Kc, dst, ka);
+                        if constexpr (!APART) store_row8<float>(p.Vc, dst, va);
+                    }
+                    if (c == 0 && !values) counts_bh[R] = size;
                 }
             }
-            if (valid) {
-                const int64_t dst = ((int64_t)bh * p.cap + R) * D + 8 * c;
-                if (p.out_is_bf16) {
-                    store_row8<bf16_t>(values ? p.Vc : p.Kc, dst, ka);
-                    if constexpr (!APART) store_row8<bf16_t>(p.Vc, dst, va);
-                } else {
-                    store_row8<float>(values ? p.Vc : p.Kc, dst, ka);
-                    if constexpr (!APART) store_row8<float>(p.Vc, dst, va);
-                }
-                if (c == 0 && !values) counts_bh[R] = size;
-            }
-        }
+        };
+        if (TWICE && split) merge_rows(std::bool_constant<TWICE>());
+        else merge_rows(std::false_type());
     }
 }
 
@@ -523,8 +550,6 @@ size_t gsc_merge_workspace_bytes(int B, int Hkv, int N_max, int d, int out_elem_
     return bytes;
 }
 
-constexpr int64_t kMergeApartTokens = 49152;      // rows of all heads, see gsc_merge_kernel
-
 template <typename T, int D>
 static hipError_t launch_typed(const GscParams &p, int grid_x, hipStream_t stream) {
     const int max_items = (p.N_max + 1 + p.chunks_per_item - 1) / p.chunks_per_item;
@@ -536,8 +561,10 @@ static hipError_t launch_typed(const GscParams &p, int grid_x, hipStream_t strea
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (p.N_max <= kInlinePrefixTokens) {
-        const dim3 twice(grid.x, 2 * grid.y, grid.z);
-        if ((int64_t)heads * p.N_max <= kMergeApartTokens && twice.y <= 65535) hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, true>), twice, dim3(kGscThreads), 0, stream, p);
+        GscParams q = p;
+        q.split_wgs = min(gx, kSplitWorkgroups / heads);
+        const dim3 more(grid.x, grid.y + q.split_wgs, grid.z);
+        if ((int64_t)heads * p.N_max <= kSplitTokens && q.split_wgs > 0 && more.y <= 65535) hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, true>), more, dim3(kGscThreads), 0, stream, q);
         else hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, false>), grid, dim3(kGscThreads), 0, stream, p);
         return hipGetLastError();
     }

@@ -330,6 +330,46 @@ def test_generic_merge_short_chunks(H, n, gap):
         assert np.array_equal(got[2][b, H - 1, 3:3 + ref["n_rows"]].cpu().numpy(), ref["counts"][:ref["n_rows"]])
 
 
+@pytest.mark.parametrize("H,n,gaps", [
+    (1, 3000, [11, 13]), (1, 3000, [11, 12]),                       # chunks of twelve tokens on average, and of fewer
+    (2, 1500, [20, 21, 19, 22]),                                    # room on the chip: split from 21 tokens on
+    (8, 6000, [32, 33, 2, 3, 5]), (8, 6000, [32, 31, 2, 3, 5]),     # none: from 33 tokens on; more items than second workgroups
+    (5, 4000, [40, 2, 2, 2]),                                       # long chunks among short ones, eleven tokens on average
+    (3, 5000, [2600, 7, 900]), (600, 80, [30, 40]),                 # one beyond the cluster indices held in LDS; more heads than second workgroups
+])
+def test_generic_merge_split_items(H, n, gaps):
+    # keys and values of an item by a workgroup each, or both by one: the same bits as in a call of so many rows that no item is split, and
+    # the oracle's rows.  Two sequences, one a token shorter.
+    rng = np.random.default_rng(n + H)
+    lens = np.array([n, n - 1], np.int32)
+    wide = min(32768, 49152 // (2 * H) + n)
+    mask = np.zeros((2, wide), dtype=np.uint8)
+    for b in range(2):
+        at = np.cumsum(np.roll(np.resize(gaps, n), b)) - 1
+        mask[b, at[at < lens[b]]] = 1
+    K, V = (rng.standard_normal((2, H, wide, 64)).astype(np.float32) for _ in range(2))
+    K[:, :, 3:n] = K[:, :, np.arange(3, n) % 3] + 0.1 * K[:, :, 3:n]
+    out = []
+    for N in (n, wide):
+        offsets, num_chunks, sl = g.run_segment(np.ascontiguousarray(mask[:, :N]), lens)
+        dK, dV = (torch.from_numpy(np.ascontiguousarray(x[:, :, :N])).to(g.DEV) for x in (K, V))
+        Kc, Vc = (torch.zeros((2, H, n, 64), dtype=torch.float32, device=g.DEV) for _ in range(2))
+        counts = torch.zeros((2, H, n), dtype=torch.int32, device=g.DEV)
+        out.append(sc.sc_gsc_merge(dK, dV, offsets, num_chunks, 0.7, seq_lens=sl, cap=n, Kc=Kc, Vc=Vc, counts=counts)[:4])
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    for b, h in ((0, 0), (1, H - 1)):
+        m = int(lens[b])
+        ref = oracle.compress_head(K[b, h, :m], V[b, h, :m], oracle.segment(mask[b], m), 0.7)
+        rows = ref["n_rows"]
+        assert int(out[0][3][b, h]) == rows and np.array_equal(out[0][2][b, h, :rows].cpu().numpy(), ref["counts"][:rows])
+        # fp32 sums of up to l members in member order: (l + 1) half-ulps of the largest partial sum, relative to the mean
+        tol = 2.0 ** -24 * (int(ref["counts"][:rows].max()) + 2)
+        for got, want, x in ((out[0][0], ref["Kc"], K), (out[0][1], ref["Vc"], V)):
+            assert np.abs(got[b, h, :rows].cpu().numpy() - want[:rows]).max() <= tol * np.abs(x[b, h, :m]).max()
+
+
 @pytest.mark.parametrize("d,bf16,G,tail", [(128, True, 4, 0), (128, True, 7, 40), (64, True, 2, 0), (64, False, 1, 25), (128, False, 3, 0)])
 def test_heads_of_one_split(d, bf16, G, tail):
     # heads that one workgroup takes alone store their outputs directly, beside heads of several splits in the same launch: no rows at
