@@ -1016,18 +1016,19 @@ __device__ __forceinline__ void probe_words(const ProbeTiles &t, const float (&t
     }
 }
 
-// COUNT: a probe of the budget search.  Only the numbers of rows are wanted: no values are read and nothing is merged.
-template <typename TO, bool COUNT>
+// PROBE: a probe of the budget search, at one threshold or at several.  Only the numbers of rows are wanted: no values are read and nothing is merged.
+enum Probe { kNoProbe, kProbeOne, kProbeSeveral };
+template <typename TO, Probe PROBE>
 __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams p) {
+    constexpr bool COUNT = PROBE != kNoProbe;
     __shared__ __attribute__((aligned(16))) CompressLds s;
     // Slots in order, (sequence, head) fastest: every workgroup waits for earlier ones only, and with a multiple of eight
     // heads the windows of a head stay on one XCD.  Long chunks are decided ahead of everything else, by ahead_per_head workgroups per
     // head that wait for nothing: a window waits for the rows of all before it, and a long chunk in between, which takes twice as long, would hold up
     // those of half the chip (8 heads x 131072, a quarter of the windows long: 225 us, decided ahead 165).
-    // (A probe's work ahead is a long chunk at one threshold.)
     const int n_bh = p.B * p.Hkv;
     const int ahead_wgs = p.ahead_wgs;
-    [[maybe_unused]] const int nodes = COUNT ? (1 << p.probe_levels) - 1 : 1;
+    [[maybe_unused]] const int nodes = PROBE == kProbeSeveral ? (1 << p.probe_levels) - 1 : 1;
     const bool ahead = (int)blockIdx.x < ahead_wgs;
     const unsigned id = ahead ? blockIdx.x : blockIdx.x - (unsigned)ahead_wgs;
     const int place = (int)(id / (unsigned)n_bh), bh_i = (int)(id - (unsigned)place * (unsigned)n_bh);
@@ -1068,6 +1069,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         }
         return false;
     };
+    // (A probe's work ahead is a long chunk at one threshold.)
     int next_long = place;
     Window win, next;
     Pair64 D = {0ull, 0ull};
@@ -1093,7 +1095,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
     auto publish = [&](int rows, bool is_long, int lane) {      // one wavefront
         SC_FRESH_PARAMS;
         if (lane == 0) {
-            if constexpr (COUNT) p.win_count[(bh * p.win_slots + slot) * kProbeWords + next_long % nodes] = rows;      // (a long chunk)
+            if constexpr (COUNT) p.win_count[(bh * p.win_slots + slot) * kProbeWords + next_long % nodes] = rows;
             else {
                 const int S = p.slots_per_segment;
                 uint32_t *pub = p.published + bh * p.win_slots;
@@ -1216,7 +1218,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         }
         __syncthreads();
         const bool odd = uniform(*reinterpret_cast<const int *>(s.odd_norms)) != 0;
-        if constexpr (COUNT) {
+        if constexpr (PROBE == kProbeSeveral) {
             SC_FRESH_LANE;
             ProbeTiles tiles;
             probe_products(s, D, R, wave, g, c, tiles);
@@ -1243,8 +1245,8 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         } else {
         // the values, on their way while the rows are decided.  (Requested with the keys they delay those of the windows behind, and with
         // them everything that waits for those windows' rows.)
-        RowRegs xv;
-        {
+        [[maybe_unused]] RowRegs xv;
+        if constexpr (!COUNT) {
             SC_FRESH_LANE;
             load_rows(xv, Vbh, p.stride_n, w0 + 32 * wave, min(32, R - 32 * wave), g, c);
         }
@@ -1260,7 +1262,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             }
         }
         __syncthreads();
-        ColumnOps kk;
+        [[maybe_unused]] ColumnOps kk;
         const int nks = (R + 31) >> 5;
         if (wave == decider) {
             SC_FRESH_LANE;
@@ -1272,7 +1274,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
                           [&](const Pair64 &ask, int oa, int ob) { return settle_pairs(s, ask, oa, ob, tau, lane, wave, nullptr, 0, nullptr); }, d);
             const int nseed = __popcll(d.seeds.a) + __popcll(d.seeds.b);
             publish(nseed, false, lane);
-            {
+            if constexpr (!COUNT) {
                 const int out_a = open_a ? rows_below(d.seeds, d.seed_a) : -1, out_b = open_b ? rows_below(d.seeds, d.seed_b) : -1;
                 SC_FRESH_PARAMS;
                 if (p.cluster_id) {
@@ -1287,10 +1289,11 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
             decided(s, lane);
         } else {
             SC_FRESH_LANE;
-            column_operands(s, wave, g, c, nks, kk);
+            if constexpr (!COUNT) column_operands(s, wave, g, c, nks, kk);
             settle_until_decided(s, tau, lane, wave, nullptr, 0, nullptr);
         }
-        {
+        if constexpr (COUNT) return;
+        else {
             // everybody has the keys: the values take their place
             SC_FRESH_LANE;
             const int nseed = uniform(s.nseed);
@@ -1841,9 +1844,10 @@ hipError_t launch_gsc_fast(const GscParams &p0, bool planned, const BudgetStart 
         if (e != hipSuccess) return e;
     }
     const dim3 grid((unsigned)((size_t)p.win_slots * bh + p.ahead_wgs));
-    if (p.count_only) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, true>), grid, dim3(kWinThreads), 0, stream, p);
-    else if (p.out_is_bf16) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, false>), grid, dim3(kWinThreads), 0, stream, p);
-    else hipLaunchKernelGGL((gsc_compress_kernel<float, false>), grid, dim3(kWinThreads), 0, stream, p);
+    if (p.count_only && p.probe_levels == 1) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, kProbeOne>), grid, dim3(kWinThreads), 0, stream, p);
+    else if (p.count_only) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, kProbeSeveral>), grid, dim3(kWinThreads), 0, stream, p);
+    else if (p.out_is_bf16) hipLaunchKernelGGL((gsc_compress_kernel<bf16_t, kNoProbe>), grid, dim3(kWinThreads), 0, stream, p);
+    else hipLaunchKernelGGL((gsc_compress_kernel<float, kNoProbe>), grid, dim3(kWinThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p.count_only) return e;
     hipLaunchKernelGGL(gsc_count_kernel, dim3((unsigned)bh), dim3(kCountThreads), 0, stream, p);
