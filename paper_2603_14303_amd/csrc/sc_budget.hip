@@ -8,9 +8,10 @@
 // whose workgroups (one per sequence and head) add up their row counts, and the last of them to arrive moves the bracket three times (where a
 // probe is a complete merge, outside the bf16 / d = 128 path, it is at one threshold, and a small kernel after it moves the bracket from the merged lengths).
 // Bound by the chain of a probe's windows (its kernel 55 us at 8 heads x 32768 tokens, against 24 for a single threshold) and by launches.  12 iterations,
-// us per call with its sc_segment, a probe a step / three steps a probe: 8 x 32768 384 / 303, 2 x 131072 411 / 320, 2 x 2000 166 / 111; chunks
-// with a long tail, where a third of the rows lies in chunks that seven workgroups decide at a threshold each: 518 / 499, 566 / 550, 255 / 137.  (Two
-// steps a probe: 331, 426, 125; 466, 599, 166.)  The
+// us per call, a probe a step / three steps a probe: 8 x 32768 379 / 292, 2 x 2000 163 / 105, 8 x 8 x 16384 1019 / 844; chunks with a long tail, 8 x 32768
+// 550 / 420, 8 x 131072 1477 / 1268; all chunks longer than a window, where the thresholds share less: 8 x 32768 in chunks of 200 589 / 524, of 400
+// 809 / 793, 8 x 131072 1527 / 1600, 1884 / 1995, 2 x 8000 295 / 175 and 545 / 300.  (Two steps a probe instead of three: 331 and 125 on the first
+// two.)  What is left over after threes takes a probe of two steps, or of one threshold (one step in all 79 / 78; by the kernel for several 87).  The
 // whole search is a fixed sequence of launches on the caller's stream with no host synchronisation.  The
 // last launch runs at the threshold found and leaves its merged cache in the outputs.
 #include "sc_device.h"

@@ -42,6 +42,7 @@ constexpr int kWinThreads = kWinWaves * kWave;
 constexpr int kWinRows = 128;            // rows of a window
 constexpr int kAheadWgs = 512;           // workgroups that decide long chunks ahead of the windows (one per head if there are more heads)
 constexpr int kAheadProbes = 1536;       // the same in a counting probe, where nobody waits for anybody (512: long-tailed chunks 558 us instead of 514, 768 to 3072 within 2 %)
+constexpr int kTogetherFrom = 3;         // see gsc_compress_kernel
 constexpr int kSegRows = 1024;           // rows of a sequence whose chunks one wavefront of the plan kernel packs
 constexpr float kFastBand = 1e-4f;       // fp32 cosine error for d = 128 is < 2e-5; inside the band -> fp64
 
@@ -303,8 +304,13 @@ struct CompressLds {
         };
     };
     float rinv[kWinRows];
-    float seed_rinv[16];                 // a long chunk's first sixteen seeds: reciprocal norms, rows of the chunk
-    int seed_row[16];
+    union {
+        struct {                         // a long chunk's first sixteen seeds: reciprocal norms, rows of the chunk
+            float seed_rinv[16];
+            int seed_row[16];
+        };
+        uint64_t sets[kProbeWords][2];   // a long chunk at all thresholds of a probe: rows of the block that are open, then the seeds among them
+    };
     int tile_steps[kWinRows / 16];       // bit ks of tile t: one of the rows 32 ks .. 32 ks + 31 belongs to it
     int any_unsure, base_lo, base_ok;
     unsigned char odd_norms[kWinWaves];  // wavefront w's rows hold one without a usable norm
@@ -1016,6 +1022,259 @@ __device__ __forceinline__ void probe_words(const ProbeTiles &t, const float (&t
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// A chunk longer than a window at all thresholds of a probe, by one workgroup: its blocks' keys are read, and the products of a block's rows formed, once
+// for all of them.  Seeds of the blocks before are listed in the workspace, those of any threshold once: row, reciprocal norm, and a bit per
+// threshold that it is a seed at.  Whether a row joins one of them, and not which, is all that counts.
+// Bound by instructions, words and decisions of seven thresholds where three steps of a search one by one need three: 8 heads x 131072 tokens in chunks of 200, 12
+// steps, 1600 us a call, 1527 with a probe a step, 3037 with a workgroup per chunk and threshold; 8 x 32768 in chunks of 200 524, 589 and 840.
+// (With the listed seeds taken by all wavefronts in turn instead of sixteen by each: chunks of 400 1010 us, 793 so; every pair inside the band settled before
+// the decisions instead of when one needs it: chunks of 200 613, 580.)
+struct ProbeSeeds {
+    int32_t *row, *rinv, *at;      // (rinv: the bits of a float)
+    int n;
+};
+__device__ __forceinline__ float max_rows(float x) {   // maximum over the four 16-lane rows, same lane position
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// sixteen listed seeds from the s0-th on: the keys as an operand (row c), reciprocal norms and thresholds of seeds 4 g + i
+struct ProbeGroup {
+    bf16x8f_t keys[4];
+    float rinv[4];
+    uint32_t at[4];
+    int row;      // of seed c
+    __device__ __forceinline__ static int row_of(const ProbeSeeds &u, int s0, int c) {
+        return c < u.n - s0 ? __hip_atomic_load(u.row + s0 + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    }
+    __device__ __forceinline__ ProbeGroup(const ProbeSeeds &u, int s0, int row_c, const bf16_t *Kch, int64_t stride_n, int g, int c) : row(row_c) {
+        const int ns = u.n - s0;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            keys[ks] = __builtin_bit_cast(bf16x8f_t, c < ns ? *reinterpret_cast<const uint4 *>(Kch + (int64_t)row * stride_n + 32 * ks + 8 * g) : make_uint4(0u, 0u, 0u, 0u));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool there = 4 * g + i < ns;
+            rinv[i] = there ? __int_as_float(__hip_atomic_load(u.rinv + s0 + 4 * g + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0.f;
+            at[i] = there ? (uint32_t)__hip_atomic_load(u.at + s0 + 4 * g + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        }
+    }
+    // cosines of seeds 4 g + i with row 16 J + c of the block
+    __device__ __forceinline__ floatx4_t cosines(const CompressLds &s, int J, int g, int c) const {
+        floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(s.rows + (16 * J + c) * kKeyRowBytes + (32 * ks + 8 * g) * 2);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(keys[ks], __builtin_bit_cast(bf16x8f_t, v), acc, 0, 0, 0);
+        }
+        const float rn = s.rinv[16 * J + c];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] *= rinv[i] * rn;
+        return acc;
+    }
+};
+// floats as integers of the same order
+__device__ __forceinline__ int ordered(float x) { const int b = __float_as_int(x); return b ^ ((b >> 31) & 0x7FFFFFFF); }
+__device__ __forceinline__ float unordered(int b) { return __int_as_float(b ^ ((b >> 31) & 0x7FFFFFFF)); }
+struct ProbeTops {      // (in place of the words of single thresholds)
+    int top[kProbeNodes][kWinRows];          // the largest cosine of a row with a listed seed of the threshold, ordered
+    uint64_t doubt[kProbeNodes][2];          // rows that fp64 decides
+    int odd_seed;                            // a listed seed has no usable norm
+};
+static_assert(sizeof(ProbeTops) <= sizeof(CompressLds::yes) + sizeof(CompressLds::unsure), "in their place");
+// The rows of a block (R of them) that resemble no listed seed of threshold t: s.sets[t].  Sixteen seeds at a time and wavefront, against all rows (one group
+// in all: its row tiles are shared out).  Per pair a choice, which takes the seed out where it is none, and a maximum for each threshold; rows
+// whose nearest seed is inside the band, or that have no usable norm, are settled in fp64.  For all wavefronts.
+__device__ __forceinline__ void probe_open_rows(CompressLds &s, const ProbeSeeds &u, const bf16_t *Kch, int64_t stride_n, int rb, int R, float tau_lo, float tau_hi, int nodes,
+                                                int wave, int lane) {
+    const int g = lane >> 4, c = lane & 15;
+    ProbeTops &tops = *reinterpret_cast<ProbeTops *>(&s.yes[0][0]);
+    for (int i = threadIdx.x; i < kProbeNodes * kWinRows; i += kWinThreads) (&tops.top[0][0])[i] = ordered(-INFINITY);
+    if (threadIdx.x == 0) tops.odd_seed = 0;
+    __syncthreads();
+    const bool shared = u.n <= 16;
+    const int own = shared ? 0 : 16 * wave;
+    if (own < u.n) {
+        float top[8][kProbeNodes];
+#pragma unroll
+        for (int J = 0; J < 8; ++J)
+#pragma unroll
+            for (int t = 0; t < kProbeNodes; ++t) top[J][t] = -INFINITY;
+        bool odd = false;
+        int row = ProbeGroup::row_of(u, own, c);
+#pragma unroll 1
+        for (int s0 = own; s0 < u.n; s0 += 16 * kWinWaves) {
+            const ProbeGroup seeds(u, s0, row, Kch, stride_n, g, c);
+            row = ProbeGroup::row_of(u, s0 + 16 * kWinWaves, c);
+            const float sum = (seeds.rinv[0] + seeds.rinv[1]) + (seeds.rinv[2] + seeds.rinv[3]);      // not a number if one of them is
+            odd = odd || !(sum == sum);
+#pragma unroll
+            for (int J = 0; J < 8; ++J) {
+                if (16 * J >= R || (shared && (J & 3) != wave)) continue;
+                const floatx4_t x = seeds.cosines(s, J, g, c);
+#pragma unroll
+                for (int t = 0; t < kProbeNodes; ++t) {
+                    float y[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) y[i] = ((seeds.at[i] >> t) & 1u) != 0u ? x[i] : -INFINITY;
+                    top[J][t] = fmaxf(fmaxf(top[J][t], y[0]), y[1]);
+                    top[J][t] = fmaxf(fmaxf(top[J][t], y[2]), y[3]);
+                }
+            }
+        }
+        if (ballot64(odd) != 0ull && lane == 0) tops.odd_seed = 1;
+#pragma unroll
+        for (int t = 0; t < kProbeNodes; ++t) {
+#pragma unroll
+            for (int J = 0; J < 8; J += 4) {      // lane group g files tile J + g
+                const float a = max_rows(top[J][t]), b = max_rows(top[J + 1][t]), d = max_rows(top[J + 2][t]), e = max_rows(top[J + 3][t]);
+                const float x = g < 2 ? (g == 0 ? a : b) : (g == 2 ? d : e);
+                if (t < nodes) atomicMax(&tops.top[t][16 * (J + g) + c], ordered(x));
+            }
+        }
+    }
+    __syncthreads();
+    const bool odd_seed = uniform(tops.odd_seed) != 0;
+    for (int t = wave; t < nodes; t += kWinWaves) {
+        const float tau = budget_node_tau(tau_lo, tau_hi, t + 1);
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int r = 64 * half + lane;
+            const float x = unordered(tops.top[t][r]) - tau, rn = s.rinv[r];
+            const uint64_t left = ballot64(r < R && !(x > kFastBand)), near = ballot64(!(x < -kFastBand) || odd_seed || !(rn == rn));
+            if (lane == 0) {
+                s.sets[t][half] = left;
+                tops.doubt[t][half] = left & near;
+            }
+        }
+    }
+    __syncthreads();
+    // in fp64: listed seeds inside the band, four pairs at a time.  Lane 8 t + J has the doubtful rows of threshold t in tile J.
+    int doubt = lane < 8 * nodes ? (int)reinterpret_cast<const uint16_t *>(tops.doubt)[lane] : 0;
+    if (ballot64(doubt != 0) == 0ull || own >= u.n) return;
+    uint32_t *open = reinterpret_cast<uint32_t *>(s.sets);      // [threshold][32 rows]
+    int row = ProbeGroup::row_of(u, own, c);
+#pragma unroll 1
+    for (int s0 = own; s0 < u.n; s0 += 16 * kWinWaves) {
+        const ProbeGroup seeds(u, s0, row, Kch, stride_n, g, c);
+        row = ProbeGroup::row_of(u, s0 + 16 * kWinWaves, c);
+#pragma unroll 1
+        for (int J = 0; J < 8; ++J) {
+            const uint64_t asked = ballot64(doubt != 0 && (lane & 7) == J);      // bit 8 t + J
+            if (asked == 0ull || (shared && (J & 3) != wave)) continue;
+            const floatx4_t x = seeds.cosines(s, J, g, c);
+#pragma unroll 1
+            for (uint64_t left = asked; left != 0ull; left &= left - 1ull) {
+                const int from = uniform(first_bit(left)), t = from >> 3;
+                int unsure = __builtin_amdgcn_readlane(doubt, from);
+                const float tau = budget_node_tau(tau_lo, tau_hi, t + 1);
+                uint32_t mine = 0u;      // the lane's pairs
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mine |= (((seeds.at[i] >> t) & 1u) != 0u && ((unsure >> c) & 1) != 0 && !(fabsf(x[i] - tau) > kFastBand)) ? 1u << i : 0u;
+                while (true) {
+                    const uint64_t ask = ballot64(mine != 0u && ((unsure >> c) & 1) != 0);
+                    if (ask == 0ull) break;
+                    const int n = min(__popcll(ask), 4), at = nth_set_bit(ask, min(g, n - 1));      // group g takes the g-th lane's next pair, or the last one's
+                    const int i = __shfl(__ffs((int)mine) - 1, at, kWave), r = 16 * J + (at & 15), seed = __shfl(seeds.row, 4 * (at >> 4) + i, kWave);
+                    const bool yes = settle_one(*reinterpret_cast<const uint4 *>(Kch + (int64_t)seed * stride_n + 8 * c),
+                                                *reinterpret_cast<const uint4 *>(Kch + (int64_t)(rb + r) * stride_n + 8 * c), tau);
+                    unsure &= ~uniform((int)or_rows(yes ? 1u << (at & 15) : 0u));
+                    uint64_t done = 0ull;
+                    for (int k = 0, m = n; k < m; ++k) done |= 1ull << nth_set_bit(ask, k);
+                    if ((done >> lane) & 1ull) mine &= mine - 1u;
+                    if (yes && c == 0) atomicAnd(open + 4 * t + (r >> 5), ~(1u << (r & 31)));
+                }
+                if (lane == from) doubt = unsure;
+            }
+        }
+    }
+}
+// One block of the chunk: rows [rb, rb + R), keys in s.rows.  Between two barriers the caller's; `fetch` asks for the next rows.  counts: seeds so far
+// at thresholds wave and wave + 4.
+template <typename Fetch>
+__device__ __forceinline__ void probe_block(CompressLds &s, ProbeSeeds &u, const bf16_t *Kch, int64_t stride_n, int rb, int R, bool last, float tau_lo, float tau_hi, int nodes,
+                                            int wave, Fetch fetch, int (&counts)[2]) {
+    SC_FRESH_LANE;
+    const bool odd = uniform(*reinterpret_cast<const int *>(s.odd_norms)) != 0;
+    if (u.n > 0) probe_open_rows(s, u, Kch, stride_n, rb, R, tau_lo, tau_hi, nodes, wave, lane);
+    else if (wave == 0 && lane < 2 * kProbeWords) s.sets[lane >> 1][lane & 1] = bits_below(max(min(R - 64 * (lane & 1), 64), 0));
+    const Pair64 none = {0ull, 0ull};
+    ProbeTiles tiles;
+    probe_products(s, none, R, wave, g, c, tiles);
+    const float rinv_a = s.rinv[lane], rinv_b = s.rinv[64 + lane];
+    __syncthreads();      // the keys have been read, the open rows are known
+    const uint64_t mine = lane < 2 * nodes ? s.sets[lane >> 1][lane & 1] : 0ull;
+    const bool any_open = ballot64(mine != 0ull) != 0ull;
+    ProbeWords &words = *reinterpret_cast<ProbeWords *>(s.rows);
+    if (any_open) {
+        for (int t0 = 0; t0 < nodes; t0 += kWinWaves) {
+            float taus[kWinWaves];
+#pragma unroll
+            for (int k = 0; k < kWinWaves; ++k) taus[k] = budget_node_tau(tau_lo, tau_hi, min(t0 + k, nodes - 1) + 1);
+            probe_words(tiles, taus, odd, wave, g, c, words.yes[t0 + g], words.unsure[t0 + g]);
+        }
+        __syncthreads();
+    }
+    if (!any_open) {
+        fetch();
+        return;
+    }
+    const uint64_t below = bits_below(lane);
+    for (int t = wave; t < nodes; t += kWinWaves) {
+        const float tau = budget_node_tau(tau_lo, tau_hi, t + 1);
+        uint32_t *list = (wave < 2 ? &s.yes[0][0] : &s.unsure[0][0]) + (wave & 1) * 2 * kWinRows;
+        const Pair64 open = {s.sets[t][0], s.sets[t][1]};
+        const bool open_a = (open.a >> lane) & 1ull, open_b = (open.b >> lane) & 1ull;
+        Words y, n;
+        y.a = open_a ? row_word(words.yes[t], lane, 0) & below & open.a : 0ull;
+        y.b0 = open_b ? row_word(words.yes[t], 64 + lane, 0) & open.a : 0ull;
+        y.b1 = open_b ? row_word(words.yes[t], 64 + lane, 1) & below & open.b : 0ull;
+        n.a = open_a ? row_word(words.unsure[t], lane, 0) & below & open.a : 0ull;
+        n.b0 = open_b ? row_word(words.unsure[t], 64 + lane, 0) & open.a : 0ull;
+        n.b1 = open_b ? row_word(words.unsure[t], 64 + lane, 1) & below & open.b : 0ull;
+        Decision d;
+        auto settle = [&](const Pair64 &ask, int oa, int ob) { return settle_alone(list, Kch + (int64_t)rb * stride_n, stride_n, ask, oa, ob, tau, lane); };
+        if (!first_fit_fixed_point(settle, y, n, open_a, open_b, lane, d)) {
+            const Pair64 all = {~0ull, ~0ull};
+            first_fit_by_seed(settle, y, n, open, all, all, lane, d);
+        }
+        const int found = __popcll(d.seeds.a) + __popcll(d.seeds.b);
+        counts[0] += t < kWinWaves ? found : 0;
+        counts[1] += t < kWinWaves ? 0 : found;
+        if (lane == 0) {
+            s.sets[t][0] = d.seeds.a;
+            s.sets[t][1] = d.seeds.b;
+        }
+    }
+    fetch();
+    __syncthreads();      // (the next rows may take the words' place)
+    if (last) return;
+    // the list grows by the rows that are seeds at any threshold
+    uint32_t at_a = 0u, at_b = 0u;
+    for (int t = 0; t < nodes; ++t) {
+        at_a |= (uint32_t)((s.sets[t][0] >> lane) & 1ull) << t;
+        at_b |= (uint32_t)((s.sets[t][1] >> lane) & 1ull) << t;
+    }
+    const uint64_t new_a = ballot64(at_a != 0u), new_b = ballot64(at_b != 0u);
+    if (wave == 0) {
+        const int to_a = u.n + __popcll(new_a & below), to_b = u.n + __popcll(new_a) + __popcll(new_b & below);
+        if (at_a != 0u) {
+            __hip_atomic_store(u.row + to_a, rb + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(u.rinv + to_a, __float_as_int(rinv_a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(u.at + to_a, (int)at_a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (at_b != 0u) {
+            __hip_atomic_store(u.row + to_b, rb + 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(u.rinv + to_b, __float_as_int(rinv_b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(u.at + to_b, (int)at_b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    u.n += __popcll(new_a) + __popcll(new_b);
+}
+
 // PROBE: a probe of the budget search, at one threshold or at several.  Only the numbers of rows are wanted: no values are read and nothing is merged.
 enum Probe { kNoProbe, kProbeOne, kProbeSeveral };
 template <typename TO, Probe PROBE>
@@ -1069,14 +1328,30 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         }
         return false;
     };
-    // (A probe's work ahead is a long chunk at one threshold.)
+    // A probe's work ahead is a long chunk at one threshold; or at all of them, where that many items would be kTogetherFrom / 2 times the workgroups
+    // (2 heads x 8000 tokens, us per call of 12 steps: chunks of 200 174 the first way and 261 the second, of 1000 885 and 1729; 8 x 32768:
+    // of 200 840 and 524, of 700, twice the workgroups, 1389 and 1481, of 850 1549 and 1907).
+    [[maybe_unused]] bool together = false;
+    if constexpr (PROBE == kProbeSeveral) {
+        if (ahead) {
+            SC_FRESH_PARAMS;
+            const int lane = fresh_lane(), segments = p.win_slots / p.slots_per_segment;
+            int all = 0;
+            for (int q = lane; q < segments; q += kWave) all += p.long_count[(int64_t)b * segments + q];
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) all += __shfl_xor(all, d, kWave);
+            all = uniform(all);
+            together = 2 * (int64_t)all * nodes > (int64_t)kTogetherFrom * p.ahead_per_head;
+            if (place >= (together ? all : all * nodes)) return;
+        }
+    }
     int next_long = place;
     Window win, next;
     Pair64 D = {0ull, 0ull};
     if (!ahead) {
         win = take_window(place, &D);
         if (win.rows <= 0 || (COUNT && (win.flags & kWinLong) != 0)) return;
-    } else {
+    } else if (!together) {
         if (!take_long(next_long / nodes, win)) return;
         D.a = D.b = 0ull;
     }
@@ -1090,6 +1365,52 @@ __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams 
         tau_lo = p.budget->lo;
         tau_hi = p.budget->hi;
         if (ahead) tau = budget_node_tau(tau_lo, tau_hi, 1 + next_long % nodes);
+    }
+    if constexpr (PROBE == kProbeSeveral) {
+        if (together) {
+            int at = place;
+            Window now, then;
+            if (!take_long(at, now)) return;
+            RowRegs x;
+            {
+                SC_FRESH_LANE;
+                load_rows<0>(x, Kbh, p.stride_n, now.first + 32 * wave, min(32, now.rows - 32 * wave), g, c);
+            }
+            for (;;) {
+                SC_FRESH_PARAMS;
+                at += p.ahead_per_head;
+                const bool more = take_long(at, then);
+                const int start = now.first, l = now.rows;
+                const bf16_t *Kch = Kbh + (int64_t)start * p.stride_n;
+                int32_t *list = reinterpret_cast<int32_t *>(p.rows_ws) + bh * kProbeWords * p.N_max + start;      // (where the means of a merge would go)
+                ProbeSeeds seeds = {list, list + p.N_max, list + 2 * (int64_t)p.N_max, 0};
+                int counts[2] = {0, 0};
+#pragma unroll 1
+                for (int rb = 0; rb < l; rb += kWinRows) {
+                    const int Rb = min(kWinRows, l - rb), nx = rb + kWinRows;
+                    {
+                        SC_FRESH_LANE;
+                        file_norms(s, x, Rb - 32 * wave, wave, g, c);
+                        park_rows(s, x, wave, g, c);
+                    }
+                    __syncthreads();
+                    auto fetch = [&]() {
+                        SC_FRESH_LANE;
+                        const int first = nx < l ? start + nx : (more ? then.first : start), rows = nx < l ? l - nx : (more ? then.rows : 0);
+                        load_rows<0>(x, Kbh, p.stride_n, first + 32 * wave, min(32, rows - 32 * wave), g, c);
+                    };
+                    probe_block(s, seeds, Kch, p.stride_n, rb, Rb, nx >= l, tau_lo, tau_hi, nodes, wave, fetch, counts);
+                }
+                if (fresh_lane() == 0) {
+                    int32_t *count = p.win_count + (bh * p.win_slots + now.slot) * kProbeWords;
+                    const int closes = (now.flags & kWinClosed) != 0 ? 1 : 0;
+                    if (wave < nodes) count[wave] = counts[0] + closes;
+                    if (wave + kWinWaves < nodes) count[wave + kWinWaves] = counts[1] + closes;
+                }
+                if (!uniform(more ? 1 : 0)) return;
+                now = Window{uniform(then.slot), uniform(then.first), uniform(then.rows), uniform(then.flags)};
+            }
+        }
     }
     // the window's rows are known: tell the windows behind it
     auto publish = [&](int rows, bool is_long, int lane) {      // one wavefront

@@ -162,19 +162,50 @@ PROBE_GAPS = {
     "short": [24, 3, 61, 40, 1, 17, 90],
     "window": [126, 127, 128, 129, 130],            # chunk lengths that just fit a window and just do not fit
     "every row": [1],
-    "long": [700, 3, 150, 40, 1025, 129, 1],        # a long chunk is counted at every threshold by a workgroup of its own
+    "long": [700, 3, 150, 40, 1025, 129, 1],
+    "two blocks": [130, 257, 200, 258, 144],        # many long chunks
     "none": [],
 }
 
 
-@pytest.mark.parametrize("layout", list(PROBE_GAPS))
-@pytest.mark.parametrize("lens,heads", [((1023, 1025), 3), ((2600, 1, 0), 8), ((100,), 1)])
-def test_every_threshold_of_a_probe_counts_exactly(layout, lens, heads):
+def _bundles(rng, n, tau):
+    """Keys at angles of their own around thirty centres, so that thresholds of every size split clusters."""
+    c = rng.standard_normal((30, 128))
+    return c[rng.integers(0, 30, n)] + rng.choice([0.05, 0.15, 0.5, 1.0], size=(n, 1)) * rng.standard_normal((n, 128))
+
+
+def _inside_the_band(rng, n, tau):
+    """Rows whose cosine with one of four directions is one of the thresholds, to within what rounding to bf16 leaves (some 1e-4, the
+    width of the band that fp64 decides), and a few of the directions themselves in front."""
+    e = np.linalg.qr(rng.standard_normal((128, 128)))[0]
+    t = rng.choice(np.asarray(tau), size=(n, 1))
+    rest = rng.standard_normal((n, 128))
+    rest -= (rest @ e[:, :4]) @ e[:, :4].T
+    rest /= np.linalg.norm(rest, axis=1, keepdims=True)
+    k = t * e[:, rng.integers(0, 4, n)].T + np.sqrt(1 - t * t) * rest
+    some = rng.random(n) < 0.05
+    k[some] = e[:, rng.integers(0, 4, int(some.sum()))].T
+    return 3.0 * k
+
+
+@pytest.mark.parametrize("layout,lens,heads,keys", [
+    *[(layout, lens, heads, _bundles) for layout in PROBE_GAPS for lens, heads in (((1023, 1025), 3), ((2600, 1, 0), 8), ((100,), 1))],
+    # long chunks at a threshold for every workgroup, and (enough of them for the workgroups) at all thresholds by one
+    *[(layout, lens, heads, _inside_the_band) for layout in ("short", "two blocks", "long") for lens, heads in (((2600, 1025), 2), ((2600, 2500), 32))],
+    ("two blocks", (2600, 2500), 32, _bundles), ("long", (2600, 2500), 32, _bundles), ("two blocks", (5200,), 256, _bundles),
+])
+def test_every_threshold_of_a_probe_counts_exactly(layout, lens, heads, keys):
     """A probe counts at seven thresholds and the search goes down their tree: with the budget set to the rows at a threshold, and to one
-    row less, a count that is off by one anywhere on the way turns the search.  Bundles of keys at angles of their own, so that
-    thresholds of every size split clusters; a zero row and a key that is not finite among them (a norm that is not usable)."""
+    row less, a count that is off by one anywhere on the way turns the search.  A zero row and a key that is not finite are among the
+    keys (a norm that is not usable)."""
     rng = np.random.default_rng(sum(lens) + 10 * heads + len(layout))
     B, N = len(lens), max(lens)
+    thresholds, todo = [], [(np.float32(-1.01), np.float32(1.0))]
+    for _ in range(7):      # what a search from this bracket may ask for in its first three steps
+        x, y = todo.pop(0)
+        m = np.float32(0.5) * (x + y)
+        thresholds.append(float(m))
+        todo += [(x, m), (m, y)]
     mask = np.zeros((B, N), np.uint8)
     K = np.zeros((B, heads, N, 128), np.float32)
     for b, n in enumerate(lens):
@@ -182,9 +213,7 @@ def test_every_threshold_of_a_probe_counts_exactly(layout, lens, heads):
             p = np.cumsum(np.roll(np.resize(PROBE_GAPS[layout], n), b)) - 1
             mask[b, p[p < n]] = 1
         for h in range(heads):
-            c = rng.standard_normal((30, 128))
-            spread = rng.choice([0.05, 0.15, 0.5, 1.0], size=(n, 1))
-            K[b, h, :n] = c[rng.integers(0, 30, n)] + spread * rng.standard_normal((n, 128))
+            K[b, h, :n] = keys(rng, n, thresholds) if h < 4 else np.roll(K[b, h % 4, :n], h, axis=0)
     K[0, 0, lens[0] // 2] = 0.0
     K[0, heads - 1, lens[0] // 3, 5] = np.inf
     K = wl.round_to_bf16(K)
