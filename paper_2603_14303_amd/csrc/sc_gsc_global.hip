@@ -11,7 +11,7 @@
 //            block of 64 earlier rows), "surely above" and "inside the +-1e-4 band" (decided later in
 //            fp64).  Only blocks that hold such a pair are written; a bit per block says which.
 //   decide   which rows are seeds and which seed every row joins, all blocks of 64 rows at once.
-//   rank, slots, place   number the clusters and their members in row order.
+//   rank, slots, place   number the clusters and their members in row order (one kernel where a sequence has few rows).
 //   sum      one 16-lane group per cluster adds up its members' keys and values in row order (fp32),
 //            scales by 1/size and writes the output row: Eq. 3.
 // A row needs comparing with SEEDS only, and one row in six is one where merging pays.  Long sequences are therefore taken in stages of 4096 rows
@@ -134,9 +134,9 @@ __global__ __launch_bounds__(256) void glob_norms_kernel(GlobParams p) {
 // the rows of block I pass through an LDS tile shared by the four wavefronts and are the A operand.  The
 // product tile leaves lane (g, c) with the dot products of row 16 Jt + c of block J and rows
 // 16 It + 4 g + i of block I: four bits of that row's word, completed by an OR over the lane groups.
-// Bound by the matrix cores, busy 55 % of the time, and the threshold step beside them.  Two quarters of a tile in registers at a time, so that three
-// workgroups share a compute unit: 8 heads x 32768 rows 606 us a call with all four and two workgroups, 576 so (x 1000 62 and 67: near the diagonal, where
-// every quarter holds a pair, they are formed twice).
+// Bound by the matrix cores and the threshold step beside them.  Two quarters of a tile in registers at a time, so that three workgroups share a
+// compute unit: 8 heads x 32768 rows 606 us a call with all four and two workgroups, 576 so.  A quarter with a pair that comes near is formed again; those of
+// a block's own rows, which all have one, are formed that way only (8 x 300 44 us a call with both, 40 so; x 1000 55 and 49).
 template <bool SEEDS>
 __global__ __launch_bounds__(kGlPairWaves *kWave, 3) void glob_pairs_kernel(GlobParams p) {
     constexpr int kListTiles = kGlSeedUnit * kGlSeedShare;
@@ -325,21 +325,24 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 3) void glob_pairs_kernel(Glob
             top[It] = (Jt == 0) ? fmaxf(t0, t1) : fmaxf(fmaxf(top[It], t0), t1);
             top[It] = fmaxf(fmaxf(top[It], t2), t3);
         };
+        int near = 15;      // quarters with a pair that comes near; a block's own rows make one of each (a row and itself), one way is enough for them
+        if (!odd && (SEEDS || I != J)) {
 #pragma unroll
-        for (int step = 0; step < 3; ++step) a[step] = operand(step >> 2, step & 3);
+            for (int step = 0; step < 3; ++step) a[step] = operand(step >> 2, step & 3);
 #pragma unroll
-        for (int step = 0; step < 16; ++step) {
-            if (step + 3 < 16) a[(step + 3) & 3] = operand((step + 3) >> 2, (step + 3) & 3);
-            product(acc[(step >> 2) & 1], a[step & 3], step & 3);
-            if (step >= 4) compare((step >> 2) - 1, step & 3);
-            __builtin_amdgcn_sched_barrier(0);      // the order of issue stays as written
+            for (int step = 0; step < 16; ++step) {
+                if (step + 3 < 16) a[(step + 3) & 3] = operand((step + 3) >> 2, (step + 3) & 3);
+                product(acc[(step >> 2) & 1], a[step & 3], step & 3);
+                if (step >= 4) compare((step >> 2) - 1, step & 3);
+                __builtin_amdgcn_sched_barrier(0);      // the order of issue stays as written
+            }
+#pragma unroll
+            for (int Jt = 0; Jt < 4; ++Jt) compare(3, Jt);
+            near = 0;
+#pragma unroll
+            for (int It = 0; It < 4; ++It) near |= ballot64(top[It] >= 0.f) != 0ull ? 1 << It : 0;
+            if (near == 0) return;
         }
-#pragma unroll
-        for (int Jt = 0; Jt < 4; ++Jt) compare(3, Jt);
-        int near = odd ? 15 : 0;      // quarters with a pair that comes near
-#pragma unroll
-        for (int It = 0; It < 4; ++It) near |= ballot64(top[It] >= 0.f) != 0ull ? 1 << It : 0;
-        if (near == 0 && (SEEDS || I != J)) return;
         for (int It = 0; It < 4; ++It) {
             if (((near >> It) & 1) == 0) continue;
             gl_float4 (&x)[4] = acc[0];
@@ -697,7 +700,8 @@ __global__ __launch_bounds__(kWave) void glob_decide_kernel(GlobParams p) {
 //           cluster has.
 //   slots   a thread per cluster: sums over the workgroups of rank, the cluster's size and where its members go (space taken in any order).
 //   place   a thread per row: its slot.
-// (One workgroup per head did all of it before: 86 us for 8 heads x 32768 rows whatever the chip had free.)
+// (One workgroup per head did all of it before: 86 us for 8 heads x 32768 rows whatever the chip had free.  Up to kGlRankRows rows it does that in less than
+// the two launches take: see glob_rank_kernel.)
 constexpr int kGlRankRows = 2048, kGlRankThreads = 512;
 
 __device__ __forceinline__ uint64_t gl_seed_mask(const unsigned long long *st, int I) {
@@ -709,13 +713,15 @@ __device__ __forceinline__ unsigned int *gl_part_sizes(const GlobParams &p, int 
     return reinterpret_cast<unsigned int *>(p.U + (long long)bh * p.tri) + (int64_t)part * (p.nbp * kGlBlock / 2);
 }
 
+// ALONE: the sequences have no more rows than that, and the same workgroup finds the clusters' slots and files the rows in them.
+template <bool ALONE>
 __global__ __launch_bounds__(kGlRankThreads) void glob_rank_kernel(GlobParams p) {
     extern __shared__ unsigned int s_size2[];       // rows filed per cluster, two 16-bit fields a word
     __shared__ unsigned long long s_mask[512];      // seeds of every block
     __shared__ int s_pref[512];                     // clusters before block J
     __shared__ int s_scan[kGlRankThreads / kWave];
     __shared__ int s_lead[kGlRankRows];
-    const int bh = (int)blockIdx.x % (p.B * p.Hkv), part = (int)blockIdx.x / (p.B * p.Hkv);
+    const int bh = (int)blockIdx.x % (p.B * p.Hkv), part = ALONE ? 0 : (int)blockIdx.x / (p.B * p.Hkv);
     const int n = __builtin_amdgcn_readfirstlane(gl_seq_len(p, bh / p.Hkv));
     const int first = part * kGlRankRows;
     if (first >= n && part > 0) return;      // (the first one reports, too)
@@ -782,15 +788,58 @@ __global__ __launch_bounds__(kGlRankThreads) void glob_rank_kernel(GlobParams p)
         }
     }
     __syncthreads();
-    int32_t *lead = p.lead + (int64_t)bh * npad;
+    auto place_of = [&](int q) {      // among the rows of its cluster here
+        const int i = q * kGlRankThreads + tid;
+        return (pl[q] & kGlLeader) ? s_lead[i] : s_lead[(i & ~63) + (pl[q] >> 8)] + (pl[q] & 0x7F);
+    };
+    if constexpr (ALONE) {
+        // first slots of four clusters a thread, in place of their sizes (kGlRankRows rows at most: 16 bits hold them)
+        static_assert(kGlRankRows <= 4 * kGlRankThreads, "a look each");
+        unsigned short *size = reinterpret_cast<unsigned short *>(s_size2);
+        int mine4[4], sum = 0;
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int i = q * kGlRankThreads + tid, j = first + i;
-        const int at = (pl[q] & kGlLeader) ? s_lead[i] : s_lead[(i & ~63) + (pl[q] >> 8)] + (pl[q] & 0x7F);
-        if (j < n) lead[j] = t[q] | (at << 16);
+        for (int q = 0; q < 4; ++q) {
+            mine4[q] = 4 * tid + q < P ? (int)size[4 * tid + q] : 0;
+            sum += mine4[q];
+        }
+        int upto = sum;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int up = __shfl_up(upto, off, kWave);
+            if (lane >= off) upto += up;
+        }
+        if (lane == kWave - 1) s_scan[wave] = upto;      // (everybody is done with the sums over the blocks)
+        __syncthreads();
+        int at = upto - sum;
+        for (int w = 0; w < wave; ++w) at += s_scan[w];
+        int32_t *mbase = p.mbase + (int64_t)bh * (npad + 1), *csize = p.csize + (int64_t)bh * npad, *counts = p.counts + (int64_t)bh * p.cap;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int c = 4 * tid + q;
+            if (c < P) {
+                mbase[c] = at;
+                csize[c] = mine4[q];
+                if (c < p.cap) counts[c] = mine4[q];
+                size[c] = (unsigned short)at;
+            }
+            at += mine4[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int j = q * kGlRankThreads + tid;
+            if (j < n) p.order[(int64_t)bh * npad + (int)size[t[q]] + place_of(q)] = j;
+        }
+    } else {
+        int32_t *lead = p.lead + (int64_t)bh * npad;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int at = place_of(q), j = first + q * kGlRankThreads + tid;
+            if (j < n) lead[j] = t[q] | (at << 16);
+        }
+        unsigned int *sizes = gl_part_sizes(p, bh, part);
+        for (int i = tid; i < (P + 1) / 2; i += kGlRankThreads) sizes[i] = s_size2[i];
     }
-    unsigned int *sizes = gl_part_sizes(p, bh, part);
-    for (int i = tid; i < (P + 1) / 2; i += kGlRankThreads) sizes[i] = s_size2[i];
 }
 
 __global__ __launch_bounds__(256) void glob_slots_kernel(GlobParams p) {
@@ -992,13 +1041,16 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     const int M = p.stage_words, stages = (p.nseg + M - 1) / M;
     // Length of a walk: the longest that leaves some five items for each of the 768 places (three workgroups on each of 256 CUs), so that the last ones do not
     // matter.  (Us per call with 8 / 16 / 32 blocks: 8 heads x 32768 619 / 600 / 599; x 20000 367 / 372 / 411; x 3000 79 / 97 / 143.)
-    int items = 0;
-    for (p.walk = 32; p.walk >= 8; p.walk /= 2) {
-        const int stage_segs = M * kGlWordBlocks / p.walk;
-        items = p.walk / kGlPairWaves * stage_segs * (stage_segs + 1) / 2;
-        if ((size_t)stages * items * BH >= 4096 || p.walk == 8) break;
+    // Items are those of the blocks that the longest sequence has: the last stage's first ones only.
+    const int last_groups = (p.nbp - (stages - 1) * M * kGlWordBlocks + kGlPairWaves - 1) / kGlPairWaves;      // of row blocks
+    size_t items = 0;
+    for (p.walk = 32;; p.walk /= 2) {
+        const int stage_segs = M * kGlWordBlocks / p.walk, per_seg = p.walk / kGlPairWaves;
+        items = (size_t)(stages - 1) * per_seg * stage_segs * (stage_segs + 1) / 2;
+        for (int jg = 0; jg < last_groups; ++jg) items += jg / per_seg + 1;
+        if (items * BH >= 4096 || p.walk == 8) break;
     }
-    hipLaunchKernelGGL((glob_pairs_kernel<false>), dim3((unsigned)(stages * items * BH)), dim3(kGlPairWaves * kWave), 0, stream, p);
+    hipLaunchKernelGGL((glob_pairs_kernel<false>), dim3((unsigned)(items * BH)), dim3(kGlPairWaves * kWave), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (p.stage = 0; p.stage < stages; ++p.stage) {
@@ -1014,29 +1066,35 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
         if (e != hipSuccess) return e;
     }
     const size_t dyn = npad * sizeof(unsigned short);
-    if (dyn > 48 * 1024) {   // a host-side setting of the kernel (per device), not a stream operation
-        int dev = 0;
-        e = hipGetDevice(&dev);
+    if (a.N_max <= kGlRankRows) {
+        hipLaunchKernelGGL((glob_rank_kernel<true>), dim3((unsigned)BH), dim3(kGlRankThreads), dyn, stream, p);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
-        static std::mutex mu;
-        static bool raised[64];
-        if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-        std::lock_guard<std::mutex> lock(mu);
-        if (!raised[dev]) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(glob_rank_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+    } else {
+        if (dyn > 48 * 1024) {   // a host-side setting of the kernel (per device), not a stream operation
+            int dev = 0;
+            e = hipGetDevice(&dev);
             if (e != hipSuccess) return e;
-            raised[dev] = true;
+            static std::mutex mu;
+            static bool raised[64];
+            if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+            std::lock_guard<std::mutex> lock(mu);
+            if (!raised[dev]) {
+                e = hipFuncSetAttribute(reinterpret_cast<const void *>(glob_rank_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+                if (e != hipSuccess) return e;
+                raised[dev] = true;
+            }
         }
+        hipLaunchKernelGGL((glob_rank_kernel<false>), dim3((unsigned)((a.N_max + kGlRankRows - 1) / kGlRankRows * BH)), dim3(kGlRankThreads), dyn, stream, p);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(glob_slots_kernel, dim3((unsigned)((a.N_max + 511) / 512), (unsigned)BH), dim3(256), 0, stream, p);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(glob_place_kernel, dim3((unsigned)((a.N_max + 255) / 256), (unsigned)BH), dim3(256), 0, stream, p);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(glob_rank_kernel, dim3((unsigned)((a.N_max + kGlRankRows - 1) / kGlRankRows * BH)), dim3(kGlRankThreads), dyn, stream, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(glob_slots_kernel, dim3((unsigned)((a.N_max + 511) / 512), (unsigned)BH), dim3(256), 0, stream, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(glob_place_kernel, dim3((unsigned)((a.N_max + 255) / 256), (unsigned)BH), dim3(256), 0, stream, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const int max_clusters = a.N_max < a.cap ? a.N_max : a.cap;
     const dim3 grid_sum((unsigned)((max_clusters + 15) / 16), (unsigned)BH, 2);
     if (p.out_is_bf16) hipLaunchKernelGGL((glob_sum_kernel<bf16_t>), grid_sum, dim3(256), 0, stream, p);

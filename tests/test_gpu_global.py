@@ -23,10 +23,12 @@ def _global_case(w, tau, **kw):
 
 
 @pytest.mark.parametrize("n,heads,tau", [(63, 2, 0.7), (64, 1, 0.7), (1000, 2, 0.7), (8192 + 11, 2, 0.7),
-                                         (3000, 2, 0.9745), (2000, 1, 1.0), (2000, 1, -1.01)])
+                                         (3000, 2, 0.9745), (2000, 1, 1.0), (2000, 1, -1.01),
+                                         (2048, 2, 0.9745), (2047, 1, 1.0), (2048, 1, 1.0), (2049, 1, 1.0), (2048, 1, -1.01)])
 def test_dedicated_path(n, heads, tau):
     # blocks of 64 rows: less than one, exactly one, many with a ragged tail; a threshold inside the band of
-    # the similarities (pairs decided in fp64, many clusters); no merging at all; everything in one cluster
+    # the similarities (pairs decided in fp64, many clusters); no merging at all; everything in one cluster; the
+    # longest sequences that one workgroup numbers, and one row more
     w = wl.get_workload("layer32k")
     case = _global_case(w, tau, n_max=n, heads=heads, exclude_near=(tau == 0.7))
     out = g.check_compress(case)
