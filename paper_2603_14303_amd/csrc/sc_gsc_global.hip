@@ -16,9 +16,8 @@
 //            scales by 1/size and writes the output row: Eq. 3.
 // A row needs comparing with SEEDS only, and one row in six is one where merging pays.  Long sequences are therefore taken in stages of 4096 rows
 // or a multiple: all pairs inside the stages (one launch), then stage by stage the rows of a stage against the seeds of the stages before, listed without
-// gaps, and the decisions of the stage.  8 heads x 32768 tokens, us per call: tau 0.7 1020 with all pairs, 576 in four stages of 8192 rows (pairs inside them 260,
-// with the seeds 46 + 78 + 90, decide 4 x 18); tau 0.979, half the rows seeds, 1045 and 853.  What that costs where every row is a seed
-// (tau 1: 1100 and 1140) buys nothing, so stages are only as short as one seed in three rows pays for.
+// gaps, and the decisions of the stage.  8 heads x 32768 tokens, us per call of all pairs and of four stages of 8192 rows: tau 0.7 900 and 555, tau 0.9745
+// 908 and 664; where every row is a seed 957 and 1135 (see glob_stage_words).
 // Everything else (other element types, head dims, longer sequences) is handed to the ordinary kernels
 // of sc_gsc_merge with offsets that describe one chunk per sequence.
 #include "sc_device.h"
@@ -66,11 +65,11 @@ struct GlobParams {
     int32_t *mbase, *csize;       // [nbp * 64 + 1], the last one: slots given out; [nbp * 64]
     int32_t *nclusters;           // [1]; before the rank kernel: blocks whose wavefronts are through
     int walk;                     // column blocks per work item of the pairs kernel: 8, 16 or 32
-    int stage_words, stage;       // words of tile flags of a stage; the stage of this launch
+    int stage_words, stages, stage;      // words of tile flags of a stage (the last one has the rest); how many; the stage of this launch
     int32_t *seedlist;            // [npad]: the seeds of the stages before, in row order (the memory of `order`)
 };
 __device__ __forceinline__ int gl_stage_blocks(const GlobParams &p) { return p.stage_words * kGlWordBlocks; }
-__device__ __forceinline__ int gl_stage_start(const GlobParams &p, int J) { return J / gl_stage_blocks(p) * gl_stage_blocks(p); }      // first block of block J's stage
+__device__ __forceinline__ int gl_stage_start(const GlobParams &p, int J) { return min(J / gl_stage_blocks(p), p.stages - 1) * gl_stage_blocks(p); }      // first block of block J's stage
 
 __device__ __forceinline__ long long gl_col_base(int I, int nbp) {   // first word of column block I
     return 64ll * ((long long)I * nbp - (long long)I * (I - 1) / 2);
@@ -161,7 +160,7 @@ __global__ __launch_bounds__(kGlPairWaves *kWave, 3) void glob_pairs_kernel(Glob
         seg = x % walks;
     } else {
         const int per_seg = p.walk / kGlPairWaves;      // groups of row blocks to a segment
-        const int stage_segs = stage_blocks / p.walk, items = per_seg * stage_segs * (stage_segs + 1) / 2, st = x / items, y = x - st * items;
+        const int stage_segs = stage_blocks / p.walk, items = per_seg * stage_segs * (stage_segs + 1) / 2, st = min(x / items, p.stages - 1), y = x - st * items;
         int q = 0;
         while (per_seg * (q + 1) * (q + 2) / 2 <= y) ++q;
         const int rem = y - per_seg * q * (q + 1) / 2;
@@ -676,7 +675,7 @@ __global__ __launch_bounds__(kWave) void glob_decide_kernel(GlobParams p) {
     const bf16_t *Kbh = p.K + b * p.stride_b + h * p.stride_h;
     const bool done = glob_decide_block(p, bh, Kbh, n, J, lane, p.polls);
     // What follows needs all seeds of this stage: the last wavefront to come through decides what others have left undecided.
-    const int last = min(first + gl_stage_blocks(p), (n + kGlBlock - 1) / kGlBlock);
+    const int nb = (n + kGlBlock - 1) / kGlBlock, last = p.stage == p.stages - 1 ? nb : min(first + gl_stage_blocks(p), nb);
     if (!done) __threadfence();      // the seeds that some of its rows have joined
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     int before = 0;
@@ -975,17 +974,27 @@ size_t gsc_global_workspace_bytes(int B, int Hkv, int N_max, int d) {
     return glob_prefix_bytes(B) + (ordinary > fast ? ordinary : fast);
 }
 
-// Words of flags (of 64 column blocks) of a stage.  In us, with a seed in about three rows: all pairs at 1.16 PFLOP/s, and what a further stage's
-// two launches and the chain of its decisions cost.  (Us per call, stages of 4096 / 8192 / 16384 rows / one: 8 heads x 32768 647 / 664 / 815 / 1030,
-// with tau 0.9745 822 / 800 / 860 / 1044; 2 heads 397 / 316 / 304 / 360; 8 heads x 9000 218 / 216 / - / 185: numbering still in one workgroup per head.)
-static int glob_stage_words(size_t heads, int n, int nseg) {
-    const double all = (double)heads * n * n * 128 / 1.16e9, stage_cost = 26.0, seeds = 0.35;
+// Stages of `m` words of flags (of 64 column blocks); the last one has what is left, half as much again or less.
+static int glob_stages(int nbp, int m) { return max(1, (2 * nbp + m * kGlWordBlocks) / (2 * m * kGlWordBlocks)); }
+// Words of a stage.  In us: all pairs at 1.25 PFLOP/s; with the seeds of the stages before 0.45 of that, which is a seed in four or five rows, and half as fast for
+// short lists of unequal length; and what a further stage's two launches and the chain of its decisions cost.  Us per call, stages of 4096 /
+// 8192 / 16384 rows / one, tau 0.7 and 0.9745 (a seed in six and in four rows) and where every row is a seed:
+//   8 heads x 32768   544 / 555 / 651 / 900    691 / 664 / 736 / 908    1279 / 1135 / 1034 / 957
+//   16 x 32768        918 / 987 / 1219 / 1813  1129 / 1165 / 1341 / 1797  2272 / 2108 / 1993 / 1878
+//   1 x 32768         261 / 173 / 139 / 158    373 / 231 / 167 / 164    563 / 318 / 205 / 172
+//   16 x 16384        371 / 403 / - / 524      446 / 455 / - / 538      719 / 635 / - / 581
+//   8 x 12365         212 / 207 / - / 207      285 / 251 / - / 213      436 / 348 / - / 226
+// So a call in stages in which next to nothing merges takes up to a fifth longer than one of all pairs would (with all pairs, and the kernels of the time before
+// stages, 8 x 32768 took 990 / 1003 / 1079); a threshold that nothing can exceed is known here, and is not taken in stages.
+static int glob_stage_words(size_t heads, int n, int nbp, float tau) {
+    const int nseg = (nbp + kGlWordBlocks - 1) / kGlWordBlocks;
+    if (tau >= 1.0f) return nseg;
+    const double all = (double)heads * n * n * 128 / 1.25e9, stage_cost = 25.0 + 0.8 * (double)heads, seeds = 0.45;
     int best = nseg;
     double least = all;
     for (int m = nseg - 1; m >= 1; --m) {
-        double own = 0.0;      // share of the pairs that lie within a stage
-        int stages = 0;
-        for (int s = 0; s < nseg; s += m, ++stages) own += (double)min(m, nseg - s) * min(m, nseg - s) / ((double)nseg * nseg);
+        const int stages = glob_stages(nbp, m), first = m * kGlWordBlocks, last = nbp - (stages - 1) * first;
+        const double own = ((double)(stages - 1) * first * first + (double)last * last) / ((double)nbp * nbp);      // share of the pairs that lie within a stage
         const double cost = all * (own + seeds * (1.0 - own)) + stage_cost * (stages - 1);
         if (cost < least) { least = cost; best = m; }
     }
@@ -1036,12 +1045,12 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     p.seedlist = p.order;
-    p.stage_words = glob_stage_words(BH, a.N_max, p.nseg);
+    p.stage_words = glob_stage_words(BH, a.N_max, p.nbp, a.tau);
     p.stage = 0;
-    const int M = p.stage_words, stages = (p.nseg + M - 1) / M;
+    const int M = p.stage_words, stages = p.stages = glob_stages(p.nbp, M);
     // Length of a walk: the longest that leaves some five items for each of the 768 places (three workgroups on each of 256 CUs), so that the last ones do not
     // matter.  (Us per call with 8 / 16 / 32 blocks: 8 heads x 32768 619 / 600 / 599; x 20000 367 / 372 / 411; x 3000 79 / 97 / 143.)
-    // Items are those of the blocks that the longest sequence has: the last stage's first ones only.
+    // Items are those of the blocks that the longest sequence has.
     const int last_groups = (p.nbp - (stages - 1) * M * kGlWordBlocks + kGlPairWaves - 1) / kGlPairWaves;      // of row blocks
     size_t items = 0;
     for (p.walk = 32;; p.walk /= 2) {
@@ -1054,7 +1063,7 @@ hipError_t launch_gsc_global(const GscMergeArgs &a, hipStream_t stream) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (p.stage = 0; p.stage < stages; ++p.stage) {
-        const int first = p.stage * M * kGlWordBlocks, blocks = min(M * kGlWordBlocks, p.nbp - first);
+        const int first = p.stage * M * kGlWordBlocks, blocks = p.stage == stages - 1 ? p.nbp - first : M * kGlWordBlocks;
         if (p.stage > 0) {
             const int groups = (blocks + kGlPairWaves - 1) / kGlPairWaves;
             hipLaunchKernelGGL((glob_pairs_kernel<true>), dim3((unsigned)(groups * (first / (kGlSeedUnit * kGlSeedShare)) * BH)), dim3(kGlPairWaves * kWave), 0, stream, p);

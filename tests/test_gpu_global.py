@@ -220,39 +220,55 @@ def test_random_structures_as_one_chunk(seed):
     print("seed", seed, "compared", compared, "N", N, "tau", tau, "rows", clens.cpu().numpy().tolist())
 
 
-@pytest.mark.parametrize("tau,polls,drift", [(0.7, 1 << 20, 0.0), (0.9745, 1 << 20, 0.0), (0.9745, 0, 0.0), (0.8, 1 << 20, 0.4), (0.99875, 0, 0.05)])
-def test_sequences_long_enough_for_stages(tau, polls, drift):
-    # 8 heads x 12365 tokens are decided in stages: rows of the second are compared with the seeds of the first, listed without
-    # gaps (pairs decided in fp64 among them); one sequence ends inside the second stage's first blocks, one inside the first stage.
+@pytest.mark.parametrize("tau,polls,drift,B,H,N", [
+    # 12365 rows, two stages of 8192 and the rest
+    (0.7, 1 << 20, 0.0, 2, 8, 12365), (0.9745, 1 << 20, 0.0, 2, 8, 12365), (0.9745, 0, 0.0, 2, 8, 12365), (0.8, 1 << 20, 0.4, 2, 8, 12365),
+    (0.99875, 0, 0.05, 2, 8, 12365),
+    # three stages of 4096, the last one with 77 rows more
+    (0.9745, 1 << 20, 0.0, 4, 8, 12365), (0.9745, 0, 0.0, 4, 8, 12365), (0.8, 1 << 20, 0.4, 4, 8, 12365),
+    # five of 4096, the last one with fewer rows; two of 4096 and 65 rows more; eight, with items of 32 column blocks
+    (0.9745, 1 << 20, 0.0, 4, 8, 20000), (0.9745, 0, 0.0, 4, 8, 20000), (0.9745, 0, 0.0, 2, 32, 8257), (0.9745, 1 << 20, 0.0, 4, 8, 32768),
+])
+def test_sequences_long_enough_for_stages(tau, polls, drift, B, H, N):
+    # Rows of the second stage are compared with the seeds of the first, listed without gaps (pairs decided in fp64 among them); one
+    # sequence ends inside another stage's first blocks, one inside the first stage where rows drift.
     # Rows that drift: chains that a stage ends in the middle of; without patience every stage is finished by its last wavefront.
     import oracle
     rng = np.random.default_rng(int(1000 * tau) + polls % 7)
-    B, H, N, d = 2, 4, 12365, 128
-    lens = np.array([N, 5003] if drift else [8192 + 65, N], np.int32)
+    tau = float(np.float32(tau))      # the call takes a float: the oracle compares with the same number (3e-8 from 0.99875, and a pair lies between)
+    d, kinds = 128, 4      # heads of their own keys, the others have the same
+    lens = np.full((B,), N, np.int32)
+    lens[:2] = [N, 5003] if drift else [8192 + 65, N]
     look = [(0, 1), (1, 2)]
     if drift:
-        K = rng.standard_normal((B, H, N, d)).astype(np.float32)
+        base = rng.standard_normal((kinds, N, d)).astype(np.float32)
         for i in range(1, N):
-            K[:, :, i] = np.sqrt(1 - drift * drift) * K[:, :, i - 1] + drift * K[:, :, i]
-        K[:, :, 8190:8195] = 0.0
+            base[:, i] = np.sqrt(1 - drift * drift) * base[:, i - 1] + drift * base[:, i]
+        base[:, 8190:8195] = 0.0
+        base[:, 4094:4098] = 0.0
     else:
-        centers = rng.standard_normal((B, H, N // 24, d)).astype(np.float32)
+        centers = rng.standard_normal((kinds, N // 24, d)).astype(np.float32)
         near = np.clip(np.arange(N) // 24 + rng.integers(-6, 7, size=N), 0, N // 24 - 1)
         near[::97] = rng.integers(0, N // 24, size=len(near[::97]))      # some resemble rows of other stages
-        K = centers[:, :, near] + 0.15 * rng.standard_normal((B, H, N, d)).astype(np.float32)
-    K = _bf16_exact(K)
-    V = _bf16_exact(rng.standard_normal((B, H, N, d)))
+        base = centers[:, near] + 0.15 * rng.standard_normal((kinds, N, d)).astype(np.float32)
+    base = _bf16_exact(base)
+    values = _bf16_exact(rng.standard_normal((kinds, N, d)))
+    which = (np.arange(B * H) % kinds).reshape(B, H)
+    at = torch.from_numpy(which).to(g.DEV)
+    Kd, Vd = g.to_device(base, True)[at], g.to_device(values, True)[at]
+    K = {bh: base[which[bh]] for bh in look}
+    V = {bh: values[which[bh]] for bh in look}
     old = sc.tune_get("global_polls")
     try:
         sc.tune_set("global_polls", polls)
-        Kc, Vc, counts, clens, cid = sc.sc_gsc_merge_global(g.to_device(K, True), g.to_device(V, True), tau, seq_lens=torch.from_numpy(lens).to(g.DEV),
-                                                            out_dtype=torch.float32, want_cluster_id=True)
+        Kc, Vc, counts, clens, cid = sc.sc_gsc_merge_global(Kd, Vd, tau, seq_lens=torch.from_numpy(lens).to(g.DEV), out_dtype=torch.float32,
+                                                            want_cluster_id=True)
         torch.cuda.synchronize()
     finally:
         sc.tune_set("global_polls", old)
     for b, h in look:
         n = int(lens[b])
-        r = oracle.compress_head(K[b, h, :n], V[b, h, :n], np.array([0, n + 1], np.int32), tau)
+        r = oracle.compress_head(K[b, h][:n], V[b, h][:n], np.array([0, n + 1], np.int32), tau)
         assert r["chunk_margin"].min() > 1e-9
         rows = r["n_rows"]
         assert int(clens[b, h]) == rows
@@ -266,7 +282,7 @@ def test_sequences_long_enough_for_stages(tau, polls, drift):
 def test_stages_in_a_captured_graph():
     # the launches of a staged call, replayed on new keys with eager work in between, give what an eager call gives
     gen = torch.Generator(g.DEV).manual_seed(4)
-    H, N, d = 8, 12365, 128
+    H, N, d = 16, 12365, 128
     K = torch.empty((1, H, N, d), dtype=torch.bfloat16, device=g.DEV)
     V = torch.empty_like(K)
 
