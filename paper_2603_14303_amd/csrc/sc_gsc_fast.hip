@@ -2127,10 +2127,11 @@ __global__ __launch_bounds__(kCountThreads) void gsc_count_kernel(GscParams p) {
 
 // ------------------------------------------------------------------------------------------------
 static int segments_of(int n_max) { return (n_max + kSegRows - 1) / kSegRows; }
-// a workgroup of the compress kernel for every slot and those ahead: fewer than 2^32 threads in a launch, and the rows of a segment in its word
+// a workgroup of the compress kernel for every slot and those ahead (a probe's, which are more than a merge's): fewer than 2^32 threads in a launch, and
+// the rows of a segment in its word
 static bool fast_holds(int heads, int n_max, int max_chunks) {
     const int S = gsc_slots_per_segment(n_max, max_chunks);
-    return segment_holds(S, n_max) && ((int64_t)segments_of(n_max) * S * heads + max(heads, kAheadWgs)) * kWinThreads < (int64_t(1) << 32);
+    return segment_holds(S, n_max) && ((int64_t)segments_of(n_max) * S * heads + max(heads, max(kAheadWgs, kAheadProbes))) * kWinThreads < (int64_t(1) << 32);
 }
 bool gsc_fast_holds(int heads, int N_max) { return fast_holds(heads, N_max, 0); }
 

@@ -239,3 +239,29 @@ def test_every_threshold_of_a_probe_counts_exactly(layout, lens, heads, keys):
                 want, _ = oracle.tau_for_budget(rows_at, budget, lo, hi, iters)
                 out = sc.sc_gsc_merge_budget(Kd, Kd, off, nch, max(0, budget), lo, hi, iters, seq_lens=sl)
                 assert out[5].item() == want and int(out[6].item()) == rows_at(want), (iters, at, budget)
+
+
+def test_probes_have_more_workgroups_than_a_merge():
+    """A window per token for 13 heads of 1.29 million tokens: with the workgroups that take long chunks in a merge these are fewer than 2^32 threads, with a
+    probe's they are more, so neither has windows of that kind."""
+    H, N = 13, 1259 * 1024
+    gen = torch.Generator(device=g.DEV).manual_seed(12)
+    K = torch.randn((1, H, N, 128), generator=gen, device=g.DEV, dtype=torch.bfloat16)
+    K[:, :, 1::2] = K[:, :, ::2]                                    # tokens in pairs
+    mask = torch.zeros((1, N), dtype=torch.uint8, device=g.DEV)
+    mask[0, 49::50] = 1
+    off, nch = sc.sc_segment(mask)
+    budget = H * N * 6 // 10
+    out = []
+    for knob in (0, 1):
+        sc.tune_set("gsc_chunks_per_task", knob)
+        try:
+            out.append(sc.sc_gsc_merge_budget(K, K, off, nch, budget, -1.01, 1.0, 3, cap=N * 6 // 10, out_dtype=torch.bfloat16)[2:])
+            torch.cuda.synchronize()
+        finally:
+            sc.tune_set("gsc_chunks_per_task", 0)
+    # a chunk of 49 tokens is 25 rows (its last token's twin is the delimiter), and its delimiter one: at every threshold from 0.5 on
+    rows = H * (N // 50) * 26 + H * ((N % 50 + 1) // 2)
+    for counts, lens, _, tau, total in out:
+        assert int(total) == rows == int(lens.sum()) and float(tau) > 0.4 and torch.equal(lens, out[0][1])
+    assert torch.equal(out[0][0][:, :, :rows // H], out[1][0][:, :, :rows // H])
