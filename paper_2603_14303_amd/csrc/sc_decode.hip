@@ -150,7 +150,7 @@ __device__ __forceinline__ void store_partial(float *p, float v, bool local) {
 }
 
 // Returns 0 in the workgroups that are done after publishing, 1 in the folding workgroup once every
-// other split of the (sequence, head) is published, -1 there if the hand-over failed.
+// other split of the (sequence, head) is published, -1 there if the hand-over failed.  S > 1: a single split stores its outputs (store_alone).
 __device__ __forceinline__ int publish_or_collect(HeadSync *hs, unsigned long long epoch, int S, int split, int tid,
                                                   bool local, int poll_budget, int *s_flag) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's partial stores are acknowledged
@@ -165,8 +165,8 @@ __device__ __forceinline__ int publish_or_collect(HeadSync *hs, unsigned long lo
     }
     if (tid < kWave) {
         int budget = poll_budget;
-        bool all = S <= 1;   // a single split has nothing to wait for
-        unsigned long long f0 = (unsigned long long)(xcc + 1), f1 = f0;
+        bool all = false;
+        unsigned long long f0 = 0ull, f1 = 0ull;
         while (!all && poll_budget >= 0) {   // a negative budget gives up without looking (host-driven test of the failure path)
             f0 = (tid < S - 1) ? __hip_atomic_load(&hs->flag[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (want << 8);
             f1 = (tid + kWave < S - 1) ? __hip_atomic_load(&hs->flag[tid + kWave], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (want << 8);

@@ -127,7 +127,8 @@ __global__ __launch_bounds__(256) void glob_norms_kernel(GlobParams p) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// pairs: workgroup (JG, bh) owns the row blocks J = 4 JG + wave and walks the column blocks I = 0 .. max J.
+// pairs: a workgroup owns the row blocks J = 4 JG + wave and walks p.walk of their stage's column blocks up to their own, or (SEEDS) its share of the seeds
+// of the stages before, 64 of the list to a column block.
 // The rows of block J are the B operand and stay in registers (lane (g, c): row 16 Jt + c, elements
 // 32 ks + 8 g .. + 7 -- v_mfma_f32_16x16x32_bf16, the form that runs at the full bf16 rate of this chip);
 // the rows of block I pass through an LDS tile shared by the four wavefronts and are the A operand.  The

@@ -158,7 +158,7 @@ struct GscParams {
     int slots_per_segment, win_slots;   // windows per kSegRows rows / per sequence that there is room for
     int max_chunks;       // chunks per window, <= 0: as many as fit
     int polls;            // looks at the windows before until a workgroup leaves its own to others
-    int count_only;       // fast path: cluster and count only (comp_lens); no values are read, no rows written
+    int count_only;       // fast path: cluster and count only, for `budget`; no values are read, no outputs written
     int chunks_per_item;  // generic path
     int probe_levels;     // steps of the search that a counting probe decides
     int short_wgs[2];     // generic path: workgroups per (sequence, head) where short chunks make items of 8 / of 16 or 32, 0: they don't (see gsc_item_shape)

@@ -50,7 +50,7 @@ struct GscMergeArgs {
     const int32_t *base_lens = nullptr;   // append mode: rows already in the outputs, [B, Hkv]
     Tuning tune;                          // the knobs when the call was made
     const float *tau_dev = nullptr;       // threshold in device memory (overrides tau)
-    bool count_only = false;              // only comp_lens is produced (bf16 / d = 128 fast path; elsewhere the full merge runs)
+    bool count_only = false;              // a counting probe, with a budget_state: row counts go to the search, no output is written (bf16 / d = 128 fast path; elsewhere the full merge runs)
     void *budget_state = nullptr;         // counting probe of the budget search: its last kernel also moves the bracket (fast path only)
     const struct BudgetStart *budget_start = nullptr;   // the search that this probe's plan starts
     int probe_levels = 1;                 // steps of the search that a counting probe decides
