@@ -55,7 +55,7 @@ def test_local_and_remote_handover_agree_bit_for_bit(B, Hkv, G, d, dtype):
 
 def test_failed_handover_is_reported_and_contained():
     B, Hkv, G, cap = 1, 8, 4, 4096
-    rows = [4096, 3000, 2000, 100, 4095, 2500, 1, 0]      # heads 3, 6, 7 have a single split: nothing to hand over
+    rows = [4096, 3000, 289, 250, 4095, 288, 1, 0]      # up to 288 rows (heads 3, 5, 6, 7) there is a single split: nothing to hand over
     Q, Kc, Vc, counts, lens = _cache(B, Hkv, G, cap, rows, seed=31)
     O_ref, lse_ref = sc.sc_decode_attn(Q, Kc, Vc, counts, lens, want_lse=True)
     torch.cuda.synchronize()
@@ -72,8 +72,8 @@ def test_failed_handover_is_reported_and_contained():
         torch.cuda.synchronize()
     finally:
         sc.tune_set("decode_poll_budget", 1 << 20)
-    multi = [h for h in range(Hkv) if rows[h] > 192]
-    single = [h for h in range(Hkv) if rows[h] <= 192]
+    multi = [h for h in range(Hkv) if rows[h] > 288]
+    single = [h for h in range(Hkv) if rows[h] <= 288]
     for h in multi:
         assert torch.isnan(O[0, h * G:(h + 1) * G].float()).all() and torch.isnan(lse[0, h * G:(h + 1) * G]).all()
     for h in single:

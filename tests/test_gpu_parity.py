@@ -449,3 +449,76 @@ def test_calls_that_the_native_marshalling_leaves_to_the_wrappers():
     assert torch.equal(got, want)
     got, _ = sc.sc_decode_attn(torch.nn.Parameter(Q), Kc, Vc, counts, lens, O=O.zero_(), workspace=ws)
     assert torch.equal(got, want)
+
+
+def test_native_marshalling_and_the_wrappers_agree(monkeypatch):
+    # every call that _native takes, with it and without it: the same outputs bit for bit, and the same refusals
+    rng = np.random.default_rng(10)
+    B, H, G, n, d, nq, tcap = 2, 2, 3, 200, 128, 5, 9
+    K, V = (g.to_device(rng.standard_normal((B, H, n, d)).astype(np.float32), True) for _ in range(2))
+    K[:, :, 1::2] = K[:, :, ::2]
+    mask = torch.zeros((B, n), dtype=torch.uint8, device=g.DEV)
+    mask[:, 9::10] = 1
+    seq = torch.tensor([n, n - 33], dtype=torch.int32, device=g.DEV)
+    Q, Qn = (g.to_device(rng.standard_normal(s).astype(np.float32), True) for s in ((B, H * G, d), (nq, B, H * G, d)))
+    Kt, Vt = (g.to_device(rng.standard_normal((B, H, tcap, d)).astype(np.float32), True) for _ in range(2))
+    tail = torch.tensor([tcap, 6], dtype=torch.int32, device=g.DEV)
+    ws = sc.gsc_merge_workspace(B, H, n, d, g.DEV, torch.bfloat16)
+    ws_d = sc.decode_attn_workspace(B, H * G, H, 2 * n, d, g.DEV)
+    ws_m = sc.Workspace(sc.load_library().sc_multi_attn_workspace_bytes(B, H * G, H, nq, 2 * n + tcap, d), g.DEV)
+    z = lambda *s, t=torch.bfloat16: torch.zeros(s, dtype=t, device=g.DEV)
+    i32 = torch.int32
+
+    def segment(**kw):
+        a = dict(dict(mask=mask, seq_lens=seq, offsets=z(B, n + 2, t=i32), num_chunks=z(B, t=i32)), **kw)
+        return sc.sc_segment(**a)
+    off, nch = segment()
+
+    def merge(**kw):
+        a = dict(dict(K=K, V=V, offsets=off, num_chunks=nch, tau=0.7, seq_lens=seq, cap=2 * n, Kc=z(B, H, 2 * n, d), Vc=z(B, H, 2 * n, d), counts=z(B, H, 2 * n, t=i32),
+                      comp_lens=z(B, H, t=i32), cluster_id=z(B, H, n, t=i32), workspace=ws), **kw)
+        return sc.sc_gsc_merge(**a)
+    Kc, Vc, counts, lens, _ = merge()
+    cache = dict(Kc=Kc, Vc=Vc, counts=counts, comp_lens=lens)
+
+    def decode(**kw):
+        a = dict(dict(cache, Q=Q, O=z(B, H * G, d), lse=z(B, H * G, t=torch.float32), workspace=ws_d), **kw)
+        return sc.sc_decode_attn(**a)
+
+    def multi(**kw):
+        a = dict(dict(cache, Q=Qn, O=z(nq, B, H * G, d), lse=z(nq, B, H * G, t=torch.float32), workspace=ws_m), **kw)
+        return sc.sc_multi_attn(**a)
+    with_tail = dict(Kt=Kt, Vt=Vt, tail_lens=tail)
+    across = K.transpose(2, 3).contiguous().transpose(2, 3)
+    fine = [(segment, {}), (segment, dict(seq_lens=None)), (segment, dict(mask=torch.cat([mask, mask], 1)[:, :n])), (merge, {}), (merge, dict(seq_lens=None, cluster_id=None)),
+            (merge, dict(base_lens=torch.full((B, H), 7, dtype=i32, device=g.DEV))), (merge, dict(Kc=z(B, H, 2 * n, d, t=torch.float32), Vc=z(B, H, 2 * n, d, t=torch.float32),
+            workspace=sc.gsc_merge_workspace(B, H, n, d, g.DEV))), (merge, dict(K=K[:, :, ::2], V=V[:, :, ::2], offsets=off[:, ::1], seq_lens=seq // 2)),
+            (merge, dict(cap=np.int64(2 * n), tau=np.float32(0.7))), (decode, {}), (decode, with_tail), (decode, dict(scale=0.5, lse=None)), (multi, {}), (multi, with_tail),
+            (multi, dict(with_tail, causal=True, tail_lens=torch.full((B,), tcap, dtype=i32, device=g.DEV))), (multi, dict(O=z(nq, B, H * G, d, t=torch.float32), scale=0.5))]
+    refused = [(segment, dict(mask=mask.to(torch.int8))), (segment, dict(mask=mask.t())), (segment, dict(offsets=z(B, 1, t=i32))), (segment, dict(num_chunks=nch.cpu())),
+               (merge, dict(K=across)), (merge, dict(V=V.float())), (merge, dict(K=K.double(), V=V.double())), (merge, dict(V=V.cpu())), (merge, dict(Kc=z(B, H, d, 2 * n).transpose(2, 3))),
+               (merge, dict(cap=0)), (merge, dict(workspace=sc.Workspace(256, g.DEV))), (merge, dict(tau=float("nan"))),
+               (merge, dict(base_lens=torch.full((B, H), 7, dtype=i32, device=g.DEV), cap=n)), (decode, dict(with_tail, Vt=Vt[:, :, :5])), (decode, dict(with_tail, Kt=Kt.float())),
+               (decode, dict(scale=float("nan"))), (multi, dict(Kc=Kc.transpose(2, 3).contiguous().transpose(2, 3))), (multi, dict(O=z(nq, B, H * G, d, t=torch.float64))),
+               (multi, dict(Q=Qn.cpu())), (multi, dict(with_tail, Kt=Kt[:, :1])), (multi, dict(with_tail, tail_lens=tail.cpu())), (multi, dict(workspace=sc.Workspace(256, g.DEV)))]
+    native = sc._native
+    taken = []
+    for name in ("segment", "merge", "decode", "multi"):
+        monkeypatch.setattr(sc._native, name, (lambda f: lambda *a: (taken.append(f(*a)), taken[-1])[1])(getattr(native, name)))
+    for call, kw in fine:
+        got = call(**{k: (v.clone() if k in ("Kc", "Vc", "workspace") and torch.is_tensor(v) else v) for k, v in kw.items()})
+        assert taken and taken.pop() == 0 and not taken, (call.__name__, sorted(kw))
+        got = [x.clone() for x in got if x is not None]
+        with monkeypatch.context() as m:
+            m.setattr(sc, "_native", None)
+            want = [x for x in call(**kw) if x is not None]
+        assert len(got) == len(want) and all(torch.equal(a, b) for a, b in zip(got, want)), (call.__name__, sorted(kw))
+    for call, kw in refused:
+        with pytest.raises(sc.SemantiCacheError) as first:
+            call(**kw)
+        with monkeypatch.context() as m:
+            m.setattr(sc, "_native", None)
+            with pytest.raises(sc.SemantiCacheError) as second:
+                call(**kw)
+        assert str(first.value) == str(second.value), (call.__name__, sorted(kw))
+    torch.cuda.synchronize()
