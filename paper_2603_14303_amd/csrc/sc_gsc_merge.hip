@@ -327,19 +327,20 @@ constexpr int kMergeCidTile = 2048;
 constexpr int kMergeInFlight = 4;
 // TWICE: some items are split between two workgroups, one adds up the keys and the other the values, eight rows in flight each.  What that
 // shortens is the largest cluster's trips to memory, so an item is split where a chunk of it is long: of more than kSplitLong tokens, or of more than
-// kSplitLongRoom in a call whose items would fill half of the places on the chip (two workgroups on each of 256 CUs) otherwise.  Where chunks are short the
+// kSplitLongRoom in a call with room for twice its items (of the 512 places on the chip, two workgroups on each of 256 CUs, kSplitRoom).  Where chunks are short the
 // second workgroup would do the first one's barriers and look-ups once more for nothing, and where the chip is full it takes a place.  Whole call without
 // sc_segment, us, never split / every item split / by this rule (delimiters at a fixed distance, or at random every 24 tokens: "geom"):
 //   8 heads x 6000 x 64 f32   distance 1 25.5 / 36.0 / 25.2, 4 29.3 / 40.6 / 29.7, 24 18.8 / 23.8 / 19.7, 64 26.7 / 23.1 / 24.5, geom 48.9 / 46.1 / 48.3
 //   8 x 6000 x 128 f32        1 37.9 / 52.6 / 35.6, 4 47.8 / 63.6 / 47.8, 24 27.2 / 31.6 / 27.7, 64 43.0 / 34.8 / 35.8, geom 61.4 / 54.1 / 56.5
 //   4 x 12000 x 64 bf16       1 20.6 / 32.4 / 20.6, 4 29.1 / 42.0 / 30.0, 24 22.2 / 28.3 / 22.5, 64 34.1 / 30.4 / 31.6, geom 61.5 / 52.2 / 58.9
-//   1 x 8000 x 64 f32         1 12.1 / 15.3 / 12.4, 4 13.8 / 17.6 / 13.8, 24 17.2 / 15.9 / 16.9, 64 26.7 / 22.6 / 23.3, geom 46.3 / 38.2 / 38.6
+//   1 x 8000 x 64 f32         1 12.1 / 15.3 / 12.4, 4 13.8 / 17.6 / 13.8, 24 17.5 / 16.5 / 17.2, 64 26.7 / 22.6 / 23.3, geom 45.7 / 37.4 / 38.1
+//   2 x 1024 x 64 f32         1 10.9 / 13.4 / 11.3, 16 16.1 / 15.2 / 14.7, 64 26.0 / 22.1 / 22.3, geom 30.3 / 26.6 / 27.1
 // (What is left where nothing is split, up to 4 % with d = 64, is the larger kernel's.)
 // The second workgroups come last, kSplitWorkgroups in all (as many as items are long: 4 x 12000 geom 59 with 512, 67 with 256; one for every item, 8 x
 // 2000 x 128 f32 with a delimiter every second token 17.2 instead of 16.8 us), and leave at once where chunks average less than kSplitMean tokens.
 // Even from 64k rows on (4 x 16000 x 64 f32 58.5 / 59.5).  (Sixteen in flight: 310 registers, a wavefront per SIMD, 4 x 8000 53, 4 x 16000 82.)
 constexpr int64_t kSplitTokens = 49152;      // rows of all heads
-constexpr int kSplitWorkgroups = 512, kSplitLong = 32, kSplitLongRoom = 20, kSplitMean = 12;
+constexpr int kSplitWorkgroups = 512, kSplitRoom = 384, kSplitLong = 32, kSplitLongRoom = 8, kSplitMean = 12;
 constexpr int kMergeInFlightSplit = 8;
 
 template <typename T, int D, bool INLINE_PREFIX, bool TWICE>
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     const bool may_split = TWICE && n >= kSplitMean * (int64_t)M;
     if (values && !may_split) return;
     const int step = values ? seconds : wgs;
-    const int split_from = (2 * (int64_t)min(items, wgs) * (p.B * p.Hkv) <= kSplitWorkgroups) ? kSplitLongRoom : kSplitLong;
+    const int split_from = (2 * (int64_t)min(items, wgs) * (p.B * p.Hkv) <= kSplitRoom) ? kSplitLongRoom : kSplitLong;
     const T *Kbh = reinterpret_cast<const T *>(p.K) + b * p.stride_b + h * p.stride_h;
     const T *Vbh = reinterpret_cast<const T *>(p.V) + b * p.stride_b + h * p.stride_h;
     const int32_t *off = p.offsets + (int64_t)b * p.offsets_stride_b;

@@ -332,7 +332,7 @@ def test_generic_merge_short_chunks(H, n, gap):
 
 @pytest.mark.parametrize("H,n,gaps", [
     (1, 3000, [11, 13]), (1, 3000, [11, 12]),                       # chunks of twelve tokens on average, and of fewer
-    (2, 1500, [20, 21, 19, 22]),                                    # room on the chip: split from 21 tokens on
+    (2, 1500, [8, 24, 9, 8, 24]), (2, 1500, [8, 8, 8, 8, 30]),      # room on the chip: split from 9 tokens on; some items are, others not
     (8, 6000, [32, 33, 2, 3, 5]), (8, 6000, [32, 31, 2, 3, 5]),     # none: from 33 tokens on; more items than second workgroups
     (5, 4000, [40, 2, 2, 2]),                                       # long chunks among short ones, eleven tokens on average
     (3, 5000, [2600, 7, 900]), (600, 80, [30, 40]),                 # one beyond the cluster indices held in LDS; more heads than second workgroups
