@@ -1276,8 +1276,8 @@ __device__ __forceinline__ void probe_block(CompressLds &s, ProbeSeeds &u, const
 }
 
 // PROBE: a probe of the budget search, at one threshold or at several.  Only the numbers of rows are wanted: no values are read and nothing is merged.
-enum Probe { kNoProbe, kProbeOne, kProbeSeveral };
-template <typename TO, Probe PROBE>
+constexpr int kNoProbe = 0, kProbeOne = 1, kProbeSeveral = 2;
+template <typename TO, int PROBE>
 __global__ __launch_bounds__(kWinThreads, 4) void gsc_compress_kernel(GscParams p) {
     constexpr bool COUNT = PROBE != kNoProbe;
     __shared__ __attribute__((aligned(16))) CompressLds s;
