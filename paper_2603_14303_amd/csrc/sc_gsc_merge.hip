@@ -344,7 +344,7 @@ constexpr int kSplitWorkgroups = 512, kSplitRoom = 384, kSplitLong = 32, kSplitL
 constexpr int kMergeInFlightSplit = 8;
 
 template <typename T, int D, bool INLINE_PREFIX, bool TWICE>
-__global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
+__global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p, int split_wgs) {      // split_wgs: second workgroups per (sequence, head)
     constexpr int LPR = D / 8;
     constexpr int RPW = kWave / LPR;            // output rows a wave works on at once
     constexpr int kGroups = kGscThreads / LPR;  // output rows a workgroup works on at once
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(kGscThreads) void gsc_merge_kernel(GscParams p) {
     const int g = lane / LPR, c = lane % LPR;
     const int gsh = g * LPR;   // position of this group's bits inside a wave ballot
     const uint64_t gmask = (LPR == 16) ? 0xffffull : 0xffull;
-    const int seconds = TWICE ? p.split_wgs : 0, launched = (int)gridDim.y - seconds;
+    const int seconds = TWICE ? split_wgs : 0, launched = (int)gridDim.y - seconds;
     const bool values = TWICE && (int)blockIdx.y >= launched;      // a second workgroup
     const int first_item = values ? (int)blockIdx.y - launched : (int)blockIdx.y;
     const int M = p.num_chunks[b];
@@ -562,17 +562,16 @@ static hipError_t launch_typed(const GscParams &p, int grid_x, hipStream_t strea
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (p.N_max <= kInlinePrefixTokens) {
-        GscParams q = p;
-        q.split_wgs = min(gx, kSplitWorkgroups / heads);
-        const dim3 more(grid.x, grid.y + q.split_wgs, grid.z);
-        if ((int64_t)heads * p.N_max <= kSplitTokens && q.split_wgs > 0 && more.y <= 65535) hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, true>), more, dim3(kGscThreads), 0, stream, q);
-        else hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, false>), grid, dim3(kGscThreads), 0, stream, p);
+        const int split_wgs = min(gx, kSplitWorkgroups / heads);
+        const dim3 more(grid.x, grid.y + split_wgs, grid.z);
+        if ((int64_t)heads * p.N_max <= kSplitTokens && split_wgs > 0 && more.y <= 65535) hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, true>), more, dim3(kGscThreads), 0, stream, p, split_wgs);
+        else hipLaunchKernelGGL((gsc_merge_kernel<T, D, true, false>), grid, dim3(kGscThreads), 0, stream, p, 0);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(gsc_scan_kernel, dim3(p.Hkv, p.B), dim3(256), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gsc_merge_kernel<T, D, false, false>), grid, dim3(kGscThreads), 0, stream, p);
+    hipLaunchKernelGGL((gsc_merge_kernel<T, D, false, false>), grid, dim3(kGscThreads), 0, stream, p, 0);
     return hipGetLastError();
 }
 

@@ -162,7 +162,6 @@ struct GscParams {
     int chunks_per_item;  // generic path
     int probe_levels;     // steps of the search that a counting probe decides
     int short_wgs[2];     // generic path: workgroups per (sequence, head) where short chunks make items of 8 / of 16 or 32, 0: they don't (see gsc_item_shape)
-    int split_wgs;        // generic path: second workgroups per (sequence, head), see gsc_merge_kernel
 };
 
 // rows already present in the outputs of (sequence, head) bh; an overflowed or impossible state counts as
