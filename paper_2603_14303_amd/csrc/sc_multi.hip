@@ -331,9 +331,9 @@ __global__ __launch_bounds__(kMwThreads, 2) void multi_wave_kernel(MqParams p) {
 // is 1.  A stretch (the rows of one split) is one sum in row order: level with four wavefronts that take a quarter each at
 // 1 500 rows (rms error with fp32 outputs 2.07e-6 / 2.05e-6 at scale 1/sqrt(d), 8.4e-7 / 8.2e-7 at 0.3), above it where one
 // split takes 8 192 (2.4e-6 / 2.1e-6 and 1.3e-6 / 8.7e-7): fewer largest weights, longer sums.
-// Bound by instruction issue: per 64 cache rows a wavefront spends 48 matrix instructions of 32 cycles and as many cycles
-// of vector work on the logits of its lanes, and the two wavefronts of a SIMD overlap little of it (counters: 46 % of the
-// time matrix, 46 % vector).  8 heads x 2048 query rows (nq = 512, G = 4) x 5 900 cache rows, 49 GFLOP: 238 us with 32 rows
+// Bound by the overlap of two wavefronts per SIMD: per 64 cache rows a wavefront spends 48 matrix instructions of 32 cycles and as many cycles
+// of vector work on the logits of its lanes, and a third of its time it waits for loads and at barriers (counters: 46 % of the
+// time matrix, 50 % vector).  8 heads x 2048 query rows (nq = 512, G = 4) x 5 900 cache rows, 49 GFLOP: 238 us with 32 rows
 // per workgroup and no sharing of tiles (208 TFLOP/s), now 100 us with the second kernel (496 TFLOP/s).
 constexpr int kMbWaves = 4;
 constexpr int kMbThreads = kMbWaves * kWave;
@@ -614,7 +614,7 @@ static void mq_shape(int B, int Hq, int Hkv, int nq, int cap /* merged + tail ro
         max_splits = max(1, min(most, max(1, tuning().multi_target_wgs) * 3 / 4 / base));
         return;
     }
-    // Bound by instruction issue.  A tile takes a workgroup alone on its compute unit 3.0 us, a pair of them 4.3; a second
+    // A tile takes a workgroup alone on its compute unit 3.0 us, a pair of them 4.3 (see multi_block_kernel); a second
     // round of pairs takes as long as the first; partials cost the second kernel 3 us and 20 ns per workgroup
     // (1400 rows, 4 heads, 5 200 cache rows: 57 us with 12 splits = 1.03 rounds, 46 us with 11).  In units of 0.1 us:
     const int64_t units = max(1, tuning().multi_target_wgs);
